@@ -12,7 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["layout.cpp", "abi.hip", "wave_attention.hip", "mfma_attention.hip", "prefill_attention.hip", "merge.hip",
+SOURCES = ["layout.cpp", "abi.hip", "wave_attention.hip", "tile_attention.hip", "mfma_attention.hip", "prefill_attention.hip", "merge.hip",
            "kv_update.hip", "probe.hip"]
 LIB = os.path.join(HERE, "libprefillshare.so")
 HOST_ASAN_LIB = os.path.join(HERE, "libprefillshare_host_asan.so")

@@ -1,6 +1,7 @@
 // Device-facing entry points of the C ABI: table upload and the attention passes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "device_common.h"
@@ -126,7 +127,12 @@ int32_t launch_set(const ps_layout* lay, const psdev::AttnParams& p, const void*
                                         reinterpret_cast<const ps_item*>(t + s.off_items), t + s.off_indptr, s.num_wg,
                                         st);
   } else {
-    rc = psdev::launch_wave_attention(p, lay->geo, begin, end - begin, st);
+    const int group = lay->geo.num_q_heads / lay->geo.num_kv_heads;
+    const int max_rows = set == WorkSet::kSuffix ? group : std::max(group, lay->max_rows_prefix);
+    const bool stream = set == WorkSet::kPrefix ? lay->stream_prefix : set == WorkSet::kSuffix ? lay->stream_suffix : lay->stream_all;
+    rc = psdev::tile_supported(p, lay->geo)
+             ? psdev::launch_tile_attention(p, lay->geo, max_rows, stream, begin, end - begin, st)
+             : psdev::launch_wave_attention(p, lay->geo, begin, end - begin, st);
   }
   if (rc != PS_OK) return rc;
   return check_hip(hipGetLastError());

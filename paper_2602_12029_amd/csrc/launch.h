@@ -8,6 +8,11 @@ namespace psdev {
 
 bool wave_supported(const ps_geometry& g);
 int32_t launch_wave_attention(const AttnParams& p, const ps_geometry& g, int item_begin, int n_items, hipStream_t st);
+// The same family for pools the tile kernel can address (blocks of 16 k tokens, see tile_supported): one workgroup per
+// item; max_rows: query rows per KV head of the widest item; stream: K/V tile loads are non-temporal.
+bool tile_supported(const AttnParams& p, const ps_geometry& g);
+int32_t launch_tile_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin,
+                              int n_items, hipStream_t st);
 // Persistent launch: workgroup w walks wg_items[wg_indptr[w] .. wg_indptr[w+1]).
 // `masked`: the set holds items whose rows see different token counts (per-request visible prefix lengths).
 // `stream`: K/V tile loads are non-temporal (the set's K/V is read by one item each, or nearly so).

@@ -98,14 +98,20 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   for (int32_t l : lay->prefix_len) { shortest = std::min(shortest, l); longest = std::max(longest, l); }
   const bool unequal = longest > 0 && int64_t(longest) * 10 > int64_t(shortest) * 11;
   const int64_t ideal = std::max<int64_t>(1, ceil_div(two_per_cu && unequal ? total * 3 / 5 : total, int64_t(num_cus)));
-  auto pick = [&](int32_t asked) -> int64_t {
-    if (asked > 0) return round_up(asked, granule);
-    return std::min<int64_t>(std::max<int64_t>(round_up(ideal, granule), round_up(256, granule)), round_up(kPsMfmaMaxChunk, granule));
-  };
   auto resolve = [&](int32_t v) { return v == PS_VARIANT_AUTO ? (mfma_ok ? PS_VARIANT_MFMA : PS_VARIANT_WAVE) : v; };
+  // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item, two and more of them resident per
+  // compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25 of it: 36 float32 requests on 12
+  // contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to
+  // 6144 tokens 51.2 / 44.5 / 43.1 us).
+  const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, 2 * int64_t(num_cus)));
+  auto pick = [&](int32_t asked, int32_t variant) -> int64_t {
+    if (asked > 0) return round_up(asked, granule);
+    const int64_t aim = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 ? tile_ideal : ideal;
+    return std::min<int64_t>(std::max<int64_t>(round_up(aim, granule), round_up(256, granule)), round_up(kPsMfmaMaxChunk, granule));
+  };
   const int64_t mfma_cap = std::max<int64_t>(granule, kPsMfmaMaxChunk / granule * granule);
-  int64_t prefix_chunk = pick(opt.prefix_chunk_tokens);
-  int64_t suffix_chunk = pick(opt.suffix_chunk_tokens);
+  int64_t prefix_chunk = pick(opt.prefix_chunk_tokens, resolve(opt.prefix_variant));
+  int64_t suffix_chunk = pick(opt.suffix_chunk_tokens, resolve(opt.suffix_variant));
   if (resolve(opt.prefix_variant) == PS_VARIANT_MFMA) prefix_chunk = std::min(prefix_chunk, mfma_cap);
   if (resolve(opt.suffix_variant) == PS_VARIANT_MFMA) suffix_chunk = std::min(suffix_chunk, mfma_cap);
 
@@ -393,24 +399,27 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   // Schedules for the persistent MFMA kernel: longest-processing-time-first packing of a set of items
   // onto the resident workgroups (cost = tokens + a fixed per-item charge), each list longest first.
   typedef ps_layout::packed_set packed;
-  auto pack = [&](int begin, int end) {
-    packed out;
-    const int count = end - begin;
-    for (int i = begin; i < end; ++i) out.max_rows = std::max(out.max_rows, lay->items[size_t(i)].n_req * group);
-    out.occ = ps_mfma_occupancy(out.max_rows, g.kv_dtype);
-    // Cache policy of the launch: K/V that one item reads is best streamed past the caches, K/V that several row
-    // groups read (kPsItemReread) should stay in them.  The policy is per launch, so it goes by the share of the
-    // set's tokens that lie in re-read items: streaming while that is under a quarter (measured: a root shared by 8
-    // row groups next to 3/4 of ordinary traffic gains 1.5 % from streaming, two row groups per prompt at 46 % of
-    // the tokens lose 5 %).
+  // Cache policy of a launch: K/V that one item reads is best streamed past the caches, K/V that several row
+  // groups read (kPsItemReread) should stay in them.  The policy is per launch, so it goes by the share of the
+  // set's tokens that lie in re-read items: streaming while that is under a quarter (measured: a root shared by 8
+  // row groups next to 3/4 of ordinary traffic gains 1.5 % from streaming, two row groups per prompt at 46 % of
+  // the tokens lose 5 %).
+  auto streams = [&](int begin, int end) {
     int64_t tokens_all = 0, tokens_reread = 0;
     for (int i = begin; i < end; ++i) {
       const ps_item& it = lay->items[size_t(i)];
       tokens_all += it.tok_end - it.tok_begin;
       if (it.kind & kPsItemReread) tokens_reread += it.tok_end - it.tok_begin;
     }
-    out.stream = opt.kv_cache_policy == PS_KV_POLICY_AUTO ? 4 * tokens_reread < tokens_all
-                                                           : opt.kv_cache_policy == PS_KV_POLICY_STREAM;
+    return opt.kv_cache_policy == PS_KV_POLICY_AUTO ? 4 * tokens_reread < tokens_all
+                                                     : opt.kv_cache_policy == PS_KV_POLICY_STREAM;
+  };
+  auto pack = [&](int begin, int end) {
+    packed out;
+    const int count = end - begin;
+    for (int i = begin; i < end; ++i) out.max_rows = std::max(out.max_rows, lay->items[size_t(i)].n_req * group);
+    out.occ = ps_mfma_occupancy(out.max_rows, g.kv_dtype);
+    out.stream = streams(begin, end);
     const int num_wg = std::max(1, std::min(count, num_cus * out.occ));
     std::vector<int> order(size_t(count), 0);
     std::iota(order.begin(), order.end(), begin);
@@ -444,6 +453,9 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   };
   const int n_items = int(lay->items.size());
   const bool pre_mfma = lay->prefix_variant == PS_VARIANT_MFMA, suf_mfma = lay->suffix_variant == PS_VARIANT_MFMA;
+  lay->stream_prefix = streams(0, lay->num_prefix_items);
+  lay->stream_suffix = streams(lay->num_prefix_items, n_items);
+  lay->stream_all = streams(0, n_items);
   const int first_packed = lay->num_rowsplit_items;   // row-split items run in the prefill kernel, one workgroup each
   lay->pk_prefix = pre_mfma ? pack(first_packed, lay->num_prefix_items) : packed{};
   lay->pk_suffix = suf_mfma ? pack(lay->num_prefix_items, n_items) : packed{};

@@ -59,6 +59,8 @@ struct ps_layout {
   std::vector<ps_item> items;        // row-split shared items, then the other shared (root, prefix) items, then suffix items
   int32_t num_rowsplit_items = 0;    // launched one workgroup each by the prefill kernel, outside the schedules
   int32_t num_prefix_items = 0;      // all shared items: root and prefix, row-split ones included
+  // K/V loads of a launch over the shared / private / all items are non-temporal (little of its K/V is read by several)
+  bool stream_prefix = true, stream_suffix = true, stream_all = true;
   std::vector<int32_t> slot_base;    // [R+1]
   int64_t num_slots = 0;
 

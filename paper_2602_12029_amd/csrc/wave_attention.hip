@@ -1,7 +1,7 @@
 // fp32 wavefront-reduction split-K attention (no matrix cores).
 //
-// Used where the grouped query rows per KV head are too few or the inputs too wide for the bf16
-// MFMA path: fp32 inputs, unusual head sizes, or on request.  One workgroup (4 waves) handles one
+// The form of the PS_VARIANT_WAVE family for the pools the tile kernel (tile_attention.h) does not take: blocks that
+// are no multiple of 16 tokens, base pointers off a 16-byte boundary, blocks of 2 GiB and more.  One workgroup (4 waves) handles one
 // work item: a token range of one KV segment for one KV head, applied to all query rows that read
 // it.  A 16-lane row of a wave owns one token at a time: lane c of the row holds d/16 consecutive
 // head-dim elements of that token's K and V, scores are completed with a DPP all-reduce over the
