@@ -138,6 +138,13 @@ int32_t launch_set(const ps_layout* lay, const psdev::AttnParams& p, const void*
   return check_hip(hipGetLastError());
 }
 
+// Both passes; where they run the same kernel family, one launch over the whole work list.
+int32_t launch_both(const ps_layout* lay, const psdev::AttnParams& p, const void* dev_tables, hipStream_t st) {
+  if (lay->prefix_variant == lay->suffix_variant) return launch_set(lay, p, dev_tables, WorkSet::kAll, st);
+  if (int32_t rc = launch_set(lay, p, dev_tables, WorkSet::kPrefix, st)) return rc;
+  return launch_set(lay, p, dev_tables, WorkSet::kSuffix, st);
+}
+
 int32_t check_pass_args(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv,
                         const float* scales, const void* workspace) {
   if (!lay || !dev_tables || !workspace || lay->parked) return PS_ERR_INVALID_ARG;
@@ -207,7 +214,7 @@ int32_t ps_merge_states(const ps_layout* lay, const void* dev_tables, const void
   if (!lay || !dev_tables || !workspace) return PS_ERR_INVALID_ARG;
   if (lay->num_requests && !out) return PS_ERR_INVALID_ARG;
   const psdev::AttnParams p = make_params(lay, dev_tables, nullptr, nullptr, nullptr, const_cast<void*>(workspace));
-  if (int32_t rc = psdev::launch_merge(p.slot_base, p.ws_o, p.ws_lse, out, out_lse, lay->num_requests, lay->geo,
+  if (int32_t rc = psdev::launch_merge(p.slot_base, nullptr, p.ws_o, p.ws_lse, out, out_lse, lay->num_requests, lay->geo,
                                        static_cast<hipStream_t>(stream)))
     return rc;
   return check_hip(hipGetLastError());
@@ -217,11 +224,7 @@ int32_t ps_prefix_suffix_attention(const ps_layout* lay, const void* dev_tables,
                                    const float* kv_scales, void* workspace, void* stream) {
   if (int32_t st = check_pass_args(lay, dev_tables, q, kv_pool, kv_scales, workspace)) return st;
   const psdev::AttnParams p = make_params(lay, dev_tables, q, kv_pool, kv_scales, workspace);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (lay->prefix_variant == lay->suffix_variant)  // same kernel: one launch over the whole work list
-    return launch_set(lay, p, dev_tables, WorkSet::kAll, st);
-  if (int32_t rc = launch_set(lay, p, dev_tables, WorkSet::kPrefix, st)) return rc;
-  return launch_set(lay, p, dev_tables, WorkSet::kSuffix, st);
+  return launch_both(lay, p, dev_tables, static_cast<hipStream_t>(stream));
 }
 
 int32_t ps_kv_ingest(const ps_layout* lay, const void* dev_tables, int32_t which, const void* src_k, const void* src_v,
@@ -292,8 +295,23 @@ int32_t ps_probe_read(const void* dev_buf, int64_t bytes, int32_t pattern, int32
 int32_t ps_decode_attention(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,
                             const float* kv_scales, void* workspace, void* out, float* out_lse, void* stream) {
   if (lay && lay->num_requests && !out) return PS_ERR_INVALID_ARG;
-  if (int32_t rc = ps_prefix_suffix_attention(lay, dev_tables, q, kv_pool, kv_scales, workspace, stream)) return rc;
-  return ps_merge_states(lay, dev_tables, workspace, out, out_lse, stream);
+  if (int32_t rc = check_pass_args(lay, dev_tables, q, kv_pool, kv_scales, workspace)) return rc;
+  psdev::AttnParams p = make_params(lay, dev_tables, q, kv_pool, kv_scales, workspace);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (!lay->any_direct) {
+    if (int32_t rc = launch_both(lay, p, dev_tables, st)) return rc;
+    return ps_merge_states(lay, dev_tables, workspace, out, out_lse, stream);
+  }
+  // Partial prefill: a context that goes out as one item leaves one partial state per row, which is the result -- the
+  // prefill kernel rounds and stores it, and only the other requests are merged.
+  p.out = out;
+  p.out_lse = out_lse;
+  if (int32_t rc = launch_both(lay, p, dev_tables, st)) return rc;
+  const int32_t* list = static_cast<const int32_t*>(dev_tables) + lay->off_merge;
+  if (int32_t rc = psdev::launch_merge(p.slot_base, list, p.ws_o, p.ws_lse, out, out_lse, int(lay->merge_req.size()),
+                                       lay->geo, st))
+    return rc;
+  return check_hip(hipGetLastError());
 }
 
 int32_t ps_decode_attention_static(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,

@@ -27,6 +27,10 @@ struct AttnParams {
   const float* scales;       // [num_blocks][Hkv][2] or null
   float* ws_o;               // [num_slots][Hq][d]
   float* ws_lse;             // [num_slots][Hq]
+  // whole step only (else null): where the prefill kernel puts the rows of a request with a single partial state, which
+  // then needs no merge
+  void* out;                 // [R][Hq][d], query format
+  float* out_lse;            // [R][Hq] or null
   int32_t num_q_heads, num_kv_heads, group, block_size;
   int64_t s_block, s_head, s_kv, s_tok;  // elements
   float scale_log2;          // log2(e) / sqrt(d)

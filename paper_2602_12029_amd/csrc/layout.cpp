@@ -395,6 +395,22 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
     lay->slot_base[r + 1] = int32_t(slots);
   }
   lay->num_slots = slots;
+  // A request whose only partial state comes from the prefill kernel needs no merge in a whole step: the kernel rounds
+  // and stores the row itself.
+  std::vector<char> direct(size_t(R), 0);
+  lay->any_direct = false;
+  for (int32_t i = 0; i < lay->num_rowsplit_items; ++i) {
+    const ps_item& it = lay->items[size_t(i)];
+    for (int32_t m = 0; m < it.n_req; ++m) {
+      const int32_t r = lay->req_list[size_t(it.req_off + m)];
+      if (lay->slot_base[size_t(r) + 1] - lay->slot_base[size_t(r)] == 1) direct[size_t(r)] = 1;
+    }
+  }
+  lay->merge_req.clear();
+  for (char d : direct) lay->any_direct |= d != 0;
+  if (lay->any_direct)
+    for (int32_t r = 0; r < R; ++r)
+      if (!direct[size_t(r)]) lay->merge_req.push_back(r);
 
   // Schedules for the persistent MFMA kernel: longest-processing-time-first packing of a set of items
   // onto the resident workgroups (cost = tokens + a fixed per-item charge), each list longest first.
@@ -475,7 +491,7 @@ int32_t ps_blob_build(ps_layout* lay) {
   auto visible_of = [&](int32_t r) { return limited ? lay->visible[size_t(r)] : lay->prefix_len[size_t(lay->req_prompt[size_t(r)])]; };
   // device blob: [block ids: prefix ++ suffix ++ root][request list: group_req ++ identity ++ root groups ++ per-chunk
   // subsets][items]
-  // [slot_base][visible][schedules]
+  // [slot_base][visible][requests to merge][schedules]
   // [per-block source offsets and valid counts][destinations of the last append]
   auto pad4 = [](int64_t n) { return (n + 3) / 4 * 4; };
   lay->off_blk = 0;
@@ -483,7 +499,8 @@ int32_t ps_blob_build(ps_layout* lay) {
   lay->off_items = pad4(lay->off_req + int64_t(lay->req_list.size()));
   lay->off_slot = pad4(lay->off_items + 8 * int64_t(lay->items.size()));
   lay->off_visible = pad4(lay->off_slot + R + 1);
-  int64_t words = pad4(lay->off_visible + R);
+  lay->off_merge = pad4(lay->off_visible + R);
+  int64_t words = pad4(lay->off_merge + int64_t(lay->merge_req.size()));
   auto place = [&](ps_layout::schedule& s, const packed& pk) {
     s = ps_layout::schedule{};
     if (pk.items.empty()) return;
@@ -586,6 +603,7 @@ int32_t ps_blob_build(ps_layout* lay) {
   std::copy(lay->root_blk.begin(), lay->root_blk.end(), b + lay->off_blk + root_blk0);
   std::copy(lay->req_list.begin(), lay->req_list.end(), b + lay->off_req);
   for (int32_t r = 0; r < R; ++r) b[lay->off_visible + r] = visible_of(r);
+  std::copy(lay->merge_req.begin(), lay->merge_req.end(), b + lay->off_merge);
   if (!lay->items.empty()) std::memcpy(b + lay->off_items, lay->items.data(), lay->items.size() * sizeof(ps_item));
   std::copy(lay->slot_base.begin(), lay->slot_base.end(), b + lay->off_slot);
   return PS_OK;

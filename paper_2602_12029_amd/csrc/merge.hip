@@ -11,17 +11,19 @@ namespace psdev {
 
 template <int QT>
 __global__ __launch_bounds__(256) void merge_states_kernel(const int32_t* __restrict__ slot_base,
+                                                           const int32_t* __restrict__ requests,
                                                            const float* __restrict__ ws_o,
                                                            const float* __restrict__ ws_lse, void* __restrict__ out,
                                                            float* __restrict__ out_lse, int num_rows, int num_q_heads,
                                                            int head_dim) {
   const int per_row = head_dim >> 2;
   const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t row = gid / per_row;
-  if (row >= num_rows) return;
+  const int64_t listed = gid / per_row;
+  if (listed >= num_rows) return;
   const int c4 = int(gid % per_row);
-  const int r = int(row / num_q_heads);
-  const int h = int(row % num_q_heads);
+  const int h = int(listed % num_q_heads);
+  const int r = requests ? requests[listed / num_q_heads] : int(listed / num_q_heads);
+  const int64_t row = int64_t(r) * num_q_heads + h;
   const int s0 = slot_base[r], s1 = slot_base[r + 1];
   const float neg_inf = -__builtin_inff();
 
@@ -74,18 +76,18 @@ __global__ __launch_bounds__(256) void merge_states_kernel(const int32_t* __rest
   if (out_lse && c4 == 0) out_lse[row] = (mx != neg_inf) ? mx + __builtin_amdgcn_logf(total) * kLn2 : neg_inf;
 }
 
-int32_t launch_merge(const int32_t* slot_base, const float* ws_o, const float* ws_lse, void* out, float* out_lse,
-                     int num_requests, const ps_geometry& g, hipStream_t st) {
+int32_t launch_merge(const int32_t* slot_base, const int32_t* requests, const float* ws_o, const float* ws_lse, void* out,
+                     float* out_lse, int num_requests, const ps_geometry& g, hipStream_t st) {
   const int64_t rows = int64_t(num_requests) * g.num_q_heads;
   if (rows == 0) return PS_OK;
   if (g.head_dim % 4 != 0) return PS_ERR_UNSUPPORTED;
   const int64_t threads = rows * (g.head_dim / 4);
   const dim3 grid(unsigned((threads + 255) / 256)), block(256);
   if (g.q_dtype == PS_F32)
-    hipLaunchKernelGGL((merge_states_kernel<PS_F32>), grid, block, 0, st, slot_base, ws_o, ws_lse, out, out_lse,
+    hipLaunchKernelGGL((merge_states_kernel<PS_F32>), grid, block, 0, st, slot_base, requests, ws_o, ws_lse, out, out_lse,
                        int(rows), g.num_q_heads, g.head_dim);
   else
-    hipLaunchKernelGGL((merge_states_kernel<PS_BF16>), grid, block, 0, st, slot_base, ws_o, ws_lse, out, out_lse,
+    hipLaunchKernelGGL((merge_states_kernel<PS_BF16>), grid, block, 0, st, slot_base, requests, ws_o, ws_lse, out, out_lse,
                        int(rows), g.num_q_heads, g.head_dim);
   return PS_OK;
 }

@@ -63,6 +63,10 @@ struct ps_layout {
   bool stream_prefix = true, stream_suffix = true, stream_all = true;
   std::vector<int32_t> slot_base;    // [R+1]
   int64_t num_slots = 0;
+  // requests whose partial states ps_decode_attention has to merge: all but those with a single one that the prefill
+  // kernel writes out itself; only filled (and in the blob) where there are such
+  std::vector<int32_t> merge_req;
+  bool any_direct = false;
 
   // persistent-kernel schedules: for a set of items, the items regrouped by workgroup (8 int32 each,
   // workgroup w owns [indptr[w], indptr[w+1])) -- one schedule per launchable set
@@ -104,6 +108,7 @@ struct ps_layout {
   // device table blob (int32 words) and section offsets in words
   std::vector<int32_t> blob;
   int64_t off_blk = 0, off_req = 0, off_items = 0, off_slot = 0;
+  int64_t off_merge = 0;             // merge_req
   int64_t off_visible = 0;           // int32[R]: effective visible prefix length of every request
   // for the cache-writing kernels, per entry of the concatenated block array: index of its first token in the
   // ragged source tensor of its kind (prefixes back to back / suffixes back to back) and its number of valid

@@ -132,3 +132,43 @@ def test_full_size_chunk_prefill_sampled_rows(gpu, name):
     torch.cuda.synchronize()
     assert torch.equal(first.view(torch.int16), case.batch.out.view(torch.int16))
     case.close()
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+def test_rows_with_one_partial_state_match_the_merged_ones(gpu, kv_dtype):
+    """The whole step stores the rows of requests with a single partial state from the prefill kernel; the two passes and
+    the merge called one by one give the same bits -- whole contexts, cut ones, rows that see nothing, a context of few
+    rows (the decode kernel), rows with a private suffix, with and without the log-sum-exp, and in place over q."""
+    geo = wl.Geometry(32, 8, 128, 16, "bf16", kv_dtype)
+    rng = np.random.default_rng(11)
+    chunks, cached = [40, 7, 66, 33], [500, 90, 0, 2100]
+    membership = [list(range(c)) for c in chunks]
+    n = sum(chunks)
+    suffix = np.where(np.arange(n) % 9 == 4, rng.integers(1, 40, n), 0)
+    w = wl.make_workload("direct_" + kv_dtype, geo, max(chunks), [a + c for a, c in zip(cached, chunks)], membership,
+                         suffix.tolist(), pool_factor=1.2, seed=29)
+    visible = np.concatenate([a + 1 + np.arange(c) for a, c in zip(cached, chunks)]).astype(np.int32)
+    visible[[3, 50, 100]] = 0
+    case = gpu(w)
+    for pc in (0, 256, 4096):
+        case.replan(pc, 0)
+        case.set_visible(visible)
+        case.poison_workspace()
+        case.batch.decode_attention()
+        torch.cuda.synchronize()
+        whole = case.batch.out.clone(), case.batch.lse.clone()
+        case.poison_workspace()
+        case.batch.prefix_attention()
+        case.batch.suffix_attention()
+        case.batch.merge_states()
+        assert torch.equal(whole[0].view(torch.int16), case.batch.out.view(torch.int16))
+        assert torch.equal(whole[1].view(torch.int32), case.batch.lse.view(torch.int32))
+        case.poison_workspace()
+        case.batch.decode_attention(with_lse=False)
+        assert torch.equal(whole[0].view(torch.int16), case.batch.out.view(torch.int16))
+        own_q, own_out = case.batch.q, case.batch.out
+        case.batch.q = case.batch.out = own_q.clone()
+        case.batch.decode_attention()
+        assert torch.equal(whole[0].view(torch.int16), case.batch.out.view(torch.int16))
+        case.batch.q, case.batch.out = own_q, own_out
+    case.close()
