@@ -214,8 +214,8 @@ int32_t ps_merge_states(const ps_layout* lay, const void* dev_tables, const void
   if (!lay || !dev_tables || !workspace) return PS_ERR_INVALID_ARG;
   if (lay->num_requests && !out) return PS_ERR_INVALID_ARG;
   const psdev::AttnParams p = make_params(lay, dev_tables, nullptr, nullptr, nullptr, const_cast<void*>(workspace));
-  if (int32_t rc = psdev::launch_merge(p.slot_base, nullptr, p.ws_o, p.ws_lse, out, out_lse, lay->num_requests, lay->geo,
-                                       static_cast<hipStream_t>(stream)))
+  if (int32_t rc = psdev::launch_merge(p.slot_base, nullptr, p.ws_o, p.ws_lse, out, out_lse, lay->num_requests,
+                                       lay->max_states, lay->geo, static_cast<hipStream_t>(stream)))
     return rc;
   return check_hip(hipGetLastError());
 }
@@ -309,7 +309,7 @@ int32_t ps_decode_attention(const ps_layout* lay, const void* dev_tables, const 
   if (int32_t rc = launch_both(lay, p, dev_tables, st)) return rc;
   const int32_t* list = static_cast<const int32_t*>(dev_tables) + lay->off_merge;
   if (int32_t rc = psdev::launch_merge(p.slot_base, list, p.ws_o, p.ws_lse, out, out_lse, int(lay->merge_req.size()),
-                                       lay->geo, st))
+                                       lay->max_states, lay->geo, st))
     return rc;
   return check_hip(hipGetLastError());
 }

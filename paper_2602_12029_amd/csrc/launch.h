@@ -34,7 +34,8 @@ int32_t launch_kv_stage(const ps_layout* lay, const void* dev_tables, bool to_im
 // Measurement aid: reads `bytes` (whole 8 KiB units of it) once with the load footprint `pattern` names.
 int32_t launch_probe_read(const void* buf, int64_t bytes, int pattern, int num_workgroups, hipStream_t st);
 // `requests`: the requests to merge (num_requests of them), or null = 0 .. num_requests - 1.
+// max_states: the most partial states a request has.
 int32_t launch_merge(const int32_t* slot_base, const int32_t* requests, const float* ws_o, const float* ws_lse, void* out,
-                     float* out_lse, int num_requests, const ps_geometry& g, hipStream_t st);
+                     float* out_lse, int num_requests, int max_states, const ps_geometry& g, hipStream_t st);
 
 }  // namespace psdev

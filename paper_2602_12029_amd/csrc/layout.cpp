@@ -102,12 +102,15 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item, two and more of them resident per
   // compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25 of it: 36 float32 requests on 12
   // contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to
-  // 6144 tokens 51.2 / 44.5 / 43.1 us).
+  // 6144 tokens 51.2 / 44.5 / 43.1 us), and at
+  // least 128 tokens, one or two tiles per wave (two requests on one 256-token prompt, launches alone: chunks of 256 /
+  // 128 / 64 tokens 9.4 / 7.9 / 7.7 us; contexts of some thousand tokens lose more in the merge than they gain).
   const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, 2 * int64_t(num_cus)));
   auto pick = [&](int32_t asked, int32_t variant) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
-    const int64_t aim = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 ? tile_ideal : ideal;
-    return std::min<int64_t>(std::max<int64_t>(round_up(aim, granule), round_up(256, granule)), round_up(kPsMfmaMaxChunk, granule));
+    const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0;
+    return std::min<int64_t>(std::max<int64_t>(round_up(tiles ? tile_ideal : ideal, granule), round_up(tiles ? 128 : 256, granule)),
+                             round_up(kPsMfmaMaxChunk, granule));
   };
   const int64_t mfma_cap = std::max<int64_t>(granule, kPsMfmaMaxChunk / granule * granule);
   int64_t prefix_chunk = pick(opt.prefix_chunk_tokens, resolve(opt.prefix_variant));
@@ -388,11 +391,13 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   lay->items.insert(lay->items.end(), suffix_items.begin(), suffix_items.end());
 
   lay->slot_base.assign(R + 1, 0);
+  lay->max_states = 0;
   int64_t slots = 0;
   for (int32_t r = 0; r < R; ++r) {
     slots += nsplit_root[r] + nsplit_prefix[r] + nsplit_suffix[r];
     if (slots > INT32_MAX) return PS_ERR_INVALID_ARG;
     lay->slot_base[r + 1] = int32_t(slots);
+    lay->max_states = std::max(lay->max_states, lay->slot_base[r + 1] - lay->slot_base[r]);
   }
   lay->num_slots = slots;
   // A request whose only partial state comes from the prefill kernel needs no merge in a whole step: the kernel rounds

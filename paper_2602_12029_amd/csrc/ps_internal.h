@@ -63,6 +63,7 @@ struct ps_layout {
   bool stream_prefix = true, stream_suffix = true, stream_all = true;
   std::vector<int32_t> slot_base;    // [R+1]
   int64_t num_slots = 0;
+  int32_t max_states = 0;            // most slots of a request
   // requests whose partial states ps_decode_attention has to merge: all but those with a single one that the prefill
   // kernel writes out itself; only filled (and in the blob) where there are such
   std::vector<int32_t> merge_req;
