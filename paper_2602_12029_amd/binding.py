@@ -90,6 +90,12 @@ def _lib():
         lib.ps_strerror.argtypes = [C.c_int32]
         lib.ps_layout_device_bytes.restype = C.c_int64
         lib.ps_workspace_bytes.restype = C.c_int64
+        # the calls of a serving loop take plain addresses: declared once, ctypes converts them without an object each
+        if not host_only:
+            for name, count in {"ps_layout_upload": 3, "ps_prefix_attention": 7, "ps_suffix_attention": 7,
+                                "ps_prefix_suffix_attention": 7, "ps_merge_states": 6, "ps_decode_attention": 9,
+                                "ps_decode_attention_static": 8, "ps_kv_append": 7}.items():
+                getattr(lib, name).argtypes = [C.c_void_p] * count
         for name in EXPORTS:
             if not (host_only and name in DEVICE_EXPORTS):
                 getattr(lib, name)                  # fail early if a symbol is missing
@@ -311,8 +317,18 @@ def ps_layout_device_bytes(layout) -> int:
     return int(_lib().ps_layout_device_bytes(layout))
 
 
+def _launch(fn, where: str, *args):
+    """Calls an entry point whose arguments are all addresses: a layout handle, integers (0 or None = NULL)."""
+    try:
+        status = fn(*args)
+    except C.ArgumentError:              # other integer types (numpy)
+        status = fn(*[a if isinstance(a, C.c_void_p) else _p(a) for a in args])
+    if status != PS_OK:
+        raise PsError(status, where)
+
+
 def ps_layout_upload(layout, dev_tables: int, stream: int = 0):
-    _check(_lib().ps_layout_upload(layout, C.c_void_p(dev_tables), C.c_void_p(stream)), "ps_layout_upload")
+    _launch(_lib().ps_layout_upload, "ps_layout_upload", layout, dev_tables, stream)
 
 
 def ps_workspace_bytes(layout) -> int:
@@ -331,38 +347,34 @@ def _p(x):
 
 
 def ps_prefix_attention(layout, dev_tables, q, kv_pool, kv_scales, workspace, stream=0):
-    _check(_lib().ps_prefix_attention(layout, _p(dev_tables), _p(q), _p(kv_pool), _p(kv_scales), _p(workspace),
-                                      _p(stream)), "ps_prefix_attention")
+    _launch(_lib().ps_prefix_attention, "ps_prefix_attention", layout, dev_tables, q, kv_pool, kv_scales, workspace, stream)
 
 
 def ps_suffix_attention(layout, dev_tables, q, kv_pool, kv_scales, workspace, stream=0):
-    _check(_lib().ps_suffix_attention(layout, _p(dev_tables), _p(q), _p(kv_pool), _p(kv_scales), _p(workspace),
-                                      _p(stream)), "ps_suffix_attention")
+    _launch(_lib().ps_suffix_attention, "ps_suffix_attention", layout, dev_tables, q, kv_pool, kv_scales, workspace, stream)
 
 
 def ps_prefix_suffix_attention(layout, dev_tables, q, kv_pool, kv_scales, workspace, stream=0):
-    _check(_lib().ps_prefix_suffix_attention(layout, _p(dev_tables), _p(q), _p(kv_pool), _p(kv_scales),
-                                             _p(workspace), _p(stream)), "ps_prefix_suffix_attention")
+    _launch(_lib().ps_prefix_suffix_attention, "ps_prefix_suffix_attention", layout, dev_tables, q, kv_pool, kv_scales,
+            workspace, stream)
 
 
 def ps_merge_states(layout, dev_tables, workspace, out, out_lse=0, stream=0):
-    _check(_lib().ps_merge_states(layout, _p(dev_tables), _p(workspace), _p(out), _p(out_lse), _p(stream)),
-           "ps_merge_states")
+    _launch(_lib().ps_merge_states, "ps_merge_states", layout, dev_tables, workspace, out, out_lse, stream)
 
 
 def ps_decode_attention(layout, dev_tables, q, kv_pool, kv_scales, workspace, out, out_lse=0, stream=0):
-    _check(_lib().ps_decode_attention(layout, _p(dev_tables), _p(q), _p(kv_pool), _p(kv_scales), _p(workspace),
-                                      _p(out), _p(out_lse), _p(stream)), "ps_decode_attention")
+    _launch(_lib().ps_decode_attention, "ps_decode_attention", layout, dev_tables, q, kv_pool, kv_scales, workspace, out,
+            out_lse, stream)
 
 
 def ps_decode_attention_static(layout, dev_tables, q, kv_pool, kv_scales, out, out_lse=0, stream=0):
-    _check(_lib().ps_decode_attention_static(layout, _p(dev_tables), _p(q), _p(kv_pool), _p(kv_scales), _p(out),
-                                             _p(out_lse), _p(stream)), "ps_decode_attention_static")
+    _launch(_lib().ps_decode_attention_static, "ps_decode_attention_static", layout, dev_tables, q, kv_pool, kv_scales,
+            out, out_lse, stream)
 
 
 def ps_kv_append(layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream=0):
-    _check(_lib().ps_kv_append(layout, _p(dev_tables), _p(new_k), _p(new_v), _p(kv_pool), _p(kv_scales), _p(stream)),
-           "ps_kv_append")
+    _launch(_lib().ps_kv_append, "ps_kv_append", layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream)
 
 
 def ps_kv_ingest(layout, dev_tables, which: int, src_k, src_v, src_stride_tok: int, src_stride_head: int, kv_pool,

@@ -9,7 +9,9 @@
 #include "prefillshare_probe.h"
 #include <atomic>
 #include <cstring>
+#include <mutex>
 #include <new>
+#include <vector>
 
 // Partial-state workspace for callers that cannot allocate (ps_decode_attention_static): part of the library's device
 // image, so every GPU the library runs on holds one copy at its own address until the process ends.  In host code
@@ -22,6 +24,7 @@ struct ps_layout::upload_staging {
   hipEvent_t done[2] = {nullptr, nullptr};   // recorded behind the copy that reads the buffer
   bool in_use[2] = {false, false};
   int next = 0;
+  int device = -1;   // of the events
 };
 
 namespace {
@@ -61,13 +64,67 @@ psdev::AttnParams make_params(const ps_layout* lay, const void* dev_tables, cons
   return p;
 }
 
-void free_upload_staging(ps_layout::upload_staging* s) {
+void destroy_upload_staging(ps_layout::upload_staging* s) {
   for (int i = 0; i < 2; ++i) {
     if (s->in_use[i]) (void)hipEventSynchronize(s->done[i]);
     if (s->done[i]) (void)hipEventDestroy(s->done[i]);
     if (s->buffer[i]) (void)hipHostFree(s->buffer[i]);
   }
   delete s;
+}
+
+// Staging of released layouts, kept for the next ones: taking and giving back pinned memory costs more (some 150 us a
+// layout: a turn of eight steps over sixteen contexts, laid out and released, takes 1.6 ms) than laying a batch out.
+// At most kKeptStagings of them with buffers of at most kKeptBytes are kept; all are given back when the last block
+// pool is destroyed.  The list is never destroyed itself (the HIP runtime may be gone by then).
+constexpr size_t kKeptStagings = 4, kKeptBytes = size_t(1) << 20;
+struct StagingPool {
+  std::mutex lock;
+  std::vector<ps_layout::upload_staging*> kept;
+};
+StagingPool& staging_pool() {
+  static StagingPool* pool = new StagingPool;
+  return *pool;
+}
+void free_upload_staging(ps_layout::upload_staging* s) {
+  if (s->capacity[0] <= kKeptBytes && s->capacity[1] <= kKeptBytes && s->device >= 0) {
+    StagingPool& pool = staging_pool();
+    const std::lock_guard<std::mutex> hold(pool.lock);
+    if (pool.kept.size() < kKeptStagings) {
+      pool.kept.push_back(s);   // a copy may still be reading a buffer: its event goes along
+      return;
+    }
+  }
+  destroy_upload_staging(s);
+}
+// One whose copies are done (so that its new owner never waits for another layout's stream), or a new one.
+ps_layout::upload_staging* take_upload_staging(int device) {
+  StagingPool& pool = staging_pool();
+  {
+    const std::lock_guard<std::mutex> hold(pool.lock);
+    for (size_t k = 0; k < pool.kept.size(); ++k) {
+      ps_layout::upload_staging* s = pool.kept[k];
+      bool idle = s->device == device;
+      for (int i = 0; i < 2 && idle; ++i) {
+        if (s->in_use[i] && hipEventQuery(s->done[i]) == hipSuccess) s->in_use[i] = false;
+        idle = !s->in_use[i];
+      }
+      if (!idle) continue;
+      pool.kept.erase(pool.kept.begin() + std::ptrdiff_t(k));
+      return s;
+    }
+  }
+  ps_layout::upload_staging* s = new (std::nothrow) ps_layout::upload_staging();
+  if (s) s->device = device;
+  return s;
+}
+void drain_staging_pool() {
+  std::vector<ps_layout::upload_staging*> all;
+  {
+    const std::lock_guard<std::mutex> hold(staging_pool().lock);
+    all.swap(staging_pool().kept);
+  }
+  for (ps_layout::upload_staging* s : all) destroy_upload_staging(s);
 }
 
 // Compute units of the current device (asked once per device), 0 if there is no device to ask: the planner's
@@ -84,7 +141,10 @@ int32_t current_device_num_cus() {
   return count;
 }
 const struct HookInstaller {
-  HookInstaller() { ps_device_num_cus_hook = current_device_num_cus; }
+  HookInstaller() {
+    ps_device_num_cus_hook = current_device_num_cus;
+    ps_last_pool_hook = drain_staging_pool;
+  }
 } g_hook_installer;
 
 // Device address of `scratch` on the current device, resolved once per device with that device current.
@@ -165,7 +225,9 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   // call returns once it is enqueued, and the next ps_layout_append may rebuild the tables while it is in flight.
   // A buffer is reused two uploads later, after the copy that last read it has finished (an event per buffer).
   if (!lay->staging) {
-    lay->staging = new (std::nothrow) ps_layout::upload_staging();
+    int device = -1;
+    if (int32_t st = check_hip(hipGetDevice(&device))) return st;
+    lay->staging = take_upload_staging(device);
     if (!lay->staging) return PS_ERR_OOM;
     lay->staging_free = free_upload_staging;
   }

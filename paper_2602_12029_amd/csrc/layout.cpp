@@ -5,6 +5,7 @@
 // request on that prompt (each decode module starts from the same base cache, Method Eq. 6), and
 // only the model-specific segment is private (Efficiency Analysis Eq. 9).
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -12,7 +13,6 @@
 #include <new>
 #include <numeric>
 #include <queue>
-#include <set>
 #include <utility>
 
 #include "ps_internal.h"
@@ -38,6 +38,8 @@ int32_t check_geometry(const ps_geometry& g) {
 }  // namespace
 
 int32_t (*ps_device_num_cus_hook)() = nullptr;
+void (*ps_last_pool_hook)() = nullptr;
+static std::atomic<int64_t> live_pools{0};
 
 bool ps_mfma_supported(const ps_geometry& g) {
   // The matrix-core kernels address a (block, head) slice through a buffer descriptor with 32-bit byte offsets
@@ -573,8 +575,21 @@ int32_t ps_blob_build(ps_layout* lay) {
       // blocks are scattered, and scattered reads (the source, now) cost less than scattered writes (measured on the
       // staging copies: 5.8 against 5.2 TB/s).
       auto by_block = [&](const std::vector<int32_t>& blk, int32_t* order) {
-        std::iota(order, order + blk.size(), 0);
-        std::sort(order, order + blk.size(), [&](int32_t a, int32_t b2) { return blk[size_t(a)] < blk[size_t(b2)]; });
+        if (blk.empty()) return;
+        // (a segment's blocks are distinct; where they fill a good part of their range of ids they are laid out by id,
+        // otherwise sorted)
+        const auto range = std::minmax_element(blk.begin(), blk.end());
+        const int32_t lowest = *range.first;
+        const size_t span = size_t(int64_t(*range.second) - lowest + 1);
+        if (span <= 16 * blk.size()) {
+          std::vector<int32_t> at(span, -1);
+          for (size_t i = 0; i < blk.size(); ++i) at[size_t(blk[i] - lowest)] = int32_t(i);
+          for (int32_t i : at)
+            if (i >= 0) *order++ = i;
+        } else {
+          std::iota(order, order + blk.size(), 0);
+          std::sort(order, order + blk.size(), [&](int32_t a, int32_t b2) { return blk[size_t(a)] < blk[size_t(b2)]; });
+        }
       };
       lay->ent_fixed_order.resize(n_fixed);
       by_block(lay->prefix_blk, lay->ent_fixed_order.data());
@@ -726,12 +741,15 @@ int32_t ps_pool_create(int32_t num_blocks, const int32_t* free_order, ps_pool** 
   } else {
     for (int32_t i = 0; i < num_blocks; ++i) p->free_list.push_back(i);
   }
+  live_pools.fetch_add(1);
   *out = p;
   return PS_OK;
 }
 
 int32_t ps_pool_destroy(ps_pool* pool) {
+  if (!pool) return PS_OK;
   delete pool;
+  if (live_pools.fetch_sub(1) == 1 && ps_last_pool_hook) ps_last_pool_hook();
   return PS_OK;
 }
 
@@ -771,13 +789,16 @@ int32_t build_layout(ps_pool* pool, const ps_geometry* geometry, int32_t num_roo
   const int32_t B = geometry->block_size;
 
   std::vector<int32_t> members_count(size_t(num_prompts), 0);
-  std::set<std::pair<int32_t, int32_t>> seen;
+  std::vector<uint64_t> seen;      // (prompt, model) of every request
+  seen.reserve(size_t(num_requests));
   for (int32_t r = 0; r < num_requests; ++r) {
     if (req_prompt[r] < 0 || req_prompt[r] >= num_prompts || req_model[r] < 0 || suffix_len[r] < 0)
       return PS_ERR_INVALID_ARG;
-    if (!seen.insert({req_prompt[r], req_model[r]}).second) return PS_ERR_INVALID_ARG;
+    seen.push_back(uint64_t(uint32_t(req_prompt[r])) << 32 | uint32_t(req_model[r]));
     ++members_count[size_t(req_prompt[r])];
   }
+  if (!std::is_sorted(seen.begin(), seen.end())) std::sort(seen.begin(), seen.end());
+  if (std::adjacent_find(seen.begin(), seen.end()) != seen.end()) return PS_ERR_INVALID_ARG;
   // requests below every root: all requests of the prompts that begin with it
   std::vector<int32_t> below_count(size_t(num_roots), 0), root_prompts(size_t(num_roots), 0);
   for (int32_t p = 0; p < num_prompts && num_roots; ++p) {
@@ -801,14 +822,15 @@ int32_t build_layout(ps_pool* pool, const ps_geometry* geometry, int32_t num_roo
   if (adopt_indptr) {
     // adopted blocks: full blocks of the prompt's prefix, alive (referenced by some layout) and named once
     if (adopt_indptr[0] != 0 || (adopt_indptr[num_prompts] > 0 && !adopt_blk)) return PS_ERR_INVALID_ARG;
-    std::set<int32_t> named;
+    std::vector<char> named(size_t(pool->num_blocks), 0);
     for (int32_t p = 0; p < num_prompts; ++p) {
       const int32_t n = adopt_indptr[p + 1] - adopt_indptr[p];
       if (n < 0 || int64_t(n) * B > prefix_len[p]) return PS_ERR_INVALID_ARG;
       for (int32_t i = adopt_indptr[p]; i < adopt_indptr[p + 1]; ++i) {
         const int32_t blk = adopt_blk[i];
-        if (blk < 0 || blk >= pool->num_blocks || pool->refcount[size_t(blk)] <= 0 || !named.insert(blk).second)
+        if (blk < 0 || blk >= pool->num_blocks || pool->refcount[size_t(blk)] <= 0 || named[size_t(blk)])
           return PS_ERR_INVALID_ARG;
+        named[size_t(blk)] = 1;
       }
       needed -= n;
     }

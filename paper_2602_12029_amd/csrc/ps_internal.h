@@ -132,6 +132,8 @@ constexpr int kPsMfmaMaxChunk = 8192;  // tokens per MFMA work item (64 tiles pe
 // library (the planner then assumes kPsDefaultNumCus); abi.hip installs it when the library is loaded.
 extern int32_t (*ps_device_num_cus_hook)();
 constexpr int32_t kPsDefaultNumCus = 256;   // MI355X
+// Called when the last block pool is destroyed (abi.hip gives back what it keeps between layouts); null as above.
+extern void (*ps_last_pool_hook)();
 
 // layout.cpp
 int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* opt);

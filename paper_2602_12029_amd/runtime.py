@@ -11,7 +11,13 @@ import torch
 from . import binding as B
 
 
+# the raw handle of torch's current stream, without building a Stream object for it (3 us a launch) where torch offers that
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
     return int(torch.cuda.current_stream().cuda_stream)
 
 
@@ -47,11 +53,13 @@ class DecodeBatch:
         self.workspace = None
         self._sync_plan()
 
-    def _sync_plan(self):
+    def _sync_plan(self, wait=True):
+        self._home = _stream()               # tables and workspace belong to this stream
         nbytes = B.ps_layout_device_bytes(self.layout)
         self.tables = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         B.ps_layout_upload(self.layout, self.tables.data_ptr(), _stream())
-        torch.cuda.current_stream().synchronize()
+        if wait:
+            torch.cuda.current_stream().synchronize()
         self.workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
 
     def replan(self, options: B.ps_plan_options | None):
@@ -63,48 +71,58 @@ class DecodeBatch:
         B.ps_layout_set_visible(self.layout, self.num_requests, prefix_visible)
         self._sync_plan()
 
+    def _stream(self) -> int:
+        """The current stream, for a launch that reads the tables (they and the workspace live until it is done there)."""
+        stream = _stream()
+        if stream != self._home:
+            for t in (self.tables, self.workspace):
+                t.record_stream(torch.cuda.current_stream())
+        return stream
+
     def _sc(self):
         return self.scales.data_ptr() if self.scales is not None else 0
 
     def prefix_attention(self):
         B.ps_prefix_attention(self.layout, self.tables.data_ptr(), self.q.data_ptr(), self.kv.data_ptr(), self._sc(),
-                              self.workspace.data_ptr(), _stream())
+                              self.workspace.data_ptr(), self._stream())
 
     def suffix_attention(self):
         B.ps_suffix_attention(self.layout, self.tables.data_ptr(), self.q.data_ptr(), self.kv.data_ptr(), self._sc(),
-                              self.workspace.data_ptr(), _stream())
+                              self.workspace.data_ptr(), self._stream())
 
     def merge_states(self, with_lse=True):
         B.ps_merge_states(self.layout, self.tables.data_ptr(), self.workspace.data_ptr(), self.out.data_ptr(),
-                          self.lse.data_ptr() if with_lse else 0, _stream())
+                          self.lse.data_ptr() if with_lse else 0, self._stream())
 
     def decode_attention(self, with_lse=True, kv: torch.Tensor | None = None):
         B.ps_decode_attention(self.layout, self.tables.data_ptr(), self.q.data_ptr(),
                               (self.kv if kv is None else kv).data_ptr(), self._sc(), self.workspace.data_ptr(),
-                              self.out.data_ptr(), self.lse.data_ptr() if with_lse else 0, _stream())
+                              self.out.data_ptr(), self.lse.data_ptr() if with_lse else 0, self._stream())
 
     def kv_ingest(self, which: int, src_k: torch.Tensor, src_v: torch.Tensor):
         """Store every segment of one kind (0 prefixes, 1 suffixes) from ragged [T, Hkv, d] sources."""
         assert src_k.stride(2) == 1 and src_v.stride() == src_k.stride()
         B.ps_kv_ingest(self.layout, self.tables.data_ptr(), which, src_k.data_ptr(), src_v.data_ptr(),
-                       src_k.stride(0), src_k.stride(1), self.kv.data_ptr(), self._sc(), _stream())
+                       src_k.stride(0), src_k.stride(1), self.kv.data_ptr(), self._sc(), self._stream())
 
     def append_step(self, pool, new_k: torch.Tensor, new_v: torch.Tensor, active=None):
         """One decode step of cache growth: tables grow on the host and are uploaded again, then the new
         tokens ([R, Hkv, d], contiguous) are stored.  Returns the destinations the host chose."""
-        dest = B.ps_layout_append(pool, self.layout, self.num_requests, active).copy()
-        self._sync_plan()
+        dest = B.ps_layout_append(pool, self.layout, self.num_requests, active)
+        # No wait for the upload: it is ordered in front of the store below on this stream, and whoever reads the new
+        # tokens from another stream has to be ordered behind that store anyway.
+        self._sync_plan(wait=False)
         assert new_k.is_contiguous() and new_v.is_contiguous()
         B.ps_kv_append(self.layout, self.tables.data_ptr(), new_k.data_ptr(), new_v.data_ptr(), self.kv.data_ptr(),
-                       self._sc(), _stream())
+                       self._sc(), self._stream())
         return dest
 
     def stage_out(self, image: torch.Tensor):
         """Copy the batch's blocks (and e4m3 scales) into `image`: uint8, device memory or pinned host memory."""
-        B.ps_kv_stage_out(self.layout, self.tables.data_ptr(), self.kv.data_ptr(), self._sc(), image.data_ptr(), _stream())
+        B.ps_kv_stage_out(self.layout, self.tables.data_ptr(), self.kv.data_ptr(), self._sc(), image.data_ptr(), self._stream())
 
     def stage_in(self, image: torch.Tensor):
-        B.ps_kv_stage_in(self.layout, self.tables.data_ptr(), image.data_ptr(), self.kv.data_ptr(), self._sc(), _stream())
+        B.ps_kv_stage_in(self.layout, self.tables.data_ptr(), image.data_ptr(), self.kv.data_ptr(), self._sc(), self._stream())
 
     def park(self, pool):
         """Hand the batch's blocks back to the pool (after stage_out has completed)."""

@@ -1,0 +1,119 @@
+"""GPU: turns that follow each other without a wait -- batches laid out, grown, attended and released back to back, their
+uploads sharing the library's pinned staging -- against the same turns with a device synchronisation after every call."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+class Session:
+    """One cached context under three models, bf16, driven turn by turn."""
+
+    def __init__(self, seed):
+        from paper_2602_12029_amd import binding as B
+        rng = np.random.default_rng(seed)
+        self.B, self.len = B, np.array([200 + 37 * seed], np.int32)
+        self.geo = B.geometry(8, 2, 128, 16, "bf16", "bf16")
+        blocks = 64
+        self.pool = B.ps_pool_create(blocks, rng.permutation(blocks).astype(np.int32))
+        self.keep = B.ps_kv_layout(self.pool, self.geo, self.len, [0], [0], [0])
+        t = B.ps_layout_tables(self.keep, 1, 1)
+        self.adopt = [t["prefix_blk"][:int(self.len[0]) // 16]]
+        gen = torch.Generator().manual_seed(seed)
+        def draw(*shape):
+            return torch.randn(*shape, generator=gen).to(torch.bfloat16).cuda()
+        self.kv = draw(blocks, 2, 2, 16, 128)
+        self.tail = [draw(int(self.len[0]) % 16, 2, 128) for _ in range(2)]
+        self.q = [draw(3, 8, 128) for _ in range(20)]
+        self.new = [(draw(3, 2, 128), draw(3, 2, 128)) for _ in range(20)]
+        torch.cuda.synchronize()
+
+    def turn(self, steps, wait):
+        from paper_2602_12029_amd.runtime import DecodeBatch
+        B = self.B
+        done = torch.cuda.synchronize if wait else (lambda: None)
+        layout = B.ps_kv_layout_adopt(self.pool, self.geo, self.len, self.adopt, [0, 0, 0], [0, 1, 2], [0, 0, 0])
+        batch = DecodeBatch(layout, self.geo, 3, self.q[0], self.kv)
+        batch.kv_ingest(0, *self.tail)
+        outs = []
+        for i in range(steps):
+            batch.append_step(self.pool, *self.new[i])
+            done()
+            batch.q = self.q[i]
+            batch.decode_attention()
+            done()
+            outs.append(batch.out.clone())
+        B.ps_layout_release(self.pool, layout)
+        return outs
+
+    def turns(self, wait):
+        return [o for steps in (1, 5, 18, 2, 2, 20) for o in self.turn(steps, wait)]
+
+    def close(self):
+        torch.cuda.synchronize()
+        self.B.ps_layout_release(self.pool, self.keep)
+        self.B.ps_pool_destroy(self.pool)
+
+
+def _same(a, b):
+    return len(a) == len(b) and all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(a, b))
+
+
+def test_turns_without_waits_and_after_the_pools_are_gone():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    for _ in range(2):                       # the second round starts with nothing kept
+        s = Session(1)
+        want = s.turns(True)
+        assert _same(s.turns(False), want)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            got = s.turns(False)
+        torch.cuda.synchronize()
+        assert _same(got, want)
+        s.close()
+
+
+def test_turns_of_several_threads_on_their_own_streams():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    sessions = [Session(i) for i in range(4)]
+    want = [s.turns(True) for s in sessions]
+    got = [None] * len(sessions)
+
+    def work(i):
+        torch.cuda.set_device(0)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[i] = sessions[i].turns(False)
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sessions))]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    for s, g, w in zip(sessions, got, want):
+        assert _same(g, w)
+        s.close()
+
+
+def test_addresses_of_other_integer_types():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_12029_amd import binding as B
+    from paper_2602_12029_amd.runtime import DecodeBatch
+    s = Session(2)
+    batch = DecodeBatch(s.keep, s.geo, 1, s.q[0][:1].contiguous(), s.kv)
+    batch.decode_attention()
+    want = batch.out.clone()
+    batch.out.zero_()
+    stream = torch.cuda.current_stream().cuda_stream
+    B.ps_decode_attention(s.keep, np.int64(batch.tables.data_ptr()), np.uint64(batch.q.data_ptr()), batch.kv.data_ptr(), None,
+                          batch.workspace.data_ptr(), batch.out.data_ptr(), np.int64(0), stream)
+    assert _same([batch.out], [want])
+    with pytest.raises(B.PsError):
+        B.ps_decode_attention(s.keep, 0, batch.q.data_ptr(), batch.kv.data_ptr(), 0, batch.workspace.data_ptr(),
+                              batch.out.data_ptr(), 0, stream)
+    s.close()
