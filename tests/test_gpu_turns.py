@@ -117,3 +117,32 @@ def test_addresses_of_other_integer_types():
         B.ps_decode_attention(s.keep, 0, batch.q.data_ptr(), batch.kv.data_ptr(), 0, batch.workspace.data_ptr(),
                               batch.out.data_ptr(), 0, stream)
     s.close()
+
+
+@pytest.mark.parametrize("requests", [1, 3, 40, 250, 1100, 3000])
+def test_uploaded_tables_are_the_layouts(requests):
+    """Table blobs on both sides of 16 KiB and of 1 MiB arrive whole, whichever way they go up."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_12029_amd import binding as B
+    geo = B.geometry(8, 8, 128, 16, "bf16", "bf16")
+    pool = B.ps_pool_create(requests * 5, None)
+    layout = B.ps_kv_layout(pool, geo, [40] * requests, np.arange(requests), np.zeros(requests, int), [20] * requests)
+    n = B.ps_layout_device_bytes(layout)
+    stream = torch.cuda.current_stream().cuda_stream
+    for rep in range(4):                     # more uploads than the layout has staging buffers
+        dev = torch.full((n + 64,), 0x5a, dtype=torch.uint8, device="cuda")
+        B.ps_layout_upload(layout, dev.data_ptr(), stream)
+        torch.cuda.synchronize()
+        words = dev[:n].cpu().numpy().view(np.int32)
+        t = B.ps_layout_tables(layout, requests, requests)
+        k = t["prefix_blk"].size
+        assert np.array_equal(words[:k], t["prefix_blk"]) and np.array_equal(words[k:k + t["suffix_blk"].size], t["suffix_blk"])
+        # the blob ends with the order the shared blocks are walked in, then the private ones as stored (and padding)
+        entries = k + t["suffix_blk"].size
+        tail = words[words.size - (entries + 3) // 4 * 4:][:entries]
+        assert np.array_equal(np.sort(tail[:k]), np.arange(k)) and np.array_equal(tail[k:], np.arange(k, entries))
+        assert (dev[n:] == 0x5a).all()
+    print(requests, n)
+    B.ps_layout_release(pool, layout)
+    B.ps_pool_destroy(pool)
