@@ -17,11 +17,11 @@
 //
 // K and V reach the waves through LDS, as ready-made A operands: per 32-token tile the eight waves fetch one eighth
 // of it each (K straight in operand layout; V as pairs of token rows, transposed inside the lane with one byte
-// permute per operand register; e4m3 codes converted to bf16 once), write it to a three-stage ring, and after one
-// barrier per tile every wave reads the 8 K and 8 V operands of the tile back, 16 bytes per lane and operand, each
+// permute per operand register; e4m3 codes converted to bf16 once), write it to a ring of three stages of one or two
+// tiles, and after the barrier that ends a stage every wave reads the 8 K and 8 V operands of the tile back, 16 bytes per lane and operand, each
 // lane exactly the slot of its own lane index (no bank conflicts).  A tile is thus fetched, transposed and
-// converted once per 256 rows.  Global loads run four tiles ahead of the products (two tiles in registers, two in
-// LDS), and a tile's K operands are requested from the ring while the tile before it is multiplied.
+// converted once per 256 rows.  Global loads run four (six) tiles ahead of the products (two tiles in registers, the
+// others in LDS), and a tile's K operands are requested from the ring while the tile before it is multiplied.
 //
 // Per wave and tile: S^T = K Q^T (A = K: lane (m, g) holds elements 16 st + 8 g .. + 7 of token m for k-step st; B =
 // Q^T likewise for query row n), whose result leaves lane (n, g) with the scores of row n against tokens
@@ -45,7 +45,6 @@ constexpr int kD = kHeadDim;
 constexpr int kWaves = 8;         // per workgroup
 constexpr int kRowsPerWave = 32;  // one 32-row tile per wave
 constexpr int kTile = kTileTokens;
-constexpr int kStages = 3;        // LDS ring: tile k read (V), tile k + 1 read (K, one tile ahead), tile k + 2 written
 constexpr float kLazy = kLazyRescale;
 constexpr float kLazyTop = 256.f;   // 2^kLazy
 static_assert(kLazyRescale == 8.f, "kLazyTop is 2^kLazyRescale");
@@ -68,8 +67,10 @@ __device__ __forceinline__ int wave_max(int x) {
 
 }  // namespace
 
-template <int KVT>
+// TPB: tiles per ring stage, and per barrier.
+template <int KVT, int TPB>
 __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnParams p, const ps_item* __restrict__ items) {
+  constexpr int kStages = 3 * TPB;
   __shared__ u32x4 sm_k[kStages][8][64];   // [stage][k-step][lane]: K as that lane's A operand
   __shared__ u32x4 sm_v[kStages][8][64];   // [stage][2 * column class + 16-token step][lane]: V^T as that lane's A operand
   __shared__ f32x4 sm_sc[kStages][2];      // e4m3: [stage][block] = (score scale in log2 units, log2 of the V scale, 1 / V scale, -)
@@ -163,6 +164,11 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
   fetch(fa, fetch_ids(0), 0);
   fetch(fb, fetch_ids(1), 1);
   const TileIds ids2 = fetch_ids(2), ids3 = fetch_ids(3);
+  Fetched fc, fd;
+  if constexpr (TPB == 2) {
+    fetch(fc, ids2, 2);
+    fetch(fd, ids3, 3);
+  }
 
   // ---- this lane's query row (row lane % 32 of the wave): request, visible length, and the row itself as the
   // eight B operands of S^T = K Q^T (k-step st, lane group g: elements 16 st + 8 g .. + 7)
@@ -368,45 +374,61 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
     pv(vt, pb);
   };
 
-  // ---- stream the token range.  The ring holds three tiles: in iteration k the wave multiplies tile k (its K
-  // operands already in registers, requested during iteration k - 1), requests the K operands of tile k + 1 (complete
-  // in the ring since the last barrier), publishes its share of tile k + 2 (fetched two iterations earlier) into the
-  // stage tile k - 1 left, requests tile k + 4 from memory, and meets the others at the barrier.  The products of a
+  // ---- stream the token range.  The ring holds three stages of TPB tiles: in iteration k the wave multiplies tile k (its
+  // K operands already in registers, requested during iteration k - 1), requests the K operands of tile k + 1 (complete
+  // in the ring since the last barrier), publishes its share of tile k + 2 TPB (fetched two iterations earlier) into the
+  // stage the tiles before k's left, requests tile k + 2 TPB + 2 from memory, and, at the end of a stage, meets the others
+  // at the barrier.  The products of a
   // tile thus start right behind the barrier instead of waiting for operands that all eight waves ask for at once.
   // No branch surrounds a load, so the counting of outstanding loads stays exact; every wave runs every iteration
   // (and every barrier), whether it has rows or not.
-  publish(fa, 0, 0, std::true_type{});
-  fetch(fa, ids2, 2);
-  publish(fb, 1, 1, std::true_type{});
-  fetch(fb, ids3, 3);
-  TileIds ids_nxt = fetch_ids(4);   // the block id of tile k + 4, asked for one iteration ahead
+  TileIds ids_nxt;   // the block id of the tile fetched next, asked for one iteration ahead
+  if constexpr (TPB == 2) {
+    publish(fa, 0, 0, std::true_type{});
+    fetch(fa, fetch_ids(4), 4);
+    publish(fb, 1, 1, std::true_type{});
+    fetch(fb, fetch_ids(5), 5);
+    publish(fc, 2, 2, std::true_type{});
+    publish(fd, 3, 3, std::true_type{});
+    ids_nxt = fetch_ids(6);
+  } else {
+    publish(fa, 0, 0, std::true_type{});
+    fetch(fa, ids2, 2);
+    publish(fb, 1, 1, std::true_type{});
+    fetch(fb, ids3, 3);
+    ids_nxt = fetch_ids(4);
+  }
   __syncthreads();
-  int st_cur = 0, st_nxt = 1, st_wr = 2;   // ring stages of tiles k, k + 1, k + 2
+  int st_cur = 0, st_nxt = 1, st_wr = 2;   // thirds of the ring: the tiles multiplied, the next ones, those written
   KOperands ka_even, ka_odd;               // K operands of the even / odd tile in flight
   if (n_tiles > 0) ka_even = read_k(0);
   // what_tag: std::false_type / std::true_type = multiply without / with the per-row limits; void* = only fetch
-  auto one_tile = [&](int k, Fetched& f_pub, const KOperands& ka, KOperands& ka_next, auto what_tag,
+  auto one_tile = [&](int k, auto second_tag, Fetched& f_pub, const KOperands& ka, KOperands& ka_next, auto what_tag,
                       auto ragged_tag) __attribute__((always_inline)) {
     constexpr bool kMultiply = !std::is_pointer<decltype(what_tag)>::value;
     // (the fetching stands in front of the score products in program order and the compiler weaves it into them:
     // a wave issues in order, so vector work finds room under matrix instructions only between them -- with the
     // products first and everything else behind a scheduling barrier the kernel is 3-13 % slower)
-    if constexpr (kMultiply) ka_next = read_k(st_nxt);   // on their way while this tile is multiplied
-    publish(f_pub, st_wr, k + 2, ragged_tag);
-    fetch(f_pub, ids_nxt, k + 4);
-    ids_nxt = fetch_ids(k + 5);
+    constexpr int kSecond = TPB == 2 ? decltype(second_tag)::value : 0;
+    // (the K operands of the tile after this one, on their way while this one is multiplied)
+    if constexpr (kMultiply) ka_next = read_k(TPB == 2 && !kSecond ? 2 * st_cur + 1 : TPB * st_nxt);
+    publish(f_pub, TPB * st_wr + kSecond, k + 2 * TPB, ragged_tag);
+    fetch(f_pub, ids_nxt, k + 2 * TPB + 2);
+    ids_nxt = fetch_ids(k + 2 * TPB + 3);
     if constexpr (kMultiply) {
       const f32x16 s = scores(ka);
       // the V operands are requested now, all eight, so that they arrive under the softmax (left to itself the
       // compiler requests each one right before its products, and the wave sits out the LDS latency eight times)
-      const VOperands vt = read_v(st_cur);
-      finish(s, vt, st_cur, k, what_tag);
+      const VOperands vt = read_v(TPB * st_cur + kSecond);
+      finish(s, vt, TPB * st_cur + kSecond, k, what_tag);
     }
-    const int st_free = st_cur;
-    st_cur = st_nxt;
-    st_nxt = st_wr;
-    st_wr = st_free;
-    __syncthreads();
+    if constexpr (TPB == 1 || kSecond) {
+      const int st_free = st_cur;
+      st_cur = st_nxt;
+      st_nxt = st_wr;
+      st_wr = st_free;
+      __syncthreads();
+    }
   };
   // Two tiles per round, so that the fetch and operand registers keep their roles.  Three loops rather than tests
   // inside one (a branch around the products would have the accumulators copied where its sides meet): the tiles
@@ -420,21 +442,21 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
   // faster with bf16 KV and 4 % slower with e4m3 than requesting the K operands a tile ahead, which the registers
   // do not allow next to it; four waves of 64 rows, one per SIMD, every operand read feeding two matrix instructions:
   // 18-29 % slower, a wave alone on its SIMD has nobody to cover its waits.)
-  // (the first loop also stops short of the item's last complete tiles, so that the tiles it publishes -- two and
-  // three ahead -- are complete ones and need no zeroing of rows past the range)
-  const int n_fast = min(n_whole, (tok_end - tok_begin) / kTile - 2);
+  // (the first loop also stops short of the item's last complete tiles, so that the tiles it publishes, up to
+  // 2 TPB + 1 ahead, are complete ones and need no zeroing of rows past the range)
+  const int n_fast = min(n_whole, (tok_end - tok_begin) / kTile - 2 * TPB);
   int k = 0;
   for (; k + 2 <= n_fast; k += 2) {
-    one_tile(k, fa, ka_even, ka_odd, std::false_type{}, std::false_type{});
-    one_tile(k + 1, fb, ka_odd, ka_even, std::false_type{}, std::false_type{});
+    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, std::false_type{}, std::false_type{});
+    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, std::false_type{}, std::false_type{});
   }
   for (; k < n_tiles; k += 2) {
-    one_tile(k, fa, ka_even, ka_odd, std::true_type{}, std::true_type{});
-    one_tile(k + 1, fb, ka_odd, ka_even, std::true_type{}, std::true_type{});
+    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, std::true_type{}, std::true_type{});
+    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, std::true_type{}, std::true_type{});
   }
   for (; k < n_tiles_wg; k += 2) {
-    one_tile(k, fa, ka_even, ka_odd, static_cast<void*>(nullptr), std::true_type{});
-    one_tile(k + 1, fb, ka_odd, ka_even, static_cast<void*>(nullptr), std::true_type{});
+    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, static_cast<void*>(nullptr), std::true_type{});
+    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, static_cast<void*>(nullptr), std::true_type{});
   }
 
   // ---- one partial state per row, straight from the accumulators: register r of column class x is column
@@ -485,10 +507,13 @@ int32_t launch_prefill_attention(const AttnParams& p, const ps_geometry& g, cons
   if (g.head_dim != kD || g.q_dtype != PS_BF16 || g.block_size % 16 != 0 || (spb & (spb - 1)) != 0)
     return PS_ERR_UNSUPPORTED;
   const dim3 grid(num_items), block(64 * kWaves);
+  // Tiles per barrier: two with bf16 KV (32 contexts of 4096 + 64..256 tokens 464 -> 452 us a step, the waves of a SIMD
+  // drifting apart by up to a tile), one with e4m3, where the second changes nothing (64 contexts of 8192 tokens 3289 /
+  // 3298 us, 3302 / 3301 us) and the ring takes half the LDS.
   if (g.kv_dtype == PS_BF16)
-    hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16>), grid, block, 0, st, p, items);
+    hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 2>), grid, block, 0, st, p, items);
   else if (g.kv_dtype == PS_FP8_E4M3)
-    hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3>), grid, block, 0, st, p, items);
+    hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1>), grid, block, 0, st, p, items);
   else
     return PS_ERR_UNSUPPORTED;
   return PS_OK;

@@ -172,3 +172,17 @@ def test_rows_with_one_partial_state_match_the_merged_ones(gpu, kv_dtype):
         assert torch.equal(whole[0].view(torch.int16), case.batch.out.view(torch.int16))
         case.batch.q, case.batch.out = own_q, own_out
     case.close()
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+def test_prefill_ring_edges(gpu, kv_dtype):
+    """Token ranges that end in and around each of the first ten tiles: a ring of three stages of one or two tiles, filled
+    up to six tiles ahead; waves with all, some and none of their rows."""
+    geo = wl.Geometry(32, 8, 128, 16, "bf16", kv_dtype)
+    cached = [32 * k + e for k in range(0, 10) for e in (-20, -19, -18)][3:]
+    chunk = [18 + (i % 3) * 7 for i in range(len(cached))]
+    w, visible = wl.chunk_prefill_workload("ring_" + kv_dtype, geo, cached, chunk, pool_factor=1.2, seed=31)
+    case = gpu(w)
+    case.set_visible(visible)
+    _run(case, visible, w.name)
+    case.close()
