@@ -141,7 +141,52 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   // one).
   // (the prefill kernel walks a range of any length -- one scalar block id per tile -- so its items are not held to
   // the persistent kernel's 64 tiles per wave: the aim for them is the uncapped share, at most 32768 tokens)
+  // The share is one of the work, which counts a range once per row group that walks it, wherever such groups hold most of
+  // the batch's tokens: 160 new tokens with eight query rows each make five items per KV head and range, and cut by their
+  // tokens alone the contexts went out in pieces of 256 tokens, each costing twelve tiles on top of its eight (batches of 1
+  // to 44 contexts of 300 to 8500 tokens: 73.9 -> 42.8, 80.3 -> 48.7, 352 -> 276, 507 -> 441, 525 -> 432 us a step; shares of
+  // 0.6 of this are slower again).
+  int64_t wide_tokens = 0;
+  for (size_t p = 0; p < lay->prefix_len.size(); ++p)
+    if (int64_t(lay->group_indptr[p + 1] - lay->group_indptr[p]) * group > 64) wide_tokens += lay->prefix_len[p];
+  for (size_t t = 0; t < lay->root_len.size(); ++t)
+    if (int64_t(lay->root_group_indptr[t + 1] - lay->root_group_indptr[t]) * group > 64) wide_tokens += lay->root_len[t];
+  wide_tokens *= g.num_kv_heads;
+  const bool wide_shares = !lay->visible.empty() && resolve(opt.prefix_variant) == PS_VARIANT_MFMA &&
+                           opt.prefix_chunk_tokens == 0 && 2 * wide_tokens > total;
+  auto wide_work = [&](int64_t rows_per_item, int64_t chunk) {   // tokens (chunk 0) or items of the wide groups, per KV head
+    int64_t sum = 0;
+    auto add = [&](int64_t len, int64_t reqs) {
+      if (reqs * group <= 64 || len <= 0) return;
+      const int64_t walks = ceil_div(reqs, std::max<int64_t>(1, rows_per_item / group));
+      sum += walks * (chunk ? std::max<int64_t>(1, ceil_div(len - chunk / 4, chunk)) : len);   // (as chunking_shared cuts)
+    };
+    for (size_t p = 0; p < lay->prefix_len.size(); ++p) add(lay->prefix_len[p], lay->group_indptr[p + 1] - lay->group_indptr[p]);
+    for (size_t t = 0; t < lay->root_len.size(); ++t) add(lay->root_len[t], lay->root_group_indptr[t + 1] - lay->root_group_indptr[t]);
+    return sum;
+  };
+  auto wide_aim = [&](int64_t rows_per_item) {
+    const int64_t share = std::max<int64_t>(1, ceil_div(wide_work(rows_per_item, 0) * g.num_kv_heads, int64_t(num_cus)));
+    int64_t aim = std::max<int64_t>(round_up(share, granule), round_up(256, granule));
+    // a few items more than compute units make a second round of the launch: larger pieces instead, up to half as large
+    // again (264 items on 256 compute units 80.8 us, 168 larger ones 72.4 us)
+    for (int64_t most = aim * 3 / 2; aim < most; aim = round_up(aim + aim / 16, granule)) {
+      const int64_t items = wide_work(rows_per_item, aim) * g.num_kv_heads;
+      if (items <= num_cus || 2 * items > 3 * int64_t(num_cus)) break;
+    }
+    return std::min<int64_t>(aim, round_up(32768, granule));
+  };
+  // Rows per item: 256, or 128 where the batch is nothing but wide groups and even those, in pieces of at most 512 tokens,
+  // leave every item a compute unit of its own -- four waves, one per SIMD, then take a tile in less time than eight that
+  // share the SIMDs (32 / 120 / 96 / 88 / 176 / 232 items of 256 rows against 56 / 224 / 176 / 136 / 256 / 236 of 128: 13.5 /
+  // 14.6 / 15.1 / 23.6 / 27.8 / 30.9 us against 11.6 / 11.6 / 12.6 / 19.4 / 23.4 / 27.0).  With more items, or longer ones,
+  // the tiles are fetched twice as often for nothing (376 items of 256 rows 29.6 us, 624 of 128 rows 31.1 us; 240 items of 28
+  // tiles 47.1, 216 of 55 tiles 56.8 us).
+  lay->rowsplit_rows = 256;
+  if (wide_shares && wide_tokens == total && wide_aim(128) <= 512 && wide_work(128, wide_aim(128)) * g.num_kv_heads <= num_cus)
+    lay->rowsplit_rows = 128;
   const int64_t wide_chunk = opt.prefix_chunk_tokens > 0 ? prefix_chunk
+                             : wide_shares ? wide_aim(lay->rowsplit_rows)
                              : std::min<int64_t>(std::max<int64_t>(round_up(ideal, granule), round_up(256, granule)), round_up(32768, granule));
   auto chunking_shared = [&](int64_t len, int64_t chunk, int32_t* n) -> int64_t {
     if (len <= 0) { *n = 0; return chunk; }
@@ -190,7 +235,7 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
     const int64_t size = wide ? chunking_shared(lay->root_len[size_t(t)], wide_chunk, &n) : chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
     for (int32_t i = 0; i < count; ++i) nsplit_root[size_t(lay->root_group_req[size_t(g0 + i)])] = n;
     const bool row_split = limited && prefix_mfma && int64_t(count) * group > 64;
-    const int32_t per_item = row_split ? std::max(1, 256 / group) : max_req;
+    const int32_t per_item = row_split ? std::max(1, lay->rowsplit_rows / group) : max_req;
     // Row groups outside, KV heads inside: items of equal cost reach the workgroups in this order (LPT, lowest
     // index on ties) and workgroup i runs on XCD i mod 8, so with a multiple of eight KV heads the row groups that
     // read one (range, head) start together on one XCD and share its L2.
@@ -225,7 +270,7 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
       if (reqs * group <= 64 || lay->prefix_len[p] <= 0) continue;
       int32_t n0 = 0;
       const int64_t size0 = chunking_shared(lay->prefix_len[p], wide_chunk, &n0);
-      const int64_t per_item = std::max(1, 256 / group);
+      const int64_t per_item = std::max(1, lay->rowsplit_rows / group);
       const wide_prompt e{p, ceil_div(reqs, per_item) * g.num_kv_heads * n0, ceil_div(std::min<int64_t>(size0, lay->prefix_len[p]), 32)};
       wp.push_back(e);
       n_items += e.items;
@@ -296,7 +341,7 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
       // tokens of a context) goes out in items of up to 256 rows, which the prefill kernel splits over its waves
       // by rows, so that a K/V tile is fetched once per 256 rows instead of once per 64.
       const bool row_split = limited && prefix_mfma && int64_t(count) * group > 64;
-      const int32_t per_item = row_split ? std::max(1, 256 / group) : max_req;
+      const int32_t per_item = row_split ? std::max(1, lay->rowsplit_rows / group) : max_req;
       for (int32_t m0 = 0; m0 < count; m0 += per_item)      // row groups outside, heads inside (see the roots)
         for (int32_t h = 0; h < g.num_kv_heads; ++h) {
           ps_item it{};

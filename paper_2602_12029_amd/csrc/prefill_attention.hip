@@ -6,7 +6,8 @@
 // step has a few dozen -- so the work is a dense contraction and the matrix cores, not HBM, are the bound.
 //
 // One workgroup of eight waves takes one work item: a token range of one context and KV head, and up to 256 query
-// rows that see into it.  The rows are split over the waves, 32 each (the query rows resident in registers as MFMA
+// rows that see into it (four waves and 128 rows where the planner finds that enough, each then fetching two eighths of
+// a tile).  The rows are split over the waves, 32 each (the query rows resident in registers as MFMA
 // B operands), and every wave walks the token range.  Two waves share a SIMD, so that the vector work of one
 // (exponentials, conversions) runs under the matrix instructions of the other.
 //
@@ -42,7 +43,6 @@ namespace psdev {
 namespace {
 
 constexpr int kD = kHeadDim;
-constexpr int kWaves = 8;         // per workgroup
 constexpr int kRowsPerWave = 32;  // one 32-row tile per wave
 constexpr int kTile = kTileTokens;
 constexpr float kLazy = kLazyRescale;
@@ -67,14 +67,15 @@ __device__ __forceinline__ int wave_max(int x) {
 
 }  // namespace
 
-// TPB: tiles per ring stage, and per barrier.
-template <int KVT, int TPB>
-__global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnParams p, const ps_item* __restrict__ items) {
+// TPB: tiles per ring stage, and per barrier.  W: waves, eight or four.
+template <int KVT, int TPB, int W>
+__global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams p, const ps_item* __restrict__ items) {
   constexpr int kStages = 3 * TPB;
   __shared__ u32x4 sm_k[kStages][8][64];   // [stage][k-step][lane]: K as that lane's A operand
   __shared__ u32x4 sm_v[kStages][8][64];   // [stage][2 * column class + 16-token step][lane]: V^T as that lane's A operand
   __shared__ f32x4 sm_sc[kStages][2];      // e4m3: [stage][block] = (score scale in log2 units, log2 of the V scale, 1 / V scale, -)
-  __shared__ int sm_see[kWaves];
+  __shared__ int sm_see[W];
+  constexpr int kShares = 8 / W;   // eighths of a tile a wave fetches: one, or the same place of both 16-token blocks
   const ps_item* it = items + blockIdx.x;
   const int blk_off = __builtin_amdgcn_readfirstlane(it->blk_off);
   const int tok_begin = __builtin_amdgcn_readfirstlane(it->tok_begin);
@@ -114,48 +115,55 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
   // 8 n + 4 (kg % 2) + x, x = 0 .. 3 -- the pair is register wave % 4 of lane (n + 16 (kg % 2), kg / 2) = this very
   // lane in the operand of column class x and step fblk; the operand's row lane % 32 is thus column
   // 8 (lane % 16) + 4 (lane / 16 % 2) + x, which the epilogue undoes.
-  const int fblk = wave >> 2, kst = wave & 3;
+  const int kst = wave & 3;
+  auto fblk = [&](int s) __attribute__((always_inline)) { return W == 8 ? wave >> 2 : s; };   // block of the wave's share s
   const int vreg = wave & 3;
   const int vrow = 4 * (kg >> 1) + 8 * ((wave >> 1) & 1) + 2 * (wave & 1);
   const int k_lane_off = n * tok_bytes + (32 * kst + 8 * kg) * kEsz;
   const int v_lane_off = kv_bytes + vrow * tok_bytes + (8 * n + 4 * (kg & 1)) * kEsz;
-  const int k_op = 2 * kst + (kg >> 1), k_slot = 16 * fblk + n + 32 * (kg & 1);
+  const int k_op = 2 * kst + (kg >> 1), k_slot = n + 32 * (kg & 1);
   // (constant address space: the table is read-only for the kernel's lifetime, which keeps the load a scalar one
   // whatever stands around it)
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const const_i32_ptr blk_seg = (const_i32_ptr)(p.blk + blk_off);
 
-  struct TileIds { int id; };   // of this wave's block of the tile
+  struct TileIds { int id[kShares]; };   // of this wave's block(s) of the tile
   auto fetch_ids = [&](int k) __attribute__((always_inline)) {   // wave-uniform
     // no branch around this load (the index is clamped into the range instead), so that the counting of
     // outstanding loads in the streaming loop stays exact; a block past the range is never fetched from
     TileIds r;
-    const int sub = max(sub0, min(sub0 + 2 * k + fblk, sub_end - 1));
-    r.id = blk_seg[sub >> sub_shift];
+#pragma unroll
+    for (int s = 0; s < kShares; ++s) {
+      const int sub = max(sub0, min(sub0 + 2 * k + fblk(s), sub_end - 1));
+      r.id[s] = blk_seg[sub >> sub_shift];
+    }
     return r;
   };
-  // this wave's share of a tile, as loaded
+  // this wave's share(s) of a tile, as loaded
   struct Fetched {
-    std::conditional_t<KVT == PS_BF16, u32x4, u32x2> k;         // 8 elements of one token
-    std::conditional_t<KVT == PS_BF16, u32x2, uint32_t> v[2];   // 4 columns of two token rows
-    f32x2 sc;                                                   // e4m3: K and V scale of the block
+    std::conditional_t<KVT == PS_BF16, u32x4, u32x2> k[kShares];         // 8 elements of one token
+    std::conditional_t<KVT == PS_BF16, u32x2, uint32_t> v[kShares][2];   // 4 columns of two token rows
+    f32x2 sc[kShares];                                                   // e4m3: K and V scale of the block
   };
   auto fetch = [&](Fetched& f, const TileIds& ids, int k) __attribute__((always_inline)) {
-    const int sub = sub0 + 2 * k + fblk;
-    const bool valid = sub < sub_end;   // a block past the range gets a zero-sized descriptor: zeros, no traffic
-    const uint64_t addr = uint64_t(head_base) + uint64_t(uint32_t(ids.id)) * blk_bytes + uint32_t((sub & sub_mask) * sub_bytes);
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, valid ? 0x7fffffff : 0, 0x00020000);
-    if constexpr (KVT == PS_BF16) {
-      f.k = __builtin_amdgcn_raw_buffer_load_b128(rs, k_lane_off, 0, 0);
-      f.v[0] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, 0, 0);
-      f.v[1] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, tok_bytes, 0);
-    } else {
-      f.k = __builtin_amdgcn_raw_buffer_load_b64(rs, k_lane_off, 0, 0);
-      f.v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, 0, 0);
-      f.v[1] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, tok_bytes, 0);
-      // (the block id is clamped into the range, so the scales of a tile past it are some block's: never used)
-      f.sc = *reinterpret_cast<const f32x2*>(p.scales + (int64_t(ids.id) * p.num_kv_heads + kv_head) * 2);
+#pragma unroll
+    for (int s = 0; s < kShares; ++s) {
+      const int sub = sub0 + 2 * k + fblk(s);
+      const bool valid = sub < sub_end;   // a block past the range gets a zero-sized descriptor: zeros, no traffic
+      const uint64_t addr = uint64_t(head_base) + uint64_t(uint32_t(ids.id[s])) * blk_bytes + uint32_t((sub & sub_mask) * sub_bytes);
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, valid ? 0x7fffffff : 0, 0x00020000);
+      if constexpr (KVT == PS_BF16) {
+        f.k[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_lane_off, 0, 0);
+        f.v[s][0] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, 0, 0);
+        f.v[s][1] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, tok_bytes, 0);
+      } else {
+        f.k[s] = __builtin_amdgcn_raw_buffer_load_b64(rs, k_lane_off, 0, 0);
+        f.v[s][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, 0, 0);
+        f.v[s][1] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, tok_bytes, 0);
+        // (the block id is clamped into the range, so the scales of a tile past it are some block's: never used)
+        f.sc[s] = *reinterpret_cast<const f32x2*>(p.scales + (int64_t(ids.id[s]) * p.num_kv_heads + kv_head) * 2);
+      }
     }
   };
   // The first two tiles and the block ids of the next two are requested at once, from the item's header alone: what
@@ -196,7 +204,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
   __syncthreads();
   int see_end_wg = tok_begin;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) see_end_wg = max(see_end_wg, sm_see[w]);
+  for (int w = 0; w < W; ++w) see_end_wg = max(see_end_wg, sm_see[w]);
   see_end_wg = __builtin_amdgcn_readfirstlane(see_end_wg);
   const int n_tiles_wg = (see_end_wg - tok_begin + kTile - 1) / kTile;   // tiles the workgroup fetches
   const int n_tiles = has_rows ? (see_end - tok_begin + kTile - 1) / kTile : 0;   // tiles this wave multiplies
@@ -208,35 +216,39 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
   // in the operand of column class x holds column 8 n + 4 (kg % 2) + x of the token rows (vrow, vrow + 1)
   // ragged_tag: std::true_type = the tile may be the item's last, which can reach past its range
   auto publish = [&](const Fetched& f, int stage, int k, auto ragged_tag) __attribute__((always_inline)) {
-    if constexpr (KVT == PS_BF16) {
-      sm_k[stage][k_op][k_slot] = f.k;
-    } else {
-      sm_k[stage][k_op][k_slot] = e4m3x8_to_bf16x8(f.k.x, f.k.y);
-      // the block's scales, once per workgroup: the K scale folded into the score scale, the V scale as the exponent
-      // offset of the probabilities and as the factor that takes it out of the row sums again
-      if (kst == 0 && lane == 0) {
-        const float lv = __builtin_amdgcn_logf(f.sc.y);
-        sm_sc[stage][fblk] = f32x4{p.scale_log2 * f.sc.x, lv, fast_exp2(-lv), 0.f};
+#pragma unroll
+    for (int s = 0; s < kShares; ++s) {
+      const int b = fblk(s);
+      if constexpr (KVT == PS_BF16) {
+        sm_k[stage][k_op][16 * b + k_slot] = f.k[s];
+      } else {
+        sm_k[stage][k_op][16 * b + k_slot] = e4m3x8_to_bf16x8(f.k[s].x, f.k[s].y);
+        // the block's scales, once per workgroup: the K scale folded into the score scale, the V scale as the exponent
+        // offset of the probabilities and as the factor that takes it out of the row sums again
+        if (kst == 0 && lane == 0) {
+          const float lv = __builtin_amdgcn_logf(f.sc[s].y);
+          sm_sc[stage][b] = f32x4{p.scale_log2 * f.sc[s].x, lv, fast_exp2(-lv), 0.f};
+        }
       }
-    }
-    // slots of tokens past the item's range may hold anything: zero them (their probabilities are zero)
-    auto v0 = f.v[0], v1 = f.v[1];
-    if (decltype(ragged_tag)::value && tok_begin + kTile * (k + 1) > tok_end) {   // (only the item's last tile can)
-      const int tok = tok_begin + kTile * k + 16 * fblk + vrow;
-      if (tok >= tok_end) v0 = decltype(v0){};
-      if (tok + 1 >= tok_end) v1 = decltype(v1){};
-    }
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&sm_v[stage][fblk][lane]) + vreg;   // operand 2 x + fblk
-    if constexpr (KVT == PS_BF16) {
+      // slots of tokens past the item's range may hold anything: zero them (their probabilities are zero)
+      auto v0 = f.v[s][0], v1 = f.v[s][1];
+      if (decltype(ragged_tag)::value && tok_begin + kTile * (k + 1) > tok_end) {   // (only the item's last tile can)
+        const int tok = tok_begin + kTile * k + 16 * b + vrow;
+        if (tok >= tok_end) v0 = decltype(v0){};
+        if (tok + 1 >= tok_end) v1 = decltype(v1){};
+      }
+      uint32_t* dst = reinterpret_cast<uint32_t*>(&sm_v[stage][b][lane]) + vreg;   // operand 2 x + b
+      if constexpr (KVT == PS_BF16) {
 #pragma unroll
-      for (int x = 0; x < 4; ++x)   // low (even column) or high (odd column) halves of the two rows: one byte permute
-        dst[x * 2 * 64 * 4] = __builtin_amdgcn_perm(v1[x >> 1], v0[x >> 1], (x & 1) ? 0x07060302u : 0x05040100u);
-    } else {
+        for (int x = 0; x < 4; ++x)   // low (even column) or high (odd column) halves of the two rows: one byte permute
+          dst[x * 2 * 64 * 4] = __builtin_amdgcn_perm(v1[x >> 1], v0[x >> 1], (x & 1) ? 0x07060302u : 0x05040100u);
+      } else {
 #pragma unroll
-      for (int cp = 0; cp < 2; ++cp) {   // the codes of columns (2 cp, 2 cp + 1) of the two rows, then converted
-        const uint32_t pair = __builtin_amdgcn_perm(v1, v0, cp ? 0x07030602u : 0x05010400u);
-        dst[(2 * cp) * 2 * 64 * 4] = e4m3x2_to_bf16x2(pair, false);
-        dst[(2 * cp + 1) * 2 * 64 * 4] = e4m3x2_to_bf16x2(pair, true);
+        for (int cp = 0; cp < 2; ++cp) {   // the codes of columns (2 cp, 2 cp + 1) of the two rows, then converted
+          const uint32_t pair = __builtin_amdgcn_perm(v1, v0, cp ? 0x07030602u : 0x05010400u);
+          dst[(2 * cp) * 2 * 64 * 4] = e4m3x2_to_bf16x2(pair, false);
+          dst[(2 * cp + 1) * 2 * 64 * 4] = e4m3x2_to_bf16x2(pair, true);
+        }
       }
     }
   };
@@ -501,19 +513,19 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_attention_kernel(AttnPara
 }
 
 int32_t launch_prefill_attention(const AttnParams& p, const ps_geometry& g, const ps_item* items, int num_items,
-                                 hipStream_t st) {
+                                 int rows, hipStream_t st) {
   if (num_items <= 0) return PS_OK;
   const int spb = g.block_size / 16;
   if (g.head_dim != kD || g.q_dtype != PS_BF16 || g.block_size % 16 != 0 || (spb & (spb - 1)) != 0)
     return PS_ERR_UNSUPPORTED;
-  const dim3 grid(num_items), block(64 * kWaves);
-  // Tiles per barrier: two with bf16 KV (32 contexts of 4096 + 64..256 tokens 464 -> 452 us a step, the waves of a SIMD
-  // drifting apart by up to a tile), one with e4m3, where the second changes nothing (64 contexts of 8192 tokens 3289 /
-  // 3298 us, 3302 / 3301 us) and the ring takes half the LDS.
-  if (g.kv_dtype == PS_BF16)
-    hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 2>), grid, block, 0, st, p, items);
-  else if (g.kv_dtype == PS_FP8_E4M3)
-    hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1>), grid, block, 0, st, p, items);
+  const dim3 grid(num_items);
+  if (g.kv_dtype == PS_BF16) {
+    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 1, 4>), grid, dim3(256), 0, st, p, items);
+    else hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 2, 8>), grid, dim3(512), 0, st, p, items);
+  } else if (g.kv_dtype == PS_FP8_E4M3) {
+    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1, 4>), grid, dim3(256), 0, st, p, items);
+    else hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1, 8>), grid, dim3(512), 0, st, p, items);
+  }
   else
     return PS_ERR_UNSUPPORTED;
   return PS_OK;

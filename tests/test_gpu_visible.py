@@ -174,15 +174,20 @@ def test_rows_with_one_partial_state_match_the_merged_ones(gpu, kv_dtype):
     case.close()
 
 
+@pytest.mark.parametrize("heads,rows", [((32, 8), 128), ((64, 8), 256)])
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
-def test_prefill_ring_edges(gpu, kv_dtype):
+def test_prefill_ring_edges(gpu, kv_dtype, heads, rows):
     """Token ranges that end in and around each of the first ten tiles: a ring of three stages of one or two tiles, filled
-    up to six tiles ahead; waves with all, some and none of their rows."""
-    geo = wl.Geometry(32, 8, 128, 16, "bf16", kv_dtype)
+    up to six tiles ahead, by four and by eight waves; waves with all, some and none of their rows."""
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(heads[0], heads[1], 128, 16, "bf16", kv_dtype)
     cached = [32 * k + e for k in range(0, 10) for e in (-20, -19, -18)][3:]
     chunk = [18 + (i % 3) * 7 for i in range(len(cached))]
     w, visible = wl.chunk_prefill_workload("ring_" + kv_dtype, geo, cached, chunk, pool_factor=1.2, seed=31)
     case = gpu(w)
     case.set_visible(visible)
+    items = B.ps_layout_plan(case.layout, w.num_requests)["items"]
+    most = int(items[(items[:, 7] & 4) != 0][:, 4].max()) * geo.group
+    assert (most <= 128) if rows == 128 else (128 < most <= 256)
     _run(case, visible, w.name)
     case.close()
