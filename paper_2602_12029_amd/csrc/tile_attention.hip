@@ -27,7 +27,9 @@ template <int D>
 bool dispatch(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin, int n_items, hipStream_t st) {
 #define PS_CASE(KVT, QT)                                                              \
   if (g.kv_dtype == KVT && g.q_dtype == QT) {                                         \
-    if (stream) launch_as<D, KVT, QT, true>(p, max_rows, item_begin, n_items, st);    \
+    /* an item with more rows than a pass carries walks its tokens again: they should still be in the caches then */ \
+    if (stream && max_rows <= 16 * wide_tiles<D, KVT, QT>())                          \
+      launch_as<D, KVT, QT, true>(p, max_rows, item_begin, n_items, st);              \
     else launch_as<D, KVT, QT, false>(p, max_rows, item_begin, n_items, st);          \
     return true;                                                                      \
   }
