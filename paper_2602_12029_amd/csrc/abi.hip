@@ -95,7 +95,11 @@ struct StagingPool {
   std::vector<ps_layout::upload_staging*> kept;
 };
 StagingPool& staging_pool() {
-  static StagingPool* pool = new StagingPool;
+  static StagingPool* pool = [] {
+    StagingPool* p = new StagingPool;
+    p->kept.reserve(kKeptStagings);   // (so that giving one back never allocates)
+    return p;
+  }();
   return *pool;
 }
 void free_upload_staging(ps_layout::upload_staging* s) {
@@ -118,7 +122,11 @@ ps_layout::upload_staging* take_upload_staging(int device) {
       ps_layout::upload_staging* s = pool.kept[k];
       bool idle = s->device == device;
       for (int i = 0; i < 2 && idle; ++i) {
-        if (s->in_use[i] && hipEventQuery(s->done[i]) == hipSuccess) s->in_use[i] = false;
+        if (s->in_use[i]) {
+          const hipError_t e = hipEventQuery(s->done[i]);
+          if (e == hipSuccess) s->in_use[i] = false;
+          else if (e == hipErrorNotReady) (void)hipGetLastError();   // no error of the launches to come
+        }
         idle = !s->in_use[i];
       }
       if (!idle) continue;

@@ -55,7 +55,8 @@ bool ps_mfma_supported(const ps_geometry& g) {
 // ---------------------------------------------------------------------------------------------------
 // Split plan: cut every segment into token chunks of (nearly) equal size, one workgroup each; a
 // request's partial states are numbered prefix chunks first, then its suffix chunks.
-int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
+// fewer_states: larger chunks where the rules below would cut finer for speed alone (see ps_plan_build).
+static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewer_states) {
   ps_plan_options opt{};
   if (user) opt = *user;
   if (opt.prefix_chunk_tokens < 0 || opt.suffix_chunk_tokens < 0 || opt.num_cus < 0) return PS_ERR_INVALID_ARG;
@@ -110,7 +111,7 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, 2 * int64_t(num_cus)));
   auto pick = [&](int32_t asked, int32_t variant) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
-    const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0;
+    const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && !fewer_states;
     return std::min<int64_t>(std::max<int64_t>(round_up(tiles ? tile_ideal : ideal, granule), round_up(tiles ? 128 : 256, granule)),
                              round_up(kPsMfmaMaxChunk, granule));
   };
@@ -153,7 +154,7 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
     if (int64_t(lay->root_group_indptr[t + 1] - lay->root_group_indptr[t]) * group > 64) wide_tokens += lay->root_len[t];
   wide_tokens *= g.num_kv_heads;
   const bool wide_shares = !lay->visible.empty() && resolve(opt.prefix_variant) == PS_VARIANT_MFMA &&
-                           opt.prefix_chunk_tokens == 0 && 2 * wide_tokens > total;
+                           opt.prefix_chunk_tokens == 0 && 2 * wide_tokens > total && !fewer_states;
   auto wide_work = [&](int64_t rows_per_item, int64_t chunk) {   // tokens (chunk 0) or items of the wide groups, per KV head
     int64_t sum = 0;
     auto add = [&](int64_t len, int64_t reqs) {
@@ -529,6 +530,20 @@ int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   lay->pk_suffix = suf_mfma ? pack(lay->num_prefix_items, n_items) : packed{};
   lay->pk_all = (pre_mfma && suf_mfma) ? pack(first_packed, n_items) : packed{};
   return ps_blob_build(lay);
+}
+
+// The plan by the rules for speed; where its partial states outgrow the static workspace and coarser chunks would keep
+// them inside it, the coarser plan (ps_decode_attention_static serves such a batch).
+int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
+  if (int32_t rc = build_plan(lay, user, false)) return rc;
+  const bool finer = lay->prefix_variant == PS_VARIANT_WAVE || lay->suffix_variant == PS_VARIANT_WAVE || lay->num_rowsplit_items > 0;
+  if (!finer || ps_workspace_bytes(lay) <= PS_STATIC_WORKSPACE_BYTES) return PS_OK;
+  int64_t least = 0;   // one state for every request that has any
+  for (int32_t r = 0; r < lay->num_requests; ++r) least += lay->slot_base[size_t(r) + 1] > lay->slot_base[size_t(r)];
+  if (least * lay->geo.num_q_heads * (lay->geo.head_dim + 1) * 4 > PS_STATIC_WORKSPACE_BYTES) return PS_OK;
+  const ps_plan_options opt = lay->opt;
+  if (int32_t rc = build_plan(lay, &opt, true)) return rc;
+  return ps_workspace_bytes(lay) <= PS_STATIC_WORKSPACE_BYTES ? PS_OK : build_plan(lay, &opt, false);
 }
 
 // Lays the tables out for the device: everything the kernels read, as one int32 blob.

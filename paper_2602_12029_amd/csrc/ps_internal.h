@@ -24,7 +24,7 @@ struct ps_item {
   int32_t split_local;  // partial-state slot of request r is slot_base[r] + split_local
   int32_t kind;         // bit 0: 0 prefix, 1 suffix; bit 1: some row of the item sees less than tok_end
 };
-// bit 2: up to 256 rows, split over the four waves of a workgroup by rows instead of by tokens (partial prefill)
+// bit 2: up to 256 rows, split over the waves of a workgroup by rows instead of by tokens (partial prefill)
 // bit 3: a root segment (a context several prompts begin with), read by every request below the root
 // bit 4: other items (further row groups of the same sharing group) read the same K/V range: keep it cacheable
 constexpr int32_t kPsItemSuffix = 1, kPsItemMasked = 2, kPsItemRowSplit = 4, kPsItemRoot = 8, kPsItemReread = 16;

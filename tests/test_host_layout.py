@@ -808,3 +808,19 @@ def test_long_prefill_chunks_fall_back_where_few_requests_see_far():
     assert np.all(items[:, 7] & 4) and (items[:, 2] - items[:, 1]).max() > 8192
     B.ps_layout_release(pool, lay)
     B.ps_pool_destroy(pool)
+
+
+def test_default_plans_stay_inside_the_static_workspace_where_coarser_chunks_do():
+    """Finer chunks (half a compute unit's share in the tile kernel, work shares in a partial prefill) are taken back where
+    they would push a batch past the 64 MiB of ps_decode_attention_static that whole shares keep it under."""
+    geo = wl.Geometry(32, 8, 128, 16, "f32", "f32")
+    for models, chunks in ((36, 1), (24, 2), (90, 2)):
+        w = wl.make_workload("static", geo, models, [4096] * 40, [list(range(models))] * 40, [16] * (40 * models))
+        pool, lay, _, _ = _both(w)
+        plan = B.ps_layout_plan(lay, w.num_requests)
+        # 36 models: three states a request would be 71 MiB, two are 45; 24: three fit; 90: not even two do
+        assert (np.diff(plan["slot_base"]) == chunks + 1).all()
+        assert (B.ps_workspace_bytes(lay) <= B.PS_STATIC_WORKSPACE_BYTES) == (models < 90)
+        _check_plan(w, lay, plan)
+        B.ps_layout_release(pool, lay)
+        B.ps_pool_destroy(pool)
