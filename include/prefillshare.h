@@ -53,7 +53,7 @@ enum {
 enum { PS_F32 = 0, PS_BF16 = 1, PS_FP8_E4M3 = 2 /* OCP e4m3fn, KV only */ };
 
 /* kernel family used for a pass */
-enum { PS_VARIANT_AUTO = 0, PS_VARIANT_WAVE = 1 /* fp32 wavefront-reduction */, PS_VARIANT_MFMA = 2 };
+enum { PS_VARIANT_AUTO = 0, PS_VARIANT_WAVE = 1 /* float32 probabilities */, PS_VARIANT_MFMA = 2 };
 
 typedef struct ps_pool ps_pool;     /* host: free list + refcounts of the physical blocks          */
 typedef struct ps_layout ps_layout; /* host: block tables, sharing groups and split plan of a batch */
