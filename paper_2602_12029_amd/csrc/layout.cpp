@@ -636,16 +636,16 @@ int32_t ps_blob_build(ps_layout* lay) {
       // staging copies: 5.8 against 5.2 TB/s).
       auto by_block = [&](const std::vector<int32_t>& blk, int32_t* order) {
         if (blk.empty()) return;
-        // (a segment's blocks are distinct; where they fill a good part of their range of ids they are laid out by id,
-        // otherwise sorted)
+        // (where the ids fill a good part of their range they are laid out by id, otherwise sorted; a permutation either
+        // way, also of ids that repeat -- a parked layout's are all -1)
         const auto range = std::minmax_element(blk.begin(), blk.end());
         const int32_t lowest = *range.first;
         const size_t span = size_t(int64_t(*range.second) - lowest + 1);
         if (span <= 16 * blk.size()) {
-          std::vector<int32_t> at(span, -1);
-          for (size_t i = 0; i < blk.size(); ++i) at[size_t(blk[i] - lowest)] = int32_t(i);
-          for (int32_t i : at)
-            if (i >= 0) *order++ = i;
+          std::vector<int32_t> at(span, 0);      // entries with a smaller id, then the next position of an id
+          for (int32_t b2 : blk) ++at[size_t(b2 - lowest)];
+          std::exclusive_scan(at.begin(), at.end(), at.begin(), 0);
+          for (size_t i = 0; i < blk.size(); ++i) order[at[size_t(blk[i] - lowest)]++] = int32_t(i);
         } else {
           std::iota(order, order + blk.size(), 0);
           std::sort(order, order + blk.size(), [&](int32_t a, int32_t b2) { return blk[size_t(a)] < blk[size_t(b2)]; });
@@ -1033,6 +1033,9 @@ int32_t ps_layout_resume(ps_pool* pool, ps_layout* lay) {
   if (blocks_of(lay) > int64_t(pool->free_list.size())) return PS_ERR_OOM;
   take_blocks(pool, lay);
   lay->parked = false;
+  lay->ent_fixed_tok0.clear();   // a plan made while parked worked the directory out without blocks
+  lay->ent_fixed_valid.clear();
+  lay->ent_fixed_order.clear();
   return ps_plan_build(lay, &lay->opt);   // options that were accepted before cannot fail
 }
 
