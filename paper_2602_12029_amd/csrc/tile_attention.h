@@ -195,18 +195,23 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
       fetch(buf[u], at[u]);
     }
     at[S::kRing - 1] = locate(S::kRing - 1);
-    // e4m3: score scale and V scale of a tile's blocks
-    struct Scales { float k[S::kBlocks], v[S::kBlocks]; };
+    // e4m3: score scale and V scale of a tile's blocks.  A K scale may be anything finite that a caller's own quantiser
+    // writes: zero (a tile of zeros by amax / 448) goes in as 2^-100, which leaves the scores 0 to the last digit and a masked
+    // slot -inf; the sign of a negative one is moved to the scores (`flip`, scalar).
+    struct Scales { float k[S::kBlocks], v[S::kBlocks]; bool flip[S::kBlocks]; };
     auto scales_of = [&](const Place& pl) __attribute__((always_inline)) {
       Scales sc;
 #pragma unroll
       for (int b = 0; b < S::kBlocks; ++b) {
         sc.k[b] = p.scale_log2;
         sc.v[b] = 1.f;
+        sc.flip[b] = false;
         if constexpr (KVT == PS_FP8_E4M3) {
           typedef const __attribute__((address_space(4))) float* const_f32_ptr;
           const const_f32_ptr s2 = (const_f32_ptr)(p.scales + (int64_t(pl.id[b]) * p.num_kv_heads + kv_head) * 2);
-          sc.k[b] *= s2[0];
+          const uint32_t bits = __float_as_uint(s2[0]), size = bits & 0x7fffffffu;
+          sc.k[b] *= __uint_as_float(size ? size : __float_as_uint(0x1p-100f));
+          sc.flip[b] = (bits >> 31) != 0;
           sc.v[b] = s2[1];
         }
       }
@@ -326,6 +331,13 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
             __builtin_amdgcn_sched_barrier(0);
           }
         }
+      }
+      if constexpr (KVT == PS_FP8_E4M3) {
+#pragma unroll
+        for (int b = 0; b < S::kBlocks; ++b)
+          if (sc.flip[b])
+#pragma unroll
+            for (int t = 0; t < M; ++t) s[t][b] = -s[t][b];
       }
       // ---- slots past the range may hold anything: their scores are -inf and their V rows zero
       if (!whole) {

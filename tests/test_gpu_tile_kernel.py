@@ -135,3 +135,22 @@ def test_infinite_values(kv, q):
     assert np.array_equal(np.where(np.isinf(got), got, 0.0), want)
     assert not np.isnan(got).any()
     case.close()
+
+
+@pytest.mark.parametrize("block", [8, 16, 32])
+@pytest.mark.parametrize("q,d", [("bf16", 64), ("bf16", 128), ("f32", 128), ("f32", 256)])
+def test_scales_of_a_callers_own_quantiser(q, d, block):
+    """e4m3 tiles whose K or V scale is zero (a tile of zeros by amax / 448) or negative, in segments that end inside a tile and
+    under visible lengths; the same bars as above, since the oracle multiplies by the same scales."""
+    w = _workload(wl.Geometry(4, 2, d, block, q, "fp8_e4m3"), [2, 9, 1, 3, 5])
+    case = _case(w)
+    sc = case.data.scales
+    pick = np.random.default_rng(17).integers(0, 4, sc.shape)
+    sc[:] = np.where(pick == 0, 0.0, np.where(pick == 1, -sc, sc)).astype(np.float32)
+    case.batch.scales.copy_(torch.from_numpy(sc))
+    case.replan(0, 0, "wave", "wave")
+    _step(case)
+    visible = np.random.default_rng(5).integers(0, w.prefix_len[w.req_prompt] + 1)
+    case.set_visible(visible)
+    _step(case, visible)
+    case.close()
