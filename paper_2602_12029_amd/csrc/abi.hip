@@ -9,23 +9,30 @@
 #include "prefillshare_probe.h"
 #include <atomic>
 #include <cstring>
-#include <mutex>
 #include <new>
-#include <vector>
+
+#include "upload_staging.h"
 
 // Partial-state workspace for callers that cannot allocate (ps_decode_attention_static): part of the library's device
 // image, so every GPU the library runs on holds one copy at its own address until the process ends.  In host code
 // this name only stands for the symbol; its device address comes from hipGetSymbolAddress (static_workspace below).
 static __device__ __align__(256) unsigned char scratch[PS_STATIC_WORKSPACE_BYTES];
 
-struct ps_layout::upload_staging {
-  void* buffer[2] = {nullptr, nullptr};   // pinned host memory
-  size_t capacity[2] = {0, 0};
-  hipEvent_t done[2] = {nullptr, nullptr};   // recorded behind the copy that reads the buffer
-  bool in_use[2] = {false, false};
-  int next = 0;
-  int device = -1;   // of the events
+namespace {
+struct StagingRuntime {
+  typedef hipEvent_t Event;
+  static bool finished(Event e) {
+    const hipError_t status = hipEventQuery(e);
+    if (status == hipErrorNotReady) (void)hipGetLastError();   // no error of the launches to come
+    return status == hipSuccess;
+  }
+  static void wait(Event e) { (void)hipEventSynchronize(e); }
+  static void destroy(Event e) { (void)hipEventDestroy(e); }
+  static void free_host(void* p) { (void)hipHostFree(p); }
 };
+}  // namespace
+
+struct ps_layout::upload_staging : UploadStaging<StagingRuntime> {};
 
 namespace {
 
@@ -76,76 +83,13 @@ psdev::AttnParams make_params(const ps_layout* lay, const void* dev_tables, cons
   return p;
 }
 
-void destroy_upload_staging(ps_layout::upload_staging* s) {
-  for (int i = 0; i < 2; ++i) {
-    if (s->in_use[i]) (void)hipEventSynchronize(s->done[i]);
-    if (s->done[i]) (void)hipEventDestroy(s->done[i]);
-    if (s->buffer[i]) (void)hipHostFree(s->buffer[i]);
-  }
-  delete s;
-}
-
-// Staging of released layouts, kept for the next ones: taking and giving back pinned memory costs more (some 150 us a
-// layout: a turn of eight steps over sixteen contexts, laid out and released, takes 1.6 ms) than laying a batch out.
-// At most kKeptStagings of them with buffers of at most kKeptBytes are kept; all are given back when the last block
-// pool is destroyed.  The list is never destroyed itself (the HIP runtime may be gone by then).
-constexpr size_t kKeptStagings = 4, kKeptBytes = size_t(1) << 20;
-struct StagingPool {
-  std::mutex lock;
-  std::vector<ps_layout::upload_staging*> kept;
-};
-StagingPool& staging_pool() {
-  static StagingPool* pool = [] {
-    StagingPool* p = new StagingPool;
-    p->kept.reserve(kKeptStagings);   // (so that giving one back never allocates)
-    return p;
-  }();
+// (never destroyed itself: the HIP runtime may be gone by then)
+StagingPool<ps_layout::upload_staging, StagingRuntime>& staging_pool() {
+  static auto* pool = new StagingPool<ps_layout::upload_staging, StagingRuntime>;
   return *pool;
 }
-void free_upload_staging(ps_layout::upload_staging* s) {
-  if (s->capacity[0] <= kKeptBytes && s->capacity[1] <= kKeptBytes && s->device >= 0) {
-    StagingPool& pool = staging_pool();
-    const std::lock_guard<std::mutex> hold(pool.lock);
-    if (pool.kept.size() < kKeptStagings) {
-      pool.kept.push_back(s);   // a copy may still be reading a buffer: its event goes along
-      return;
-    }
-  }
-  destroy_upload_staging(s);
-}
-// One whose copies are done (so that its new owner never waits for another layout's stream), or a new one.
-ps_layout::upload_staging* take_upload_staging(int device) {
-  StagingPool& pool = staging_pool();
-  {
-    const std::lock_guard<std::mutex> hold(pool.lock);
-    for (size_t k = 0; k < pool.kept.size(); ++k) {
-      ps_layout::upload_staging* s = pool.kept[k];
-      bool idle = s->device == device;
-      for (int i = 0; i < 2 && idle; ++i) {
-        if (s->in_use[i]) {
-          const hipError_t e = hipEventQuery(s->done[i]);
-          if (e == hipSuccess) s->in_use[i] = false;
-          else if (e == hipErrorNotReady) (void)hipGetLastError();   // no error of the launches to come
-        }
-        idle = !s->in_use[i];
-      }
-      if (!idle) continue;
-      pool.kept.erase(pool.kept.begin() + std::ptrdiff_t(k));
-      return s;
-    }
-  }
-  ps_layout::upload_staging* s = new (std::nothrow) ps_layout::upload_staging();
-  if (s) s->device = device;
-  return s;
-}
-void drain_staging_pool() {
-  std::vector<ps_layout::upload_staging*> all;
-  {
-    const std::lock_guard<std::mutex> hold(staging_pool().lock);
-    all.swap(staging_pool().kept);
-  }
-  for (ps_layout::upload_staging* s : all) destroy_upload_staging(s);
-}
+void free_upload_staging(ps_layout::upload_staging* s) { staging_pool().give(s); }
+void drain_staging_pool() { staging_pool().drain(); }
 
 // Compute units of the current device (asked once per device), 0 if there is no device to ask: the planner's
 // default for ps_plan_options.num_cus = 0.
@@ -247,7 +191,7 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   if (!lay->staging) {
     int device = -1;
     if (int32_t st = check_hip(hipGetDevice(&device))) return st;
-    lay->staging = take_upload_staging(device);
+    lay->staging = staging_pool().take(device);
     if (!lay->staging) return PS_ERR_OOM;
     lay->staging_free = free_upload_staging;
   }
@@ -267,8 +211,10 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
     if (int32_t st = check_hip(hipHostMalloc(&s->buffer[i], want, hipHostMallocDefault))) return st;
     s->capacity[i] = want;
   }
-  if (!s->done[i])
+  if (!s->done[i]) {
+    if (int32_t st = check_hip(hipGetDevice(&s->device[i]))) return st;
     if (int32_t st = check_hip(hipEventCreateWithFlags(&s->done[i], hipEventDisableTiming))) return st;
+  }
   std::memcpy(s->buffer[i], lay->blob.data(), bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (bytes > kKernelUploadAbove && bytes <= kKernelUploadBytes && bytes % 16 == 0 && reinterpret_cast<uintptr_t>(dev_tables) % 16 == 0) {

@@ -1,0 +1,79 @@
+// Which upload buffers of released layouts are handed to other layouts (upload_staging.h), with a runtime of counters in
+// place of HIP.
+#include "upload_staging.h"
+
+#include <cstdio>
+#include <cstdlib>
+
+struct Event_ {
+  int device;
+  bool done;
+};
+struct Runtime {
+  typedef Event_* Event;
+  static inline int waits = 0, destroyed = 0, freed = 0;
+  static bool finished(Event e) { return e->done; }
+  static void wait(Event e) { ++waits; e->done = true; }
+  static void destroy(Event e) { ++destroyed; delete e; }
+  static void free_host(void*) { ++freed; }
+};
+typedef UploadStaging<Runtime> Staging;
+typedef StagingPool<Staging, Runtime> Pool;
+
+#define REQUIRE(x) do { if (!(x)) { std::printf("FAILED line %d: %s\n", __LINE__, #x); std::exit(1); } } while (0)
+
+static Staging* used(int device0, int device1, bool done = true) {   // two uploads behind it (device -1: not made)
+  Staging* s = new Staging;
+  const int device[2] = {device0, device1};
+  for (int i = 0; i < 2; ++i)
+    if (device[i] >= 0) {
+      s->done[i] = new Event_{device[i], done};
+      s->device[i] = device[i];
+      s->in_use[i] = true;
+      s->buffer[i] = s;
+      s->capacity[i] = 4096;
+    }
+  return s;
+}
+
+static void events_of_two_devices() {
+  Pool pool;
+  pool.give(used(0, 1));
+  REQUIRE(Runtime::freed == 2);                     // such a pair serves no one else
+  Staging* one = used(1, -1);
+  pool.give(one);
+  Staging* fresh = pool.take(0);
+  REQUIRE(fresh != one && !fresh->done[0]);
+  REQUIRE(pool.take(1) == one);
+  pool.give(fresh);
+  pool.give(one);
+  pool.drain();
+}
+
+static void finished_and_bounded() {
+  Pool pool;
+  Staging* busy = used(0, 0, false);
+  pool.give(busy);
+  Staging* other = pool.take(0);
+  REQUIRE(other != busy);                           // nobody waits for another layout's stream
+  busy->done[0]->done = busy->done[1]->done = true;
+  REQUIRE(pool.take(0) == busy && !busy->in_use[0] && !busy->in_use[1]);
+  delete other;
+  delete busy;
+  const int freed = Runtime::freed;
+  for (size_t i = 0; i < Pool::kKept + 3; ++i) pool.give(used(0, 0));
+  REQUIRE(Runtime::freed == freed + 2 * 3);
+  Staging* large = used(0, 0);
+  large->capacity[1] = Pool::kBytes + 1;
+  pool.give(large);
+  REQUIRE(Runtime::freed == freed + 2 * 4);
+  pool.drain();
+  REQUIRE(Runtime::freed == freed + 2 * (4 + int(Pool::kKept)));
+}
+
+int main() {
+  events_of_two_devices();
+  finished_and_bounded();
+  std::puts("ok");
+  return 0;
+}

@@ -9,7 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_12029_amd", "csrc")
 
 
-@pytest.mark.parametrize("program", ["block_order"])
+@pytest.mark.parametrize("program", ["block_order", "upload_staging"])
 def test_native(program, tmp_path):
     exe = str(tmp_path / program)
     subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
