@@ -21,11 +21,8 @@ static __device__ __align__(256) unsigned char scratch[PS_STATIC_WORKSPACE_BYTES
 namespace {
 struct StagingRuntime {
   typedef hipEvent_t Event;
-  static bool finished(Event e) {
-    const hipError_t status = hipEventQuery(e);
-    if (status == hipErrorNotReady) (void)hipGetLastError();   // no error of the launches to come
-    return status == hipSuccess;
-  }
+  static bool query(Event e) { return hipEventQuery(e) == hipSuccess; }
+  static void forget_error() { (void)hipGetLastError(); }
   static void wait(Event e) { (void)hipEventSynchronize(e); }
   static void destroy(Event e) { (void)hipEventDestroy(e); }
   static void free_host(void* p) { (void)hipHostFree(p); }

@@ -59,7 +59,11 @@ class StagingPool {
         Staging* s = kept_[k];
         bool idle = s->belongs_to(device);
         for (int i = 0; i < 2 && idle; ++i) {
-          if (s->in_use[i] && Runtime::finished(s->done[i])) s->in_use[i] = false;
+          if (s->in_use[i]) {
+            // (whatever else the answer is -- not ready, or an event that cannot be asked -- is no error of the launches to come)
+            if (Runtime::query(s->done[i])) s->in_use[i] = false;
+            else Runtime::forget_error();
+          }
           idle = !s->in_use[i];
         }
         if (!idle) continue;

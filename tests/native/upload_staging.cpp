@@ -8,11 +8,16 @@
 struct Event_ {
   int device;
   bool done;
+  bool refuses = false;   // cannot be asked
 };
 struct Runtime {
   typedef Event_* Event;
-  static inline int waits = 0, destroyed = 0, freed = 0;
-  static bool finished(Event e) { return e->done; }
+  static inline int waits = 0, destroyed = 0, freed = 0, last_error = 0;
+  static bool query(Event e) {
+    if (!e->done || e->refuses) last_error = e->refuses ? 2 : 1;
+    return e->done && !e->refuses;
+  }
+  static void forget_error() { last_error = 0; }
   static void wait(Event e) { ++waits; e->done = true; }
   static void destroy(Event e) { ++destroyed; delete e; }
   static void free_host(void*) { ++freed; }
@@ -71,9 +76,23 @@ static void finished_and_bounded() {
   REQUIRE(Runtime::freed == freed + 2 * (4 + int(Pool::kKept)));
 }
 
+static void answers_of_events_are_no_errors() {
+  for (bool refuses : {false, true}) {
+    Pool pool;
+    Staging* s = used(0, 0, refuses);
+    s->done[0]->refuses = s->done[1]->refuses = refuses;
+    pool.give(s);
+    Staging* fresh = pool.take(0);
+    REQUIRE(fresh != s && Runtime::last_error == 0);
+    delete fresh;
+    pool.drain();
+  }
+}
+
 int main() {
   events_of_two_devices();
   finished_and_bounded();
+  answers_of_events_are_no_errors();
   std::puts("ok");
   return 0;
 }
