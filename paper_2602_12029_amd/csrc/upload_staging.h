@@ -5,7 +5,6 @@
 #include <cstddef>
 #include <mutex>
 #include <new>
-#include <vector>
 
 template <class Runtime>
 struct UploadStaging {
@@ -30,20 +29,18 @@ struct UploadStaging {
 // Staging of released layouts, kept for the next ones: taking and giving back pinned memory costs more (some 150 us a
 // layout: a turn of eight steps over sixteen contexts, laid out and released, takes 1.6 ms) than laying a batch out.
 // At most kKept of them with buffers of at most kBytes are kept; all are given back when the last block pool is
-// destroyed.
+// destroyed.  The list is an array: giving one back happens where a layout is destroyed and must not allocate.
 template <class Staging, class Runtime>
 class StagingPool {
  public:
   static constexpr size_t kKept = 4, kBytes = size_t(1) << 20;
 
-  StagingPool() { kept_.reserve(kKept); }   // (so that giving one back never allocates)
-
   void give(Staging* s) {
     const bool one_device = s->done[0] ? s->belongs_to(s->device[0]) : true;
     if (s->capacity[0] <= kBytes && s->capacity[1] <= kBytes && one_device) {
       const std::lock_guard<std::mutex> hold(lock_);
-      if (kept_.size() < kKept) {
-        kept_.push_back(s);   // a copy may still be reading a buffer: its event goes along
+      if (count_ < kKept) {
+        kept_[count_++] = s;   // a copy may still be reading a buffer: its event goes along
         return;
       }
     }
@@ -55,7 +52,7 @@ class StagingPool {
   Staging* take(int device) {
     {
       const std::lock_guard<std::mutex> hold(lock_);
-      for (size_t k = 0; k < kept_.size(); ++k) {
+      for (size_t k = 0; k < count_; ++k) {
         Staging* s = kept_[k];
         bool idle = s->belongs_to(device);
         for (int i = 0; i < 2 && idle; ++i) {
@@ -67,7 +64,7 @@ class StagingPool {
           idle = !s->in_use[i];
         }
         if (!idle) continue;
-        kept_.erase(kept_.begin() + std::ptrdiff_t(k));
+        kept_[k] = kept_[--count_];
         return s;
       }
     }
@@ -75,15 +72,17 @@ class StagingPool {
   }
 
   void drain() {
-    std::vector<Staging*> all;
+    Staging* all[kKept];
+    size_t n = 0;
     {
       const std::lock_guard<std::mutex> hold(lock_);
-      all.swap(kept_);
+      for (; count_; ++n) all[n] = kept_[--count_];
     }
-    for (Staging* s : all) delete s;
+    for (size_t k = 0; k < n; ++k) delete all[k];
   }
 
  private:
   std::mutex lock_;
-  std::vector<Staging*> kept_;
+  Staging* kept_[kKept] = {};
+  size_t count_ = 0;
 };

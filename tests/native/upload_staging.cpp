@@ -5,6 +5,14 @@
 #include <cstdio>
 #include <cstdlib>
 
+static bool no_memory = false;
+void* operator new(size_t n) {
+  if (no_memory) throw std::bad_alloc();
+  return std::malloc(n ? n : 1);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
 struct Event_ {
   int device;
   bool done;
@@ -89,10 +97,23 @@ static void answers_of_events_are_no_errors() {
   }
 }
 
+static void giving_back_needs_no_memory() {
+  Pool pool;
+  for (int round = 0; round < 3; ++round) {
+    Staging* s[Pool::kKept + 1];
+    for (Staging*& one : s) one = used(0, 0);
+    no_memory = true;
+    for (Staging* one : s) pool.give(one);          // (from a destructor: an exception would end the process)
+    pool.drain();                                   // the last block pool is destroyed
+    no_memory = false;
+  }
+}
+
 int main() {
   events_of_two_devices();
   finished_and_bounded();
   answers_of_events_are_no_errors();
+  giving_back_needs_no_memory();
   std::puts("ok");
   return 0;
 }
