@@ -10,6 +10,7 @@ void* operator new(size_t n) {
   if (no_memory) throw std::bad_alloc();
   return std::malloc(n ? n : 1);
 }
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return no_memory ? nullptr : std::malloc(n ? n : 1); }
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, size_t) noexcept { std::free(p); }
 
