@@ -214,6 +214,8 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   }
   std::memcpy(s->buffer[i], lay->blob.data(), bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const bool unrecorded = s->unrecorded;
+  s->unrecorded = true;   // (until the event stands behind the copy: an error below may leave one under way)
   if (bytes > kKernelUploadAbove && bytes <= kKernelUploadBytes && bytes % 16 == 0 && reinterpret_cast<uintptr_t>(dev_tables) % 16 == 0) {
     void* src = nullptr;
     if (int32_t rc = check_hip(hipHostGetDevicePointer(&src, s->buffer[i], 0))) return rc;
@@ -226,6 +228,7 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   }
   if (int32_t rc = check_hip(hipEventRecord(s->done[i], st))) return rc;
   s->in_use[i] = true;
+  s->unrecorded = unrecorded;
   return PS_OK;
 }
 

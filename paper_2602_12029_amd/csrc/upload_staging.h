@@ -14,6 +14,7 @@ struct UploadStaging {
   int device[2] = {-1, -1};               // ... which each was created on: streams of another one refuse it
   bool in_use[2] = {false, false};
   int next = 0;
+  bool unrecorded = false;                // a buffer may be read by a copy that its event does not stand behind
 
   ~UploadStaging() {
     for (int i = 0; i < 2; ++i) {
@@ -37,7 +38,7 @@ class StagingPool {
 
   void give(Staging* s) {
     const bool one_device = s->done[0] ? s->belongs_to(s->device[0]) : true;
-    if (s->capacity[0] <= kBytes && s->capacity[1] <= kBytes && one_device) {
+    if (s->capacity[0] <= kBytes && s->capacity[1] <= kBytes && one_device && !s->unrecorded) {
       const std::lock_guard<std::mutex> hold(lock_);
       if (count_ < kKept) {
         kept_[count_++] = s;   // a copy may still be reading a buffer: its event goes along

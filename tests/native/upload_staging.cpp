@@ -110,11 +110,23 @@ static void giving_back_needs_no_memory() {
   }
 }
 
+static void copies_without_an_event() {
+  Pool pool;
+  Staging* s = used(0, 0);
+  s->in_use[1] = false;
+  s->unrecorded = true;                             // the upload went out, its event was refused
+  const int freed = Runtime::freed;
+  pool.give(s);
+  REQUIRE(Runtime::freed == freed + 2);
+  pool.drain();
+}
+
 int main() {
   events_of_two_devices();
   finished_and_bounded();
   answers_of_events_are_no_errors();
   giving_back_needs_no_memory();
+  copies_without_an_event();
   std::puts("ok");
   return 0;
 }
