@@ -185,10 +185,18 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   // The tables go through one of two pinned host buffers the layout owns, so the copy is truly asynchronous: the
   // call returns once it is enqueued, and the next ps_layout_append may rebuild the tables while it is in flight.
   // A buffer is reused two uploads later, after the copy that last read it has finished (an event per buffer).
+  // An upload recorded into a graph has buffers of its own, which no other layout gets: its replays read them again, and
+  // the events of kept ones cannot be asked under capture.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusActive;   // (the default stream while another one captures: not to be asked either)
+  }
+  const bool captured = capture != hipStreamCaptureStatusNone;
   if (!lay->staging) {
     int device = -1;
     if (int32_t st = check_hip(hipGetDevice(&device))) return st;
-    lay->staging = staging_pool().take(device);
+    lay->staging = captured ? new (std::nothrow) ps_layout::upload_staging() : staging_pool().take(device);
     if (!lay->staging) return PS_ERR_OOM;
     lay->staging_free = free_upload_staging;
   }
@@ -214,7 +222,7 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   }
   std::memcpy(s->buffer[i], lay->blob.data(), bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool unrecorded = s->unrecorded;
+  const bool unrecorded = s->unrecorded || captured;
   s->unrecorded = true;   // (until the event stands behind the copy: an error below may leave one under way)
   if (bytes > kKernelUploadAbove && bytes <= kKernelUploadBytes && bytes % 16 == 0 && reinterpret_cast<uintptr_t>(dev_tables) % 16 == 0) {
     void* src = nullptr;

@@ -14,7 +14,7 @@ struct UploadStaging {
   int device[2] = {-1, -1};               // ... which each was created on: streams of another one refuse it
   bool in_use[2] = {false, false};
   int next = 0;
-  bool unrecorded = false;                // a buffer may be read by a copy that its event does not stand behind
+  bool unrecorded = false;                // a buffer may be read by a copy that its event does not stand behind: a replay, or one refused an event
 
   ~UploadStaging() {
     for (int i = 0; i < 2; ++i) {

@@ -119,6 +119,53 @@ def test_addresses_of_other_integer_types():
     s.close()
 
 
+@pytest.mark.parametrize("requests", [3, 250, 1100, 3000])
+def test_uploads_recorded_in_a_graph(requests):
+    """Replays bring the tables again after other layouts came and went; once the layout is released, the next ones upload
+    as usual (its buffers are not handed on, and its events, which cannot be asked, are no error of theirs)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_12029_amd import binding as B
+    geo = B.geometry(8, 8, 128, 16, "bf16", "bf16")
+    pool = B.ps_pool_create(requests * 10, None)
+
+    def new_layout(suffix):
+        return B.ps_kv_layout(pool, geo, [40] * requests, np.arange(requests), np.zeros(requests, int), [suffix] * requests)
+
+    def upload(layout):
+        dev = torch.full((B.ps_layout_device_bytes(layout),), 0x5a, dtype=torch.uint8, device="cuda")
+        B.ps_layout_upload(layout, dev.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        return dev
+
+    def others():
+        for suffix in (1, 17, 30):
+            lay = new_layout(suffix)
+            t = B.ps_layout_tables(lay, requests, requests)
+            ids = np.concatenate([t["prefix_blk"], t["suffix_blk"]])
+            for _ in range(3):
+                assert np.array_equal(upload(lay).cpu().numpy().view(np.int32)[:ids.size], ids)
+            B.ps_layout_release(pool, lay)
+
+    layout = new_layout(20)
+    want = [upload(layout) for _ in range(2)][0].cpu()       # both of its buffers exist
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    dev = torch.zeros_like(want, device="cuda")
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        B.ps_layout_upload(layout, dev.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    for _ in range(4):
+        dev.fill_(0xa5)
+        graph.replay()
+        others()
+        torch.cuda.synchronize()
+        assert torch.equal(dev.cpu(), want)
+    del graph
+    torch.cuda.synchronize()
+    B.ps_layout_release(pool, layout)
+    others()
+    B.ps_pool_destroy(pool)
+
+
 @pytest.mark.parametrize("requests", [1, 3, 40, 250, 1100, 3000])
 def test_uploaded_tables_are_the_layouts(requests):
     """Table blobs on both sides of 16 KiB and of 1 MiB arrive whole, whichever way they go up."""
