@@ -229,9 +229,7 @@ int32_t ps_prefix_suffix_attention(const ps_layout* layout, const void* dev_tabl
 int32_t ps_merge_states(const ps_layout* layout, const void* dev_tables, const void* workspace,
                         void* out, float* out_lse, void* stream);
 /* ps_decode_attention (Background Eq. 2 / Eq. 4, Method Eq. 6: one decode step's attention over the whole cache):
- * the whole step -- the result of ps_prefix_suffix_attention, then ps_merge_states -- on one stream.  `workspace` is
- * scratch here: what it holds afterwards is unspecified (a request whose only partial state is its result, as in a
- * partial prefill, is written to `out` without one). */
+ * the whole step -- ps_prefix_suffix_attention, then ps_merge_states -- on one stream. */
 int32_t ps_decode_attention(const ps_layout* layout, const void* dev_tables, const void* q,
                             const void* kv_pool, const float* kv_scales, void* workspace,
                             void* out, float* out_lse, void* stream);

@@ -337,8 +337,13 @@ int32_t ps_probe_read(const void* dev_buf, int64_t bytes, int32_t pattern, int32
   return check_hip(hipGetLastError());
 }
 
-int32_t ps_decode_attention(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,
-                            const float* kv_scales, void* workspace, void* out, float* out_lse, void* stream) {
+}  // extern "C"
+
+namespace {
+
+// keep_states: the caller can read the workspace, which then holds every partial state of the batch.
+int32_t decode_step(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool, const float* kv_scales,
+                    void* workspace, bool keep_states, void* out, float* out_lse, void* stream) {
   if (lay && lay->num_requests && !out) return PS_ERR_INVALID_ARG;
   if (int32_t rc = check_pass_args(lay, dev_tables, q, kv_pool, kv_scales, workspace)) return rc;
   psdev::AttnParams p = make_params(lay, dev_tables, q, kv_pool, kv_scales, workspace);
@@ -348,15 +353,25 @@ int32_t ps_decode_attention(const ps_layout* lay, const void* dev_tables, const 
     return ps_merge_states(lay, dev_tables, workspace, out, out_lse, stream);
   }
   // Partial prefill: a context that goes out as one item leaves one partial state per row, which is the result -- the
-  // prefill kernel rounds and stores it, and only the other requests are merged.
+  // prefill kernel rounds and stores it as well, and only the other requests are merged.
   p.out = out;
   p.out_lse = out_lse;
+  p.keep_states = keep_states;
   if (int32_t rc = launch_both(lay, p, dev_tables, st)) return rc;
   const int32_t* list = static_cast<const int32_t*>(dev_tables) + lay->off_merge;
   if (int32_t rc = psdev::launch_merge(p.slot_base, list, p.ws_o, p.ws_lse, out, out_lse, int(lay->merge_req.size()),
                                        lay->max_states, lay->geo, st))
     return rc;
   return check_hip(hipGetLastError());
+}
+
+}  // namespace
+
+extern "C" {
+
+int32_t ps_decode_attention(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,
+                            const float* kv_scales, void* workspace, void* out, float* out_lse, void* stream) {
+  return decode_step(lay, dev_tables, q, kv_pool, kv_scales, workspace, true, out, out_lse, stream);
 }
 
 int32_t ps_decode_attention_static(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,
@@ -367,7 +382,7 @@ int32_t ps_decode_attention_static(const ps_layout* lay, const void* dev_tables,
   if (int32_t st = static_workspace(&workspace)) return st;
   // the same launches as ps_decode_attention, with the library's own buffer as the workspace (a kernel argument like
   // any other device pointer); nothing here or below allocates
-  return ps_decode_attention(lay, dev_tables, q, kv_pool, kv_scales, workspace, out, out_lse, stream);
+  return decode_step(lay, dev_tables, q, kv_pool, kv_scales, workspace, false, out, out_lse, stream);
 }
 
 }  // extern "C"

@@ -31,6 +31,7 @@ struct AttnParams {
   // then needs no merge
   void* out;                 // [R][Hq][d], query format
   float* out_lse;            // [R][Hq] or null
+  bool keep_states;          // ... and whether it stores their partial states too (the caller can read the workspace)
   int32_t num_q_heads, num_kv_heads, group, block_size;
   int64_t s_block, s_head, s_kv, s_tok;  // elements
   float scale_log2;          // log2(e) / sqrt(d)

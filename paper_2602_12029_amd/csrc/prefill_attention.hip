@@ -482,10 +482,22 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
       const int h = kv_head * G + row % G;
       const int first_slot = p.slot_base[req_of];
       const float lse = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
-      if (p.out && p.slot_base[req_of + 1] - first_slot == 1) {
-        // The request's only partial state is the result: rounded and stored here, 16 bytes per lane and store (the
-        // state's 512 bytes per row are neither written nor read back by a merge: on 32 contexts of 4096 + 64..256
-        // tokens the merge was 37 us of 471, on 64 contexts of 8192 tokens with 64 query heads 120 us of 3150).
+      const bool direct = p.out && p.slot_base[req_of + 1] - first_slot == 1;
+      if (!direct || p.keep_states) {
+        const int64_t slot = int64_t(first_slot) + split_local;
+        float* state = p.ws_o + (slot * p.num_q_heads + h) * kD + 32 * g;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int r = 8 * (i & 1) + (i >> 1);   // (in the order of the columns)
+          *reinterpret_cast<f32x4*>(state + 64 * ((r >> 2) & 1) + 8 * (r & 3) + 4 * (r >> 3)) =
+              f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]} * inv;
+        }
+        if (g == 0) p.ws_lse[slot * p.num_q_heads + h] = lse;
+      }
+      if (direct) {
+        // The request's only partial state is the result: rounded and stored here as well, 16 bytes per lane and store, so
+        // that no merge has to read it back (32 contexts of 4096 + 64..256 tokens, a step with state and merge / state and
+        // row / row alone 415 / 403 / 383 us; 64 contexts of 8192 tokens, 64 query heads, e4m3 KV 2763 / 2704 / 2641 us).
         uint16_t* o = static_cast<uint16_t*>(p.out) + (int64_t(req_of) * p.num_q_heads + h) * kD + 32 * g;
         const bool some = l > 0.f;   // a row that saw nothing is zero
 #pragma unroll
@@ -499,14 +511,6 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
           *reinterpret_cast<bf16x8*>(o + 64 * (r >> 2) + 8 * (r & 3)) = w;
         }
         if (p.out_lse && g == 0) p.out_lse[int64_t(req_of) * p.num_q_heads + h] = lse;
-      } else {
-        const int64_t slot = int64_t(first_slot) + split_local;
-        float* o = p.ws_o + (slot * p.num_q_heads + h) * kD + 32 * g;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          *reinterpret_cast<f32x4*>(o + 64 * ((r >> 2) & 1) + 8 * (r & 3) + 4 * (r >> 3)) =
-              f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]} * inv;
-        if (g == 0) p.ws_lse[slot * p.num_q_heads + h] = lse;
       }
     }
   }

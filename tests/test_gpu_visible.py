@@ -174,6 +174,38 @@ def test_rows_with_one_partial_state_match_the_merged_ones(gpu, kv_dtype):
     case.close()
 
 
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+def test_the_whole_step_leaves_every_partial_state(gpu, kv_dtype):
+    """The workspace holds the same states after the whole step as after its two passes, rows that are stored without a merge
+    included, so that a merge behind it gives the same output; the step on the library's own buffer gives it too."""
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(32, 8, 128, 16, "bf16", kv_dtype)
+    w, visible = wl.chunk_prefill_workload("states_" + kv_dtype, geo, [500, 90, 2100, 20], [40, 66, 33, 3], pool_factor=1.2, seed=37)
+    case = gpu(w)
+    for pc in (0, 512, 4096):
+        case.replan(pc, 0)
+        case.set_visible(visible)
+        case.poison_workspace()
+        case.batch.prefix_attention()
+        case.batch.suffix_attention()
+        want = case.batch.workspace.clone()
+        case.poison_workspace()
+        case.batch.decode_attention()
+        assert torch.equal(case.batch.workspace, want)
+        out, lse = case.batch.out.clone(), case.batch.lse.clone()
+        case.batch.out.zero_()
+        case.batch.merge_states()
+        assert torch.equal(out.view(torch.int16), case.batch.out.view(torch.int16))
+        assert torch.equal(lse.view(torch.int32), case.batch.lse.view(torch.int32))
+        case.poison_workspace()
+        b = case.batch
+        B.ps_decode_attention_static(case.layout, b.tables.data_ptr(), b.q.data_ptr(), b.kv.data_ptr(),
+                                     b.scales.data_ptr() if b.scales is not None else 0, b.out.data_ptr(), b.lse.data_ptr(),
+                                     torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(out.view(torch.int16), b.out.view(torch.int16)) and torch.equal(lse.view(torch.int32), b.lse.view(torch.int32))
+    case.close()
+
+
 @pytest.mark.parametrize("heads,rows", [((32, 8), 128), ((64, 8), 256)])
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 def test_prefill_ring_edges(gpu, kv_dtype, heads, rows):
