@@ -348,7 +348,8 @@ int32_t decode_step(const ps_layout* lay, const void* dev_tables, const void* q,
   if (int32_t rc = check_pass_args(lay, dev_tables, q, kv_pool, kv_scales, workspace)) return rc;
   psdev::AttnParams p = make_params(lay, dev_tables, q, kv_pool, kv_scales, workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!lay->any_direct) {
+  // (the rows are stored 16 bytes at a time; the merge stores 8)
+  if (!lay->any_direct || reinterpret_cast<uintptr_t>(out) % 16 != 0) {
     if (int32_t rc = launch_both(lay, p, dev_tables, st)) return rc;
     return ps_merge_states(lay, dev_tables, workspace, out, out_lse, stream);
   }

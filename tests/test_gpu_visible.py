@@ -203,6 +203,12 @@ def test_the_whole_step_leaves_every_partial_state(gpu, kv_dtype):
                                      b.scales.data_ptr() if b.scales is not None else 0, b.out.data_ptr(), b.lse.data_ptr(),
                                      torch.cuda.current_stream().cuda_stream)
         assert torch.equal(out.view(torch.int16), b.out.view(torch.int16)) and torch.equal(lse.view(torch.int32), b.lse.view(torch.int32))
+        own = b.out                                      # an output off a 16-byte boundary
+        b.out = torch.zeros(own.numel() + 8, dtype=own.dtype, device="cuda")[4:4 + own.numel()].view(own.shape)
+        assert b.out.data_ptr() % 16 == 8
+        b.decode_attention()
+        assert torch.equal(out.view(torch.int16), b.out.view(torch.int16))
+        b.out = own
     case.close()
 
 
