@@ -193,6 +193,8 @@ int32_t ps_layout_schedule(const ps_layout* layout, int32_t which, int32_t* num_
  * first one's copy, the fourth for the second's, and so on. */
 int64_t ps_layout_device_bytes(const ps_layout* layout);
 int32_t ps_layout_upload(const ps_layout* layout, void* dev_tables, void* stream);
+/* Orders what follows on `stream` behind the layout's uploads so far, wherever they were enqueued.  Asynchronous; not for a stream under capture. */
+int32_t ps_layout_upload_wait(const ps_layout* layout, void* stream);
 /* Partial-state workspace: fp32 o[num_slots][Hq][d] followed, at lse_offset_bytes, by fp32
  * lse[num_slots][Hq]. */
 int64_t ps_workspace_bytes(const ps_layout* layout);

@@ -24,7 +24,8 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libprefills
 EXPORTS = [
     "ps_pool_create", "ps_pool_destroy", "ps_pool_num_free", "ps_pool_free_list", "ps_pool_refcounts",
     "ps_kv_layout", "ps_layout_release", "ps_layout_tables", "ps_layout_replan", "ps_layout_plan",
-    "ps_layout_schedule", "ps_layout_device_bytes", "ps_layout_upload", "ps_workspace_bytes", "ps_workspace_layout",
+    "ps_layout_schedule", "ps_layout_device_bytes", "ps_layout_upload", "ps_layout_upload_wait", "ps_workspace_bytes",
+    "ps_workspace_layout",
     "ps_prefix_attention", "ps_suffix_attention", "ps_prefix_suffix_attention", "ps_merge_states", "ps_decode_attention",
     "ps_layout_lengths", "ps_layout_append", "ps_kv_append", "ps_kv_ingest",
     "ps_layout_set_visible", "ps_layout_request_list", "ps_kv_layout_tree", "ps_layout_root_tables",
@@ -36,7 +37,7 @@ EXPORTS = [
 
 # entry points that enqueue device work or query the HIP runtime (csrc/abi.hip); the rest is host-only (csrc/layout.cpp)
 DEVICE_EXPORTS = {
-    "ps_layout_upload", "ps_prefix_attention", "ps_suffix_attention", "ps_prefix_suffix_attention", "ps_merge_states",
+    "ps_layout_upload", "ps_layout_upload_wait", "ps_prefix_attention", "ps_suffix_attention", "ps_prefix_suffix_attention", "ps_merge_states",
     "ps_decode_attention", "ps_decode_attention_static", "ps_kv_append", "ps_kv_ingest", "ps_kv_stage_out", "ps_kv_stage_in",
     "ps_probe_read",
     "ps_last_hip_error",
@@ -329,6 +330,10 @@ def _launch(fn, where: str, *args):
 
 def ps_layout_upload(layout, dev_tables: int, stream: int = 0):
     _launch(_lib().ps_layout_upload, "ps_layout_upload", layout, dev_tables, stream)
+
+
+def ps_layout_upload_wait(layout, stream: int = 0):
+    _check(_lib().ps_layout_upload_wait(layout, _p(stream)), "ps_layout_upload_wait")
 
 
 def ps_workspace_bytes(layout) -> int:

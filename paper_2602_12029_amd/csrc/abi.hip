@@ -240,6 +240,15 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   return PS_OK;
 }
 
+int32_t ps_layout_upload_wait(const ps_layout* lay, void* stream) {
+  if (!lay) return PS_ERR_INVALID_ARG;
+  const ps_layout::upload_staging* s = lay->staging;
+  for (int i = 0; s && i < 2; ++i)   // (uploads before the last two are done: their buffers were waited for)
+    if (s->in_use[i])
+      if (int32_t rc = check_hip(hipStreamWaitEvent(static_cast<hipStream_t>(stream), s->done[i], 0))) return rc;
+  return PS_OK;
+}
+
 int32_t ps_prefix_attention(const ps_layout* lay, const void* dev_tables, const void* q, const void* kv_pool,
                             const float* kv_scales, void* workspace, void* stream) {
   if (int32_t st = check_pass_args(lay, dev_tables, q, kv_pool, kv_scales, workspace)) return st;

@@ -58,6 +58,7 @@ class DecodeBatch:
         nbytes = B.ps_layout_device_bytes(self.layout)
         self.tables = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         B.ps_layout_upload(self.layout, self.tables.data_ptr(), _stream())
+        self._pending = not wait             # other streams have to wait for the upload on the GPU
         if wait:
             torch.cuda.current_stream().synchronize()
         self.workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
@@ -72,11 +73,16 @@ class DecodeBatch:
         self._sync_plan()
 
     def _stream(self) -> int:
-        """The current stream, for a launch that reads the tables (they and the workspace live until it is done there)."""
+        """The current stream, for a launch that reads the tables: behind their upload, whichever stream that went to, and
+        they and the workspace live until the launch is done."""
         stream = _stream()
         if stream != self._home:
+            current = torch.cuda.current_stream()
+            # (a launch that is only recorded runs with the graph, whose replays the caller orders)
+            if self._pending and not torch.cuda.is_current_stream_capturing():
+                B.ps_layout_upload_wait(self.layout, stream)
             for t in (self.tables, self.workspace):
-                t.record_stream(torch.cuda.current_stream())
+                t.record_stream(current)
         return stream
 
     def _sc(self):
@@ -108,9 +114,11 @@ class DecodeBatch:
     def append_step(self, pool, new_k: torch.Tensor, new_v: torch.Tensor, active=None):
         """One decode step of cache growth: tables grow on the host and are uploaded again, then the new
         tokens ([R, Hkv, d], contiguous) are stored.  Returns the destinations the host chose."""
+        if torch.cuda.is_current_stream_capturing():
+            raise RuntimeError("append_step changes the tables on the host: it cannot be recorded into a graph")
         dest = B.ps_layout_append(pool, self.layout, self.num_requests, active)
-        # No wait for the upload: it is ordered in front of the store below on this stream, and whoever reads the new
-        # tokens from another stream has to be ordered behind that store anyway.
+        # No wait on the host for the upload: it is ordered in front of the store below on this stream, and launches of this
+        # batch on other streams wait for it there.
         self._sync_plan(wait=False)
         assert new_k.is_contiguous() and new_v.is_contiguous()
         B.ps_kv_append(self.layout, self.tables.data_ptr(), new_k.data_ptr(), new_v.data_ptr(), self.kv.data_ptr(),

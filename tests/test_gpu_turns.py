@@ -99,6 +99,64 @@ def test_turns_of_several_threads_on_their_own_streams():
         s.close()
 
 
+def test_append_step_is_ordered_in_front_of_other_streams():
+    """A pass over the shared segments, which needs nothing of the step's own token, on another stream right behind
+    append_step while the upload is still held up: it waits for the tables there, as for the host before."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_12029_amd import binding as B
+    from paper_2602_12029_amd.runtime import DecodeBatch
+    s = Session(3)
+    layout = B.ps_kv_layout_adopt(s.pool, s.geo, s.len, s.adopt, [0, 0, 0], [0, 1, 2], [0, 0, 0])
+    batch = DecodeBatch(layout, s.geo, 3, s.q[0], s.kv)
+    batch.kv_ingest(0, *s.tail)
+    side = torch.cuda.Stream()
+    busy = torch.randn(4096, 4096, device="cuda")
+    for i in range(4):
+        torch.cuda.synchronize()
+        for _ in range(20):
+            torch.mm(busy, busy)                   # some milliseconds in front of the upload
+        batch.append_step(s.pool, *s.new[i])
+        with torch.cuda.stream(side):
+            batch.prefix_attention()
+            got = batch.workspace.clone()
+        torch.cuda.synchronize()
+        batch.prefix_attention()
+        torch.cuda.synchronize()
+        assert torch.equal(got, batch.workspace)   # (slots the pass does not write hold what they held)
+    B.ps_layout_release(s.pool, layout)
+    s.close()
+
+
+def test_append_step_is_refused_under_capture():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_12029_amd import binding as B
+    from paper_2602_12029_amd.runtime import DecodeBatch
+    s = Session(4)
+    layout = B.ps_kv_layout_adopt(s.pool, s.geo, s.len, s.adopt, [0, 0, 0], [0, 1, 2], [0, 0, 0])
+    batch = DecodeBatch(layout, s.geo, 3, s.q[0], s.kv)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(RuntimeError):
+            batch.append_step(s.pool, *s.new[0])
+    assert not B.ps_layout_lengths(layout, 1, 3)["suffix_len"].any()
+    batch.append_step(s.pool, *s.new[0])
+    # the step's attention recorded behind it and replayed, as before
+    batch.decode_attention()
+    want = batch.out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        batch.decode_attention()
+    for _ in range(3):
+        batch.out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _same([batch.out], [want])
+    B.ps_layout_release(s.pool, layout)
+    s.close()
+
+
 def test_addresses_of_other_integer_types():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
