@@ -91,12 +91,13 @@ def _lib():
         lib.ps_strerror.argtypes = [C.c_int32]
         lib.ps_layout_device_bytes.restype = C.c_int64
         lib.ps_workspace_bytes.restype = C.c_int64
-        # the calls of a serving loop take plain addresses: declared once, ctypes converts them without an object each
+        # the calls of a serving loop take plain addresses: declared once, ctypes converts them without an object each (as
+        # integers, since a declared pointer would take text and ctypes objects too)
         if not host_only:
             for name, count in {"ps_layout_upload": 3, "ps_prefix_attention": 7, "ps_suffix_attention": 7,
                                 "ps_prefix_suffix_attention": 7, "ps_merge_states": 6, "ps_decode_attention": 9,
                                 "ps_decode_attention_static": 8, "ps_kv_append": 7}.items():
-                getattr(lib, name).argtypes = [C.c_void_p] * count
+                getattr(lib, name).argtypes = [C.c_void_p] + [C.c_size_t] * (count - 1)
         for name in EXPORTS:
             if not (host_only and name in DEVICE_EXPORTS):
                 getattr(lib, name)                  # fail early if a symbol is missing
@@ -322,8 +323,8 @@ def _launch(fn, where: str, *args):
     """Calls an entry point whose arguments are all addresses: a layout handle, integers (0 or None = NULL)."""
     try:
         status = fn(*args)
-    except C.ArgumentError:              # other integer types (numpy)
-        status = fn(*[a if isinstance(a, C.c_void_p) else _p(a) for a in args])
+    except C.ArgumentError:              # None, other integer types (numpy)
+        status = fn(args[0], *[int(a) if a else 0 for a in args[1:]])
     if status != PS_OK:
         raise PsError(status, where)
 

@@ -1,5 +1,6 @@
 """Host-side internals without an entry point of their own, CPU only: small C++ programs under tests/native, compiled with
 the library's host sources under AddressSanitizer and UndefinedBehaviorSanitizer."""
+import ctypes
 import os
 import subprocess
 
@@ -7,6 +8,25 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_12029_amd", "csrc")
+
+
+def test_addresses_are_numbers():
+    """The calls of a serving loop take addresses as integers; text, bytes and ctypes objects are refused before the library."""
+    from paper_2602_12029_amd import binding as B
+    geo = B.geometry(4, 2, 64, 16, "f32", "f32")
+    pool = B.ps_pool_create(8)
+    layout = B.ps_kv_layout(pool, geo, [20], [0], [0], [3])
+    for bad in (b"tables", "tables", ctypes.create_string_buffer(4096), ctypes.pointer(ctypes.c_int(0)), object()):
+        with pytest.raises((TypeError, ValueError)):
+            B.ps_layout_upload(layout, bad)
+        with pytest.raises((TypeError, ValueError)):
+            B.ps_merge_states(layout, 16, bad, 16)
+    for none in (None, 0):
+        with pytest.raises(B.PsError) as e:
+            B.ps_layout_upload(layout, none)
+        assert e.value.status == B.PS_ERR_INVALID_ARG
+    B.ps_layout_release(pool, layout)
+    B.ps_pool_destroy(pool)
 
 
 @pytest.mark.parametrize("program", ["block_order", "upload_staging"])
