@@ -102,13 +102,21 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   const bool unequal = longest > 0 && int64_t(longest) * 10 > int64_t(shortest) * 11;
   const int64_t ideal = std::max<int64_t>(1, ceil_div(two_per_cu && unequal ? total * 3 / 5 : total, int64_t(num_cus)));
   auto resolve = [&](int32_t v) { return v == PS_VARIANT_AUTO ? (mfma_ok ? PS_VARIANT_MFMA : PS_VARIANT_WAVE) : v; };
-  // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item, two and more of them resident per
-  // compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25 of it: 36 float32 requests on 12
-  // contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to
-  // 6144 tokens 51.2 / 44.5 / 43.1 us), and at
+  // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item.  Heads of up to 128 with up to 16 rows
+  // leave room for two and more of them per compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25
+  // of it: 36 float32 requests on 12 contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide
+  // heads on 24 contexts of 1024 to 6144 tokens 51.2 / 44.5 / 43.1 us).  Where one is resident -- more rows, or 256-wide
+  // heads -- a second round only adds starts and states, and the share is a whole one (whole / half: bf16 queries over bf16
+  // or e4m3 KV, groups of 20 to 64 rows on 8 to 60 contexts, d = 64 60.2 / 68.1, 31.0 / 34.9, 56.9 / 65.9, d = 128 84.1 /
+  // 93.1, 42.9 / 45.3, 78.6 / 90.8 us; d = 256 26.8 / 34.7, 52.2 / 62.2, 85.0 / 92.9, in float32 44.7 / 56.3, 96.9 / 112,
+  // 147 / 142, 236 / 229 us), but not with float32 products of up to 128: those are bound by the matrix cores, and the
+  // finer cut evens the ends out (groups of 20 to 64 rows, d = 64 99.8 / 90.2, 50.5 / 40.9, 161 / 140, 114 / 122, d = 128 101 /
+  // 83.3, 144 / 134, 296 / 291, 181 / 187, 172 / 187 us).  The vector kernel, which takes a pool that starts off a 16-byte
+  // boundary with the same chunks, is faster with halves too (426 / 364, 170 / 134, 280 / 254, 280 / 230, 116 / 92 us).  At
   // least 128 tokens, one or two tiles per wave (two requests on one 256-token prompt, launches alone: chunks of 256 /
   // 128 / 64 tokens 9.4 / 7.9 / 7.7 us; contexts of some thousand tokens lose more in the merge than they gain).
-  const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, 2 * int64_t(num_cus)));
+  const bool tile_halves = g.head_dim < 256 && (widest <= 16 || g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
+  const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, (tile_halves ? 2 : 1) * int64_t(num_cus)));
   auto pick = [&](int32_t asked, int32_t variant) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
     const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && !fewer_states;

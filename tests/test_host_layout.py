@@ -627,6 +627,27 @@ def test_park_resume_random_batches_against_oracle_and_parked_layouts_refuse_wor
         B.ps_blocks_needed(16, [5], [-1])
 
 
+@pytest.mark.parametrize("kv,q,d,models,share", [
+    ("f32", "f32", 128, 4, 2), ("bf16", "bf16", 64, 4, 2), ("f32", "f32", 64, 5, 2), ("fp8_e4m3", "f32", 128, 8, 2),
+    ("bf16", "bf16", 64, 5, 1), ("fp8_e4m3", "bf16", 64, 16, 1), ("f32", "f32", 256, 4, 1), ("bf16", "bf16", 256, 1, 1)])
+def test_chunks_of_the_tile_kernel_follow_its_residency(kv, q, d, models, share):
+    """Chunks aim at half a compute unit's share of the tokens where two workgroups of the tile kernel fit on one (up to 16 rows
+    per KV head, heads up to 128) or its products are float32, at a whole one otherwise; never below 128 tokens."""
+    geo = B.geometry(8, 2, d, 16, q, kv)
+    for length, cus in ((4000, 8), (30000, 16), (900, 64)):
+        pool = B.ps_pool_create(2 * (length // 16 + 2))
+        lay = B.ps_kv_layout(pool, geo, [length, length - 100], np.repeat([0, 1], models), np.tile(np.arange(models), 2),
+                             np.zeros(2 * models, int))
+        B.ps_layout_replan(lay, B.plan_options(num_cus=cus))
+        items = B.ps_layout_plan(lay, 2 * models)["items"]
+        up32 = lambda n: -(-n // 32) * 32
+        aim = min(max(up32(-(-(2 * length - 100) * 2 // (share * cus))), 128), 8192)
+        cut = [up32(-(-n // -(-n // aim))) for n in (length, length - 100)]
+        assert (items[:, 2] - items[:, 1]).max() == max(cut)
+        B.ps_layout_release(pool, lay)
+        B.ps_pool_destroy(pool)
+
+
 def test_adopted_blocks_hand_worked_and_rules():
     """tests/test_oracle_layout.py::test_adopted_blocks_hand_worked and ::test_adoption_rules through the C ABI."""
     geo = B.geometry(4, 2, 64, 4, "f32", "f32")
