@@ -55,7 +55,8 @@ bool ps_mfma_supported(const ps_geometry& g) {
 // ---------------------------------------------------------------------------------------------------
 // Split plan: cut every segment into token chunks of (nearly) equal size, one workgroup each; a
 // request's partial states are numbered prefix chunks first, then its suffix chunks.
-// fewer_states: larger chunks where the rules below would cut finer for speed alone (see ps_plan_build).
+// fewer_states: without the rules below that choose another chunk than a compute unit's share of the tokens for speed
+// alone (see ps_plan_build).
 static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewer_states) {
   ps_plan_options opt{};
   if (user) opt = *user;
@@ -117,17 +118,19 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // 128 / 64 tokens 9.4 / 7.9 / 7.7 us; contexts of some thousand tokens lose more in the merge than they gain).
   const bool tile_halves = g.head_dim < 256 && (widest <= 16 || g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
   const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, (tile_halves ? 2 : 1) * int64_t(num_cus)));
-  auto pick = [&](int32_t asked, int32_t variant) -> int64_t {
+  auto pick = [&](int32_t asked, int32_t variant, bool fewer) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
-    const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && !fewer_states;
+    const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && !fewer;
     return std::min<int64_t>(std::max<int64_t>(round_up(tiles ? tile_ideal : ideal, granule), round_up(tiles ? 128 : 256, granule)),
                              round_up(kPsMfmaMaxChunk, granule));
   };
   const int64_t mfma_cap = std::max<int64_t>(granule, kPsMfmaMaxChunk / granule * granule);
-  int64_t prefix_chunk = pick(opt.prefix_chunk_tokens, resolve(opt.prefix_variant));
-  int64_t suffix_chunk = pick(opt.suffix_chunk_tokens, resolve(opt.suffix_variant));
-  if (resolve(opt.prefix_variant) == PS_VARIANT_MFMA) prefix_chunk = std::min(prefix_chunk, mfma_cap);
-  if (resolve(opt.suffix_variant) == PS_VARIANT_MFMA) suffix_chunk = std::min(suffix_chunk, mfma_cap);
+  auto chunk_for = [&](int32_t asked, int32_t variant, bool fewer) {
+    const int64_t chunk = pick(asked, variant, fewer);
+    return variant == PS_VARIANT_MFMA ? std::min(chunk, mfma_cap) : chunk;
+  };
+  const int64_t prefix_chunk = chunk_for(opt.prefix_chunk_tokens, resolve(opt.prefix_variant), fewer_states);
+  const int64_t suffix_chunk = chunk_for(opt.suffix_chunk_tokens, resolve(opt.suffix_variant), fewer_states);
 
   lay->opt = opt;
   lay->prefix_variant = resolve(opt.prefix_variant);
@@ -194,9 +197,8 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   lay->rowsplit_rows = 256;
   if (wide_shares && wide_tokens == total && wide_aim(128) <= 512 && wide_work(128, wide_aim(128)) * g.num_kv_heads <= num_cus)
     lay->rowsplit_rows = 128;
-  const int64_t wide_chunk = opt.prefix_chunk_tokens > 0 ? prefix_chunk
-                             : wide_shares ? wide_aim(lay->rowsplit_rows)
-                             : std::min<int64_t>(std::max<int64_t>(round_up(ideal, granule), round_up(256, granule)), round_up(32768, granule));
+  const int64_t token_share = std::min<int64_t>(std::max<int64_t>(round_up(ideal, granule), round_up(256, granule)), round_up(32768, granule));
+  const int64_t wide_chunk = opt.prefix_chunk_tokens > 0 ? prefix_chunk : wide_shares ? wide_aim(lay->rowsplit_rows) : token_share;
   auto chunking_shared = [&](int64_t len, int64_t chunk, int32_t* n) -> int64_t {
     if (len <= 0) { *n = 0; return chunk; }
     if (opt.prefix_chunk_tokens > 0) return chunking(len, chunk, n);   // a chunk size the caller asked for is taken as it is
@@ -456,6 +458,33 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     lay->max_states = std::max(lay->max_states, lay->slot_base[r + 1] - lay->slot_base[r]);
   }
   lay->num_slots = slots;
+  // What the rules for fewer states would leave, where they are others than the ones that were followed: the states by
+  // their chunk sizes alone (the last round's extra cut of the prefill launch can only add to them).
+  lay->coarser_slots = -1;
+  const int64_t coarse_prefix = chunk_for(opt.prefix_chunk_tokens, lay->prefix_variant, true);
+  const int64_t coarse_suffix = chunk_for(opt.suffix_chunk_tokens, lay->suffix_variant, true);
+  if (!fewer_states && (wide_shares || coarse_prefix != prefix_chunk || coarse_suffix != suffix_chunk) &&
+      ps_workspace_bytes(lay) > PS_STATIC_WORKSPACE_BYTES) {
+    const int64_t coarse_wide = opt.prefix_chunk_tokens > 0 ? coarse_prefix : token_share;
+    lay->coarser_slots = 0;
+    int32_t n = 0;
+    for (int32_t t = 0; t < lay->num_roots; ++t) {
+      const int64_t count = lay->root_group_indptr[size_t(t) + 1] - lay->root_group_indptr[size_t(t)];
+      if (limited && prefix_mfma && count * group > 64) chunking_shared(lay->root_len[size_t(t)], coarse_wide, &n);
+      else chunking(lay->root_len[size_t(t)], coarse_prefix, &n);
+      lay->coarser_slots += n * count;
+    }
+    for (int32_t p = 0; p < P; ++p) {
+      const int32_t g0 = lay->group_indptr[p], g1 = lay->group_indptr[p + 1];
+      const bool wide = limited && prefix_mfma && int64_t(g1 - g0) * group > 64;
+      const int64_t size = wide ? chunking_shared(lay->prefix_len[p], coarse_wide, &n) : chunking(lay->prefix_len[p], coarse_prefix, &n);
+      for (int32_t i = g0; i < g1; ++i) lay->coarser_slots += ceil_div(visible_of(lay->group_req[size_t(i)]), size);
+    }
+    for (int32_t r = 0; r < R; ++r) {
+      chunking(lay->suffix_len[r], coarse_suffix, &n);
+      lay->coarser_slots += n;
+    }
+  }
   // A request whose only partial state comes from the prefill kernel needs no merge in a whole step: the kernel rounds
   // and stores the row itself.
   std::vector<char> direct(size_t(R), 0);
@@ -540,15 +569,15 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   return ps_blob_build(lay);
 }
 
-// The plan by the rules for speed; where its partial states outgrow the static workspace and coarser chunks would keep
-// them inside it, the coarser plan (ps_decode_attention_static serves such a batch).
+// The plan by the rules for speed; where its partial states outgrow the static workspace and those by the rules for fewer
+// states (a compute unit's whole share of the tokens per chunk) would not, the plan by these: ps_decode_attention_static
+// serves such a batch, and callers with a workspace of their own lose nothing by it, since
+// that many states cost more in the merge than the finer cut brings (float32, fewer / more states: 96 requests on 8 contexts
+// of 8000 tokens and one KV head 248 / 319 us, 160 with 64-wide heads 152 / 195, 54 on 6 contexts and two KV heads 228 / 304).
 int32_t ps_plan_build(ps_layout* lay, const ps_plan_options* user) {
   if (int32_t rc = build_plan(lay, user, false)) return rc;
-  const bool finer = lay->prefix_variant == PS_VARIANT_WAVE || lay->suffix_variant == PS_VARIANT_WAVE || lay->num_rowsplit_items > 0;
-  if (!finer || ps_workspace_bytes(lay) <= PS_STATIC_WORKSPACE_BYTES) return PS_OK;
-  int64_t least = 0;   // one state for every request that has any
-  for (int32_t r = 0; r < lay->num_requests; ++r) least += lay->slot_base[size_t(r) + 1] > lay->slot_base[size_t(r)];
-  if (least * lay->geo.num_q_heads * (lay->geo.head_dim + 1) * 4 > PS_STATIC_WORKSPACE_BYTES) return PS_OK;
+  const int64_t slot_bytes = int64_t(lay->geo.num_q_heads) * (lay->geo.head_dim + 1) * 4;
+  if (lay->coarser_slots < 0 || lay->coarser_slots * slot_bytes > PS_STATIC_WORKSPACE_BYTES) return PS_OK;
   const ps_plan_options opt = lay->opt;
   if (int32_t rc = build_plan(lay, &opt, true)) return rc;
   return ps_workspace_bytes(lay) <= PS_STATIC_WORKSPACE_BYTES ? PS_OK : build_plan(lay, &opt, false);

@@ -65,6 +65,7 @@ struct ps_layout {
   std::vector<int32_t> slot_base;    // [R+1]
   int64_t num_slots = 0;
   int32_t max_states = 0;            // most slots of a request
+  int64_t coarser_slots = -1;        // slots by the rules for fewer states (at least); -1: nothing to gain or no need
   // requests whose partial states ps_decode_attention has to merge: all but those with a single one that the prefill
   // kernel writes out itself; only filled (and in the blob) where there are such
   std::vector<int32_t> merge_req;
