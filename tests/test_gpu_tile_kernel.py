@@ -90,11 +90,35 @@ def test_block_sizes_and_visible_lengths(kv, q, d, block):
 
 
 @pytest.mark.parametrize("layout", ["token_major", "planes"])
-@pytest.mark.parametrize("kv,q,d", [("f32", "f32", 128), ("bf16", "bf16", 256)])
+@pytest.mark.parametrize("kv,q,d", [("f32", "f32", 128), ("bf16", "bf16", 256), ("fp8_e4m3", "bf16", 64)])
 def test_pool_layouts(kv, q, d, layout):
     case = _case(_workload(wl.Geometry(8, 2, d, 32, q, kv), [1, 5, 2, 1, 4]), pool_layout=layout)
     _step(case)
     case.close()
+
+
+@pytest.mark.parametrize("kv,q", [("f32", "f32"), ("bf16", "bf16"), ("fp8_e4m3", "bf16")])
+def test_planes_far_apart(kv, q):
+    """K and V planes more than 2 GiB apart: past the matrix-core decode kernel's offsets, so the plan takes this family."""
+    from paper_2602_12029_amd import binding as B
+    from paper_2602_12029_amd.runtime import DecodeBatch
+    geo = wl.Geometry(8, 2, 128, 16, q, kv)
+    case = _case(_workload(geo, [1, 5, 2, 1, 4]), pool_layout="planes")
+    w, near = case.w, case.batch.kv
+    plane = near[0].numel()
+    far = (1 << 31) // near.element_size() + 4096 + plane
+    flat = torch.zeros(far + plane, dtype=near.dtype, device="cuda")
+    flat[:plane] = near[0].reshape(-1)
+    flat[far:] = near[1].reshape(-1)
+    wide = B.geometry(8, 2, 128, 16, q, kv, (2 * 16 * 128, 16 * 128, far, 128))
+    pool = B.ps_pool_create(w.num_blocks, w.free_order)
+    layout = B.ps_kv_layout(pool, wide, w.prefix_len, w.req_prompt, w.req_model, w.suffix_len)
+    assert B.ps_layout_plan(layout, w.num_requests)["prefix_variant"] == B.PS_VARIANT_WAVE
+    case.batch = DecodeBatch(layout, wide, w.num_requests, case.batch.q, flat, case.batch.scales)
+    _step(case)
+    case.close()
+    B.ps_layout_release(pool, layout)
+    B.ps_pool_destroy(pool)
 
 
 def test_cache_policies_and_misaligned_pool():

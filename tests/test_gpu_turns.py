@@ -226,21 +226,30 @@ def test_uploads_recorded_in_a_graph(requests):
 
 @pytest.mark.parametrize("requests", [1, 3, 40, 250, 1100, 3000])
 def test_uploaded_tables_are_the_layouts(requests):
-    """Table blobs on both sides of 16 KiB and of 1 MiB arrive whole, whichever way they go up."""
+    """Table blobs on both sides of 16 KiB and of 1 MiB arrive whole, whichever way they go up, and as they were when their
+    upload was called."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2602_12029_amd import binding as B
     geo = B.geometry(8, 8, 128, 16, "bf16", "bf16")
-    pool = B.ps_pool_create(requests * 5, None)
-    layout = B.ps_kv_layout(pool, geo, [40] * requests, np.arange(requests), np.zeros(requests, int), [20] * requests)
-    n = B.ps_layout_device_bytes(layout)
+    pool = B.ps_pool_create(requests * 6, None)
+    layout = B.ps_kv_layout(pool, geo, [40] * requests, np.arange(requests), np.zeros(requests, int), [30] * requests)
     stream = torch.cuda.current_stream().cuda_stream
-    for rep in range(4):                     # more uploads than the layout has staging buffers
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    sent = []
+    for rep in range(6):                     # more uploads than the layout has staging buffers, the tables changing in between
+        if rep % 2 == 0:
+            for _ in range(10):              # ... and the stream held up, so that a buffer read late would show
+                torch.mm(busy, busy)
+        n = B.ps_layout_device_bytes(layout)
         dev = torch.full((n + 64,), 0x5a, dtype=torch.uint8, device="cuda")
         B.ps_layout_upload(layout, dev.data_ptr(), stream)
-        torch.cuda.synchronize()
+        sent.append((n, dev, B.ps_layout_tables(layout, requests, requests)))
+        B.ps_layout_append(pool, layout, requests, np.arange(requests) % (rep + 1) == 0)
+    torch.cuda.synchronize()
+    for n, dev, t in sent:
         words = dev[:n].cpu().numpy().view(np.int32)
-        t = B.ps_layout_tables(layout, requests, requests)
         k = t["prefix_blk"].size
         assert np.array_equal(words[:k], t["prefix_blk"]) and np.array_equal(words[k:k + t["suffix_blk"].size], t["suffix_blk"])
         # the blob ends with the order the shared blocks are walked in, then the private ones as stored (and padding)
@@ -248,6 +257,7 @@ def test_uploaded_tables_are_the_layouts(requests):
         tail = words[words.size - (entries + 3) // 4 * 4:][:entries]
         assert np.array_equal(np.sort(tail[:k]), np.arange(k)) and np.array_equal(tail[k:], np.arange(k, entries))
         assert (dev[n:] == 0x5a).all()
+    assert sent[0][2]["suffix_blk"].size < sent[-1][2]["suffix_blk"].size
     print(requests, n)
     B.ps_layout_release(pool, layout)
     B.ps_pool_destroy(pool)
