@@ -17,13 +17,16 @@
  *     uploaded table blob); the library owns only the opaque host objects it creates.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Kernels are enqueued
  *     asynchronously and never synchronise; ps_layout_upload stages the tables in pinned host
- *     memory the layout owns (two buffers, used alternately) and returns once the copy is enqueued.
+ *     memory (two buffers per layout, used alternately, which a released layout leaves to the next
+ *     ones until the last pool is destroyed) and returns once the copy is enqueued.
  *   - q and out are [R][Hq][d] contiguous in q_dtype.  The KV pool is addressed as
  *         elem(block, kv_head, which, slot, c) = block*kv_stride_block + kv_head*kv_stride_head
  *                                               + which*kv_stride_kv + slot*kv_stride_tok + c
  *     (which: 0 = K, 1 = V; strides in elements; the head_dim axis is contiguous; every stride must
- *     be a multiple of 16 bytes; where kv_stride_kv + block_size*kv_stride_tok reaches 2 GiB the
- *     matrix-core kernels do not apply and the plan uses the wavefront kernel).  kv_scales (fp8 only) is [num_blocks][Hkv][2] fp32: K scale, V scale.
+ *     be a multiple of 16 bytes; where kv_stride_kv + block_size*kv_stride_tok reaches 2 GiB,
+ *     PS_VARIANT_MFMA does not apply and the plan uses PS_VARIANT_WAVE).  kv_scales (fp8 only) is
+ *     [num_blocks][Hkv][2] fp32: K scale, V scale; positive, as the cache-writing calls store them
+ *     (PS_VARIANT_WAVE takes any finite ones).
  *   - q head h reads KV head h / (Hq / Hkv).  Every stored token of both segments is attended to,
  *     unless ps_layout_set_visible limits how much of the shared prefix a request sees.  Scores are
  *     scaled by 1/sqrt(head_dim).

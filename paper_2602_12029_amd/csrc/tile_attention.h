@@ -20,11 +20,12 @@
 //     probability goes in as the sum of three bf16 terms (8 + 8 + 8 bits: the split is exact), three products instead
 //     of one, on an instruction of sixteen times the rate.  V is transposed inside the lane as in the decode kernel.
 //
-// Bound: HBM up to 32 rows per KV head (float32: 64 products of 32 cycles per 16 KiB tile and wave let 19.6 TB/s
-// through at 16 rows); the vector form this replaces repeats its softmax on every lane of a row and walks the tokens once
+// Bound: HBM with up to 16 rows per KV head, and with bf16 products up to 32 rows of heads up to 128 (float32: 64 products
+// of 32 cycles per 16 KiB tile and wave let 19.6 TB/s through at 16 rows; a pass with 256-wide heads carries 16 rows, so
+// that more of them walk the tokens again); the vector form this replaces repeats its softmax on every lane of a row and walks the tokens once
 // per 8 query rows.  Measured, whole step with the merge: 36 float32 requests on 12 contexts of 512 to 4096 tokens, d = 128,
 // 214 MB, 137 -> 45.8 us (4.7 TB/s); 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to 6144 tokens, 193 MB,
-// 319 -> 44.2 us (4.4 TB/s); two requests on one 256-token prompt 18.3 -> 10.9 us.  Error of float32 outputs against 64
+// 319 -> 44.2 us (4.4 TB/s); two requests on one 256-token prompt 18.3 -> 8.4 us.  Error of float32 outputs against 64
 // bits, mean over sixteen batches: 3.4e-7 -> 3.1e-7 (with the products in one chain per score it was 4.8e-7).
 #pragma once
 #include "device_common.h"
