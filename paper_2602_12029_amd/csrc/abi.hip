@@ -182,7 +182,7 @@ int32_t ps_last_hip_error(void) { return g_last_hip_error; }
 
 int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   if (!lay || !dev_tables) return PS_ERR_INVALID_ARG;
-  // The tables go through one of two pinned host buffers the layout owns, so the copy is truly asynchronous: the
+  // The tables go through one of the layout's two pinned host buffers, so the copy is truly asynchronous: the
   // call returns once it is enqueued, and the next ps_layout_append may rebuild the tables while it is in flight.
   // A buffer is reused two uploads later, after the copy that last read it has finished (an event per buffer).
   // An upload recorded into a graph has buffers of its own, which no other layout gets: its replays read them again, and

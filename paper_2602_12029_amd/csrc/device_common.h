@@ -28,7 +28,7 @@ struct AttnParams {
   float* ws_o;               // [num_slots][Hq][d]
   float* ws_lse;             // [num_slots][Hq]
   // whole step only (else null): where the prefill kernel puts the rows of a request with a single partial state, which
-  // then needs no merge
+  // then needs no merge; out on a 16-byte boundary
   void* out;                 // [R][Hq][d], query format
   float* out_lse;            // [R][Hq] or null
   bool keep_states;          // ... and whether it stores their partial states too (the caller can read the workspace)

@@ -93,7 +93,7 @@ struct ps_layout {
   std::vector<int32_t> suffix_chunk_size, suffix_chunks;
   int32_t planned_root_blk0 = 0;
   // upload staging (abi.hip): two pinned host buffers used alternately, so that ps_layout_upload returns as soon as
-  // its copy is enqueued and the tables may change again right away; released with the layout
+  // its copy is enqueued and the tables may change again right away; given to later layouts, or freed, with the layout
   struct upload_staging;
   mutable upload_staging* staging = nullptr;
   mutable void (*staging_free)(upload_staging*) = nullptr;

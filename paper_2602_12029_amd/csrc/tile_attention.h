@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
       // ---- O^T += V^T P^T
       if constexpr (S::kSplit) {
         // The probability as an exact sum of three bf16 terms, by truncation: its upper eight bits, the next eight, the
-        // rest, none negative.  Terms that would be zero are 2^-126 (lost in the sums) where the probability is not:
+        // rest, none negative (or none positive, where e4m3's V scale is negative: no infinities there).  Terms that would be zero are 2^-126 (lost in the sums) where the probability is not:
         // an infinite V then gives the infinity it should and no 0 * inf.
         bf16x8 pb[M][3];
         constexpr float kTiny = 0x1p-126f;
