@@ -56,6 +56,12 @@ __device__ __forceinline__ float row16_allreduce_sum(float x) {
   return x;
 }
 
+// What other lanes of the wave have written to LDS is read after this (no wave waits for another; LDS keeps a wave's order).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ float lane_xor(float x, int mask) {
   const int lane = int(threadIdx.x) & 63;
   return __int_as_float(__builtin_amdgcn_ds_bpermute((lane ^ mask) << 2, __float_as_int(x)));

@@ -9,15 +9,17 @@ namespace psdev {
 bool wave_supported(const ps_geometry& g);
 int32_t launch_wave_attention(const AttnParams& p, const ps_geometry& g, int item_begin, int n_items, hipStream_t st);
 // The same family for pools the tile kernel can address (blocks of 16 k tokens, see tile_supported): one workgroup per
-// item; max_rows: query rows per KV head of the widest item; stream: K/V tile loads are non-temporal.
+// item, the last n_solo of them (of up to 16 rows) four to a workgroup, from workgroup solo_block on; max_rows: query rows per KV head of the widest
+// item; stream: K/V tile loads are non-temporal.
 bool tile_supported(const AttnParams& p, const ps_geometry& g);
 int32_t launch_tile_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin,
-                              int n_items, hipStream_t st);
+                              int n_items, int n_solo, int solo_block, hipStream_t st);
 // Persistent launch: workgroup w walks wg_items[wg_indptr[w] .. wg_indptr[w+1]).
+// wg_solo: per workgroup, from which of its items on every wave takes one of its own (null: none).
 // `masked`: the set holds items whose rows see different token counts (per-request visible prefix lengths).
 // `stream`: K/V tile loads are non-temporal (the set's K/V is read by one item each, or nearly so).
-int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max_rows, int occ, bool masked, bool stream,
-                              const ps_item* wg_items, const int32_t* wg_indptr, int num_wg, hipStream_t st);
+int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool masked, bool stream,
+                              const ps_item* wg_items, const int32_t* wg_indptr, const int32_t* wg_solo, int num_wg, hipStream_t st);
 // Partial prefill: one workgroup per row-split item (up to `rows` query rows, 128 or 256, split over the waves by rows).
 int32_t launch_prefill_attention(const AttnParams& p, const ps_geometry& g, const ps_item* items, int num_items,
                                  int rows, hipStream_t st);

@@ -444,6 +444,21 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   if (prefix_mfma)
     for (const ps_item& it : prefix_items)
       if (!(it.kind & kPsItemRowSplit) && it.tok_end - it.tok_begin > mfma_cap) return PS_ERR_INVALID_ARG;
+  // Short private items of the tile kernel go four to a workgroup as well, a wave each, where the items are more than two
+  // rounds of the workgroups that are resident together (their last waves would otherwise end the launch: 736 items in 1.4
+  // rounds, float32, private segments of 1 to 256 tokens, 44.7 us without, 46 / 47.8 / 55.7 with those of up to 64 / 128 /
+  // 256).  Without and with (longest 64 / 128 / 256 tokens): 64-wide heads, 310 requests with up to 12 private tokens 21.9 /
+  // 14.7 / 14.7 / 14.7 us, 72 with up to 256 43.5 / 43.9 / 43.7 / 42.2; 256-wide, 659 with up to 119 163 / 143 / 131 / 131, in
+  // float32 147 with up to 142 56.4 / 56.3 / 51.3 / 52.1.
+  lay->num_solo_items = 0;
+  {
+    const int rows = std::max(group, lay->max_rows_prefix);
+    const int resident = g.head_dim == 256 || rows > 16 ? 1 : 2;
+    if (lay->suffix_variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && group <= 16 &&
+        int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident)
+      for (size_t i = suffix_items.size(); i-- > 0 && suffix_items[i].tok_end - suffix_items[i].tok_begin <= kPsSoloTokensTile;)
+        ++lay->num_solo_items;
+  }
   lay->num_prefix_items = int32_t(prefix_items.size());
   lay->items = std::move(prefix_items);
   lay->items.insert(lay->items.end(), suffix_items.begin(), suffix_items.end());
@@ -520,13 +535,12 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     return opt.kv_cache_policy == PS_KV_POLICY_AUTO ? 4 * tokens_reread < tokens_all
                                                      : opt.kv_cache_policy == PS_KV_POLICY_STREAM;
   };
-  auto pack = [&](int begin, int end) {
+  auto pack = [&](int begin, int end, bool solo_allowed) {
     packed out;
     const int count = end - begin;
     for (int i = begin; i < end; ++i) out.max_rows = std::max(out.max_rows, lay->items[size_t(i)].n_req * group);
     out.occ = ps_mfma_occupancy(out.max_rows, g.kv_dtype);
     out.stream = streams(begin, end);
-    const int num_wg = std::max(1, std::min(count, num_cus * out.occ));
     std::vector<int> order(size_t(count), 0);
     std::iota(order.begin(), order.end(), begin);
     auto cost = [&](int i) { return int64_t(lay->items[size_t(i)].tok_end - lay->items[size_t(i)].tok_begin) + 64; };
@@ -537,23 +551,57 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     if (!std::is_sorted(order.begin(), order.begin() + split, heavier)) std::stable_sort(order.begin(), order.begin() + split, heavier);
     if (!std::is_sorted(order.begin() + split, order.end(), heavier)) std::stable_sort(order.begin() + split, order.end(), heavier);
     std::inplace_merge(order.begin(), order.begin() + split, order.end(), heavier);
+    // Short items go four to a workgroup, one per wave (which fetches up to ps_solo_rows of query rows): the waves then neither
+    // share out a few tiles each nor meet to merge them, and a workgroup passes a quarter of the item boundaries.  Only where
+    // the items outnumber the workgroups: where each has one, a wave alone takes longer (four models on one context of 2741
+    // tokens, private segments of 1 to 256: 15.1 -> 18.8 us).  Measured, whole steps, longest such item 0 / 256 / 512 / 1024
+    // tokens: 256 prompts of 512 to 16384 tokens under 2 to 6 models, private 1 to 1024, 1179 / 1170 / 1160 / 1155 us; 52 of
+    // 20843, private 1 to 537, 739 / 722 / 703 / 705; 40 of 1024 to 6144, private 1 to 256, 118.2 / 115.6 / 115.5 / 115.5; e4m3,
+    // 64 of 8192, private 1 to 512, 219.3 / 217.8 / 215.5 / 215.7; 162 requests with up to 7 private tokens on 114 contexts
+    // 78.4 / 71.9; 87 requests on as many contexts of 147 tokens (two rows: the shared items too) 22.7 / 18.0.
+    const int64_t solo_tokens = count > num_cus * out.occ ? kPsSoloTokens : 0;
+    auto solo = [&](int i) {
+      const ps_item& it = lay->items[size_t(i)];
+      return solo_allowed && !lay->any_masked && it.tok_end - it.tok_begin <= solo_tokens && it.n_req * group <= ps_solo_rows(out.max_rows);
+    };
+    const int n_full = int(std::stable_partition(order.begin(), order.end(), [&](int i) { return !solo(i); }) - order.begin());
+    struct unit { int64_t cost; int first, count; };   // of `order`
+    std::vector<unit> units;
+    units.reserve(size_t(count));
+    for (int n = 0; n < n_full; ++n) units.push_back({cost(order[size_t(n)]), n, 1});
+    for (int n = n_full; n < count; n += 4) {
+      unit u{0, n, std::min(4, count - n)};
+      for (int i = 0; i < u.count; ++i) u.cost += cost(order[size_t(n + i)]);
+      units.push_back(u);
+    }
+    auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
+    std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
+    const int num_wg = std::max(1, std::min(int(units.size()), num_cus * out.occ));
     // least-loaded workgroup first, lowest index on ties: a min-heap of (assigned cost, workgroup)
     typedef std::pair<int64_t, int> slot;
     std::priority_queue<slot, std::vector<slot>, std::greater<slot>> load;
     for (int w = 0; w < num_wg; ++w) load.push({0, w});
-    std::vector<int> wg_of(size_t(count), 0), fill(size_t(num_wg) + 1, 0);
-    for (int n = 0; n < count; ++n) {
+    std::vector<int> wg_of(units.size(), 0), fill(size_t(num_wg) + 1, 0), full(size_t(num_wg), 0);
+    for (size_t n = 0; n < units.size(); ++n) {
       const slot least = load.top();
       load.pop();
-      wg_of[size_t(n)] = least.second;
-      ++fill[size_t(least.second) + 1];
-      load.push({least.first + cost(order[size_t(n)]), least.second});
+      wg_of[n] = least.second;
+      fill[size_t(least.second) + 1] += units[n].count;
+      if (units[n].first < n_full) ++full[size_t(least.second)];
+      load.push({least.first + units[n].cost, least.second});
     }
     for (int w = 0; w < num_wg; ++w) fill[size_t(w) + 1] += fill[size_t(w)];
     out.indptr.assign(fill.begin(), fill.end());
+    if (count > n_full)
+      for (int w = 0; w < num_wg; ++w) out.solo.push_back(out.indptr[size_t(w)] + full[size_t(w)]);
+    // a workgroup's items keep the order in which they were assigned, a wave's own ones after the others
     out.items.resize(size_t(count));
-    for (int n = 0; n < count; ++n)      // a workgroup's items keep the order in which they were assigned
-      out.items[size_t(fill[size_t(wg_of[size_t(n)])]++)] = lay->items[size_t(order[size_t(n)])];
+    std::vector<int> at_full(out.indptr.begin(), out.indptr.end()), at_solo(out.solo);
+    for (size_t n = 0; n < units.size(); ++n) {
+      const unit& u = units[n];
+      int& at = (u.first < n_full ? at_full : at_solo)[size_t(wg_of[n])];
+      for (int i = 0; i < u.count; ++i) out.items[size_t(at++)] = lay->items[size_t(order[size_t(u.first + i)])];
+    }
     if (count == 0) out.indptr.assign(1, 0);
     return out;
   };
@@ -563,9 +611,9 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   lay->stream_suffix = streams(lay->num_prefix_items, n_items);
   lay->stream_all = streams(0, n_items);
   const int first_packed = lay->num_rowsplit_items;   // row-split items run in the prefill kernel, one workgroup each
-  lay->pk_prefix = pre_mfma ? pack(first_packed, lay->num_prefix_items) : packed{};
-  lay->pk_suffix = suf_mfma ? pack(lay->num_prefix_items, n_items) : packed{};
-  lay->pk_all = (pre_mfma && suf_mfma) ? pack(first_packed, n_items) : packed{};
+  lay->pk_prefix = pre_mfma ? pack(first_packed, lay->num_prefix_items, false) : packed{};
+  lay->pk_suffix = suf_mfma ? pack(lay->num_prefix_items, n_items, false) : packed{};
+  lay->pk_all = (pre_mfma && suf_mfma) ? pack(first_packed, n_items, true) : packed{};
   return ps_blob_build(lay);
 }
 
@@ -616,6 +664,10 @@ int32_t ps_blob_build(ps_layout* lay) {
     words = pad4(words + 8 * int64_t(pk.items.size()));
     s.off_indptr = words;
     words = pad4(words + int64_t(pk.indptr.size()));
+    if (!pk.solo.empty()) {
+      s.off_solo = words;
+      words = pad4(words + int64_t(pk.solo.size()));
+    }
   };
   place(lay->sched_prefix, pk_prefix);
   place(lay->sched_suffix, pk_suffix);
@@ -711,6 +763,7 @@ int32_t ps_blob_build(ps_layout* lay) {
     if (pk.items.empty()) return;
     std::memcpy(b + s.off_items, pk.items.data(), pk.items.size() * sizeof(ps_item));
     std::copy(pk.indptr.begin(), pk.indptr.end(), b + s.off_indptr);
+    if (s.off_solo >= 0) std::copy(pk.solo.begin(), pk.solo.end(), b + s.off_solo);
   };
   fill(lay->sched_prefix, pk_prefix);
   fill(lay->sched_suffix, pk_suffix);
@@ -1169,6 +1222,19 @@ int32_t ps_layout_append(ps_pool* pool, ps_layout* lay, const int32_t* active, c
     else
       lay->suffix_chunk_size[size_t(r)] = int32_t(size);
   }
+  // (nor may an item that a wave has to itself outgrow it)
+  for (size_t i = lay->items.size() - size_t(lay->num_solo_items); i < lay->items.size() && same_structure; ++i) {
+    const ps_item& it = lay->items[i];
+    const int32_t r = it.req_off - R;
+    same_structure = std::min(lay->suffix_len[size_t(r)] - it.tok_begin, lay->suffix_chunk_size[size_t(r)]) <= 2 * kPsSoloTokens;
+  }
+  for (size_t w = 0; w < lay->pk_all.solo.size() && same_structure; ++w)
+    for (int32_t i = lay->pk_all.solo[w]; i < lay->pk_all.indptr[w + 1] && same_structure; ++i) {
+      const ps_item& it = lay->pk_all.items[size_t(i)];
+      if (!(it.kind & kPsItemSuffix)) continue;
+      const int32_t r = it.req_off - R;
+      same_structure = std::min(lay->suffix_len[size_t(r)] - it.tok_begin, lay->suffix_chunk_size[size_t(r)]) <= 2 * kPsSoloTokens;
+    }
   if (same_structure) {
     const int32_t prefix_blocks = int32_t(lay->prefix_blk.size());
     const int32_t root_shift = int32_t(lay->prefix_blk.size() + lay->suffix_blk.size()) - lay->planned_root_blk0;

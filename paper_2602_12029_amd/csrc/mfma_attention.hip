@@ -25,6 +25,12 @@
 // fetch the first tiles of the workgroup's next item, whose block ids and query rows were fetched
 // one item earlier, so the cross-wave merge and partial-state store at the end of an item overlap
 // with loads in flight.
+//
+// Short items (private segments of a few hundred tokens, shared ones of a few rows) come four at a time, one per wave: such an
+// item is a handful of tiles, shared out over four waves it is mostly the meeting at its end, and what bounds a launch of many
+// is the number of those meetings.  A wave then keeps the item's queries in a row tile of its own, takes all its tiles, and
+// stores its rows without a barrier, so the four run apart.  78 contexts of 161 to 644 tokens under three models with one to
+// six private tokens each: 55.8 -> 36 us a launch; 256 contexts of 512 to 16384 tokens with up to 1024 private ones: 1.6 %.
 #include <type_traits>
 
 #include "device_common.h"
@@ -58,9 +64,11 @@ struct TileRegs<PS_FP8_E4M3> {
 
 // Wave-uniform view of one work item for one wave.
 struct ItemCtx {
-  int blk_off, tok_begin, tok_end, req_off, n_req, kv_head, split_local;
-  int rows, nt_used, my_tiles, sub0, sub_end;
-  int kind;            // the item's flag bits
+  int blk_off, tok_end, req_off, kv_head, split_local;
+  int rows, nt_used, my_tiles;
+  int first_sub, tile_shift, sub_end;   // this wave's tile k starts at 16-token block first_sub + (k << tile_shift) of the segment
+  int solo;            // this wave has the item to itself (and its neighbours in the list one each)
+  int q_tile;          // first row tile of the item's queries in LDS
   int masked;          // non-zero: some row of the item sees fewer tokens than tok_end (MASKED kernels only)
   // (fourteen ints, then the 64-bit address: no padding anywhere, so the struct still splits into registers)
   int64_t head_base;   // address of the item's KV head slice in block 0
@@ -112,10 +120,14 @@ __device__ __forceinline__ int k_step_elem(int step, int kg) {
   return 32 * kg + 8 * step;
 }
 
-template <int NT>
-struct QIndex { int idx[NT]; };   // global q row (request * Hq + head) this thread fetches per row tile, -1 = padding
-template <int NT>
-struct QRegs { u32x4 piece[NT]; };
+// 16-byte query pieces a thread fetches per item: one per row tile, or the four rows 4 t .. 4 t + 3 of a wave's own item
+// (at least two, so that private items of up to eight rows can have a wave to themselves)
+template <int NT, bool SOLO>
+constexpr int q_pieces() { return SOLO && NT < 2 ? 2 : NT; }
+template <int N>
+struct QIndex { int idx[N]; };   // global q row (request * Hq + head) per piece, -1 = padding
+template <int N>
+struct QRegs { u32x4 piece[N]; };
 template <int NT>
 struct RowLimit { int lim[NT]; };  // per row tile: first token that row (lane % 16) of the tile does not see
 
@@ -123,17 +135,20 @@ struct RowLimit { int lim[NT]; };  // per row tile: first token that row (lane %
 
 // NT: 16-row tiles carried; NB: tile buffers in the register ring; OCC: waves per SIMD the register
 // budget is sized for; MASKED: rows may see only a leading part of an item's token range (per-request visible
-// prefix length), which costs a compare per score and guards against rows that have seen nothing yet.
-template <int NT, int KVT, int NB, int OCC, bool MASKED, bool STREAM>
+// prefix length), which costs a compare per score and guards against rows that have seen nothing yet; SOLO: the lists end
+// with short items that a wave takes alone (a launch without them keeps the smaller kernel: some 3 KB less code to fetch).
+template <int NT, int KVT, int NB, int OCC, bool MASKED, bool STREAM, bool SOLO>
 __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, const ps_item* __restrict__ wg_items,
-                                                                  const int32_t* __restrict__ wg_indptr) {
+                                                                  const int32_t* __restrict__ wg_indptr,
+                                                                  const int32_t* __restrict__ wg_solo) {
   __shared__ float sm_o[kWaves][16][kLdsRow];
   __shared__ float sm_m[kWaves][16];
   __shared__ float sm_l[kWaves][16];
-  __shared__ __attribute__((aligned(16))) uint16_t sm_q[NT][16][kQRow];
+  __shared__ __attribute__((aligned(16))) uint16_t sm_q[SOLO && NT < kWaves ? kWaves : NT][16][kQRow];
   __shared__ __attribute__((aligned(16))) int32_t sm_hdr[kHdrRing][8];
 
   const int j_first = wg_indptr[blockIdx.x], j_last = wg_indptr[blockIdx.x + 1];
+  const int j_solo = SOLO ? wg_solo[blockIdx.x] : j_last;   // from here on an item per wave, four at a time
   if (j_first >= j_last) return;
 
   const int lane = threadIdx.x & 63;
@@ -142,6 +157,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   const int kg = lane >> 4;
   const int G = p.group;
   const float neg_inf = -__builtin_inff();
+  constexpr int kPieces = q_pieces<NT, SOLO>();
   // 16-token sub-blocks per physical block: a power of two (the launcher checks), so index math is shifts
   const int sub_shift = __builtin_ctz(unsigned(p.block_size >> 4));
   const int sub_mask = (p.block_size >> 4) - 1;
@@ -162,23 +178,36 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
     for (int i = threadIdx.x; i < count * 8; i += 256)
       sm_hdr[((first - j_first) + (i >> 3)) % kHdrRing][i & 7] = src[i];
   };
+  auto next_item = [&](int j) { return SOLO && j >= j_solo ? j + kWaves : j + 1; };
+  static_assert(kWaves == 4, "the tiles of an item that four waves share lie eight 16-token blocks apart");
   auto item_ctx = [&](int j) {
-    const int32_t* h = sm_hdr[(j - j_first) % kHdrRing];
     ItemCtx c;
+    c.solo = SOLO && j >= j_solo;
+    const int mine = c.solo ? min(j + wave, j_last - 1) : j;
+    const int32_t* h = sm_hdr[(mine - j_first) % kHdrRing];
     c.blk_off = __builtin_amdgcn_readfirstlane(h[0]);
-    c.tok_begin = __builtin_amdgcn_readfirstlane(h[1]);
+    const int tok_begin = __builtin_amdgcn_readfirstlane(h[1]);
     c.tok_end = __builtin_amdgcn_readfirstlane(h[2]);
     c.req_off = __builtin_amdgcn_readfirstlane(h[3]);
-    c.n_req = __builtin_amdgcn_readfirstlane(h[4]);
+    c.rows = __builtin_amdgcn_readfirstlane(h[4]) * G;
     c.kv_head = __builtin_amdgcn_readfirstlane(h[5]);
     c.split_local = __builtin_amdgcn_readfirstlane(h[6]);
-    c.kind = __builtin_amdgcn_readfirstlane(h[7]);
-    c.masked = MASKED ? (c.kind & kPsItemMasked) : 0;
-    c.rows = c.n_req * G;
+    c.masked = MASKED ? (__builtin_amdgcn_readfirstlane(h[7]) & kPsItemMasked) : 0;
+    const int tiles_total = (c.tok_end - tok_begin + kTile - 1) / kTile;
+    if (c.solo) {
+      const bool none = j + wave >= j_last;   // the last four may be fewer
+      c.rows = none ? 0 : c.rows;
+      c.my_tiles = none ? 0 : tiles_total;
+      c.first_sub = tok_begin >> 4;
+      c.tile_shift = 1;
+      c.q_tile = wave;
+    } else {
+      c.my_tiles = tiles_total > wave ? (tiles_total - wave + kWaves - 1) / kWaves : 0;
+      c.first_sub = (tok_begin >> 4) + 2 * wave;
+      c.tile_shift = 3;
+      c.q_tile = 0;
+    }
     c.nt_used = (c.rows + 15) >> 4;
-    const int tiles_total = (c.tok_end - c.tok_begin + kTile - 1) / kTile;
-    c.my_tiles = tiles_total > wave ? (tiles_total - wave + kWaves - 1) / kWaves : 0;
-    c.sub0 = c.tok_begin >> 4;
     c.sub_end = (c.tok_end + 15) >> 4;
     c.head_base = kv_base + int64_t(c.kv_head) * p.s_head * kEsz;
     return c;
@@ -190,7 +219,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       const int k = 32 * r + (lane >> 1);
-      const int sub = c.sub0 + 2 * (wave + kWaves * k) + (lane & 1);
+      const int sub = c.first_sub + (k << c.tile_shift) + (lane & 1);
       if (k < c.my_tiles && sub < c.sub_end) {
         m.ids[r] = p.blk[c.blk_off + (sub >> sub_shift)];
         if constexpr (KVT == PS_FP8_E4M3) {
@@ -219,23 +248,24 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
     return r;
   };
 
-  // query rows: one 16-byte piece per thread and row tile (row = thread / 16, piece = thread % 16)
+  // query rows: one 16-byte piece per thread and row tile (row = thread / 16, piece = thread % 16); of a wave's own item
+  // the wave's 64 lanes fetch four rows a piece
+  auto q_row = [&](const ItemCtx& c, int t) { return c.solo ? 4 * t + kg : 16 * t + (int(threadIdx.x) >> 4); };
   auto q_row_index = [&](const ItemCtx& c) {
-    QIndex<NT> r;
-    const int rr = threadIdx.x >> 4;
+    QIndex<kPieces> r;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int row = 16 * t + rr;
+    for (int t = 0; t < kPieces; ++t) {
+      const int row = q_row(c, t);
       r.idx[t] = -1;
       if (row < c.rows) r.idx[t] = p.req_list[c.req_off + row / G] * p.num_q_heads + c.kv_head * G + row % G;
     }
     return r;
   };
-  auto load_q = [&](const QIndex<NT>& rows_idx) {
-    QRegs<NT> q;
+  auto load_q = [&](const QIndex<kPieces>& rows_idx) {
+    QRegs<kPieces> q;
     const int cpiece = threadIdx.x & 15;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t = 0; t < kPieces; ++t) {
       q.piece[t] = u32x4{0, 0, 0, 0};
       if (rows_idx.idx[t] >= 0)
         q.piece[t] = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(p.q) +
@@ -243,10 +273,13 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
     }
     return q;
   };
-  auto store_q = [&](const QRegs<NT>& q) {
-    const int rr = threadIdx.x >> 4, cpiece = threadIdx.x & 15;
+  auto store_q = [&](const QRegs<kPieces>& q, const ItemCtx& c) {
+    const int cpiece = threadIdx.x & 15;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) *reinterpret_cast<u32x4*>(&sm_q[t][rr][8 * cpiece]) = q.piece[t];
+    for (int t = 0; t < kPieces; ++t) {
+      const int row = 16 * c.q_tile + q_row(c, t);   // (rows past the item's tiles: into tiles that no wave reads)
+      *reinterpret_cast<u32x4*>(&sm_q[row >> 4][row & 15][8 * cpiece]) = q.piece[t];
+    }
   };
 
   // ---- tile loads: buffer loads, block base in SGPRs, two loop-invariant VGPR offsets ---------------------
@@ -256,7 +289,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   // immediate of the load and a branch around loads would spoil the wait counts, hence one choice per launch.
   constexpr int kPolicy = STREAM ? kNonTemporal : 0;
   auto load_item_tile = [&](TileRegs<KVT>& tr, const ItemCtx& c, const ItemMeta& m, int k, bool live) {
-    const int sub_a = c.sub0 + 2 * (wave + kWaves * k);
+    const int sub_a = c.first_sub + (k << c.tile_shift);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int sub = sub_a + b;
@@ -303,7 +336,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   auto compute_tile = [&](TileRegs<KVT>& tr, const ItemCtx& c, const ItemMeta& meta, const RowLimit<NT>& rl, int k,
                           auto all_rows_tag, auto full_tag) {
     constexpr bool kAllRows = decltype(all_rows_tag)::value, kFull = decltype(full_tag)::value;
-    const int tok0 = c.tok_begin + kTile * (wave + kWaves * k);  // first token of the tile
+    const int tok0 = 16 * (c.first_sub + (k << c.tile_shift));  // first token of the tile
     const bool full = kFull || tok0 + kTile <= c.tok_end;
     // Per 16-token block: scores are raw dot products times sc_k (1/sqrt(d) in log2 units, times the block's K
     // scale); the block's V scale rides in the exponent of the probabilities (lvs = log2 of it), so that the
@@ -345,7 +378,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
         bf16x8 qb[4];
 #pragma unroll
         for (int st = 0; st < 4; ++st)
-          qb[st] = as_bf16x8(*reinterpret_cast<const u32x4*>(&sm_q[t][n][k_step_elem<KVT>(st, kg)]));
+          qb[st] = as_bf16x8(*reinterpret_cast<const u32x4*>(&sm_q[c.q_tile + t][n][k_step_elem<KVT>(st, kg)]));
         f32x4 s[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -445,6 +478,26 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
     }
   };
 
+  // a wave's own item: nothing to merge, no wave to wait for
+  auto epilogue_solo = [&](const ItemCtx& c) {
+    float l = l_run[0];
+    l += lane_xor(l, 16);
+    l += lane_xor(l, 32);
+    if (n < c.rows) {
+      const float inv = l > 0.f ? 1.f / l : 0.f;
+      const int64_t slot = int64_t(p.slot_base[p.req_list[c.req_off + n / G]]) + c.split_local;
+      const int64_t row = slot * p.num_q_heads + c.kv_head * G + n % G;
+      float* o = p.ws_o + row * kD + 32 * kg;
+      // lane (n, kg), acc[cc][j] = O[row n][32 kg + 8 j + cc]
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        *reinterpret_cast<f32x4*>(o + 8 * j) = f32x4{acc[0][0][j], acc[0][1][j], acc[0][2][j], acc[0][3][j]} * inv;
+        *reinterpret_cast<f32x4*>(o + 8 * j + 4) = f32x4{acc[0][4][j], acc[0][5][j], acc[0][6][j], acc[0][7][j]} * inv;
+      }
+      if (kg == 0) p.ws_lse[row] = l > 0.f ? (m_run[0] + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
+    }
+  };
+
   // merge the four waves of the item and write one partial state per row
   auto epilogue = [&](const ItemCtx& c) {
 #pragma unroll
@@ -517,31 +570,33 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   TileRegs<KVT> buf[NB];
 #pragma unroll
   for (int u = 0; u < NB - 1; ++u) load_item_tile(buf[u], cur, meta, u, true);
-  store_q(load_q(q_row_index(cur)));
-  bool has_next = j_first + 1 < j_last;
+  store_q(load_q(q_row_index(cur)), cur);
+  int j = j_first, j_next = next_item(j);
+  bool has_next = j_next < j_last;
   ItemCtx nxt = cur;
   ItemMeta meta_nxt = kNoMeta;
-  QIndex<NT> q_idx_nxt{};
+  QIndex<kPieces> q_idx_nxt{};
   RowLimit<NT> lim_nxt{};
   if (has_next) {
-    nxt = item_ctx(j_first + 1);
+    nxt = item_ctx(j_next);
     meta_nxt = fetch_meta(nxt);
     lim_nxt = fetch_limits(nxt);
     q_idx_nxt = q_row_index(nxt);
   }
   __syncthreads();
 
-  for (int j = j_first; j < j_last; ++j) {
+  for (;;) {
     // query rows of the next item (their indices arrived long ago), fetches for the item after it
-    QRegs<NT> q_nxt{};
+    QRegs<kPieces> q_nxt{};
     if (has_next) q_nxt = load_q(q_idx_nxt);
-    const bool has_nn = j + 2 < j_last;
+    const int j_nn = next_item(j_next);
+    const bool has_nn = has_next && j_nn < j_last;
     ItemCtx nn = nxt;
     ItemMeta meta_nn = kNoMeta;
-    QIndex<NT> q_idx_nn{};
+    QIndex<kPieces> q_idx_nn{};
     RowLimit<NT> lim_nn{};
     if (has_nn) {
-      nn = item_ctx(j + 2);
+      nn = item_ctx(j_nn);
       meta_nn = fetch_meta(nn);
       lim_nn = fetch_limits(nn);
       q_idx_nn = q_row_index(nn);
@@ -573,15 +628,25 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
       if (s0 + u < cur.my_tiles) compute_tile(buf[u], cur, meta, lim, s0 + u, std::false_type{}, std::false_type{});
     }
 
-    epilogue(cur);   // ends with a barrier: sm_q and the consumed half of the header ring are free
+    if (cur.solo) epilogue_solo(cur);
+    else epilogue(cur);   // ends with a barrier: sm_q and the consumed half of the header ring are free
+    if (!has_next) break;
 
-    if (has_next) store_q(q_nxt);
-    const int li = j + 1 - j_first;                     // items consumed so far
-    if ((li % (kHdrRing / 2)) == 0) {                   // refill the half of the header ring just used up
-      const int first = j_first + li + kHdrRing / 2;
-      if (first < j_last) stage_headers(first, min(kHdrRing / 2, j_last - first));
+    // refill the half of the header ring just used up (four items at a time may step over its end)
+    constexpr int kHalf = kHdrRing / 2;
+    const int half = (j_next - j_first) / kHalf;
+    const bool refill = half != (j - j_first) / kHalf;
+    // (a wave with an item of its own reads and writes query rows of its own, and so it does for the items after it)
+    store_q(q_nxt, nxt);
+    if (cur.solo && refill) __syncthreads();
+    if (refill) {
+      const int first = j_first + (half + 1) * kHalf;
+      if (first < j_last) stage_headers(first, min(kHalf, j_last - first));
     }
-    __syncthreads();
+    if (cur.solo && !refill) wave_lds_order();
+    else __syncthreads();
+    j = j_next;
+    j_next = j_nn;
     cur = nxt;
     meta = meta_nxt;
     lim = lim_nxt;
@@ -593,37 +658,41 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   }
 }
 
-int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max_rows, int occ, bool masked, bool stream,
-                              const ps_item* wg_items, const int32_t* wg_indptr, int num_wg, hipStream_t st) {
+int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool masked, bool stream,
+                              const ps_item* wg_items, const int32_t* wg_indptr, const int32_t* wg_solo, int num_wg, hipStream_t st) {
   if (num_wg <= 0) return PS_OK;
   const int spb = g.block_size / 16;
   if (g.head_dim != kD || g.q_dtype != PS_BF16 || g.block_size % 16 != 0 || (spb & (spb - 1)) != 0 || max_rows > 64)
     return PS_ERR_UNSUPPORTED;
   if (g.kv_dtype != PS_BF16 && g.kv_dtype != PS_FP8_E4M3) return PS_ERR_UNSUPPORTED;
+  if (wg_solo && (masked || g.num_q_heads / g.num_kv_heads > ps_solo_rows(max_rows))) return PS_ERR_UNSUPPORTED;
   const dim3 grid(num_wg), block(256);
   const int nt = max_rows <= 16 ? 1 : (max_rows <= 32 ? 2 : 4);
-#define PS_LAUNCH_AS(NT, KVT, NB, OCC, MASKED, STREAM) \
-  hipLaunchKernelGGL((mfma_attention_kernel<NT, KVT, NB, OCC, MASKED, STREAM>), grid, block, 0, st, p, wg_items, wg_indptr)
-#define PS_LAUNCH(NT, KVT, NB, OCC)                                \
-  do {                                                             \
-    if (masked) {                                                  \
-      if (stream) PS_LAUNCH_AS(NT, KVT, NB, OCC, true, true);      \
-      else PS_LAUNCH_AS(NT, KVT, NB, OCC, true, false);            \
-    } else {                                                       \
-      if (stream) PS_LAUNCH_AS(NT, KVT, NB, OCC, false, true);     \
-      else PS_LAUNCH_AS(NT, KVT, NB, OCC, false, false);           \
-    }                                                              \
+#define PS_LAUNCH_AS(NT, KVT, OCC, MASKED, STREAM, SOLO) \
+  hipLaunchKernelGGL((mfma_attention_kernel<NT, KVT, 2, OCC, MASKED, STREAM, SOLO>), grid, block, 0, st, p, wg_items, wg_indptr, wg_solo)
+#define PS_LAUNCH(NT, KVT, OCC)                                  \
+  do {                                                           \
+    if (masked) {                                                \
+      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, true, true, false); \
+      else PS_LAUNCH_AS(NT, KVT, OCC, true, false, false);       \
+    } else if (wg_solo) {                                        \
+      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, false, true, true); \
+      else PS_LAUNCH_AS(NT, KVT, OCC, false, false, true);       \
+    } else {                                                     \
+      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, false, true, false); \
+      else PS_LAUNCH_AS(NT, KVT, OCC, false, false, false);      \
+    }                                                            \
   } while (0)
-  // two tile buffers per wave everywhere (deeper rings measured no faster); `occ` is the residency the
-  // plan sized the grid for (ps_mfma_occupancy)
+  // two tile buffers per wave everywhere (deeper rings measured no faster); the waves per SIMD are those that the plan
+  // sized the grid for (ps_mfma_occupancy)
   if (g.kv_dtype == PS_BF16) {
-    if (nt == 1) { if (occ == 2) PS_LAUNCH(1, PS_BF16, 2, 2); else PS_LAUNCH(1, PS_BF16, 2, 1); }
-    else if (nt == 2) PS_LAUNCH(2, PS_BF16, 2, 1);
-    else PS_LAUNCH(4, PS_BF16, 2, 1);
+    if (nt == 1) PS_LAUNCH(1, PS_BF16, 2);
+    else if (nt == 2) PS_LAUNCH(2, PS_BF16, 1);
+    else PS_LAUNCH(4, PS_BF16, 1);
   } else {
-    if (nt == 1) { if (occ == 2) PS_LAUNCH(1, PS_FP8_E4M3, 2, 2); else PS_LAUNCH(1, PS_FP8_E4M3, 2, 1); }
-    else if (nt == 2) { if (occ == 2) PS_LAUNCH(2, PS_FP8_E4M3, 2, 2); else PS_LAUNCH(2, PS_FP8_E4M3, 2, 1); }
-    else PS_LAUNCH(4, PS_FP8_E4M3, 2, 1);
+    if (nt == 1) PS_LAUNCH(1, PS_FP8_E4M3, 2);
+    else if (nt == 2) PS_LAUNCH(2, PS_FP8_E4M3, 2);
+    else PS_LAUNCH(4, PS_FP8_E4M3, 1);
   }
 #undef PS_LAUNCH
 #undef PS_LAUNCH_AS

@@ -59,6 +59,7 @@ struct ps_layout {
   std::vector<ps_item> items;        // row-split shared items, then the other shared (root, prefix) items, then suffix items
   int32_t rowsplit_rows = 256;       // most rows of a row-split item: the prefill kernel's workgroup takes 32 a wave
   int32_t num_rowsplit_items = 0;    // launched one workgroup each by the prefill kernel, outside the schedules
+  int32_t num_solo_items = 0;        // tile kernel: the last items, private and short, a wave each
   int32_t num_prefix_items = 0;      // all shared items: root and prefix, row-split ones included
   // K/V loads of a launch over the shared / private / all items are non-temporal (little of its K/V is read by several)
   bool stream_prefix = true, stream_suffix = true, stream_all = true;
@@ -75,6 +76,7 @@ struct ps_layout {
   // workgroup w owns [indptr[w], indptr[w+1])) -- one schedule per launchable set
   struct schedule {
     int64_t off_items = 0, off_indptr = 0;  // blob offsets in words
+    int64_t off_solo = -1;  // int32[num_wg]: the workgroup's first item that a wave takes alone; -1: no such items
     int32_t num_wg = 0, max_rows = 0, occ = 1;  // occ: workgroups per compute unit the grid was sized for
     bool stream = true;   // K/V loads of the launch are non-temporal (little of the set's K/V is read by several items)
   };
@@ -84,6 +86,7 @@ struct ps_layout {
   struct packed_set {
     std::vector<ps_item> items;
     std::vector<int32_t> indptr;
+    std::vector<int32_t> solo;       // empty, or per workgroup where its solo items begin (see kPsSoloTokens)
     int32_t max_rows = 0, occ = 1;
     bool stream = true;
   };
@@ -129,6 +132,13 @@ inline int ps_mfma_occupancy(int max_rows, int kv_dtype) {
   return 1;
 }
 constexpr int kPsMfmaMaxChunk = 8192;  // tokens per MFMA work item (64 tiles per wave: their block ids fill two registers)
+// Items short enough for one wave, four at a time in a workgroup, in the persistent and in the tile kernel (the rules and
+// their figures are in build_plan).  A private one that appends have made twice as long is planned again, well inside the
+// 64 tiles of a wave.
+constexpr int kPsSoloTokens = 512, kPsSoloTokensTile = 256;
+static_assert(2 * kPsSoloTokens <= kPsMfmaMaxChunk / 4, "a wave's own item holds up to 64 tiles of 32 tokens");
+// Rows of such an item in the persistent kernel: what a wave fetches of the queries, by the row tiles the launch carries.
+inline int ps_solo_rows(int max_rows) { return max_rows <= 32 ? 8 : 16; }
 
 // Compute units of the current device, or 0 if none can be asked.  Null in a build without the device side of the
 // library (the planner then assumes kPsDefaultNumCus); abi.hip installs it when the library is loaded.

@@ -5,7 +5,8 @@
 // One workgroup (4 waves) takes one work item: a token range of one KV segment and one KV head, applied to every query
 // row that reads it.  The waves take 16- or 32-token tiles of the range in turn, stream K and V straight into matrix
 // operand registers, keep an online softmax per row and merge through LDS at the end; one partial state per row leaves
-// the workgroup.  As in the bf16 decode kernel the products are the transposed ones,
+// the workgroup.  (Short private items go four to a workgroup, a wave each, with nothing to merge: 748 items of 1 to 257 tokens
+// 19.9 -> 12.7 us a launch, 3076 of 256-wide heads 159 -> 125.)  As in the bf16 decode kernel the products are the transposed ones,
 //   S^T[token, row] = K[token, :] . Q[row, :]        A = K, B = Q^T
 //   O^T[dcol, row] += V^T[dcol, token] . P^T[token, row]        A = V^T, B = P^T
 // so that a lane's scores are, in place, its operand of the second product, and no cross-lane traffic is needed but
@@ -103,22 +104,36 @@ struct Regs {
   typename LoadWords<S::kVWords>::type v[S::kBlocks][4][S::kVLoads];   // [block][token 4 kg + j][piece of the row]
 };
 
-}  // namespace tile
-
-// NT: 16-row tiles a pass over the tokens carries at most (an item with fewer rows takes the narrowest of 1, 2, 4
-// that holds them; one with more walks its tokens again).  OCC: waves per SIMD the registers are budgeted for.
-// STREAM: K/V loads are non-temporal (the launch's ranges are read by one item each, or nearly so).
-template <int D, int KVT, int QT, int NT, int OCC, bool STREAM>
-__global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, int item_begin) {
-  using namespace tile;
+// LDS of a workgroup: query rows (of a wave's own item: 16 each), then what the waves of a shared item merge.
+template <int D, int KVT, int QT, int NT>
+struct Lds {
   typedef Shape<D, KVT, QT> S;
   typedef std::conditional_t<S::kSplit, uint16_t, float> q_elem;
-  __shared__ __attribute__((aligned(16))) q_elem sm_q[16 * NT][S::kQRow];
-  __shared__ __attribute__((aligned(16))) float sm_o[kWaves][16][D + 4];
-  __shared__ float sm_m[kWaves][16];
-  __shared__ float sm_l[kWaves][16];
+  union {
+    struct {
+      __attribute__((aligned(16))) q_elem q[16 * NT][S::kQRow];
+      __attribute__((aligned(16))) float o[kWaves][16][D + 4];
+      float m[kWaves][16], l[kWaves][16];
+    };
+    __attribute__((aligned(16))) q_elem q_own[kWaves][16][S::kQRow];
+  };
+};
 
-  const ps_item* ip = p.items + item_begin + blockIdx.x;
+// One item: by the four waves of a workgroup, or (SOLO, up to 16 rows) by one wave alone.
+// NT: 16-row tiles a pass over the tokens carries at most (an item with fewer rows takes the narrowest of 1, 2, 4
+// that holds them; one with more walks its tokens again).
+// STREAM: K/V loads are non-temporal (the launch's ranges are read by one item each, or nearly so).
+template <int D, int KVT, int QT, int NT, bool STREAM, bool SOLO, typename LDS>
+__device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& lds) {
+  typedef Shape<D, KVT, QT> S;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  auto* sm_q = SOLO ? lds.q_own[wave] : lds.q;
+  auto* sm_o = lds.o;
+  auto* sm_m = lds.m;
+  auto* sm_l = lds.l;
+  const int tile0 = SOLO ? 0 : wave;
+  constexpr int kStep = SOLO ? 1 : kWaves;   // the wave's tiles of the item: tile0, tile0 + kStep, ...
+  const ps_item* ip = p.items + item;
   const int blk_off = __builtin_amdgcn_readfirstlane(ip->blk_off);
   const int tok_begin = __builtin_amdgcn_readfirstlane(ip->tok_begin);
   const int tok_end = __builtin_amdgcn_readfirstlane(ip->tok_end);
@@ -129,7 +144,6 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
   const bool masked = (__builtin_amdgcn_readfirstlane(ip->kind) & kPsItemMasked) != 0;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int n = lane & 15;   // query row of a row tile / token of a block (K) / column lane (V), by role
   const int kg = lane >> 4;
   const int G = p.group;
@@ -148,7 +162,7 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const const_i32_ptr blk_seg = (const_i32_ptr)(p.blk + blk_off);
   const int tiles_total = (sub_end - sub0 + S::kBlocks - 1) / S::kBlocks;
-  const int my_tiles = tiles_total > wave ? (tiles_total - wave + kWaves - 1) / kWaves : 0;
+  const int my_tiles = SOLO ? tiles_total : tiles_total > wave ? (tiles_total - wave + kWaves - 1) / kWaves : 0;
 
   // where a tile's blocks lie (scalar): physical block, and byte offset of the 16 tokens in it (-1: past the range)
   struct Place { int id[S::kBlocks], off[S::kBlocks]; };
@@ -158,7 +172,7 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
     Place pl;
 #pragma unroll
     for (int b = 0; b < S::kBlocks; ++b) {
-      const int sub = sub0 + S::kBlocks * (wave + kWaves * k) + b;
+      const int sub = sub0 + S::kBlocks * (tile0 + kStep * k) + b;
       const int c = min(sub, sub_end - 1);
       const int block = spb == 1 ? c : c / spb;
       pl.id[b] = blk_seg[block];
@@ -222,11 +236,13 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
 #pragma unroll
     for (int u = 0; u < S::kRing - 1; ++u) scl[u] = scales_of(at[u]);
 
-    // query rows -> LDS (float32 form: widened; rows past the item: zero)
+    // query rows -> LDS (float32 form: widened; rows past the item: zero).  A wave with an item of its own fills those
+    // that the item has (the others' sums go nowhere).
     {
       constexpr int kQEsz = QT == PS_F32 ? 4 : 2;
       constexpr int kPieces = D * kQEsz / 16;          // 16-byte pieces of a query row
-      for (int i = threadIdx.x; i < 16 * M * kPieces; i += 256) {
+      const int pieces = (SOLO ? rows : 16 * M) * kPieces;
+      for (int i = SOLO ? lane : int(threadIdx.x); i < pieces; i += SOLO ? 64 : 256) {
         const int r = i / kPieces, c = i % kPieces;
         u32x4 w = {0, 0, 0, 0};
         if (row0 + r < rows) {
@@ -251,7 +267,8 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
       const int row = row0 + 16 * t + n;
       if (masked && row < rows) lim[t] = min(tok_end, p.visible[p.req_list[req_off + row / G]]);
     }
-    __syncthreads();
+    if constexpr (SOLO) wave_lds_order();
+    else __syncthreads();
 
     float m_run[M], l_run[M];
     f32x4 acc[M][S::kGroups];
@@ -264,7 +281,7 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
     }
 
     auto multiply = [&](Regs<D, KVT, QT>& r, const Scales& sc, int k) __attribute__((always_inline)) {
-      const int tok0 = tok_begin + S::kTokens * (wave + kWaves * k);
+      const int tok0 = tok_begin + S::kTokens * (tile0 + kStep * k);
       const bool whole = !masked && tok0 + S::kTokens <= tok_end;   // every row sees the whole tile
       // ---- scores of every row tile
       // (float32 form: the products are summed as a tree -- four chains over two 64-byte pieces, their pairs, the pieces of
@@ -447,22 +464,22 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
       } else {
         // (a block's sixteen tokens are summed by themselves and then added to the row's sum: fewer roundings at the
         // magnitude of the whole)
-        constexpr int kStep = 4;   // column groups at a time
+        constexpr int kCols = 4;   // column groups at a time
 #pragma unroll
         for (int b = 0; b < S::kBlocks; ++b)
 #pragma unroll
           for (int c = 0; c < S::kVLoads; ++c)
 #pragma unroll
-            for (int e4 = 0; e4 < S::kVElems; e4 += kStep) {
-              f32x4 sum[M][kStep];
+            for (int e4 = 0; e4 < S::kVElems; e4 += kCols) {
+              f32x4 sum[M][kCols];
 #pragma unroll
               for (int t = 0; t < M; ++t)
 #pragma unroll
-                for (int e = 0; e < kStep; ++e) sum[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int e = 0; e < kCols; ++e) sum[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
               for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int e = 0; e < kStep; ++e) {
+                for (int e = 0; e < kCols; ++e) {
                   const float vf = widen<KVT>(r.v[b][j][c], e4 + e);
 #pragma unroll
                   for (int t = 0; t < M; ++t) sum[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, s[t][b][j], sum[t][e], 0, 0, 0);
@@ -470,7 +487,7 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
 #pragma unroll
               for (int t = 0; t < M; ++t)
 #pragma unroll
-                for (int e = 0; e < kStep; ++e) acc[t][c * S::kVElems + e4 + e] += sum[t][e];
+                for (int e = 0; e < kCols; ++e) acc[t][c * S::kVElems + e4 + e] += sum[t][e];
               // (left to itself the compiler starts every group at once and spills, and scratch traffic is counted with the
               // tile loads: 51.4 us against 45.5 on the float32 batch above)
               __builtin_amdgcn_sched_barrier(0);
@@ -489,6 +506,30 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
         at[u] = locate(k0 + u + R);
         if (k0 + u < my_tiles) multiply(buf[u], scl[u], k0 + u);
       }
+    }
+
+    // ---- a wave's own item: nothing to merge
+    if constexpr (SOLO) {
+      float l = l_run[0];
+      l += lane_xor(l, 16);
+      l += lane_xor(l, 32);
+      if (n < rows) {
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        const int64_t slot = int64_t(p.slot_base[p.req_list[req_off + n / G]]) + split_local;
+        const int64_t row = slot * p.num_q_heads + kv_head * G + n % G;
+        float* o = p.ws_o + row * D;
+#pragma unroll
+        for (int c = 0; c < S::kVLoads; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < S::kVElems; e += 4)
+              *reinterpret_cast<f32x4*>(o + 16 * S::kVElems * c + (4 * kg + j) * S::kVElems + e) =
+                  f32x4{acc[0][c * S::kVElems + e][j], acc[0][c * S::kVElems + e + 1][j], acc[0][c * S::kVElems + e + 2][j],
+                        acc[0][c * S::kVElems + e + 3][j]} * inv;
+        if (kg == 0) p.ws_lse[row] = l > 0.f ? (m_run[0] + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
+      }
+      return;
     }
 
     // ---- merge the four waves and write one partial state per row
@@ -558,6 +599,29 @@ __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, 
       else pass(row0, std::integral_constant<int, NT>{});
     }
   }
+}
+
+}  // namespace tile
+
+// Which workgroups of a launch take which items: those from `solo_block` on, `solo_blocks` of them, the items from `solo_item`
+// to `item_end`, a wave each; the others one item each, from `item_begin` on.
+struct TileGrid { int item_begin, item_end, solo_item, solo_block, solo_blocks; };
+
+// OCC: waves per SIMD the registers are budgeted for.  SOLO: the launch has short items that a wave takes alone.
+template <int D, int KVT, int QT, int NT, int OCC, bool STREAM, bool SOLO>
+__global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, TileGrid grid) {
+  __shared__ tile::Lds<D, KVT, QT, NT> lds;
+  int block = int(blockIdx.x);
+  if constexpr (SOLO) {
+    const int ahead = block - grid.solo_block;
+    if (ahead >= 0 && ahead < grid.solo_blocks) {
+      const int item = grid.solo_item + ahead * tile::kWaves + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+      if (item < grid.item_end) tile::attend_item<D, KVT, QT, 1, STREAM, true>(p, item, lds);
+      return;
+    }
+    if (ahead >= 0) block -= grid.solo_blocks;
+  }
+  tile::attend_item<D, KVT, QT, NT, STREAM, false>(p, grid.item_begin + block, lds);
 }
 
 }  // namespace psdev

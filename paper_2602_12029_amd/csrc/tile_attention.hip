@@ -13,24 +13,29 @@ namespace {
 template <int D, int KVT, int QT>
 constexpr int wide_tiles() { return D == 256 ? 1 : (tile::Shape<D, KVT, QT>::kSplit && D == 64 ? 4 : 2); }
 
-template <int D, int KVT, int QT, bool STREAM>
-void launch_as(const AttnParams& p, int max_rows, int item_begin, int n_items, hipStream_t st) {
+template <int D, int KVT, int QT, bool STREAM, bool SOLO>
+void launch_as(const AttnParams& p, int max_rows, const TileGrid& items, hipStream_t st) {
   constexpr int kWide = wide_tiles<D, KVT, QT>();
-  const dim3 grid(n_items), block(256);
+  const dim3 grid(items.solo_item - items.item_begin + items.solo_blocks), block(256);
   if (kWide == 1 || max_rows <= 16)
-    hipLaunchKernelGGL((tile_attention_kernel<D, KVT, QT, 1, D == 256 ? 1 : 2, STREAM>), grid, block, 0, st, p, item_begin);
+    hipLaunchKernelGGL((tile_attention_kernel<D, KVT, QT, 1, D == 256 ? 1 : 2, STREAM, SOLO>), grid, block, 0, st, p, items);
   else
-    hipLaunchKernelGGL((tile_attention_kernel<D, KVT, QT, kWide, 1, STREAM>), grid, block, 0, st, p, item_begin);
+    hipLaunchKernelGGL((tile_attention_kernel<D, KVT, QT, kWide, 1, STREAM, SOLO>), grid, block, 0, st, p, items);
 }
 
 template <int D>
-bool dispatch(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin, int n_items, hipStream_t st) {
+bool dispatch(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, const TileGrid& items, hipStream_t st) {
 #define PS_CASE(KVT, QT)                                                              \
   if (g.kv_dtype == KVT && g.q_dtype == QT) {                                         \
     /* an item with more rows than a pass carries walks its tokens again: they should still be in the caches then */ \
-    if (stream && max_rows <= 16 * wide_tiles<D, KVT, QT>())                          \
-      launch_as<D, KVT, QT, true>(p, max_rows, item_begin, n_items, st);              \
-    else launch_as<D, KVT, QT, false>(p, max_rows, item_begin, n_items, st);          \
+    const bool streams = stream && max_rows <= 16 * wide_tiles<D, KVT, QT>();         \
+    if (items.solo_blocks) {                                                          \
+      if (streams) launch_as<D, KVT, QT, true, true>(p, max_rows, items, st);         \
+      else launch_as<D, KVT, QT, false, true>(p, max_rows, items, st);                \
+    } else {                                                                          \
+      if (streams) launch_as<D, KVT, QT, true, false>(p, max_rows, items, st);        \
+      else launch_as<D, KVT, QT, false, false>(p, max_rows, items, st);               \
+    }                                                                                 \
     return true;                                                                      \
   }
   PS_CASE(PS_F32, PS_F32)
@@ -54,13 +59,14 @@ bool tile_supported(const AttnParams& p, const ps_geometry& g) {
 }
 
 int32_t launch_tile_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin,
-                              int n_items, hipStream_t st) {
+                              int n_items, int n_solo, int solo_block, hipStream_t st) {
   if (n_items <= 0) return PS_OK;
+  const TileGrid items{item_begin, item_begin + n_items, item_begin + n_items - n_solo, solo_block, (n_solo + 3) / 4};
   bool ok = false;
   switch (g.head_dim) {
-    case 64: ok = dispatch<64>(p, g, max_rows, stream, item_begin, n_items, st); break;
-    case 128: ok = dispatch<128>(p, g, max_rows, stream, item_begin, n_items, st); break;
-    case 256: ok = dispatch<256>(p, g, max_rows, stream, item_begin, n_items, st); break;
+    case 64: ok = dispatch<64>(p, g, max_rows, stream, items, st); break;
+    case 128: ok = dispatch<128>(p, g, max_rows, stream, items, st); break;
+    case 256: ok = dispatch<256>(p, g, max_rows, stream, items, st); break;
     default: break;
   }
   return ok ? PS_OK : PS_ERR_UNSUPPORTED;
