@@ -10,6 +10,8 @@
 //
 // Both kernels are plain streaming code: one wavefront per (block, kv head, K|V) tile (ingest) or per
 // (request, kv head, K|V) row (append); HBM-bound, no matrix work.
+#include <algorithm>
+
 #include "device_common.h"
 #include "launch.h"
 
@@ -59,57 +61,37 @@ struct KvWriteParams {
 };
 
 // ---- ingest, storage formats that keep the source bits (T = uint16_t for bf16, float) --------------------
-// One wavefront per TILES consecutive (entry, head, K|V) tiles (K and V of neighbouring heads: a contiguous run on
-// the pool side in the dense layout); all loads of a step -- four 16-byte pieces per lane and tile -- go out
-// before the first store.
-template <typename T, int TILES>
+// One wavefront per piece of an (entry, head, K|V) tile: 256 16-byte chunks, four a lane, all fetched before the first
+// store; `ppt` pieces a tile.  HBM-bound; with a wave per tile a batch of a few hundred larger blocks left most of the chip
+// idle (25 contexts of 3130 tokens in blocks of 32, two launches: 36.3 -> 34.1 us).
+template <typename T>
 __global__ __launch_bounds__(256) void ingest_copy_kernel(KvWriteParams p, const T* __restrict__ src_k,
                                                           const T* __restrict__ src_v, int64_t src_s_tok,
-                                                          int64_t src_s_head, int entry0, int num_entries) {
+                                                          int64_t src_s_head, int entry0, uint32_t num_tiles, uint32_t ppt) {
   constexpr int kVec = 16 / int(sizeof(T));
   const int lane = threadIdx.x & 63;
-  const int64_t num_tiles = int64_t(num_entries) * p.num_kv_heads * 2;
-  const int64_t tile0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * TILES;
-  if (tile0 >= num_tiles) return;
+  const uint64_t piece = uint64_t(blockIdx.x) * 4 + uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6));
+  const uint32_t tile = ppt == 1 ? uint32_t(piece) : uint32_t(piece / ppt);
+  if (piece >= uint64_t(num_tiles) * ppt) return;
   const int cpt = p.head_dim / kVec;   // 16-byte chunks per token
-  const T* src[TILES];
-  T* dst[TILES];
-  int chunks[TILES];
-  int most = 0;
+  const int which = int(tile & 1u);
+  const int h = int((tile >> 1) % uint32_t(p.num_kv_heads));
+  const int e = p.ent_order[entry0 + int((tile >> 1) / uint32_t(p.num_kv_heads))];
+  // a block adopted from another layout has no valid tokens here: its contents are already there
+  const int chunks = max(0, p.ent_valid[e]) * cpt;
+  const int c0 = int(piece - uint64_t(tile) * ppt) * 256 + lane;
+  const T* src = (which ? src_v : src_k) + int64_t(p.ent_tok0[e]) * src_s_tok + int64_t(h) * src_s_head;
+  T* dst = static_cast<T*>(p.kv) + int64_t(p.blk[e]) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
+  u32x4 v[4];
 #pragma unroll
-  for (int i = 0; i < TILES; ++i) {
-    const int64_t tile = min(tile0 + i, num_tiles - 1);
-    const int which = int(tile & 1);
-    const int h = int((tile >> 1) % p.num_kv_heads);
-    const int e = p.ent_order[entry0 + int((tile >> 1) / p.num_kv_heads)];
-    // a block adopted from another layout has no valid tokens here: its contents are already there
-    chunks[i] = tile0 + i < num_tiles ? max(0, p.ent_valid[e]) * cpt : 0;
-    most = max(most, chunks[i]);
-    src[i] = (which ? src_v : src_k) + int64_t(p.ent_tok0[e]) * src_s_tok + int64_t(h) * src_s_head;
-    dst[i] = static_cast<T*>(p.kv) + int64_t(p.blk[e]) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
+  for (int u = 0; u < 4; ++u) {
+    const int c = c0 + 64 * u;
+    if (c < chunks) v[u] = stream_load(reinterpret_cast<const u32x4*>(src + int64_t(c / cpt) * src_s_tok + (c % cpt) * kVec));
   }
-  for (int c0 = 0; c0 < most; c0 += 256) {
-    u32x4 v[TILES][4];
 #pragma unroll
-    for (int i = 0; i < TILES; ++i)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = c0 + 64 * u + lane;
-        if (c < chunks[i]) {
-          const int t = c / cpt, col = (c % cpt) * kVec;
-          v[i][u] = stream_load(reinterpret_cast<const u32x4*>(src[i] + int64_t(t) * src_s_tok + col));
-        }
-      }
-#pragma unroll
-    for (int i = 0; i < TILES; ++i)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = c0 + 64 * u + lane;
-        if (c < chunks[i]) {
-          const int t = c / cpt, col = (c % cpt) * kVec;
-          stream_store(reinterpret_cast<u32x4*>(dst[i] + int64_t(t) * p.s_tok + col), v[i][u]);
-        }
-      }
+  for (int u = 0; u < 4; ++u) {
+    const int c = c0 + 64 * u;
+    if (c < chunks) stream_store(reinterpret_cast<u32x4*>(dst + int64_t(c / cpt) * p.s_tok + (c % cpt) * kVec), v[u]);
   }
 }
 
@@ -225,6 +207,72 @@ __global__ __launch_bounds__(256) void append_copy_kernel(KvWriteParams p, const
   for (int c = lane; c < p.head_dim; c += 64) dst[c] = src[c];
 }
 
+// e4m3 with rows of 2^row_shift eight-element pieces: one wavefront per (request, kv head, K|V), eight elements a lane.  The
+// stored tokens of a tile whose scale has grown are rewritten 64 >> row_shift at a time, and four of those rounds are fetched
+// together: a block of sixteen 128-wide tokens in one round trip (a byte at a time the launch was bound by the chain of those
+// rewrites: 64 requests, eight heads, tokens of changing magnitude 8.5 -> 5.2 us).
+__global__ __launch_bounds__(256) void append_e4m3x8_kernel(KvWriteParams p, const u32x4* __restrict__ new_k,
+                                                            const u32x4* __restrict__ new_v, int row_shift) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x;
+  const int row = int(blockIdx.y) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);   // of the token: (head, K|V)
+  if (row >= 2 * p.num_kv_heads) return;
+  const int dest = p.dest[r];
+  if (dest < 0) return;
+  const int h = row >> 1, which = row & 1;
+  const int id = dest / p.block_size, slot = dest % p.block_size;
+  uint8_t* tile = static_cast<uint8_t*>(p.kv) + int64_t(id) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
+  float* scale_ptr = p.scales + (int64_t(id) * p.num_kv_heads + h) * 2 + which;
+  const int c = lane & ((1 << row_shift) - 1), tok0 = lane >> row_shift, toks = 64 >> row_shift;
+  // (every token group of the wave holds the whole row)
+  const u32x4 raw = (which ? new_v : new_k)[((int64_t(r) * p.num_kv_heads + h) << row_shift) + c];
+  const float old = *scale_ptr;   // (of a fresh block: anything, and not used)
+  float x[8], amax = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    x[2 * j] = bf16_bits_to_f32(raw[j] & 0xffffu);
+    x[2 * j + 1] = bf16_bits_to_f32(raw[j] >> 16);
+    amax = fmaxf(amax, fmaxf(fabsf(x[2 * j]), fabsf(x[2 * j + 1])));
+  }
+  amax = wave_max(amax);
+  const float cand = amax / 448.f;
+  float scale;
+  auto encode = [](const float (&y)[8]) {
+    u32x2 out;
+    out[0] = uint32_t(__builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false), true));
+    out[1] = uint32_t(__builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], 0, false), true));
+    return out;
+  };
+  if (slot == 0) {
+    scale = amax > 0.f ? cand : 1.f;
+  } else {
+    scale = fmaxf(old, cand);
+    if (scale != old) {   // the tile's scale grew: re-encode what is stored, from the stored values
+      for (int t0 = tok0; t0 < slot; t0 += 4 * toks) {
+        u32x2 code[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (t0 + u * toks < slot) code[u] = *reinterpret_cast<const u32x2*>(tile + int64_t(t0 + u * toks) * p.s_tok + 8 * c);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (t0 + u * toks < slot) {
+            float y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = (e4m3_to_f32((code[u][j >> 2] >> (8 * (j & 3))) & 0xffu) * old) / scale;
+            *reinterpret_cast<u32x2*>(tile + int64_t(t0 + u * toks) * p.s_tok + 8 * c) = encode(y);
+          }
+      }
+    }
+  }
+  if (lane == 0) *scale_ptr = scale;
+  if (tok0 == 0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = x[j] / scale;
+    *reinterpret_cast<u32x2*>(tile + int64_t(slot) * p.s_tok + 8 * c) = encode(x);
+  }
+}
+
+// Any head size and alignment.
 __global__ __launch_bounds__(256) void append_e4m3_kernel(KvWriteParams p, const uint16_t* __restrict__ new_k,
                                                           const uint16_t* __restrict__ new_v, int num_requests) {
   const int lane = threadIdx.x & 63;
@@ -262,55 +310,62 @@ __global__ __launch_bounds__(256) void append_e4m3_kernel(KvWriteParams p, const
 }
 
 // ---- staging of whole blocks (cold KV parked in host memory and reloaded, Appendix B.2) -------------------
-// One wavefront per TILES consecutive (entry, KV head, K|V) tiles of B x d elements; the image is dense,
+// One wavefront per TILES consecutive pieces of (entry, KV head, K|V) tiles of B x d elements -- 256 16-byte chunks of a
+// tile, `ppt` pieces a tile --; the image is dense,
 // [entry][head][K|V][slot][d] in table order, followed by the e4m3 scales [entry][head][K|V].  TO_IMAGE: pool ->
-// image, else image -> pool.  Bits are copied, 16 bytes per lane and step, four loads per tile in flight before the
-// first store.
+// image, else image -> pool.  Bits are copied, 16 bytes per lane, four loads per piece in flight before the first store.
+// (A wave used to walk whole tiles: ten requests' blocks of 64 tokens, 54 MB there and back, in 103 workgroups 85.8 us, in
+// 1648 23.2; 16-token blocks of bf16, 2.55 GB, where a tile is a piece, 451 -> 439 from the shorter index arithmetic.)
 template <bool TO_IMAGE, int TILES>
 __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_t* __restrict__ image,
-                                                         float* __restrict__ image_scales, int num_entries,
-                                                         int elem_bytes) {
+                                                         float* __restrict__ image_scales, uint32_t num_tiles,
+                                                         uint32_t ppt, int elem_bytes) {
   const int lane = threadIdx.x & 63;
-  const int64_t num_tiles = int64_t(num_entries) * p.num_kv_heads * 2;
-  const int64_t tile0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * TILES;   // (entry, head, which), TILES in a row
-  if (tile0 >= num_tiles) return;
+  const uint64_t num_pieces = uint64_t(num_tiles) * ppt;
+  // (tile = (entry, head, which), piece), TILES in a row
+  const uint64_t piece0 = (uint64_t(blockIdx.x) * 4 + uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6))) * TILES;
+  if (piece0 >= num_pieces) return;
   const int row_bytes = p.head_dim * elem_bytes;
   const int row_chunks = row_bytes >> 4;
   const int chunks = p.block_size * row_chunks;
   const int64_t tok_bytes = p.s_tok * elem_bytes;
   uint8_t* pool_tile[TILES];
   uint8_t* image_tile[TILES];
-  int live[TILES];
+  int first[TILES], last[TILES];   // chunks of the tile
 #pragma unroll
   for (int i = 0; i < TILES; ++i) {
-    const int64_t tile = min(tile0 + i, num_tiles - 1);
-    live[i] = tile0 + i < num_tiles;
+    const uint64_t piece = min(piece0 + i, num_pieces - 1);
+    const uint32_t tile = ppt == 1 ? uint32_t(piece) : uint32_t(piece / ppt);
+    const int part = int(piece - uint64_t(tile) * ppt);
+    const bool live = piece0 + i < num_pieces;
+    first[i] = 256 * part;
+    last[i] = live ? min(chunks, first[i] + 256) : 0;
     const int which = int(tile & 1);
-    const int h = int((tile >> 1) % p.num_kv_heads);
+    const int h = int((tile >> 1) % uint32_t(p.num_kv_heads));
     // Into the pool the shared blocks are walked in the order of their addresses there, so that the scattered side of
     // the copy is the read of the image (scattered writes cost more); out of it in table order, for the same reason.
-    const int pos = int((tile >> 1) / p.num_kv_heads);
+    const int pos = int((tile >> 1) / uint32_t(p.num_kv_heads));
     const int e = TO_IMAGE ? pos : p.ent_order[pos];
     const int64_t image_tile_index = (int64_t(e) * p.num_kv_heads + h) * 2 + which;
     const int id = p.blk[e];
     pool_tile[i] = static_cast<uint8_t*>(p.kv) +
                    (int64_t(id) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv) * elem_bytes;
     image_tile[i] = image + image_tile_index * int64_t(p.block_size) * row_bytes;
-    if (image_scales && lane == 0 && live[i]) {
+    if (image_scales && lane == 0 && live && part == 0) {
       float* pool_scale = p.scales + (int64_t(id) * p.num_kv_heads + h) * 2 + which;
       if (TO_IMAGE) image_scales[image_tile_index] = *pool_scale;
       else *pool_scale = image_scales[image_tile_index];
     }
   }
-  // every load of a step (four 16-byte pieces per lane and tile) goes out before the first store
-  for (int c0 = 0; c0 < chunks; c0 += 256) {
+  // every load goes out before the first store
+  {
     u32x4 v[TILES][4];
 #pragma unroll
     for (int i = 0; i < TILES; ++i)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int c = c0 + 64 * u + lane;
-        if (c < chunks && live[i]) {
+        const int c = first[i] + 64 * u + lane;
+        if (c < last[i]) {
           const int slot = c / row_chunks, col = c % row_chunks;
           const uint8_t* src = TO_IMAGE ? pool_tile[i] + slot * tok_bytes + 16 * col : image_tile[i] + 16 * int64_t(c);
           v[i][u] = stream_load(reinterpret_cast<const u32x4*>(src));
@@ -320,8 +375,8 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_
     for (int i = 0; i < TILES; ++i)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int c = c0 + 64 * u + lane;
-        if (c < chunks && live[i]) {
+        const int c = first[i] + 64 * u + lane;
+        if (c < last[i]) {
           const int slot = c / row_chunks, col = c % row_chunks;
           uint8_t* dst = TO_IMAGE ? image_tile[i] + 16 * int64_t(c) : pool_tile[i] + slot * tok_bytes + 16 * col;
           stream_store(reinterpret_cast<u32x4*>(dst), v[i][u]);
@@ -367,14 +422,18 @@ int32_t launch_kv_ingest(const ps_layout* lay, const void* dev_tables, int which
   if (tiles > INT32_MAX) return PS_ERR_INVALID_ARG;
   const dim3 grid{unsigned(grid64)}, block{256};
   const KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);
+  // (formats that keep the source bits: pieces of 4 KiB)
+  const int64_t ppt = std::max<int64_t>(1, (int64_t(g.block_size) * g.head_dim * (g.kv_dtype == PS_F32 ? 4 : 2) / 16 + 255) / 256);
+  if (ppt > INT32_MAX / 256 || tiles * ppt > int64_t(4) * INT32_MAX) return PS_ERR_INVALID_ARG;
+  const dim3 copy_grid{unsigned((tiles * ppt + 3) / 4)};
   if (g.kv_dtype == PS_F32) {
     if (g.head_dim % 4) return PS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((ingest_copy_kernel<float, 1>), grid, block, 0, st, p, static_cast<const float*>(src_k),
-                       static_cast<const float*>(src_v), src_s_tok, src_s_head, entry0, num_entries);
+    hipLaunchKernelGGL((ingest_copy_kernel<float>), copy_grid, block, 0, st, p, static_cast<const float*>(src_k),
+                       static_cast<const float*>(src_v), src_s_tok, src_s_head, entry0, uint32_t(tiles), uint32_t(ppt));
   } else if (g.kv_dtype == PS_BF16) {
     if (g.head_dim % 8) return PS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((ingest_copy_kernel<uint16_t, 1>), grid, block, 0, st, p, static_cast<const uint16_t*>(src_k),
-                       static_cast<const uint16_t*>(src_v), src_s_tok, src_s_head, entry0, num_entries);
+    hipLaunchKernelGGL((ingest_copy_kernel<uint16_t>), copy_grid, block, 0, st, p, static_cast<const uint16_t*>(src_k),
+                       static_cast<const uint16_t*>(src_v), src_s_tok, src_s_head, entry0, uint32_t(tiles), uint32_t(ppt));
   } else {
     if (g.head_dim % 8) return PS_ERR_UNSUPPORTED;
     const int64_t chunks = (int64_t(g.block_size) * (g.head_dim / 8) + 63) / 64;   // per lane, whole tile in registers
@@ -406,7 +465,15 @@ int32_t launch_kv_append(const ps_layout* lay, const void* dev_tables, const voi
   const int64_t rows = int64_t(lay->num_requests) * g.num_kv_heads * 2;
   const dim3 grid{unsigned((rows + 3) / 4)}, block{256};
   const KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);
-  if (g.kv_dtype == PS_F32)
+  // e4m3: eight elements a lane where a row is a power of two of such pieces and every address a multiple of one (pool
+  // strides are multiples of 16 bytes).  The copying formats gain nothing from wider stores: their launch is its dependent reads.
+  const int pieces = g.head_dim / 8, wgs_y = (2 * g.num_kv_heads + 3) / 4;
+  const bool whole = g.kv_dtype == PS_FP8_E4M3 && g.head_dim % 8 == 0 && pieces <= 64 && (pieces & (pieces - 1)) == 0 && wgs_y <= 65535 &&
+                     (reinterpret_cast<uintptr_t>(new_k) | reinterpret_cast<uintptr_t>(new_v) | reinterpret_cast<uintptr_t>(kv)) % 16 == 0;
+  if (whole)
+    hipLaunchKernelGGL(append_e4m3x8_kernel, dim3(unsigned(lay->num_requests), unsigned(wgs_y)), block, 0, st, p,
+                       static_cast<const u32x4*>(new_k), static_cast<const u32x4*>(new_v), __builtin_ctz(unsigned(pieces)));
+  else if (g.kv_dtype == PS_F32)
     hipLaunchKernelGGL(append_copy_kernel<float>, grid, block, 0, st, p, static_cast<const float*>(new_k),
                        static_cast<const float*>(new_v), lay->num_requests);
   else if (g.kv_dtype == PS_BF16)
@@ -433,10 +500,14 @@ int32_t launch_kv_stage(const ps_layout* lay, const void* dev_tables, bool to_im
   // Tiles per wave: four consecutive tiles are K and V of two neighbouring heads, 16 KiB in a row on the pool side
   // for bf16 -- measured on scattered blocks, stage_in (dense reads, scattered writes) gains 9 % from the longer
   // runs (5.16 -> 5.65 TB/s), stage_out is unchanged; with the 2 KiB tiles of e4m3 more tiles per wave only lose.
-  const int per_wave = esz >= 2 ? 4 : 1;
+  // A small batch keeps to one piece a wave, so that it fills the chip.
+  const int64_t tile_chunks = int64_t(g.block_size) * g.head_dim * esz / 16, ppt = (tile_chunks + 255) / 256;
+  if (ppt > INT32_MAX / 256 || tiles * ppt > int64_t(4) * INT32_MAX) return PS_ERR_INVALID_ARG;
+  const int64_t pieces = tiles * ppt;
+  const int per_wave = esz >= 2 && pieces > 4 * 4096 ? 4 : 1;
 #define PS_STAGE(TO, N)                                                                                             \
-  hipLaunchKernelGGL((stage_copy_kernel<TO, N>), dim3{unsigned((tiles + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
-                     img_scales, int(entries), esz)
+  hipLaunchKernelGGL((stage_copy_kernel<TO, N>), dim3{unsigned((pieces + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
+                     img_scales, uint32_t(tiles), uint32_t(ppt), esz)
   if (to_image) {
     if (per_wave == 4) PS_STAGE(true, 4); else PS_STAGE(true, 1);
   } else {

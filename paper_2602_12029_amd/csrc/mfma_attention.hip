@@ -30,7 +30,7 @@
 // item is a handful of tiles, shared out over four waves it is mostly the meeting at its end, and what bounds a launch of many
 // is the number of those meetings.  A wave then keeps the item's queries in a row tile of its own, takes all its tiles, and
 // stores its rows without a barrier, so the four run apart.  78 contexts of 161 to 644 tokens under three models with one to
-// six private tokens each: 55.8 -> 36 us a launch; 256 contexts of 512 to 16384 tokens with up to 1024 private ones: 1.6 %.
+// six private tokens each: 55.8 -> 42.8 us a launch; 256 contexts of 512 to 16384 tokens with up to 1024 private ones: 1.6 %.
 #include <type_traits>
 
 #include "device_common.h"

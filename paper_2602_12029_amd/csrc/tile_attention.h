@@ -6,7 +6,7 @@
 // row that reads it.  The waves take 16- or 32-token tiles of the range in turn, stream K and V straight into matrix
 // operand registers, keep an online softmax per row and merge through LDS at the end; one partial state per row leaves
 // the workgroup.  (Short private items go four to a workgroup, a wave each, with nothing to merge: 748 items of 1 to 257 tokens
-// 19.9 -> 12.7 us a launch, 3076 of 256-wide heads 159 -> 125.)  As in the bf16 decode kernel the products are the transposed ones,
+// 19.9 -> 12.8 us a launch, 3076 of 256-wide heads 159 -> 126.)  As in the bf16 decode kernel the products are the transposed ones,
 //   S^T[token, row] = K[token, :] . Q[row, :]        A = K, B = Q^T
 //   O^T[dcol, row] += V^T[dcol, token] . P^T[token, row]        A = V^T, B = P^T
 // so that a lane's scores are, in place, its operand of the second product, and no cross-lane traffic is needed but
