@@ -155,7 +155,7 @@ int32_t launch_set(const ps_layout* lay, const psdev::AttnParams& p, const void*
     // end of the launch they would be its end (float32, 12 contexts, private items of up to 128 tokens: 47.8 us, last 53.5)
     const int n_solo = set == WorkSet::kPrefix ? 0 : lay->num_solo_items;
     rc = psdev::tile_supported(p, lay->geo)
-             ? psdev::launch_tile_attention(p, lay->geo, max_rows, stream, begin, end - begin, n_solo, lay->num_prefix_items - begin, st)
+             ? psdev::launch_tile_attention(p, lay->geo, max_rows, lay->tile_spread, stream, begin, end - begin, n_solo, lay->num_prefix_items - begin, st)
              : psdev::launch_wave_attention(p, lay->geo, begin, end - begin, st);
   }
   if (rc != PS_OK) return rc;

@@ -10,9 +10,9 @@ bool wave_supported(const ps_geometry& g);
 int32_t launch_wave_attention(const AttnParams& p, const ps_geometry& g, int item_begin, int n_items, hipStream_t st);
 // The same family for pools the tile kernel can address (blocks of 16 k tokens, see tile_supported): one workgroup per
 // item, the last n_solo of them (of up to 16 rows) four to a workgroup, from workgroup solo_block on; max_rows: query rows per KV head of the widest
-// item; stream: K/V tile loads are non-temporal.
+// item; spread: row tiles of an item go to waves of their own; stream: K/V tile loads are non-temporal.
 bool tile_supported(const AttnParams& p, const ps_geometry& g);
-int32_t launch_tile_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool stream, int item_begin,
+int32_t launch_tile_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool spread, bool stream, int item_begin,
                               int n_items, int n_solo, int solo_block, hipStream_t st);
 // Persistent launch: workgroup w walks wg_items[wg_indptr[w] .. wg_indptr[w+1]).
 // wg_solo: per workgroup, from which of its items on every wave takes one of its own (null: none).

@@ -103,10 +103,30 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   const bool unequal = longest > 0 && int64_t(longest) * 10 > int64_t(shortest) * 11;
   const int64_t ideal = std::max<int64_t>(1, ceil_div(two_per_cu && unequal ? total * 3 / 5 : total, int64_t(num_cus)));
   auto resolve = [&](int32_t v) { return v == PS_VARIANT_AUTO ? (mfma_ok ? PS_VARIANT_MFMA : PS_VARIANT_WAVE) : v; };
+  // Row groups of more than 16 rows in the tile kernel: a wave per row tile (spread), where the waves of a tile's row groups
+  // fetch it one after the other out of the caches, or all row tiles in every wave.  The first carries no more registers than
+  // the 16-row kernel, so that two workgroups share a compute unit, and walks 64 rows in one pass; the second fetches every
+  // line once, which pays where the launch streams from HBM and the products are cheap.  All row tiles a wave / spread, us
+  // (batch, MB): d = 256 (passes of 16 rows there), bf16 276 MB 130 / 99, 1.5 GB 559 / 357, float32 552 MB 312 / 238, 267 MB 144 /
+  // 144; d = 128, float32 463 MB 141 / 127, 555 MB 153 / 152, 1.2 GB 303 / 297, 279 MB 152 / 108, float32 queries over bf16 139 /
+  // 119, 310 / 262, over e4m3 128 / 108; d = 64, e4m3 45 / 40, 35 / 34, float32 232 MB 68 / 64, 140 MB 71 / 62, but 593 MB 143 / 149;
+  // bf16 products over bf16: d = 64 47 MB 37.9 / 34.7, 65 MB 30.9 / 28.8, 86 MB 40.6 / 42.1, 139 MB 40.2 / 43.1, 743 MB 150 / 162,
+  // d = 128 138 MB 56 / 53, 277 MB 60 / 73, 338 MB 74 / 101.
+  // Where such groups hold under a quarter of the tokens (a short root), the rest decides: 16-row items, two workgroups a
+  // compute unit (14 contexts of 2999 to 11998 tokens with 64-wide heads under a root of 32: 44.0 -> 40.2 us).
+  int64_t wide_group_tokens = 0;
+  for (size_t p = 0; p + 1 < lay->group_indptr.size(); ++p)
+    if (int64_t(lay->group_indptr[p + 1] - lay->group_indptr[p]) * group > 16) wide_group_tokens += lay->prefix_len[p];
+  for (size_t t = 0; t + 1 < lay->root_group_indptr.size(); ++t)
+    if (int64_t(lay->root_group_indptr[t + 1] - lay->root_group_indptr[t]) * group > 16) wide_group_tokens += lay->root_len[t];
+  const bool tile_narrow = group <= 16 && 4 * wide_group_tokens * g.num_kv_heads < total;
+  const int64_t kv_mb = total * 2 * g.head_dim * (g.kv_dtype == PS_F32 ? 4 : g.kv_dtype == PS_BF16 ? 2 : 1) / 1000000;
+  lay->tile_spread = tile_narrow || g.head_dim == 256 || g.kv_dtype == PS_FP8_E4M3 || g.kv_dtype != g.q_dtype ||
+                     (g.kv_dtype == PS_BF16 ? kv_mb <= (g.head_dim == 64 ? 70 : 140) : g.head_dim != 64 || kv_mb <= 400);
   // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item.  Heads of up to 128 with up to 16 rows
-  // leave room for two and more of them per compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25
+  // a wave leave room for two and more of them per compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25
   // of it: 36 float32 requests on 12 contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide
-  // heads on 24 contexts of 1024 to 6144 tokens 51.2 / 44.5 / 43.1 us).  Where one is resident -- more rows, or 256-wide
+  // heads on 24 contexts of 1024 to 6144 tokens 51.2 / 44.5 / 43.1 us).  Where one is resident -- more rows a wave, or 256-wide
   // heads -- a second round only adds starts and states, and the share is a whole one (whole / half: bf16 queries over bf16
   // or e4m3 KV, groups of 20 to 64 rows on 8 to 60 contexts, d = 64 60.2 / 68.1, 31.0 / 34.9, 56.9 / 65.9, d = 128 84.1 /
   // 93.1, 42.9 / 45.3, 78.6 / 90.8 us; d = 256 26.8 / 34.7, 52.2 / 62.2, 85.0 / 92.9, in float32 44.7 / 56.3, 96.9 / 112,
@@ -116,7 +136,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // boundary with the same chunks, is faster with halves too (426 / 364, 170 / 134, 280 / 254, 280 / 230, 116 / 92 us).  At
   // least 128 tokens, one or two tiles per wave (two requests on one 256-token prompt, launches alone: chunks of 256 /
   // 128 / 64 tokens 9.4 / 7.9 / 7.7 us; contexts of some thousand tokens lose more in the merge than they gain).
-  const bool tile_halves = g.head_dim < 256 && (widest <= 16 || g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
+  const bool tile_halves = g.head_dim < 256 && (widest <= 16 || tile_narrow || g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
   const int64_t tile_ideal = std::max<int64_t>(1, ceil_div(total, (tile_halves ? 2 : 1) * int64_t(num_cus)));
   auto pick = [&](int32_t asked, int32_t variant, bool fewer) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
@@ -453,7 +473,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   lay->num_solo_items = 0;
   {
     const int rows = std::max(group, lay->max_rows_prefix);
-    const int resident = g.head_dim == 256 || rows > 16 ? 1 : 2;
+    const int resident = g.head_dim == 256 || (rows > 16 && !lay->tile_spread) ? 1 : 2;
     if (lay->suffix_variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && group <= 16 &&
         int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident)
       for (size_t i = suffix_items.size(); i-- > 0 && suffix_items[i].tok_end - suffix_items[i].tok_begin <= kPsSoloTokensTile;)
@@ -525,12 +545,20 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // set's tokens that lie in re-read items: streaming while that is under a quarter (measured: a root shared by 8
   // row groups next to 3/4 of ordinary traffic gains 1.5 % from streaming, two row groups per prompt at 46 % of
   // the tokens lose 5 %).
+  // In the tile kernel so is a range that several row tiles fetch, or several passes (24-row groups, 256-wide heads, streamed /
+  // cacheable 37.0 / 29.9, 128 / 114, 50.4 / 39.8 us; where they hold a few of the tokens beside private segments, float32, 110 /
+  // 121, 132 / 144 us).
+  const int32_t rows_at_once = lay->tile_spread ? 16 : g.head_dim == 64 && g.kv_dtype == PS_BF16 ? 64 : 32;
+  auto fetched_again = [&](const ps_item& it) {
+    const int32_t variant = (it.kind & kPsItemSuffix) ? lay->suffix_variant : lay->prefix_variant;
+    return (it.kind & kPsItemReread) != 0 || (variant == PS_VARIANT_WAVE && it.n_req * group > rows_at_once);
+  };
   auto streams = [&](int begin, int end) {
     int64_t tokens_all = 0, tokens_reread = 0;
     for (int i = begin; i < end; ++i) {
       const ps_item& it = lay->items[size_t(i)];
       tokens_all += it.tok_end - it.tok_begin;
-      if (it.kind & kPsItemReread) tokens_reread += it.tok_end - it.tok_begin;
+      if (fetched_again(it)) tokens_reread += it.tok_end - it.tok_begin;
     }
     return opt.kv_cache_policy == PS_KV_POLICY_AUTO ? 4 * tokens_reread < tokens_all
                                                      : opt.kv_cache_policy == PS_KV_POLICY_STREAM;

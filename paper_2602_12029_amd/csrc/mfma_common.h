@@ -37,6 +37,26 @@ __device__ __forceinline__ u32x4 e4m3x8_to_bf16x8(uint32_t lo, uint32_t hi) {
   return r;
 }
 
+// K rows reach the lanes in whole 128-byte lines: one load instruction covers 8 tokens, 8 lanes each -- lane (n, kg)
+// takes 16 bytes at chunk (n >> 3) + 2 kg of the line, for token 8 T + (n & 7).  (Fetching 16 bytes per lane for token n
+// directly would ask for half a line per token and instruction; a read kernel with that footprint tops out at 6.2 TB/s
+// on this chip against 7.0 TB/s with whole lines.)  Lanes n < 8 then hold their own token in the T = 0 load and lane
+// (n + 8)'s token in the T = 1 load, lanes n >= 8 the other way round; one rotation by 8 inside each row of 16 lanes
+// hands the foreign half over.  Afterwards every lane (n, kg) holds chunks 2 kg (even) and 2 kg + 1 (odd) of token n.
+constexpr int kRowRor8 = 0x128;   // DPP control: rotate by 8 lanes within each row of 16
+__device__ __forceinline__ u32x4 k_even(u32x4 t0, u32x4 t1) {   // lanes n < 8 keep t0, lanes n >= 8 get lane (n - 8)'s t1
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_update_dpp(t0[i], t1[i], kRowRor8, 0xF, 0xC, false);
+  return r;
+}
+__device__ __forceinline__ u32x4 k_odd(u32x4 t0, u32x4 t1) {    // lanes n >= 8 keep t1, lanes n < 8 get lane (n + 8)'s t0
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_update_dpp(t1[i], t0[i], kRowRor8, 0xF, 0x3, false);
+  return r;
+}
+
 // Largest of the four scores of a block.  The fold starts from the constant -inf, which lets the compiler emit two
 // three-input maxima and nothing else (a two-input float maximum first quiets its inputs, one instruction each).
 __device__ __forceinline__ float max_of4(f32x4 s) {

@@ -59,6 +59,7 @@ struct ps_layout {
   std::vector<ps_item> items;        // row-split shared items, then the other shared (root, prefix) items, then suffix items
   int32_t rowsplit_rows = 256;       // most rows of a row-split item: the prefill kernel's workgroup takes 32 a wave
   int32_t num_rowsplit_items = 0;    // launched one workgroup each by the prefill kernel, outside the schedules
+  bool tile_spread = true;           // tile kernel: row groups of more than 16 rows go a row tile to a wave
   int32_t num_solo_items = 0;        // tile kernel: the last items, private and short, a wave each
   int32_t num_prefix_items = 0;      // all shared items: root and prefix, row-split ones included
   // K/V loads of a launch over the shared / private / all items are non-temporal (little of its K/V is read by several)

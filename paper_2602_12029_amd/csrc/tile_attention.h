@@ -55,6 +55,7 @@ struct Shape {
   static constexpr int kTokens = 16 * kBlocks;
   static constexpr int kKLoads = D * kEsz / 64;                    // 16-byte loads per lane and block of K
   static constexpr int kKElems = 16 / kEsz;                        // elements per such load
+  static constexpr bool kLines = kKLoads % 2 == 0;                 // K is fetched in whole 128-byte lines (rows of 64 bytes: no)
   static constexpr int kVBytes = (D / 16) * kEsz;                  // bytes of a V row per lane
   static constexpr int kVChunk = kVBytes < 16 ? kVBytes : 16;      // ... fetched in loads of this size
   static constexpr int kVLoads = kVBytes / kVChunk;
@@ -105,13 +106,13 @@ struct Regs {
 };
 
 // LDS of a workgroup: query rows (of a wave's own item: 16 each), then what the waves of a shared item merge.
-template <int D, int KVT, int QT, int NT>
+template <int D, int KVT, int QT, int ROW_TILES>
 struct Lds {
   typedef Shape<D, KVT, QT> S;
   typedef std::conditional_t<S::kSplit, uint16_t, float> q_elem;
   union {
     struct {
-      __attribute__((aligned(16))) q_elem q[16 * NT][S::kQRow];
+      __attribute__((aligned(16))) q_elem q[16 * ROW_TILES][S::kQRow];
       __attribute__((aligned(16))) float o[kWaves][16][D + 4];
       float m[kWaves][16], l[kWaves][16];
     };
@@ -123,7 +124,7 @@ struct Lds {
 // NT: 16-row tiles a pass over the tokens carries at most (an item with fewer rows takes the narrowest of 1, 2, 4
 // that holds them; one with more walks its tokens again).
 // STREAM: K/V loads are non-temporal (the launch's ranges are read by one item each, or nearly so).
-template <int D, int KVT, int QT, int NT, bool STREAM, bool SOLO, typename LDS>
+template <int D, int KVT, int QT, int NT, bool STREAM, bool SOLO, bool SPREAD, typename LDS>
 __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& lds) {
   typedef Shape<D, KVT, QT> S;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
@@ -131,8 +132,6 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
   auto* sm_o = lds.o;
   auto* sm_m = lds.m;
   auto* sm_l = lds.l;
-  const int tile0 = SOLO ? 0 : wave;
-  constexpr int kStep = SOLO ? 1 : kWaves;   // the wave's tiles of the item: tile0, tile0 + kStep, ...
   const ps_item* ip = p.items + item;
   const int blk_off = __builtin_amdgcn_readfirstlane(ip->blk_off);
   const int tok_begin = __builtin_amdgcn_readfirstlane(ip->tok_begin);
@@ -156,30 +155,15 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
   const int64_t plane_bytes = p.s_kv * S::kEsz;
   const int64_t blk_bytes = p.s_block * S::kEsz;
   const int sub_bytes = 16 * tok_bytes;
-  const int k_lane_off = n * tok_bytes + 16 * kg;
+  const int k_lane_off = S::kLines ? (n & 7) * tok_bytes + 16 * ((n >> 3) + 2 * kg) : n * tok_bytes + 16 * kg;
   const int v_lane_off = 4 * kg * tok_bytes + n * S::kVChunk;
   const int sub0 = tok_begin >> 4, sub_end = (tok_end + 15) >> 4;
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const const_i32_ptr blk_seg = (const_i32_ptr)(p.blk + blk_off);
   const int tiles_total = (sub_end - sub0 + S::kBlocks - 1) / S::kBlocks;
-  const int my_tiles = SOLO ? tiles_total : tiles_total > wave ? (tiles_total - wave + kWaves - 1) / kWaves : 0;
 
   // where a tile's blocks lie (scalar): physical block, and byte offset of the 16 tokens in it (-1: past the range)
   struct Place { int id[S::kBlocks], off[S::kBlocks]; };
-  // The table entry is read without a branch (index clamped into the range), so that outstanding loads are counted
-  // exactly in the streaming loop; a block past the range gets a descriptor of size zero and is not fetched.
-  auto locate = [&](int k) __attribute__((always_inline)) {
-    Place pl;
-#pragma unroll
-    for (int b = 0; b < S::kBlocks; ++b) {
-      const int sub = sub0 + S::kBlocks * (tile0 + kStep * k) + b;
-      const int c = min(sub, sub_end - 1);
-      const int block = spb == 1 ? c : c / spb;
-      pl.id[b] = blk_seg[block];
-      pl.off[b] = sub < sub_end ? (c - block * spb) * sub_bytes : -1;
-    }
-    return pl;
-  };
   constexpr int kPolicy = STREAM ? kNonTemporal : 0;
   auto fetch = [&](Regs<D, KVT, QT>& r, const Place& pl) __attribute__((always_inline)) {
 #pragma unroll
@@ -189,7 +173,9 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
       const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, size, 0x00020000);
       const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr + plane_bytes), 0, size, 0x00020000);
 #pragma unroll
-      for (int s = 0; s < S::kKLoads; ++s) r.k[b][s] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane_off + 64 * s, 0, kPolicy);
+      for (int s = 0; s < S::kKLoads; ++s)   // kLines: tokens 8 (s % 2) .., line s / 2 of their rows
+        r.k[b][s] = S::kLines ? __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane_off + 128 * (s >> 1), 8 * (s & 1) * tok_bytes, kPolicy)
+                              : __builtin_amdgcn_raw_buffer_load_b128(rk, k_lane_off + 64 * s, 0, kPolicy);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -198,9 +184,27 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
     }
   };
 
-  // One pass over the tokens for rows [row0, row0 + 16 M).
-  auto pass = [&](int row0, auto tiles_tag) __attribute__((always_inline)) {
+  // One pass over the tokens for rows [row0, row0 + 16 M), or, SPREAD, [row0, row0 + (16 << spread)).
+  auto pass = [&](int row0, auto tiles_tag, int spread) __attribute__((always_inline)) {
     constexpr int M = decltype(tiles_tag)::value;
+    const int row_tile = SPREAD ? wave & ((1 << spread) - 1) : 0;
+    // the wave's tiles of the item: tile0 + (k << step_shift)
+    const int step_shift = SOLO ? 0 : SPREAD ? 2 - spread : 2, tile0 = SOLO ? 0 : SPREAD ? wave >> spread : wave;
+    const int my_tiles = tiles_total > tile0 ? ((tiles_total - tile0 - 1) >> step_shift) + 1 : 0;
+    // The table entry is read without a branch (index clamped into the range), so that outstanding loads are counted
+    // exactly in the streaming loop; a block past the range gets a descriptor of size zero and is not fetched.
+    auto locate = [&](int k) __attribute__((always_inline)) {
+      Place pl;
+#pragma unroll
+      for (int b = 0; b < S::kBlocks; ++b) {
+        const int sub = sub0 + S::kBlocks * (tile0 + (k << step_shift)) + b;
+        const int c = min(sub, sub_end - 1);
+        const int block = spb == 1 ? c : c / spb;
+        pl.id[b] = blk_seg[block];
+        pl.off[b] = sub < sub_end ? (c - block * spb) * sub_bytes : -1;
+      }
+      return pl;
+    };
     // the first tiles go out from the header and the block table alone; the query rows follow while they fly
     Regs<D, KVT, QT> buf[S::kRing];
     Place at[S::kRing];
@@ -241,7 +245,7 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
     {
       constexpr int kQEsz = QT == PS_F32 ? 4 : 2;
       constexpr int kPieces = D * kQEsz / 16;          // 16-byte pieces of a query row
-      const int pieces = (SOLO ? rows : 16 * M) * kPieces;
+      const int pieces = (SOLO ? rows : SPREAD ? 16 << spread : 16 * M) * kPieces;
       for (int i = SOLO ? lane : int(threadIdx.x); i < pieces; i += SOLO ? 64 : 256) {
         const int r = i / kPieces, c = i % kPieces;
         u32x4 w = {0, 0, 0, 0};
@@ -264,7 +268,7 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
 #pragma unroll
     for (int t = 0; t < M; ++t) {
       lim[t] = tok_end;
-      const int row = row0 + 16 * t + n;
+      const int row = row0 + 16 * (row_tile + t) + n;
       if (masked && row < rows) lim[t] = min(tok_end, p.visible[p.req_list[req_off + row / G]]);
     }
     if constexpr (SOLO) wave_lds_order();
@@ -281,8 +285,19 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
     }
 
     auto multiply = [&](Regs<D, KVT, QT>& r, const Scales& sc, int k) __attribute__((always_inline)) {
-      const int tok0 = tok_begin + S::kTokens * (tile0 + kStep * k);
+      const int tok0 = tok_begin + S::kTokens * (tile0 + (k << step_shift));
       const bool whole = !masked && tok0 + S::kTokens <= tok_end;   // every row sees the whole tile
+      if constexpr (S::kLines) {   // every lane its own token: chunks 2 kg and 2 kg + 1 of line s / 2
+#pragma unroll
+        for (int b = 0; b < S::kBlocks; ++b)
+#pragma unroll
+          for (int s = 0; s < S::kKLoads; s += 2) {
+            const u32x4 even = k_even(r.k[b][s], r.k[b][s + 1]), odd = k_odd(r.k[b][s], r.k[b][s + 1]);
+            r.k[b][s] = even;
+            r.k[b][s + 1] = odd;
+          }
+      }
+      auto k_elem = [&](int st) { return (S::kLines ? 128 * (st >> 1) + 32 * kg + 16 * (st & 1) : 64 * st + 16 * kg) / S::kEsz; };
       // ---- scores of every row tile
       // (float32 form: the products are summed as a tree -- four chains over two 64-byte pieces, their pairs, the pieces of
       // each half of the row, the halves -- since long runs of roundings at the magnitude of a large score would cost the
@@ -310,7 +325,7 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
               ka[b] = KVT == PS_BF16 ? as_bf16x8(r.k[b][st]) : as_bf16x8(e4m3x8_to_bf16x8(r.k[b][st][2 * half], r.k[b][st][2 * half + 1]));
 #pragma unroll
             for (int t = 0; t < M; ++t) {
-              const bf16x8 qb = as_bf16x8(*reinterpret_cast<const u32x4*>(&sm_q[16 * t + n][st * (64 / S::kEsz) + kg * S::kKElems + 8 * half]));
+              const bf16x8 qb = as_bf16x8(*reinterpret_cast<const u32x4*>(&sm_q[16 * (row_tile + t) + n][k_elem(st) + 8 * half]));
 #pragma unroll
               for (int b = 0; b < S::kBlocks; ++b) s[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[b], qb, s[t][b], 0, 0, 0);
             }
@@ -325,7 +340,7 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
               for (int e = 0; e < 4; ++e) kf[b][e] = widen<KVT>(r.k[b][st], e4 + e);
 #pragma unroll
             for (int t = 0; t < M; ++t) {
-              const f32x4 qf = *reinterpret_cast<const f32x4*>(&sm_q[16 * t + n][st * (64 / S::kEsz) + kg * S::kKElems + e4]);
+              const f32x4 qf = *reinterpret_cast<const f32x4*>(&sm_q[16 * (row_tile + t) + n][k_elem(st) + e4]);
 #pragma unroll
               for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -533,6 +548,7 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
     }
 
     // ---- merge the four waves and write one partial state per row
+    // (SPREAD: the waves of every row tile hand in theirs at once)
 #pragma unroll
     for (int t = 0; t < M; ++t) {
       if (row0 + 16 * t >= rows) break;
@@ -555,48 +571,59 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
                       acc[t][c * S::kVElems + e + 3][j]};
       __syncthreads();
       const int rr = threadIdx.x >> 4;
-      const int row = row0 + 16 * t + rr;
-      if (row < rows) {
-        float mw[kWaves], mn = neg_inf;
+      for (int tile = t; tile < (SPREAD ? 1 << spread : t + 1); ++tile) {
+        const int row = row0 + 16 * tile + rr;
+        if (row < rows) {
+          float mw[kWaves], mn = neg_inf;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          mw[w] = sm_m[w][rr];
-          mn = fmaxf(mn, mw[w]);
+          for (int w = 0; w < kWaves; ++w) {
+            mw[w] = !SPREAD || (w & ((1 << spread) - 1)) == tile ? sm_m[w][rr] : neg_inf;
+            mn = fmaxf(mn, mw[w]);
+          }
+          float coef[kWaves], lsum = 0.f;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) {
+            coef[w] = (mw[w] == neg_inf) ? 0.f : fast_exp2(mw[w] - mn);
+            lsum += coef[w] * sm_l[w][rr];
+          }
+          const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+          const int req = p.req_list[req_off + row / G];
+          const int h = kv_head * G + row % G;
+          const int64_t slot = int64_t(p.slot_base[req]) + split_local;
+          float* o = p.ws_o + (slot * p.num_q_heads + h) * D;
+#pragma unroll
+          for (int c0 = 0; c0 < D; c0 += 64) {
+            const int col = c0 + 4 * (threadIdx.x & 15);
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+              if (!SPREAD || coef[w] != 0.f) v += coef[w] * *reinterpret_cast<const f32x4*>(&sm_o[w][rr][col]);
+            *reinterpret_cast<f32x4*>(o + col) = v * inv;
+          }
+          if ((threadIdx.x & 15) == 0)
+            p.ws_lse[slot * p.num_q_heads + h] = lsum > 0.f ? (mn + __builtin_amdgcn_logf(lsum)) * kLn2 : neg_inf;
         }
-        float coef[kWaves], lsum = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          coef[w] = (mw[w] == neg_inf) ? 0.f : fast_exp2(mw[w] - mn);
-          lsum += coef[w] * sm_l[w][rr];
-        }
-        const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-        const int req = p.req_list[req_off + row / G];
-        const int h = kv_head * G + row % G;
-        const int64_t slot = int64_t(p.slot_base[req]) + split_local;
-        float* o = p.ws_o + (slot * p.num_q_heads + h) * D;
-#pragma unroll
-        for (int c0 = 0; c0 < D; c0 += 64) {
-          const int col = c0 + 4 * (threadIdx.x & 15);
-          f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int w = 0; w < kWaves; ++w) v += coef[w] * *reinterpret_cast<const f32x4*>(&sm_o[w][rr][col]);
-          *reinterpret_cast<f32x4*>(o + col) = v * inv;
-        }
-        if ((threadIdx.x & 15) == 0)
-          p.ws_lse[slot * p.num_q_heads + h] = lsum > 0.f ? (mn + __builtin_amdgcn_logf(lsum)) * kLn2 : neg_inf;
       }
       __syncthreads();
     }
   };
 
+  if constexpr (SPREAD) {
+    for (int row0 = 0; row0 < rows;) {
+      const int spread = rows - row0 <= 16 ? 0 : rows - row0 <= 32 ? 1 : 2;
+      pass(row0, std::integral_constant<int, 1>{}, spread);
+      row0 += 16 << spread;
+    }
+    return;
+  }
   for (int row0 = 0; row0 < rows; row0 += 16 * NT) {
     const int left = rows - row0;
     if constexpr (NT == 1) {
-      pass(row0, std::integral_constant<int, 1>{});
+      pass(row0, std::integral_constant<int, 1>{}, 0);
     } else {
-      if (left <= 16) pass(row0, std::integral_constant<int, 1>{});
-      else if (NT == 2 || left <= 32) pass(row0, std::integral_constant<int, 2>{});
-      else pass(row0, std::integral_constant<int, NT>{});
+      if (left <= 16) pass(row0, std::integral_constant<int, 1>{}, 0);
+      else if (NT == 2 || left <= 32) pass(row0, std::integral_constant<int, 2>{}, 0);
+      else pass(row0, std::integral_constant<int, NT>{}, 0);
     }
   }
 }
@@ -608,20 +635,20 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
 struct TileGrid { int item_begin, item_end, solo_item, solo_block, solo_blocks; };
 
 // OCC: waves per SIMD the registers are budgeted for.  SOLO: the launch has short items that a wave takes alone.
-template <int D, int KVT, int QT, int NT, int OCC, bool STREAM, bool SOLO>
+template <int D, int KVT, int QT, int NT, int OCC, bool STREAM, bool SOLO, bool SPREAD>
 __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, TileGrid grid) {
-  __shared__ tile::Lds<D, KVT, QT, NT> lds;
+  __shared__ tile::Lds<D, KVT, QT, SPREAD ? tile::kWaves : NT> lds;
   int block = int(blockIdx.x);
   if constexpr (SOLO) {
     const int ahead = block - grid.solo_block;
     if (ahead >= 0 && ahead < grid.solo_blocks) {
       const int item = grid.solo_item + ahead * tile::kWaves + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-      if (item < grid.item_end) tile::attend_item<D, KVT, QT, 1, STREAM, true>(p, item, lds);
+      if (item < grid.item_end) tile::attend_item<D, KVT, QT, 1, STREAM, true, false>(p, item, lds);
       return;
     }
     if (ahead >= 0) block -= grid.solo_blocks;
   }
-  tile::attend_item<D, KVT, QT, NT, STREAM, false>(p, grid.item_begin + block, lds);
+  tile::attend_item<D, KVT, QT, NT, STREAM, false, SPREAD>(p, grid.item_begin + block, lds);
 }
 
 }  // namespace psdev
