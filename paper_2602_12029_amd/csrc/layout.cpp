@@ -587,20 +587,34 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     // 20843, private 1 to 537, 739 / 722 / 703 / 705; 40 of 1024 to 6144, private 1 to 256, 118.2 / 115.6 / 115.5 / 115.5; e4m3,
     // 64 of 8192, private 1 to 512, 219.3 / 217.8 / 215.5 / 215.7; 162 requests with up to 7 private tokens on 114 contexts
     // 78.4 / 71.9; 87 requests on as many contexts of 147 tokens (two rows: the shared items too) 22.7 / 18.0.
-    const int64_t solo_tokens = count > num_cus * out.occ ? kPsSoloTokens : 0;
+    // A short launch takes shorter ones only: a wave's time with an item (some t / 32 + 1 tiles) is to stay under 7/8 of what a
+    // workgroup has to do (t / 128 + 2 tiles for an item of four waves; 32 requests on 17 contexts of 990 to 3960 tokens, 0 / 64 /
+    // 128 / 512: 33.2 / 32.4 / 29.4 / 41.4 us; 46 on 13 of 141 to 566 24.1 / 21.7 / 18.3 / 21.2).  And the four-row-tile kernel, whose registers this overflows further, only where the short items are a good
+    // part of the work or the launch is a long one (205 requests with a few private tokens on 31 contexts 34.0 -> 31.0 us a
+    // launch; 81 on 52 contexts of 20843 tokens 723 -> 702 a step, 174 on 53 of 1180 to 18892 370 -> 351; but 39 on 16 of 2015 to
+    // 8060 68.7 -> 72.9).
+    int64_t work = 0, solo_tokens = 0;
+    for (int i = begin; i < end; ++i) work += cost(i) + 192;
+    if (solo_allowed && !lay->any_masked && count > num_cus * out.occ)
+      solo_tokens = std::min<int64_t>(kPsSoloTokens, std::max<int64_t>(32, (work / (num_cus * out.occ) * 7 / 8 - 128) / 4));
     auto solo = [&](int i) {
       const ps_item& it = lay->items[size_t(i)];
-      return solo_allowed && !lay->any_masked && it.tok_end - it.tok_begin <= solo_tokens && it.n_req * group <= ps_solo_rows(out.max_rows);
+      return it.tok_end - it.tok_begin <= solo_tokens && it.n_req * group <= ps_solo_rows(out.max_rows);
     };
+    if (out.max_rows > 32 && work < int64_t(kPsMfmaMaxChunk) * num_cus * out.occ && 4 * 256 * std::count_if(order.begin(), order.end(), solo) < work) solo_tokens = 0;
     const int n_full = int(std::stable_partition(order.begin(), order.end(), [&](int i) { return !solo(i); }) - order.begin());
     struct unit { int64_t cost; int first, count; };   // of `order`
     std::vector<unit> units;
     units.reserve(size_t(count));
-    for (int n = 0; n < n_full; ++n) units.push_back({cost(order[size_t(n)]), n, 1});
+    // Where there are such items, costs in time as above (by tokens + 64 alone the fours looked like whole chunks: 47 requests on
+    // 7 contexts of 293 to 4690 tokens 24.8 -> 21.9 us, 54 on a few of some thousand 33.3 -> 28.4).  A four in a chain of several
+    // costs a tile more than the first, whose start the launch waits for anyway (301 requests with up to 11 private tokens, 2.4
+    // fours and two shared items a workgroup: 250 / 202 us; the former two 21.9 / 23.5 and 28.0 / 34.7).
+    const int64_t solo_extra = n_full + (count - n_full + 3) / 4 <= 2 * num_cus * out.occ ? 128 : 256;
+    for (int n = 0; n < n_full; ++n) units.push_back({cost(order[size_t(n)]) + (n_full < count ? 192 : 0), n, 1});
     for (int n = n_full; n < count; n += 4) {
-      unit u{0, n, std::min(4, count - n)};
-      for (int i = 0; i < u.count; ++i) u.cost += cost(order[size_t(n + i)]);
-      units.push_back(u);
+      const ps_item& longest_of_four = lay->items[size_t(order[size_t(n)])];
+      units.push_back({4 * int64_t(longest_of_four.tok_end - longest_of_four.tok_begin) + solo_extra, n, std::min(4, count - n)});
     }
     auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
     std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);

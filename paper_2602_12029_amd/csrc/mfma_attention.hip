@@ -611,7 +611,7 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
 
     if (cur.solo) epilogue_solo(cur);
     else epilogue(cur);   // ends with a barrier: sm_q and the consumed half of the header ring are free
-    if (!has_next) break;
+    if (!has_next) return;   // (out of the loop by a branch instead: twelve more spilled registers with four row tiles)
 
     // refill the half of the header ring just used up (four items at a time may step over its end)
     constexpr int kHalf = kHdrRing / 2;
