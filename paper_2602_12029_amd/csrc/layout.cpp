@@ -469,14 +469,17 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // rounds, float32, private segments of 1 to 256 tokens, 44.7 us without, 46 / 47.8 / 55.7 with those of up to 64 / 128 /
   // 256).  Without and with (longest 64 / 128 / 256 tokens): 64-wide heads, 310 requests with up to 12 private tokens 21.9 /
   // 14.7 / 14.7 / 14.7 us, 72 with up to 256 43.5 / 43.9 / 43.7 / 42.2; 256-wide, 659 with up to 119 163 / 143 / 131 / 131, in
-  // float32 147 with up to 142 56.4 / 56.3 / 51.3 / 52.1.
+  // float32 147 with up to 142 56.0 / 54.8 / 48.9 / 50.4.  Float32 tokens are twice the bytes: half as many (171 requests with up
+  // to 190 on 70 short contexts 45.8 / 45.4 / 46.0 / 54.2, 159 with up to 514 72.0 / 72.3 / 73.2 / 76.5; 525 with up to 160 127 /
+  // 120 / 116 / 111).
   lay->num_solo_items = 0;
   {
     const int rows = std::max(group, lay->max_rows_prefix);
+    const int longest_solo = g.kv_dtype == PS_F32 ? kPsSoloTokensTile / 2 : kPsSoloTokensTile;
     const int resident = g.head_dim == 256 || (rows > 16 && !lay->tile_spread) ? 1 : 2;
     if (lay->suffix_variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && group <= 16 &&
         int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident)
-      for (size_t i = suffix_items.size(); i-- > 0 && suffix_items[i].tok_end - suffix_items[i].tok_begin <= kPsSoloTokensTile;)
+      for (size_t i = suffix_items.size(); i-- > 0 && suffix_items[i].tok_end - suffix_items[i].tok_begin <= longest_solo;)
         ++lay->num_solo_items;
   }
   lay->num_prefix_items = int32_t(prefix_items.size());
