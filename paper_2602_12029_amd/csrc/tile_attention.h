@@ -22,11 +22,17 @@
 //     of one, on an instruction of sixteen times the rate.  V is transposed inside the lane as in the decode kernel.
 //
 // Bound: HBM with up to 16 rows per KV head, and with bf16 products up to 32 rows of heads up to 128 (float32: 64 products
-// of 32 cycles per 16 KiB tile and wave let 19.6 TB/s through at 16 rows; a pass with 256-wide heads carries 16 rows, so
-// that more of them walk the tokens again); the vector form this replaces repeats its softmax on every lane of a row and walks the tokens once
+// of 32 cycles per 16 KiB tile and wave let 19.6 TB/s through at 16 rows); the vector form this replaces repeats its softmax on
+// every lane of a row and walks the tokens once
 // per 8 query rows.  Measured, whole step with the merge: 36 float32 requests on 12 contexts of 512 to 4096 tokens, d = 128,
-// 214 MB, 137 -> 45.8 us (4.7 TB/s); 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to 6144 tokens, 193 MB,
-// 319 -> 44.2 us (4.4 TB/s); two requests on one 256-token prompt 18.3 -> 8.4 us.  Error of float32 outputs against 64
+// 214 MB, 137 -> 42.7 us (5.0 TB/s); 72 bf16 requests with 64-wide heads on 24 contexts of 1024 to 6144 tokens, 193 MB,
+// 319 -> 38.9 us (5.0 TB/s); two requests on one 256-token prompt 18.3 -> 8.4 us.  K comes in whole 128-byte lines, as in the
+// decode kernel: with half a line per token and load the two batches took 44.9 and 42.3 us.
+// More rows are spread over the waves (SPREAD): two or four of them take a row tile each of the same tokens, and what the first
+// fetches the others find in the caches.  That keeps the registers of the 16-row form -- two workgroups a compute unit with heads
+// of up to 128 -- and walks the tokens once for 64 rows: 480 requests on 60 contexts with 256-wide heads 559 -> 357 us against
+// passes of 16 rows.  Where a launch streams from HBM with bf16 products the form with all row tiles in a wave is faster (the
+// planner's rule has both sides).  Error of float32 outputs against 64
 // bits, mean over sixteen batches: 3.4e-7 -> 3.1e-7 (with the products in one chain per score it was 4.8e-7).
 #pragma once
 #include "device_common.h"
@@ -124,6 +130,7 @@ struct Lds {
 // NT: 16-row tiles a pass over the tokens carries at most (an item with fewer rows takes the narrowest of 1, 2, 4
 // that holds them; one with more walks its tokens again).
 // STREAM: K/V loads are non-temporal (the launch's ranges are read by one item each, or nearly so).
+// SPREAD: items of more than 16 rows go a row tile to a wave (NT is 1).
 template <int D, int KVT, int QT, int NT, bool STREAM, bool SOLO, bool SPREAD, typename LDS>
 __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& lds) {
   typedef Shape<D, KVT, QT> S;
@@ -634,7 +641,8 @@ __device__ __forceinline__ void attend_item(const AttnParams& p, int item, LDS& 
 // to `item_end`, a wave each; the others one item each, from `item_begin` on.
 struct TileGrid { int item_begin, item_end, solo_item, solo_block, solo_blocks; };
 
-// OCC: waves per SIMD the registers are budgeted for.  SOLO: the launch has short items that a wave takes alone.
+// OCC: waves per SIMD the registers are budgeted for.  SOLO: the launch has short items that a wave takes alone (a body of their
+// own: as a branch inside the other one they cost its items 3 to 9 %).
 template <int D, int KVT, int QT, int NT, int OCC, bool STREAM, bool SOLO, bool SPREAD>
 __global__ __launch_bounds__(256, OCC) void tile_attention_kernel(AttnParams p, TileGrid grid) {
   __shared__ tile::Lds<D, KVT, QT, SPREAD ? tile::kWaves : NT> lds;
