@@ -612,15 +612,16 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     std::vector<unit> units;
     units.reserve(size_t(count));
     // Where there are such items, costs in time as above (by tokens + 64 alone the fours looked like whole chunks: 47 requests on
-    // 7 contexts of 293 to 4690 tokens 24.8 -> 21.9 us, 54 on a few of some thousand 33.3 -> 28.4).  A four in a chain of several
+    // 7 contexts of 293 to 4690 tokens 24.8 -> 21.9 us, 54 on a few of some thousand 33.3 -> 28.4), of whole tiles: a wave spends one
+    // on a single token (64 requests on 16 contexts of 1024 to 6144 tokens with one private token each 54.2 -> 44.2 us, with 128
+    // 82.5 -> 62.4, e4m3 under groups of eight 48.5 -> 37.0; by the fours' tiles alone the 47 requests take 23.2).  A four in a chain of several
     // costs a tile more than the first, whose start the launch waits for anyway (301 requests with up to 11 private tokens, 2.4
-    // fours and two shared items a workgroup: 250 / 202 us; the former two 21.9 / 23.5 and 28.0 / 34.7).
+    // fours and two shared items a workgroup: 206 us without that, 202 with; 46 on 13
+    // of 173 to 564 17.5 / 21.2, 54 on 11 of 136 to 1659 28.1 / 34.8).
     const int64_t solo_extra = n_full + (count - n_full + 3) / 4 <= 2 * num_cus * out.occ ? 128 : 256;
-    for (int n = 0; n < n_full; ++n) units.push_back({cost(order[size_t(n)]) + (n_full < count ? 192 : 0), n, 1});
-    for (int n = n_full; n < count; n += 4) {
-      const ps_item& longest_of_four = lay->items[size_t(order[size_t(n)])];
-      units.push_back({4 * int64_t(longest_of_four.tok_end - longest_of_four.tok_begin) + solo_extra, n, std::min(4, count - n)});
-    }
+    auto tiles = [&](int i) { return round_up(cost(order[size_t(i)]) - 64, 32); };   // in tokens
+    for (int n = 0; n < n_full; ++n) units.push_back({n_full < count ? tiles(n) + 256 : cost(order[size_t(n)]), n, 1});
+    for (int n = n_full; n < count; n += 4) units.push_back({4 * tiles(n) + solo_extra, n, std::min(4, count - n)});   // (longest of the four)
     auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
     std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
     const int num_wg = std::max(1, std::min(int(units.size()), num_cus * out.occ));

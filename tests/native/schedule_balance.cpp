@@ -1,0 +1,106 @@
+// The schedule of a whole step is even: what its heaviest workgroup has to do, in tiles -- a shared item or one of four waves
+// takes ceil(tokens / 128) and two more, four that a wave each takes ceil(longest / 32) and one -- is what dealing them out
+// heaviest first, each to the workgroup with the least to do, comes to.
+#include <algorithm>
+#include <cstdio>
+#include <functional>
+#include <queue>
+#include <vector>
+
+#include "ps_internal.h"
+
+struct Turn {
+  const char* what;
+  int32_t q_heads, kv_heads, kv_dtype, contexts, shortest, longest, models;
+};
+
+// (lengths spread evenly, in an order that is not sorted)
+static std::vector<int32_t> context_lengths(const Turn& t) {
+  std::vector<int32_t> len;
+  for (int32_t p = 0; p < t.contexts; ++p)
+    len.push_back(t.shortest + int32_t(int64_t(t.longest - t.shortest) * ((7 * p) % t.contexts) / std::max(1, t.contexts - 1)));
+  return len;
+}
+
+// Most tiles of a workgroup; dealt: the same of these items and fours when dealt out by their tiles.
+static int64_t heaviest(const ps_layout* lay, int64_t* dealt) {
+  const auto& pk = lay->pk_all;
+  auto tiles = [](const ps_item& it, int64_t per) { return (it.tok_end - it.tok_begin + per - 1) / per; };
+  std::vector<int64_t> units;
+  int64_t most = 0;
+  for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
+    const int32_t first_solo = pk.solo.empty() ? pk.indptr[w + 1] : pk.solo[w];
+    const size_t first_unit = units.size();
+    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) units.push_back(tiles(pk.items[size_t(i)], 128) + 2);
+    for (int32_t i = first_solo; i < pk.indptr[w + 1]; i += 4) {
+      int64_t longest = 0;
+      for (int32_t k = i; k < std::min(i + 4, pk.indptr[w + 1]); ++k) longest = std::max(longest, tiles(pk.items[size_t(k)], 32));
+      units.push_back(longest + 1);
+    }
+    int64_t load = 0;
+    for (size_t u = first_unit; u < units.size(); ++u) load += units[u];
+    most = std::max(most, load);
+  }
+  std::sort(units.begin(), units.end(), std::greater<int64_t>());
+  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> load;
+  for (int w = 0; w < 256 * pk.occ; ++w) load.push(0);
+  *dealt = 0;
+  for (int64_t u : units) {
+    const int64_t sum = load.top() + u;
+    load.pop();
+    load.push(sum);
+    *dealt = std::max(*dealt, sum);
+  }
+  return most;
+}
+
+static int fail(const Turn& t, int step, int64_t have, int64_t want) {
+  std::printf("FAILED: %s: step %d: heaviest workgroup %lld tiles, dealt out evenly %lld\n", t.what, step, (long long)have, (long long)want);
+  return 1;
+}
+
+static int run(const Turn& t) {
+  const int32_t n = t.contexts * t.models;
+  const int64_t tile = 16 * 128;
+  ps_geometry g{t.q_heads, t.kv_heads, 128, 16, PS_BF16, t.kv_dtype, t.kv_heads * 2 * tile, 2 * tile, tile, 128};
+  const std::vector<int32_t> len = context_lengths(t), suffix(size_t(n), 0);
+  std::vector<int32_t> prompt, model;
+  int32_t blocks = 0;
+  for (int32_t p = 0; p < t.contexts; ++p) {
+    blocks += (len[size_t(p)] + 15) / 16;
+    for (int32_t m = 0; m < t.models; ++m) {
+      prompt.push_back(p);
+      model.push_back(m);
+    }
+  }
+  ps_pool* pool = nullptr;
+  ps_layout* lay = nullptr;
+  if (ps_pool_create(blocks + n, nullptr, &pool) != PS_OK ||
+      ps_kv_layout(pool, &g, t.contexts, len.data(), n, prompt.data(), model.data(), suffix.data(), &lay) != PS_OK)
+    return fail(t, -1, 0, 0);
+  // the first token of a turn
+  if (ps_layout_append(pool, lay, nullptr, nullptr) != PS_OK) return fail(t, 0, 0, 0);
+  int64_t dealt = 0;
+  const int64_t most = heaviest(lay, &dealt);
+  if (10 * most > 11 * dealt) return fail(t, 0, most, dealt);
+  ps_layout_release(pool, lay);
+  ps_pool_destroy(pool);
+  return 0;
+}
+
+int main() {
+  const Turn turns[] = {
+      {"16 contexts, four models", 32, 8, PS_BF16, 16, 1024, 6144, 4},
+      {"24 contexts, four models", 32, 8, PS_BF16, 24, 2000, 8000, 4},
+      {"40 contexts, four models", 32, 8, PS_BF16, 40, 1024, 6144, 4},
+      {"17 contexts, two models", 32, 8, PS_BF16, 17, 990, 3960, 2},
+      {"16 contexts, four models, e4m3 under groups of eight", 64, 8, PS_FP8_E4M3, 16, 1024, 6144, 4},
+      {"60 short contexts, six models", 32, 8, PS_BF16, 60, 200, 1000, 6},
+      {"8 long contexts, four models", 32, 8, PS_BF16, 8, 8000, 16000, 4},
+  };
+  int bad = 0;
+  for (const Turn& t : turns) bad += run(t);
+  if (bad) return 1;
+  std::puts("ok");
+  return 0;
+}
