@@ -52,6 +52,56 @@ bool ps_mfma_supported(const ps_geometry& g) {
          (g.num_q_heads / g.num_kv_heads) <= 64 && slice_span < (int64_t(1) << 31);
 }
 
+// What a workgroup of a schedule spends on an item that its waves share, in tokens, and on four that a wave each takes, by the
+// longest of them.  Where there are fours, costs in time (an item of t tokens takes t / 128 + 2 tiles, a four t / 32 + 1 or + 2;
+// by tokens + 64 alone the fours looked like whole chunks: 47 requests on 7 contexts of 383 to 4074 tokens 24.8 -> 21.9 us, 54 on
+// 11 of 136 to 1659 33.3 -> 28.4), of whole tiles: a wave spends one on a single token (64 requests on 16 contexts of 1024 to
+// 6144 tokens with one private token each 54.2 -> 44.2 us, with 128 82.5 -> 62.4, e4m3 under groups of eight 48.5 -> 37.0; with
+// whole tiles for the fours alone the 47 requests take 23.2).
+static int64_t shared_cost(const ps_layout::packed_set& pk, int64_t tokens) { return pk.four_extra ? round_up(tokens, 32) + 256 : tokens + 64; }
+static int64_t four_cost(const ps_layout::packed_set& pk, int64_t longest) { return 4 * round_up(longest, 32) + pk.four_extra; }
+
+// Whether the private segments have grown so far since the whole step's schedule was packed that it is worth planning anew: its
+// heaviest workgroup has a quarter more to do than any schedule of these items makes unavoidable, and it has got an eighth more, or
+// all together a sixteenth, since (so that a batch that cannot be had more even is not planned at every step).  16 contexts
+// of 1024 to 6144 tokens under four models, the plan of the first token kept / planned anew, after 128, 512 and 768 tokens 83 / 44,
+// 202 / 58 and 281 / 72 us a launch (72, 121 and 159 with four waves on every item); a plan takes some 0.2 ms on the host.
+static bool outgrown(const ps_layout* lay) {
+  const ps_layout::packed_set& pk = lay->pk_all;
+  auto tokens = [&](int32_t i) { return int64_t(pk.items[size_t(i)].tok_end - pk.items[size_t(i)].tok_begin); };
+  int64_t most = 0, sum = 0, unavoidable = 0;
+  for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
+    const int32_t last = pk.indptr[w + 1], first_solo = pk.solo.empty() ? last : pk.solo[w];
+    int64_t load = 0;
+    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) {
+      load += shared_cost(pk, tokens(i));
+      unavoidable = std::max(unavoidable, shared_cost(pk, tokens(i)));
+    }
+    for (int32_t i = first_solo; i < last; i += 4) {
+      int64_t longest = 0;
+      for (int32_t k = i; k < std::min(i + 4, last); ++k) longest = std::max(longest, tokens(k));
+      if (longest > kPsSoloTokens * 3 / 2) return true;
+      load += four_cost(pk, longest);
+      unavoidable = std::max(unavoidable, shared_cost(pk, longest));
+    }
+    most = std::max(most, load);
+    sum += load;
+  }
+  unavoidable = std::max(unavoidable, ceil_div(sum, int64_t(lay->num_cus) * pk.occ));
+  return 4 * most > 5 * unavoidable && (8 * most >= 9 * pk.heaviest || 16 * sum >= 17 * pk.all);
+}
+
+// The tile kernel's short private items, which a wave takes alone, are the last of all; those that have grown past their limit go
+// in front of them.
+static void find_solo_items(ps_layout* lay) {
+  auto too_long = [&](const ps_item& it) { return it.tok_end - it.tok_begin > lay->solo_limit; };
+  if (std::any_of(lay->items.end() - lay->num_solo_items, lay->items.end(), too_long))
+    std::stable_partition(lay->items.end() - lay->num_solo_items, lay->items.end(), too_long);
+  lay->num_solo_items = 0;
+  if (lay->solo_limit > 0)
+    for (size_t i = lay->items.size(); i-- > size_t(lay->num_prefix_items) && !too_long(lay->items[i]);) ++lay->num_solo_items;
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Split plan: cut every segment into token chunks of (nearly) equal size, one workgroup each; a
 // request's partial states are numbered prefix chunks first, then its suffix chunks.
@@ -73,6 +123,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   int32_t num_cus = opt.num_cus;
   if (num_cus == 0 && ps_device_num_cus_hook) num_cus = ps_device_num_cus_hook();
   if (num_cus <= 0) num_cus = kPsDefaultNumCus;
+  lay->num_cus = num_cus;
 
   // chunk boundaries fall on block boundaries and on the 32-token MFMA tile
   const int64_t granule = std::lcm<int64_t>(g.block_size, 32);
@@ -472,19 +523,26 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // float32 147 with up to 142 56.0 / 54.8 / 48.9 / 50.4.  Float32 tokens are twice the bytes: half as many (171 requests with up
   // to 190 on 70 short contexts 45.8 / 45.4 / 46.0 / 54.2, 159 with up to 514 72.0 / 72.3 / 73.2 / 76.5; 525 with up to 160 127 /
   // 120 / 116 / 111).
-  lay->num_solo_items = 0;
+  // Bf16 queries, longer ones, without / with: beyond 256 tokens only where the fours alone fill the resident workgroups (64-wide
+  // heads, 60 contexts of 200 to 1000 tokens under six models, 384 / 512 / 1000 private tokens 97.6 / 76.2, 114 / 91.4, 163 / 148
+  // us, with e4m3 43.3 / 39.1, 52.7 / 46.5, 89.7 / 88.3; 256-wide heads 168 / 158, 201 / 193, 296 / 311), since they end a shorter
+  // launch (64-wide heads, 24 contexts of 1024 to 6144 tokens under four models 42.8 / 48.0, 48.7 / 55.0, 62.8 / 77.6, 90 of 300 to
+  // 1500 with sixteen rows 37.4 / 40.5, 40.4 / 44.6, 55.8 / 56.2; though 12 of 500 to 3000 under eight 30.4 / 25.4, 36.5 / 29.0).
+  lay->solo_limit = 0;
   {
     const int rows = std::max(group, lay->max_rows_prefix);
-    const int longest_solo = g.kv_dtype == PS_F32 ? kPsSoloTokensTile / 2 : kPsSoloTokensTile;
     const int resident = g.head_dim == 256 || (rows > 16 && !lay->tile_spread) ? 1 : 2;
     if (lay->suffix_variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && group <= 16 &&
-        int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident)
-      for (size_t i = suffix_items.size(); i-- > 0 && suffix_items[i].tok_end - suffix_items[i].tok_begin <= longest_solo;)
-        ++lay->num_solo_items;
+        int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident) {
+      const bool many = g.q_dtype == PS_BF16 && int64_t(suffix_items.size()) >= 4 * int64_t(num_cus) * resident;
+      lay->solo_limit = g.kv_dtype == PS_F32 ? kPsSoloTokensTile / 2 : !many ? kPsSoloTokensTile : g.head_dim == 64 ? 1024 : 512;
+    }
   }
   lay->num_prefix_items = int32_t(prefix_items.size());
   lay->items = std::move(prefix_items);
   lay->items.insert(lay->items.end(), suffix_items.begin(), suffix_items.end());
+  lay->num_solo_items = 0;
+  find_solo_items(lay);
 
   lay->slot_base.assign(R + 1, 0);
   lay->max_states = 0;
@@ -592,14 +650,15 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     // 78.4 / 71.9; 87 requests on as many contexts of 147 tokens (two rows: the shared items too) 22.7 / 18.0.
     // A short launch takes shorter ones only: a wave's time with an item (some t / 32 + 1 tiles) is to stay under 7/8 of what a
     // workgroup has to do (t / 128 + 2 tiles for an item of four waves; 32 requests on 17 contexts of 990 to 3960 tokens, 0 / 64 /
-    // 128 / 512: 33.2 / 32.4 / 29.4 / 41.4 us; 46 on 13 of 141 to 566 24.1 / 21.7 / 18.3 / 21.2).  And the four-row-tile kernel, whose registers this overflows further, only where the short items are a good
-    // part of the work or the launch is a long one (205 requests with a few private tokens on 31 contexts 34.0 -> 31.0 us a
-    // launch; 81 on 52 contexts of 20843 tokens 723 -> 702 a step, 174 on 53 of 1180 to 18892 370 -> 351; but 39 on 16 of 2015 to
-    // 8060 68.7 -> 72.9).
+    // 128 / 512: 33.2 / 32.4 / 29.4 / 41.4 us; 46 on 13 of 141 to 566 24.1 / 21.7 / 18.3 / 21.2).  And the
+    // four-row-tile kernel, whose registers this overflows further, only where the short items are a good part of the work or
+    // the launch is a long one (205 requests with a few private tokens on 31 contexts 34.0 -> 31.0 us a launch; 81 on 52 contexts
+    // of 20843 tokens 723 -> 702 a step, 174 on 53 of 1180 to 18892 370 -> 351; but 39 on 16 of 2015 to 8060 68.7 -> 72.9).
     int64_t work = 0, solo_tokens = 0;
     for (int i = begin; i < end; ++i) work += cost(i) + 192;
-    // (nor where one item is longer than all of a workgroup's work, and the launch waits for it whatever becomes of the rest: its
-    // tiles take a little longer in the kernel that has both forms; 32 contexts of 4096 tokens on 512 workgroups 108.6 -> 111.3)
+    // (nor where one item is more than 5/4 of a workgroup's share of the work, and the launch waits for it whatever becomes of
+    // the rest: its tiles take a little longer in the kernel that has both forms; 32 contexts of 4096 tokens on 512 workgroups,
+    // an item each and 16 tokens of private ones, 108.6 -> 111.3)
     if (solo_allowed && !lay->any_masked && count > num_cus * out.occ && 4 * (cost(order[0]) + 192) <= 5 * (work / (num_cus * out.occ)))
       solo_tokens = std::min<int64_t>(kPsSoloTokens, std::max<int64_t>(32, (work / (num_cus * out.occ) * 7 / 8 - 128) / 4));
     auto solo = [&](int i) {
@@ -611,17 +670,12 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     struct unit { int64_t cost; int first, count; };   // of `order`
     std::vector<unit> units;
     units.reserve(size_t(count));
-    // Where there are such items, costs in time as above (by tokens + 64 alone the fours looked like whole chunks: 47 requests on
-    // 7 contexts of 293 to 4690 tokens 24.8 -> 21.9 us, 54 on a few of some thousand 33.3 -> 28.4), of whole tiles: a wave spends one
-    // on a single token (64 requests on 16 contexts of 1024 to 6144 tokens with one private token each 54.2 -> 44.2 us, with 128
-    // 82.5 -> 62.4, e4m3 under groups of eight 48.5 -> 37.0; by the fours' tiles alone the 47 requests take 23.2).  A four in a chain of several
-    // costs a tile more than the first, whose start the launch waits for anyway (301 requests with up to 11 private tokens, 2.4
-    // fours and two shared items a workgroup: 206 us without that, 202 with; 46 on 13
-    // of 173 to 564 17.5 / 21.2, 54 on 11 of 136 to 1659 28.1 / 34.8).
-    const int64_t solo_extra = n_full + (count - n_full + 3) / 4 <= 2 * num_cus * out.occ ? 128 : 256;
-    auto tiles = [&](int i) { return round_up(cost(order[size_t(i)]) - 64, 32); };   // in tokens
-    for (int n = 0; n < n_full; ++n) units.push_back({n_full < count ? tiles(n) + 256 : cost(order[size_t(n)]), n, 1});
-    for (int n = n_full; n < count; n += 4) units.push_back({4 * tiles(n) + solo_extra, n, std::min(4, count - n)});   // (longest of the four)
+    // A four in a chain of several costs a tile more than the first, whose start the launch waits for anyway (301 requests with
+    // up to 11 private tokens, 2.4 fours and two shared items a workgroup: 206 us without that, 202 with; 46 on 13 of 173 to 564
+    // 17.5 / 21.2, 54 on 11 of 136 to 1659 28.1 / 34.8).
+    out.four_extra = n_full == count ? 0 : n_full + (count - n_full + 3) / 4 <= 2 * num_cus * out.occ ? 128 : 256;
+    for (int n = 0; n < n_full; ++n) units.push_back({shared_cost(out, cost(order[size_t(n)]) - 64), n, 1});
+    for (int n = n_full; n < count; n += 4) units.push_back({four_cost(out, cost(order[size_t(n)]) - 64), n, std::min(4, count - n)});
     auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
     std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
     const int num_wg = std::max(1, std::min(int(units.size()), num_cus * out.occ));
@@ -630,6 +684,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     std::priority_queue<slot, std::vector<slot>, std::greater<slot>> load;
     for (int w = 0; w < num_wg; ++w) load.push({0, w});
     std::vector<int> wg_of(units.size(), 0), fill(size_t(num_wg) + 1, 0), full(size_t(num_wg), 0);
+    for (const unit& u : units) out.all += u.cost;
     for (size_t n = 0; n < units.size(); ++n) {
       const slot least = load.top();
       load.pop();
@@ -637,6 +692,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       fill[size_t(least.second) + 1] += units[n].count;
       if (units[n].first < n_full) ++full[size_t(least.second)];
       load.push({least.first + units[n].cost, least.second});
+      out.heaviest = std::max(out.heaviest, least.first + units[n].cost);
     }
     for (int w = 0; w < num_wg; ++w) fill[size_t(w) + 1] += fill[size_t(w)];
     out.indptr.assign(fill.begin(), fill.end());
@@ -1256,7 +1312,7 @@ int32_t ps_layout_append(ps_pool* pool, ps_layout* lay, const int32_t* active, c
   // A step that leaves the chunk structure of every private segment as it is (same number of chunks, same chunk
   // size where there are several) only moves token ends and block offsets: the plan -- items, their order, the
   // packing onto workgroups -- is kept and patched, and only the tables are laid out again.  Anything else (a first
-  // token, a segment outgrowing its chunks) plans afresh.
+  // token, a segment outgrowing its chunks, a schedule its balance) plans afresh.
   bool same_structure = lay->suffix_chunks.size() == size_t(R) && lay->suffix_chunk > 0;
   const int64_t granule = std::lcm<int64_t>(B, 32);
   for (int32_t r = 0; r < R && same_structure; ++r) {
@@ -1270,19 +1326,6 @@ int32_t ps_layout_append(ps_pool* pool, ps_layout* lay, const int32_t* active, c
     else
       lay->suffix_chunk_size[size_t(r)] = int32_t(size);
   }
-  // (nor may an item that a wave has to itself outgrow it)
-  for (size_t i = lay->items.size() - size_t(lay->num_solo_items); i < lay->items.size() && same_structure; ++i) {
-    const ps_item& it = lay->items[i];
-    const int32_t r = it.req_off - R;
-    same_structure = std::min(lay->suffix_len[size_t(r)] - it.tok_begin, lay->suffix_chunk_size[size_t(r)]) <= 2 * kPsSoloTokens;
-  }
-  for (size_t w = 0; w < lay->pk_all.solo.size() && same_structure; ++w)
-    for (int32_t i = lay->pk_all.solo[w]; i < lay->pk_all.indptr[w + 1] && same_structure; ++i) {
-      const ps_item& it = lay->pk_all.items[size_t(i)];
-      if (!(it.kind & kPsItemSuffix)) continue;
-      const int32_t r = it.req_off - R;
-      same_structure = std::min(lay->suffix_len[size_t(r)] - it.tok_begin, lay->suffix_chunk_size[size_t(r)]) <= 2 * kPsSoloTokens;
-    }
   if (same_structure) {
     const int32_t prefix_blocks = int32_t(lay->prefix_blk.size());
     const int32_t root_shift = int32_t(lay->prefix_blk.size() + lay->suffix_blk.size()) - lay->planned_root_blk0;
@@ -1302,10 +1345,10 @@ int32_t ps_layout_append(ps_pool* pool, ps_layout* lay, const int32_t* active, c
     patch(lay->pk_suffix.items);
     patch(lay->pk_all.items);
     lay->planned_root_blk0 += root_shift;
-    if (int32_t st = ps_blob_build(lay)) return st;
-  } else {
-    if (int32_t st = ps_plan_build(lay, &lay->opt)) return st;
+    find_solo_items(lay);
+    same_structure = !outgrown(lay);
   }
+  if (int32_t st = same_structure ? ps_blob_build(lay) : ps_plan_build(lay, &lay->opt)) return st;
   if (dest) *dest = lay->append_dest.data();
   return PS_OK;
 }

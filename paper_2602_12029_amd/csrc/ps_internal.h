@@ -53,6 +53,7 @@ struct ps_layout {
 
   // split plan
   ps_plan_options opt{};
+  int32_t num_cus = 0;               // compute units the plan spreads the work over
   int32_t prefix_variant = PS_VARIANT_WAVE, suffix_variant = PS_VARIANT_WAVE;
   int32_t prefix_chunk = 0, suffix_chunk = 0;
   int32_t max_rows_prefix = 0;       // largest n_req * G over prefix items
@@ -60,7 +61,8 @@ struct ps_layout {
   int32_t rowsplit_rows = 256;       // most rows of a row-split item: the prefill kernel's workgroup takes 32 a wave
   int32_t num_rowsplit_items = 0;    // launched one workgroup each by the prefill kernel, outside the schedules
   bool tile_spread = true;           // tile kernel: row groups of more than 16 rows go a row tile to a wave
-  int32_t num_solo_items = 0;        // tile kernel: the last items, private and short, a wave each
+  int32_t solo_limit = 0;            // tile kernel: most tokens of a private item that a wave takes alone; 0: none does
+  int32_t num_solo_items = 0;        // tile kernel: the last items, those within it
   int32_t num_prefix_items = 0;      // all shared items: root and prefix, row-split ones included
   // K/V loads of a launch over the shared / private / all items are non-temporal (little of its K/V is read by several)
   bool stream_prefix = true, stream_suffix = true, stream_all = true;
@@ -88,6 +90,8 @@ struct ps_layout {
     std::vector<ps_item> items;
     std::vector<int32_t> indptr;
     std::vector<int32_t> solo;       // empty, or per workgroup where its solo items begin (see kPsSoloTokens)
+    int64_t four_extra = 0;          // cost of four such items besides their tiles; 0: there are none
+    int64_t heaviest = 0, all = 0;   // cost of the heaviest workgroup, and of all, when it was packed
     int32_t max_rows = 0, occ = 1;
     bool stream = true;
   };
@@ -134,10 +138,12 @@ inline int ps_mfma_occupancy(int max_rows, int kv_dtype) {
 }
 constexpr int kPsMfmaMaxChunk = 8192;  // tokens per MFMA work item (64 tiles per wave: their block ids fill two registers)
 // Items short enough for one wave, four at a time in a workgroup, in the persistent and in the tile kernel (the rules and
-// their figures are in build_plan).  A private one that appends have made twice as long is planned again, well inside the
-// 64 tiles of a wave.
+// their figures are in build_plan).  Appends make private ones longer: in the tile kernel one that passes its limit is shared out
+// over four waves again; a schedule of the persistent kernel is planned anew where a workgroup has come to have too much to do,
+// and at the latest when such an item is half as long again as this (60 contexts of 200 to 1000 tokens under six models, 768 /
+// 1000 private tokens: 236 / 298 us without such items, 240 / 303 with), well inside the 64 tiles of a wave.
 constexpr int kPsSoloTokens = 512, kPsSoloTokensTile = 256;
-static_assert(2 * kPsSoloTokens <= kPsMfmaMaxChunk / 4, "a wave's own item holds up to 64 tiles of 32 tokens");
+static_assert(kPsSoloTokens * 3 / 2 <= kPsMfmaMaxChunk / 4, "a wave's own item holds up to 64 tiles of 32 tokens");
 // Rows of such an item in the persistent kernel: what a wave fetches of the queries, by the row tiles the launch carries.
 inline int ps_solo_rows(int max_rows) { return max_rows <= 32 ? 8 : 16; }
 

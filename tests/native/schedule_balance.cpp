@@ -1,6 +1,8 @@
 // The schedule of a whole step is even: what its heaviest workgroup has to do, in tiles -- a shared item or one of four waves
 // takes ceil(tokens / 128) and two more, four that a wave each takes ceil(longest / 32) and one -- is what dealing them out
-// heaviest first, each to the workgroup with the least to do, comes to.
+// heaviest first, each to the workgroup with the least to do, comes to.  And it stays so through a long turn: while every step
+// makes the private segments longer the heaviest workgroup has no more than a quarter more to do than in a plan made afresh, and
+// batch is not planned anew at every step for it.
 #include <algorithm>
 #include <cstdio>
 #include <functional>
@@ -8,6 +10,12 @@
 #include <vector>
 
 #include "ps_internal.h"
+
+static int plans = 0;   // (the planner asks for the compute units once per plan)
+static int32_t count_plans() {
+  ++plans;
+  return 256;
+}
 
 struct Turn {
   const char* what;
@@ -59,36 +67,68 @@ static int fail(const Turn& t, int step, int64_t have, int64_t want) {
   return 1;
 }
 
-static int run(const Turn& t) {
-  const int32_t n = t.contexts * t.models;
-  const int64_t tile = 16 * 128;
-  ps_geometry g{t.q_heads, t.kv_heads, 128, 16, PS_BF16, t.kv_dtype, t.kv_heads * 2 * tile, 2 * tile, tile, 128};
-  const std::vector<int32_t> len = context_lengths(t), suffix(size_t(n), 0);
-  std::vector<int32_t> prompt, model;
-  int32_t blocks = 0;
-  for (int32_t p = 0; p < t.contexts; ++p) {
-    blocks += (len[size_t(p)] + 15) / 16;
-    for (int32_t m = 0; m < t.models; ++m) {
-      prompt.push_back(p);
-      model.push_back(m);
-    }
-  }
+struct Batch {
   ps_pool* pool = nullptr;
   ps_layout* lay = nullptr;
-  if (ps_pool_create(blocks + n, nullptr, &pool) != PS_OK ||
-      ps_kv_layout(pool, &g, t.contexts, len.data(), n, prompt.data(), model.data(), suffix.data(), &lay) != PS_OK)
-    return fail(t, -1, 0, 0);
-  // the first token of a turn
-  if (ps_layout_append(pool, lay, nullptr, nullptr) != PS_OK) return fail(t, 0, 0, 0);
-  int64_t dealt = 0;
-  const int64_t most = heaviest(lay, &dealt);
-  if (10 * most > 11 * dealt) return fail(t, 0, most, dealt);
-  ps_layout_release(pool, lay);
-  ps_pool_destroy(pool);
+  // `grow`: room for as many more tokens per request
+  int make(const Turn& t, const std::vector<int32_t>& suffix, int32_t grow) {
+    const int32_t n = t.contexts * t.models;
+    const int64_t tile = 16 * 128;
+    ps_geometry g{t.q_heads, t.kv_heads, 128, 16, PS_BF16, t.kv_dtype, t.kv_heads * 2 * tile, 2 * tile, tile, 128};
+    const std::vector<int32_t> len = context_lengths(t);
+    std::vector<int32_t> prompt, model;
+    int32_t blocks = 0;
+    for (int32_t p = 0; p < t.contexts; ++p) {
+      blocks += (len[size_t(p)] + 15) / 16;
+      for (int32_t m = 0; m < t.models; ++m) {
+        blocks += (suffix[prompt.size()] + grow + 15) / 16 + 1;
+        prompt.push_back(p);
+        model.push_back(m);
+      }
+    }
+    return ps_pool_create(blocks, nullptr, &pool) == PS_OK &&
+           ps_kv_layout(pool, &g, t.contexts, len.data(), n, prompt.data(), model.data(), suffix.data(), &lay) == PS_OK;
+  }
+  ~Batch() {
+    if (lay) ps_layout_release(pool, lay);
+    if (pool) ps_pool_destroy(pool);
+  }
+};
+
+// every: a request appends at every `every`-th step only, each at its own (1: all at every step)
+static int run(const Turn& t, int every) {
+  const int kSteps = 1100;
+  const int32_t n = t.contexts * t.models;
+  std::vector<int32_t> len(size_t(n), 0), active(size_t(n), 1);
+  Batch batch;
+  if (!batch.make(t, len, kSteps)) return fail(t, -1, 0, 0);
+  int planned = 0;
+  for (int step = 1; step <= kSteps; ++step) {
+    for (int32_t r = 0; r < n; ++r) {
+      active[size_t(r)] = (step + r) % every == 0 || step == 1;
+      len[size_t(r)] += active[size_t(r)];
+    }
+    plans = 0;
+    if (ps_layout_append(batch.pool, batch.lay, active.data(), nullptr) != PS_OK) return fail(t, step, 0, 0);
+    planned += plans;
+    int64_t dealt = 0, dealt_afresh = 0;
+    const int64_t most = heaviest(batch.lay, &dealt);
+    if (step == 1 && 10 * most > 11 * dealt) return fail(t, step, most, dealt);
+    if (step % 50 && step > 8) continue;
+    Batch afresh;
+    if (!afresh.make(t, len, 0)) return fail(t, -1, 0, 0);
+    const int64_t even = heaviest(afresh.lay, &dealt_afresh);
+    if (4 * most > 5 * (even + 1)) return fail(t, step, most, even);   // (costs are rounded to tiles)
+  }
+  if (planned > 40) {
+    std::printf("FAILED: %s: planned %d times in %d steps\n", t.what, planned, kSteps);
+    return 1;
+  }
   return 0;
 }
 
 int main() {
+  ps_device_num_cus_hook = count_plans;
   const Turn turns[] = {
       {"16 contexts, four models", 32, 8, PS_BF16, 16, 1024, 6144, 4},
       {"24 contexts, four models", 32, 8, PS_BF16, 24, 2000, 8000, 4},
@@ -99,7 +139,7 @@ int main() {
       {"8 long contexts, four models", 32, 8, PS_BF16, 8, 8000, 16000, 4},
   };
   int bad = 0;
-  for (const Turn& t : turns) bad += run(t);
+  for (const Turn& t : turns) bad += run(t, 1) + run(t, 3);
   if (bad) return 1;
   std::puts("ok");
   return 0;

@@ -1,5 +1,5 @@
 // Short items that a wave takes alone: which ones the schedules and the tile kernel's tail hold, and that appends never let one
-// outgrow what a wave holds.
+// outgrow its limit.
 #include <cstdio>
 #include <vector>
 
@@ -10,13 +10,14 @@ static int fail(const char* what, int at) {
   return 1;
 }
 
+// limit: of the tile kernel's items
 static int run(int32_t q_heads, int32_t kv_heads, int32_t head_dim, int32_t dtype, const std::vector<int32_t>& contexts, int32_t models,
-               const std::vector<int32_t>& lens, int32_t num_cus, bool want_solo) {
+               const std::vector<int32_t>& lens, int32_t num_cus, bool want_solo, int32_t limit = kPsSoloTokens * 3 / 2) {
   const bool mfma = dtype == PS_BF16 && head_dim == 128;
   const int32_t group = q_heads / kv_heads, n = int32_t(contexts.size()) * models;
   const int64_t tile = int64_t(16) * head_dim;
   ps_geometry g{q_heads, kv_heads, head_dim, 16, dtype, dtype, kv_heads * 2 * tile, 2 * tile, tile, head_dim};
-  std::vector<int32_t> prompt, model, suffix;
+  std::vector<int32_t> prompt, model, suffix, active(size_t(n), 1);
   int32_t blocks = 0;
   for (size_t p = 0; p < contexts.size(); ++p)
     for (int32_t m = 0; m < models; ++m) {
@@ -41,17 +42,24 @@ static int run(int32_t q_heads, int32_t kv_heads, int32_t head_dim, int32_t dtyp
         if (pk.solo[w] < pk.indptr[w] || pk.solo[w] > pk.indptr[w + 1]) return fail("bounds", step);
         for (int32_t i = pk.solo[w]; i < pk.indptr[w + 1]; ++i) {
           const ps_item& it = pk.items[size_t(i)];
-          if (it.tok_end - it.tok_begin > 1024 || it.n_req * group > ps_solo_rows(pk.max_rows) || (it.kind & kPsItemMasked)) return fail("item", step);
+          if (it.tok_end - it.tok_begin > limit || it.n_req * group > ps_solo_rows(pk.max_rows) || (it.kind & kPsItemMasked)) return fail("item", step);
         }
       }
     } else {
       if ((lay->num_solo_items == 0) == want_solo && step == 0) return fail("solo items", step);
       for (size_t i = lay->items.size() - size_t(lay->num_solo_items); i < lay->items.size(); ++i) {
         const ps_item& it = lay->items[i];
-        if (!(it.kind & kPsItemSuffix) || it.tok_end - it.tok_begin > 1024 || it.n_req * group > 16) return fail("item", step);
+        if (!(it.kind & kPsItemSuffix) || it.tok_end - it.tok_begin > limit || it.n_req * group > 16) return fail("item", step);
+      }
+      // (and all that are within it, whatever order the appends have left)
+      for (size_t i = size_t(lay->num_prefix_items); want_solo && i < lay->items.size() - size_t(lay->num_solo_items); ++i) {
+        const ps_item& it = lay->items[i];
+        if (it.tok_end - it.tok_begin <= limit) return fail("missed", step);
       }
     }
-    if (ps_layout_append(pool, lay, nullptr, nullptr) != PS_OK) return fail("append", step);
+    // (every seventh request never grows)
+    for (int32_t r = 0; r < n; ++r) active[size_t(r)] = r % 7 != 3;
+    if (ps_layout_append(pool, lay, active.data(), nullptr) != PS_OK) return fail("append", step);
   }
   ps_layout_release(pool, lay);
   ps_pool_destroy(pool);
@@ -66,8 +74,10 @@ int main() {
   if (int rc = run(16, 8, 128, PS_BF16, {300, 40, 520}, 1, lens, 4, true)) return rc;     // shared items of two rows
   if (int rc = run(32, 2, 128, PS_BF16, {300, 40, 520}, 1, lens, 1, false)) return rc;    // sixteen rows: more than a wave fetches
   if (int rc = run(32, 8, 128, PS_BF16, {2000}, 2, lens, 256, false)) return rc;          // fewer items than workgroups
-  if (int rc = run(32, 8, 64, PS_BF16, {2000, 600, 40}, 4, lens, 4, true)) return rc;
-  if (int rc = run(16, 4, 256, PS_F32, {2000, 600, 40}, 4, lens, 4, true)) return rc;
+  if (int rc = run(32, 8, 64, PS_BF16, {2000, 600, 40}, 4, lens, 4, true, 1024)) return rc;          // fours for every workgroup
+  if (int rc = run(32, 8, 64, PS_BF16, {6000, 600, 40}, 4, lens, 16, true, 256)) return rc;
+  if (int rc = run(16, 4, 256, PS_BF16, {2000, 600, 40}, 4, lens, 8, true, 512)) return rc;
+  if (int rc = run(16, 4, 256, PS_F32, {2000, 600, 40}, 4, lens, 4, true, 128)) return rc;
   if (int rc = run(32, 1, 64, PS_F32, {2000, 600, 40}, 4, lens, 1, false)) return rc;     // thirty-two rows
   std::puts("ok");
   return 0;
