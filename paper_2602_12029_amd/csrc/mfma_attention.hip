@@ -639,6 +639,33 @@ __global__ __launch_bounds__(256, OCC) void mfma_attention_kernel(AttnParams p, 
   }
 }
 
+namespace {
+
+template <int NT, int KVT>
+int32_t launch_as(const AttnParams& p, bool masked, bool stream, const ps_item* wg_items, const int32_t* wg_indptr, const int32_t* wg_solo,
+                  int num_wg, hipStream_t st) {
+  // two tile buffers per wave everywhere (deeper rings measured no faster)
+  constexpr int kBuffers = 2, kOcc = ps_mfma_occupancy(16 * NT, KVT);
+#define PS_LAUNCH(MASKED, STREAM, SOLO) \
+  hipLaunchKernelGGL((mfma_attention_kernel<NT, KVT, kBuffers, kOcc, MASKED, STREAM, SOLO>), dim3(num_wg), dim3(256), 0, st, p, wg_items, wg_indptr, wg_solo)
+  if (masked) {
+    if (stream) PS_LAUNCH(true, true, false);
+    else PS_LAUNCH(true, false, false);
+  } else if (wg_solo) {
+    // (items over e4m3 are cut at 32 rows, so that four row tiles mean groups of more, and no item that a wave could take alone)
+    if constexpr (NT == 4 && KVT == PS_FP8_E4M3) return PS_ERR_UNSUPPORTED;
+    else if (stream) PS_LAUNCH(false, true, true);
+    else PS_LAUNCH(false, false, true);
+  } else {
+    if (stream) PS_LAUNCH(false, true, false);
+    else PS_LAUNCH(false, false, false);
+  }
+#undef PS_LAUNCH
+  return PS_OK;
+}
+
+}  // namespace
+
 int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max_rows, bool masked, bool stream,
                               const ps_item* wg_items, const int32_t* wg_indptr, const int32_t* wg_solo, int num_wg, hipStream_t st) {
   if (num_wg <= 0) return PS_OK;
@@ -647,37 +674,13 @@ int32_t launch_mfma_attention(const AttnParams& p, const ps_geometry& g, int max
     return PS_ERR_UNSUPPORTED;
   if (g.kv_dtype != PS_BF16 && g.kv_dtype != PS_FP8_E4M3) return PS_ERR_UNSUPPORTED;
   if (wg_solo && (masked || g.num_q_heads / g.num_kv_heads > ps_solo_rows(max_rows))) return PS_ERR_UNSUPPORTED;
-  const dim3 grid(num_wg), block(256);
-  const int nt = max_rows <= 16 ? 1 : (max_rows <= 32 ? 2 : 4);
-#define PS_LAUNCH_AS(NT, KVT, OCC, MASKED, STREAM, SOLO) \
-  hipLaunchKernelGGL((mfma_attention_kernel<NT, KVT, 2, OCC, MASKED, STREAM, SOLO>), grid, block, 0, st, p, wg_items, wg_indptr, wg_solo)
-#define PS_LAUNCH(NT, KVT, OCC)                                  \
-  do {                                                           \
-    if (masked) {                                                \
-      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, true, true, false); \
-      else PS_LAUNCH_AS(NT, KVT, OCC, true, false, false);       \
-    } else if (wg_solo) {                                        \
-      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, false, true, true); \
-      else PS_LAUNCH_AS(NT, KVT, OCC, false, false, true);       \
-    } else {                                                     \
-      if (stream) PS_LAUNCH_AS(NT, KVT, OCC, false, true, false); \
-      else PS_LAUNCH_AS(NT, KVT, OCC, false, false, false);      \
-    }                                                            \
-  } while (0)
-  // two tile buffers per wave everywhere (deeper rings measured no faster); the waves per SIMD are those that the plan
-  // sized the grid for (ps_mfma_occupancy)
-  if (g.kv_dtype == PS_BF16) {
-    if (nt == 1) PS_LAUNCH(1, PS_BF16, 2);
-    else if (nt == 2) PS_LAUNCH(2, PS_BF16, 1);
-    else PS_LAUNCH(4, PS_BF16, 1);
-  } else {
-    if (nt == 1) PS_LAUNCH(1, PS_FP8_E4M3, 2);
-    else if (nt == 2) PS_LAUNCH(2, PS_FP8_E4M3, 2);
-    else PS_LAUNCH(4, PS_FP8_E4M3, 1);
-  }
-#undef PS_LAUNCH
-#undef PS_LAUNCH_AS
-  return PS_OK;
+#define PS_ROWS(NT)                                                                                                        \
+  return g.kv_dtype == PS_BF16 ? launch_as<NT, PS_BF16>(p, masked, stream, wg_items, wg_indptr, wg_solo, num_wg, st)      \
+                               : launch_as<NT, PS_FP8_E4M3>(p, masked, stream, wg_items, wg_indptr, wg_solo, num_wg, st)
+  if (max_rows <= 16) PS_ROWS(1);
+  if (max_rows <= 32) PS_ROWS(2);
+  PS_ROWS(4);
+#undef PS_ROWS
 }
 
 }  // namespace psdev

@@ -129,7 +129,7 @@ struct ps_layout {
 };
 
 // Waves per SIMD the MFMA kernel is built for, by the widest row group it must carry.
-inline int ps_mfma_occupancy(int max_rows, int kv_dtype) {
+constexpr int ps_mfma_occupancy(int max_rows, int kv_dtype) {
   // two workgroups per compute unit where the kernel fits in 256 VGPRs: one 16-row tile, or e4m3 KV
   // (half-size tile buffers) with up to two
   if (max_rows <= 16) return 2;

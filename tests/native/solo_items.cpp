@@ -13,10 +13,10 @@ static int fail(const char* what, int at) {
 // limit: of the tile kernel's items
 static int run(int32_t q_heads, int32_t kv_heads, int32_t head_dim, int32_t dtype, const std::vector<int32_t>& contexts, int32_t models,
                const std::vector<int32_t>& lens, int32_t num_cus, bool want_solo, int32_t limit = kPsSoloTokens * 3 / 2) {
-  const bool mfma = dtype == PS_BF16 && head_dim == 128;
+  const bool mfma = dtype != PS_F32 && head_dim == 128;
   const int32_t group = q_heads / kv_heads, n = int32_t(contexts.size()) * models;
   const int64_t tile = int64_t(16) * head_dim;
-  ps_geometry g{q_heads, kv_heads, head_dim, 16, dtype, dtype, kv_heads * 2 * tile, 2 * tile, tile, head_dim};
+  ps_geometry g{q_heads, kv_heads, head_dim, 16, dtype == PS_F32 ? PS_F32 : PS_BF16, dtype, kv_heads * 2 * tile, 2 * tile, tile, head_dim};
   std::vector<int32_t> prompt, model, suffix, active(size_t(n), 1);
   int32_t blocks = 0;
   for (size_t p = 0; p < contexts.size(); ++p)
@@ -38,6 +38,8 @@ static int run(int32_t q_heads, int32_t kv_heads, int32_t head_dim, int32_t dtyp
     const auto& pk = lay->pk_all;
     if (mfma) {
       if (pk.solo.empty() == want_solo && step == 0) return fail("solo items", step);
+      // (the kernel with four row tiles over e4m3 has no form for them)
+      if (dtype == PS_FP8_E4M3 && !pk.solo.empty() && pk.max_rows > 32) return fail("four row tiles", step);
       for (size_t w = 0; w < pk.solo.size(); ++w) {
         if (pk.solo[w] < pk.indptr[w] || pk.solo[w] > pk.indptr[w + 1]) return fail("bounds", step);
         for (int32_t i = pk.solo[w]; i < pk.indptr[w + 1]; ++i) {
@@ -71,6 +73,9 @@ int main() {
   if (int rc = run(32, 8, 128, PS_BF16, {2000, 600, 40}, 4, lens, 4, true)) return rc;
   if (int rc = run(64, 8, 128, PS_BF16, {2000, 600, 40}, 4, lens, 4, true)) return rc;
   if (int rc = run(28, 4, 128, PS_BF16, {2000, 600, 40}, 7, lens, 4, true)) return rc;
+  if (int rc = run(64, 8, 128, PS_FP8_E4M3, {2000, 600, 40}, 12, lens, 4, true)) return rc;   // groups of more than 64 rows
+  if (int rc = run(32, 2, 128, PS_FP8_E4M3, {2000, 600, 40}, 5, lens, 4, false)) return rc;
+  if (int rc = run(48, 1, 128, PS_FP8_E4M3, {2000, 600, 40}, 5, lens, 1, false)) return rc;   // four row tiles
   if (int rc = run(16, 8, 128, PS_BF16, {300, 40, 520}, 1, lens, 4, true)) return rc;     // shared items of two rows
   if (int rc = run(32, 2, 128, PS_BF16, {300, 40, 520}, 1, lens, 1, false)) return rc;    // sixteen rows: more than a wave fetches
   if (int rc = run(32, 8, 128, PS_BF16, {2000}, 2, lens, 256, false)) return rc;          // fewer items than workgroups
