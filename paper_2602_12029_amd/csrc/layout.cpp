@@ -762,7 +762,6 @@ int32_t ps_blob_build(ps_layout* lay) {
     if (pk.items.empty()) return;
     s.num_wg = int32_t(pk.indptr.size()) - 1;
     s.max_rows = pk.max_rows;
-    s.occ = pk.occ;
     s.stream = pk.stream;
     s.off_items = words;
     words = pad4(words + 8 * int64_t(pk.items.size()));

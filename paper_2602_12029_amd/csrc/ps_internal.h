@@ -80,7 +80,7 @@ struct ps_layout {
   struct schedule {
     int64_t off_items = 0, off_indptr = 0;  // blob offsets in words
     int64_t off_solo = -1;  // int32[num_wg]: the workgroup's first item that a wave takes alone; -1: no such items
-    int32_t num_wg = 0, max_rows = 0, occ = 1;  // occ: workgroups per compute unit the grid was sized for
+    int32_t num_wg = 0, max_rows = 0;
     bool stream = true;   // K/V loads of the launch are non-temporal (little of the set's K/V is read by several items)
   };
   schedule sched_prefix, sched_suffix, sched_all;
@@ -92,7 +92,7 @@ struct ps_layout {
     std::vector<int32_t> solo;       // empty, or per workgroup where its solo items begin (see kPsSoloTokens)
     int64_t four_extra = 0;          // cost of four such items besides their tiles; 0: there are none
     int64_t heaviest = 0, all = 0;   // cost of the heaviest workgroup, and of all, when it was packed
-    int32_t max_rows = 0, occ = 1;
+    int32_t max_rows = 0, occ = 1;   // occ: workgroups per compute unit (ps_mfma_occupancy)
     bool stream = true;
   };
   packed_set pk_prefix, pk_suffix, pk_all;
