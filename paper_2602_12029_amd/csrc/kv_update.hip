@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void append_e4m3_kernel(KvWriteParams p, const
 // 1648 23.2; 16-token blocks of bf16, 2.55 GB, where a tile is a piece, 451 -> 439 from the shorter index arithmetic.)
 template <bool TO_IMAGE, int TILES>
 __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_t* __restrict__ image,
-                                                         float* __restrict__ image_scales, uint32_t num_tiles,
+                                                         float* __restrict__ image_scales, int entry0, uint32_t num_tiles,
                                                          uint32_t ppt, int elem_bytes) {
   const int lane = threadIdx.x & 63;
   const uint64_t num_pieces = uint64_t(num_tiles) * ppt;
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_
     const int h = int((tile >> 1) % uint32_t(p.num_kv_heads));
     // Into the pool the shared blocks are walked in the order of their addresses there, so that the scattered side of
     // the copy is the read of the image (scattered writes cost more); out of it in table order, for the same reason.
-    const int pos = int((tile >> 1) / uint32_t(p.num_kv_heads));
+    const int pos = entry0 + int((tile >> 1) / uint32_t(p.num_kv_heads));
     const int e = TO_IMAGE ? pos : p.ent_order[pos];
     const int64_t image_tile_index = (int64_t(e) * p.num_kv_heads + h) * 2 + which;
     const int id = p.blk[e];
@@ -422,18 +422,22 @@ int32_t launch_kv_ingest(const ps_layout* lay, const void* dev_tables, int which
   if (tiles > INT32_MAX) return PS_ERR_INVALID_ARG;
   const dim3 grid{unsigned(grid64)}, block{256};
   const KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);
-  // (formats that keep the source bits: pieces of 4 KiB)
-  const int64_t ppt = std::max<int64_t>(1, (int64_t(g.block_size) * g.head_dim * (g.kv_dtype == PS_F32 ? 4 : 2) / 16 + 255) / 256);
-  if (ppt > INT32_MAX / 256 || tiles * ppt > int64_t(4) * INT32_MAX) return PS_ERR_INVALID_ARG;
-  const dim3 copy_grid{unsigned((tiles * ppt + 3) / 4)};
-  if (g.kv_dtype == PS_F32) {
-    if (g.head_dim % 4) return PS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((ingest_copy_kernel<float>), copy_grid, block, 0, st, p, static_cast<const float*>(src_k),
-                       static_cast<const float*>(src_v), src_s_tok, src_s_head, entry0, uint32_t(tiles), uint32_t(ppt));
-  } else if (g.kv_dtype == PS_BF16) {
-    if (g.head_dim % 8) return PS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((ingest_copy_kernel<uint16_t>), copy_grid, block, 0, st, p, static_cast<const uint16_t*>(src_k),
-                       static_cast<const uint16_t*>(src_v), src_s_tok, src_s_head, entry0, uint32_t(tiles), uint32_t(ppt));
+  if (g.kv_dtype != PS_FP8_E4M3) {   // formats that keep the source bits: pieces of 4 KiB
+    const int vec = g.kv_dtype == PS_F32 ? 4 : 8;
+    if (g.head_dim % vec) return PS_ERR_UNSUPPORTED;
+    const int64_t ppt = (int64_t(g.block_size) * (g.head_dim / vec) + 255) / 256;
+    if (ppt > INT32_MAX / 256) return PS_ERR_INVALID_ARG;
+    const int64_t per_entry = int64_t(g.num_kv_heads) * 2, step = entries_per_launch(num_entries, per_entry * ppt, 4);
+    for (int64_t first = 0; first < num_entries; first += step) {
+      const int64_t n = std::min<int64_t>(step, num_entries - first) * per_entry;
+      const dim3 copy_grid{unsigned((n * ppt + 3) / 4)};
+      if (g.kv_dtype == PS_F32)
+        hipLaunchKernelGGL((ingest_copy_kernel<float>), copy_grid, block, 0, st, p, static_cast<const float*>(src_k),
+                           static_cast<const float*>(src_v), src_s_tok, src_s_head, entry0 + int(first), uint32_t(n), uint32_t(ppt));
+      else
+        hipLaunchKernelGGL((ingest_copy_kernel<uint16_t>), copy_grid, block, 0, st, p, static_cast<const uint16_t*>(src_k),
+                           static_cast<const uint16_t*>(src_v), src_s_tok, src_s_head, entry0 + int(first), uint32_t(n), uint32_t(ppt));
+    }
   } else {
     if (g.head_dim % 8) return PS_ERR_UNSUPPORTED;
     const int64_t chunks = (int64_t(g.block_size) * (g.head_dim / 8) + 63) / 64;   // per lane, whole tile in registers
@@ -468,7 +472,7 @@ int32_t launch_kv_append(const ps_layout* lay, const void* dev_tables, const voi
   // e4m3: eight elements a lane where a row is a power of two of such pieces and every address a multiple of one (pool
   // strides are multiples of 16 bytes).  The copying formats gain nothing from wider stores: their launch is its dependent reads.
   const int pieces = g.head_dim / 8, wgs_y = (2 * g.num_kv_heads + 3) / 4;
-  const bool whole = g.kv_dtype == PS_FP8_E4M3 && g.head_dim % 8 == 0 && pieces <= 64 && (pieces & (pieces - 1)) == 0 && wgs_y <= 65535 &&
+  const bool whole = g.kv_dtype == PS_FP8_E4M3 && g.head_dim % 8 == 0 && pieces <= 64 && (pieces & (pieces - 1)) == 0 && wgs_y <= 65535 && lay->num_requests <= kMaxWorkgroups &&
                      (reinterpret_cast<uintptr_t>(new_k) | reinterpret_cast<uintptr_t>(new_v) | reinterpret_cast<uintptr_t>(kv)) % 16 == 0;
   if (whole)
     hipLaunchKernelGGL(append_e4m3x8_kernel, dim3(unsigned(lay->num_requests), unsigned(wgs_y)), block, 0, st, p,
@@ -502,16 +506,19 @@ int32_t launch_kv_stage(const ps_layout* lay, const void* dev_tables, bool to_im
   // runs (5.16 -> 5.65 TB/s), stage_out is unchanged; with the 2 KiB tiles of e4m3 more tiles per wave only lose.
   // A small batch keeps to one piece a wave, so that it fills the chip.
   const int64_t tile_chunks = int64_t(g.block_size) * g.head_dim * esz / 16, ppt = (tile_chunks + 255) / 256;
-  if (ppt > INT32_MAX / 256 || tiles * ppt > int64_t(4) * INT32_MAX) return PS_ERR_INVALID_ARG;
-  const int64_t pieces = tiles * ppt;
-  const int per_wave = esz >= 2 && pieces > 4 * 4096 ? 4 : 1;
-#define PS_STAGE(TO, N)                                                                                             \
-  hipLaunchKernelGGL((stage_copy_kernel<TO, N>), dim3{unsigned((pieces + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
-                     img_scales, uint32_t(tiles), uint32_t(ppt), esz)
-  if (to_image) {
-    if (per_wave == 4) PS_STAGE(true, 4); else PS_STAGE(true, 1);
-  } else {
-    if (per_wave == 4) PS_STAGE(false, 4); else PS_STAGE(false, 1);
+  if (ppt > INT32_MAX / 256) return PS_ERR_INVALID_ARG;
+  const int per_wave = esz >= 2 && tiles * ppt > 4 * 4096 ? 4 : 1;
+  const int64_t per_entry = int64_t(g.num_kv_heads) * 2, step = entries_per_launch(entries, per_entry * ppt, 4 * per_wave);
+#define PS_STAGE(TO, N)                                                                                               \
+  hipLaunchKernelGGL((stage_copy_kernel<TO, N>), dim3{unsigned((n * ppt + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
+                     img_scales, int(first), uint32_t(n), uint32_t(ppt), esz)
+  for (int64_t first = 0; first < entries; first += step) {
+    const int64_t n = std::min<int64_t>(step, entries - first) * per_entry;
+    if (to_image) {
+      if (per_wave == 4) PS_STAGE(true, 4); else PS_STAGE(true, 1);
+    } else {
+      if (per_wave == 4) PS_STAGE(false, 4); else PS_STAGE(false, 1);
+    }
   }
 #undef PS_STAGE
   return PS_OK;

@@ -147,6 +147,14 @@ static_assert(kPsSoloTokens * 3 / 2 <= kPsMfmaMaxChunk / 4, "a wave's own item h
 // Rows of such an item in the persistent kernel: what a wave fetches of the queries, by the row tiles the launch carries.
 inline int ps_solo_rows(int max_rows) { return max_rows <= 32 ? 8 : 16; }
 
+// A launch takes fewer than 2^32 threads a dimension: workgroups of 256.  The copies of whole blocks go out in ranges of entries
+// that stay under it (a block's tile of a little over a piece is two pieces, so that a pool of 140 GB would pass it).
+constexpr int64_t kMaxWorkgroups = (int64_t(1) << 24) - 1;
+inline int64_t entries_per_launch(int64_t entries, int64_t pieces_per_entry, int64_t pieces_per_workgroup) {
+  const int64_t most = kMaxWorkgroups * pieces_per_workgroup / pieces_per_entry;
+  return entries <= most ? entries : most > 0 ? most : 1;
+}
+
 // Compute units of the current device, or 0 if none can be asked.  Null in a build without the device side of the
 // library (the planner then assumes kPsDefaultNumCus); abi.hip installs it when the library is loaded.
 extern int32_t (*ps_device_num_cus_hook)();
