@@ -160,9 +160,13 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // line once, which pays where the launch streams from HBM and the products are cheap.  All row tiles a wave / spread, us
   // (batch, MB): d = 256 (passes of 16 rows there), bf16 276 MB 130 / 99, 1.5 GB 559 / 357, float32 552 MB 312 / 238, 267 MB 144 /
   // 144; d = 128, float32 463 MB 141 / 127, 555 MB 153 / 152, 1.2 GB 303 / 297, 279 MB 152 / 108, float32 queries over bf16 139 /
-  // 119, 310 / 262, over e4m3 128 / 108; d = 64, e4m3 45 / 40, 35 / 34, float32 232 MB 68 / 64, 140 MB 71 / 62, but 593 MB 143 / 149;
-  // bf16 products over bf16: d = 64 47 MB 37.9 / 34.7, 65 MB 30.9 / 28.8, 86 MB 40.6 / 42.1, 139 MB 40.2 / 43.1, 743 MB 150 / 162,
-  // d = 128 138 MB 56 / 53, 277 MB 60 / 73, 338 MB 74 / 101.
+  // 119, 310 / 262, over e4m3 128 / 108; d = 64, e4m3 45 / 40, 35 / 34.
+  // The other formats by the bytes of the whole batch, 24 or 32 rows and 56 or 64 rows a group on 8 to 40 contexts, spread against
+  // all row tiles a wave: bf16, d = 128, 80 MB -11 to -8 and -14 to -11 %, 110 MB -4 to -2 and -9 to -3, 140 MB +1 to +3 and -2 to +6,
+  // 170 MB +2 to +6 and -2 to +12, 280 MB +10 to +15 and +11 to +24; d = 64, 40 MB -13 to -11 and -5, 55 MB -5 to -3 and +3 to +4, 70 MB
+  // +1 to +4 and +9 to +16, 140 MB +13 to +19 and +29 to +46; float32, d = 64, 300 MB -12 to -10 and -17 to -13, 400 MB -3 to +2 and
+  // -15 to -13, 650 MB +1 to +6 and -16 to -13 (two passes in the form with all row tiles).  Private segments beside them count: half
+  // of a bf16 batch of 220 MB, d = 128, -16 to +34, of one of 170, d = 64, -10 to +44.
   // Where such groups hold under a quarter of the tokens (a short root), the rest decides: 16-row items, two workgroups a
   // compute unit (14 contexts of 2999 to 11998 tokens with 64-wide heads under a root of 32: 44.0 -> 40.2 us).
   int64_t wide_group_tokens = 0;
@@ -173,7 +177,8 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   const bool tile_narrow = group <= 16 && 4 * wide_group_tokens * g.num_kv_heads < total;
   const int64_t kv_mb = total * 2 * g.head_dim * (g.kv_dtype == PS_F32 ? 4 : g.kv_dtype == PS_BF16 ? 2 : 1) / 1000000;
   lay->tile_spread = tile_narrow || g.head_dim == 256 || g.kv_dtype == PS_FP8_E4M3 || g.kv_dtype != g.q_dtype ||
-                     (g.kv_dtype == PS_BF16 ? kv_mb <= (g.head_dim == 64 ? 70 : 140) : g.head_dim != 64 || kv_mb <= 400);
+                     (g.kv_dtype == PS_BF16 ? kv_mb <= (g.head_dim != 64 ? 140 : widest <= 32 ? 65 : 45)
+                                            : g.head_dim != 64 || widest > 32 || kv_mb <= 400);
   // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item.  Heads of up to 128 with up to 16 rows
   // a wave leave room for two and more of them per compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25
   // of it: 36 float32 requests on 12 contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide

@@ -29,7 +29,7 @@ def test_addresses_are_numbers():
     B.ps_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("program", ["block_order", "upload_staging", "plan_builds", "solo_items", "schedule_balance", "copy_ranges"])
+@pytest.mark.parametrize("program", ["block_order", "upload_staging", "plan_builds", "solo_items", "schedule_balance", "copy_ranges", "tile_rows"])
 def test_native(program, tmp_path):
     exe = str(tmp_path / program)
     subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
