@@ -52,43 +52,47 @@ bool ps_mfma_supported(const ps_geometry& g) {
          (g.num_q_heads / g.num_kv_heads) <= 64 && slice_span < (int64_t(1) << 31);
 }
 
-// What a workgroup of a schedule spends on an item that its waves share, in tokens, and on four that a wave each takes, by the
-// longest of them.  Where there are fours, costs in time (an item of t tokens takes t / 128 + 2 tiles, a four t / 32 + 1 or + 2;
-// by tokens + 64 alone the fours looked like whole chunks: 47 requests on 7 contexts of 383 to 4074 tokens 24.8 -> 21.9 us, 54 on
-// 11 of 136 to 1659 33.3 -> 28.4), of whole tiles: a wave spends one on a single token (64 requests on 16 contexts of 1024 to
-// 6144 tokens with one private token each 54.2 -> 44.2 us, with 128 82.5 -> 62.4, e4m3 under groups of eight 48.5 -> 37.0; with
-// whole tiles for the fours alone the 47 requests take 23.2).
-static int64_t shared_cost(const ps_layout::packed_set& pk, int64_t tokens) { return pk.four_extra ? round_up(tokens, 32) + 256 : tokens + 64; }
-static int64_t four_cost(const ps_layout::packed_set& pk, int64_t longest) { return 4 * round_up(longest, 32) + pk.four_extra; }
+// What a workgroup of a schedule spends on an item that its waves share, in 64ths of a token, and on four that a wave each takes, by
+// the longest of them, behind `before`.  Where there are fours, costs in time: an item of t tokens takes t / 128 + 2 tiles; a four, of
+// whole 16-token blocks since a wave spends one on a single token, t / 32 + 1 and one more behind something else (the start of the
+// first is one that the launch waits for anyway).  By tokens + 64 alone the fours looked like whole chunks (47 requests on 7
+// contexts of 383 to 4074 tokens 24.8 us, 22.4 now; 54 on 11 of 136 to 1659 33.3, 28.1 now).  Four by their tokens, with one tile
+// more for all of them or none / as here: 64 requests on 16 contexts of 1024 to 6144 tokens with one private token each 54.1 /
+// 42.6 us, e4m3 under groups of eight 48.1 / 33.0, the 47 22.0 / 22.4, 160 on 40 contexts 99.7 / 101.4; no tile more for any, 301
+// requests with up to 11 private tokens 206 against 201.6; for all, 46 on 13 of 173 to 564 21.2 against 17.5.  Equal ones by their
+// tokens (155 requests on as many contexts of 9 to 157 tokens, 620 fours on 512 workgroups, 22.7 us, the first of the equal 26.2).
+static int64_t shared_cost(bool fours, int64_t tokens) { return fours ? 64 * (round_up(tokens, 32) + 256) + tokens : 64 * (tokens + 64); }
+static int64_t four_cost(int64_t longest, int64_t before) { return 64 * (4 * round_up(longest, 16) + (before ? 256 : 128)) + 4 * longest; }
 
 // Whether the private segments have grown so far since the whole step's schedule was packed that it is worth planning anew: its
-// heaviest workgroup has a quarter more to do than any schedule of these items makes unavoidable, and it has got an eighth more, or
-// all together a sixteenth, since (so that a batch that cannot be had more even is not planned at every step).  16 contexts
+// heaviest workgroup has a quarter more to do than any schedule of these items makes unavoidable, and it has got a sixteenth more, or
+// all together a hundredth, since (so that a batch that cannot be had more even is not planned at every step).  16 contexts
 // of 1024 to 6144 tokens under four models, the plan of the first token kept / planned anew, after 128, 512 and 768 tokens 83 / 44,
 // 202 / 58 and 281 / 72 us a launch (72, 121 and 159 with four waves on every item); a plan takes some 0.2 ms on the host.
 static bool outgrown(const ps_layout* lay) {
   const ps_layout::packed_set& pk = lay->pk_all;
   auto tokens = [&](int32_t i) { return int64_t(pk.items[size_t(i)].tok_end - pk.items[size_t(i)].tok_begin); };
+  const bool fours = !pk.solo.empty();
   int64_t most = 0, sum = 0, unavoidable = 0;
   for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
     const int32_t last = pk.indptr[w + 1], first_solo = pk.solo.empty() ? last : pk.solo[w];
     int64_t load = 0;
     for (int32_t i = pk.indptr[w]; i < first_solo; ++i) {
-      load += shared_cost(pk, tokens(i));
-      unavoidable = std::max(unavoidable, shared_cost(pk, tokens(i)));
+      load += shared_cost(fours, tokens(i));
+      unavoidable = std::max(unavoidable, shared_cost(fours, tokens(i)));
     }
     for (int32_t i = first_solo; i < last; i += 4) {
       int64_t longest = 0;
       for (int32_t k = i; k < std::min(i + 4, last); ++k) longest = std::max(longest, tokens(k));
       if (longest > kPsSoloTokens * 3 / 2) return true;
-      load += four_cost(pk, longest);
-      unavoidable = std::max(unavoidable, shared_cost(pk, longest));
+      load += four_cost(longest, load);
+      unavoidable = std::max(unavoidable, shared_cost(fours, longest));
     }
     most = std::max(most, load);
     sum += load;
   }
   unavoidable = std::max(unavoidable, ceil_div(sum, int64_t(lay->num_cus) * pk.occ));
-  return 4 * most > 5 * unavoidable && (8 * most >= 9 * pk.heaviest || 16 * sum >= 17 * pk.all);
+  return 4 * most > 5 * unavoidable && (16 * most >= 17 * pk.heaviest || 100 * sum >= 101 * pk.all);
 }
 
 // The tile kernel's short private items, which a wave takes alone, are the last of all; those that have grown past their limit go
@@ -675,12 +679,8 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     struct unit { int64_t cost; int first, count; };   // of `order`
     std::vector<unit> units;
     units.reserve(size_t(count));
-    // A four in a chain of several costs a tile more than the first, whose start the launch waits for anyway (301 requests with
-    // up to 11 private tokens, 2.4 fours and two shared items a workgroup: 206 us without that, 202 with; 46 on 13 of 173 to 564
-    // 17.5 / 21.2, 54 on 11 of 136 to 1659 28.1 / 34.8).
-    out.four_extra = n_full == count ? 0 : n_full + (count - n_full + 3) / 4 <= 2 * num_cus * out.occ ? 128 : 256;
-    for (int n = 0; n < n_full; ++n) units.push_back({shared_cost(out, cost(order[size_t(n)]) - 64), n, 1});
-    for (int n = n_full; n < count; n += 4) units.push_back({four_cost(out, cost(order[size_t(n)]) - 64), n, std::min(4, count - n)});
+    for (int n = 0; n < n_full; ++n) units.push_back({shared_cost(n_full < count, cost(order[size_t(n)]) - 64), n, 1});
+    for (int n = n_full; n < count; n += 4) units.push_back({four_cost(cost(order[size_t(n)]) - 64, 0), n, std::min(4, count - n)});
     auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
     std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
     const int num_wg = std::max(1, std::min(int(units.size()), num_cus * out.occ));
@@ -689,15 +689,16 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     std::priority_queue<slot, std::vector<slot>, std::greater<slot>> load;
     for (int w = 0; w < num_wg; ++w) load.push({0, w});
     std::vector<int> wg_of(units.size(), 0), fill(size_t(num_wg) + 1, 0), full(size_t(num_wg), 0);
-    for (const unit& u : units) out.all += u.cost;
     for (size_t n = 0; n < units.size(); ++n) {
       const slot least = load.top();
       load.pop();
       wg_of[n] = least.second;
       fill[size_t(least.second) + 1] += units[n].count;
       if (units[n].first < n_full) ++full[size_t(least.second)];
-      load.push({least.first + units[n].cost, least.second});
-      out.heaviest = std::max(out.heaviest, least.first + units[n].cost);
+      const int64_t spent = units[n].first < n_full ? units[n].cost : four_cost(cost(order[size_t(units[n].first)]) - 64, least.first);
+      load.push({least.first + spent, least.second});
+      out.heaviest = std::max(out.heaviest, least.first + spent);
+      out.all += spent;
     }
     for (int w = 0; w < num_wg; ++w) fill[size_t(w) + 1] += fill[size_t(w)];
     out.indptr.assign(fill.begin(), fill.end());

@@ -1,6 +1,6 @@
-// The schedule of a whole step is even: what its heaviest workgroup has to do, in tiles -- a shared item or one of four waves
-// takes ceil(tokens / 128) and two more, four that a wave each takes ceil(longest / 32) and one -- is what dealing them out
-// heaviest first, each to the workgroup with the least to do, comes to.  And it stays so through a long turn: while every step
+// The schedule of a whole step is even: what its heaviest workgroup has to do, in half tiles -- an item of four waves takes
+// ceil(tokens / 128) tiles and two more, four that a wave each takes half a tile for every 16 tokens of the longest and one more, two
+// behind something else -- is what dealing them out heaviest first, each to the workgroup with the least to do, comes to.  And it stays so through a long turn: while every step
 // makes the private segments longer the heaviest workgroup has no more than a quarter more to do than in a plan made afresh, and
 // batch is not planned anew at every step for it.
 #include <algorithm>
@@ -30,31 +30,34 @@ static std::vector<int32_t> context_lengths(const Turn& t) {
   return len;
 }
 
-// Most tiles of a workgroup; dealt: the same of these items and fours when dealt out by their tiles.
+// Most half tiles of a workgroup; dealt: the same of these items and fours when dealt out by their half tiles.
 static int64_t heaviest(const ps_layout* lay, int64_t* dealt) {
   const auto& pk = lay->pk_all;
   auto tiles = [](const ps_item& it, int64_t per) { return (it.tok_end - it.tok_begin + per - 1) / per; };
-  std::vector<int64_t> units;
+  struct unit { int64_t cost; bool four; };
+  std::vector<unit> units;
   int64_t most = 0;
   for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
     const int32_t first_solo = pk.solo.empty() ? pk.indptr[w + 1] : pk.solo[w];
-    const size_t first_unit = units.size();
-    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) units.push_back(tiles(pk.items[size_t(i)], 128) + 2);
+    int64_t load = 0;
+    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) {
+      units.push_back({2 * tiles(pk.items[size_t(i)], 128) + 4, false});
+      load += units.back().cost;
+    }
     for (int32_t i = first_solo; i < pk.indptr[w + 1]; i += 4) {
       int64_t longest = 0;
-      for (int32_t k = i; k < std::min(i + 4, pk.indptr[w + 1]); ++k) longest = std::max(longest, tiles(pk.items[size_t(k)], 32));
-      units.push_back(longest + 1);
+      for (int32_t k = i; k < std::min(i + 4, pk.indptr[w + 1]); ++k) longest = std::max(longest, tiles(pk.items[size_t(k)], 16));
+      units.push_back({longest + 2, true});
+      load += longest + (load ? 4 : 2);
     }
-    int64_t load = 0;
-    for (size_t u = first_unit; u < units.size(); ++u) load += units[u];
     most = std::max(most, load);
   }
-  std::sort(units.begin(), units.end(), std::greater<int64_t>());
+  std::sort(units.begin(), units.end(), [](const unit& a, const unit& b) { return a.cost > b.cost; });
   std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> load;
   for (int w = 0; w < 256 * pk.occ; ++w) load.push(0);
   *dealt = 0;
-  for (int64_t u : units) {
-    const int64_t sum = load.top() + u;
+  for (const unit& u : units) {
+    const int64_t sum = load.top() + u.cost + (u.four && load.top() ? 2 : 0);
     load.pop();
     load.push(sum);
     *dealt = std::max(*dealt, sum);
@@ -63,7 +66,7 @@ static int64_t heaviest(const ps_layout* lay, int64_t* dealt) {
 }
 
 static int fail(const Turn& t, int step, int64_t have, int64_t want) {
-  std::printf("FAILED: %s: step %d: heaviest workgroup %lld tiles, dealt out evenly %lld\n", t.what, step, (long long)have, (long long)want);
+  std::printf("FAILED: %s: step %d: heaviest workgroup %lld half tiles, dealt out evenly %lld\n", t.what, step, (long long)have, (long long)want);
   return 1;
 }
 
@@ -118,7 +121,7 @@ static int run(const Turn& t, int every) {
     Batch afresh;
     if (!afresh.make(t, len, 0)) return fail(t, -1, 0, 0);
     const int64_t even = heaviest(afresh.lay, &dealt_afresh);
-    if (4 * most > 5 * (even + 1)) return fail(t, step, most, even);   // (costs are rounded to tiles)
+    if (4 * most > 5 * (even + 2)) return fail(t, step, most, even);   // (costs are rounded to tiles)
   }
   if (planned > 40) {
     std::printf("FAILED: %s: planned %d times in %d steps\n", t.what, planned, kSteps);
