@@ -63,8 +63,11 @@ struct KvWriteParams {
 // ---- ingest, storage formats that keep the source bits (T = uint16_t for bf16, float) --------------------
 // One wavefront per piece of an (entry, head, K|V) tile: 256 16-byte chunks, four a lane, all fetched before the first
 // store; `ppt` pieces a tile.  HBM-bound; with a wave per tile a batch of a few hundred larger blocks left most of the chip
-// idle (25 contexts of 3130 tokens in blocks of 32, two launches: 36.3 -> 34.1 us).
-template <typename T>
+// idle (25 contexts of 3130 tokens in blocks of 32, two launches: 36.3 -> 34.1 us).  The four loads of a small launch stand without
+// branches: a chunk past the tile's end reads the last one again, which costs less than the wait that a branch leaves behind each
+// (one context of 10366 tokens in blocks of 16: 15.0 -> 12.9 us).  PACED: a large one keeps them, HBM
+// bounds it anyway and takes shorter bursts better (a GB in blocks of 64: 90.7 us, without 91.5; in blocks of 16 209.7 / 210.3).
+template <typename T, bool PACED>
 __global__ __launch_bounds__(256) void ingest_copy_kernel(KvWriteParams p, const T* __restrict__ src_k,
                                                           const T* __restrict__ src_v, int64_t src_s_tok,
                                                           int64_t src_s_head, int entry0, uint32_t num_tiles, uint32_t ppt) {
@@ -82,11 +85,12 @@ __global__ __launch_bounds__(256) void ingest_copy_kernel(KvWriteParams p, const
   const int c0 = int(piece - uint64_t(tile) * ppt) * 256 + lane;
   const T* src = (which ? src_v : src_k) + int64_t(p.ent_tok0[e]) * src_s_tok + int64_t(h) * src_s_head;
   T* dst = static_cast<T*>(p.kv) + int64_t(p.blk[e]) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
+  if (c0 - lane >= chunks) return;
   u32x4 v[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int c = c0 + 64 * u;
-    if (c < chunks) v[u] = stream_load(reinterpret_cast<const u32x4*>(src + int64_t(c / cpt) * src_s_tok + (c % cpt) * kVec));
+    const int c = PACED ? c0 + 64 * u : min(c0 + 64 * u, chunks - 1);
+    if (!PACED || c < chunks) v[u] = stream_load(reinterpret_cast<const u32x4*>(src + int64_t(c / cpt) * src_s_tok + (c % cpt) * kVec));
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -313,10 +317,11 @@ __global__ __launch_bounds__(256) void append_e4m3_kernel(KvWriteParams p, const
 // One wavefront per TILES consecutive pieces of (entry, KV head, K|V) tiles of B x d elements -- 256 16-byte chunks of a
 // tile, `ppt` pieces a tile --; the image is dense,
 // [entry][head][K|V][slot][d] in table order, followed by the e4m3 scales [entry][head][K|V].  TO_IMAGE: pool ->
-// image, else image -> pool.  Bits are copied, 16 bytes per lane, four loads per piece in flight before the first store.
+// image, else image -> pool.  Bits are copied, 16 bytes per lane, four loads per piece before the first store.
 // (A wave used to walk whole tiles: ten requests' blocks of 64 tokens, 54 MB there and back, in 103 workgroups 85.8 us, in
 // 1648 23.2; 16-token blocks of bf16, 2.55 GB, where a tile is a piece, 451 -> 439 from the shorter index arithmetic.)
-template <bool TO_IMAGE, int TILES>
+// LOADS: chunks a lane has of a piece (two for the 2 KiB tiles of e4m3 in blocks of 16).
+template <bool TO_IMAGE, int TILES, int LOADS>
 __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_t* __restrict__ image,
                                                          float* __restrict__ image_scales, int entry0, uint32_t num_tiles,
                                                          uint32_t ppt, int elem_bytes) {
@@ -359,13 +364,15 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_
   }
   // every load goes out before the first store
   {
-    u32x4 v[TILES][4];
+    u32x4 v[TILES][LOADS];
 #pragma unroll
     for (int i = 0; i < TILES; ++i)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = first[i] + 64 * u + lane;
-        if (c < last[i]) {
+      for (int u = 0; u < LOADS; ++u) {
+        // (a piece a wave: no branch around a load, as in the ingest; with four the waits between them pace a launch that HBM
+        // bounds anyway: 16-token blocks of bf16, 2.55 GB, 437 us, all sixteen loads at once 450)
+        const int at = first[i] + 64 * u + lane, c = TILES == 1 ? min(at, chunks - 1) : at;
+        if (TILES == 1 || c < last[i]) {
           const int slot = c / row_chunks, col = c % row_chunks;
           const uint8_t* src = TO_IMAGE ? pool_tile[i] + slot * tok_bytes + 16 * col : image_tile[i] + 16 * int64_t(c);
           v[i][u] = stream_load(reinterpret_cast<const u32x4*>(src));
@@ -374,7 +381,7 @@ __global__ __launch_bounds__(256) void stage_copy_kernel(KvWriteParams p, uint8_
 #pragma unroll
     for (int i = 0; i < TILES; ++i)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < LOADS; ++u) {
         const int c = first[i] + 64 * u + lane;
         if (c < last[i]) {
           const int slot = c / row_chunks, col = c % row_chunks;
@@ -428,15 +435,19 @@ int32_t launch_kv_ingest(const ps_layout* lay, const void* dev_tables, int which
     const int64_t ppt = (int64_t(g.block_size) * (g.head_dim / vec) + 255) / 256;
     if (ppt > INT32_MAX / 256) return PS_ERR_INVALID_ARG;
     const int64_t per_entry = int64_t(g.num_kv_heads) * 2, step = entries_per_launch(num_entries, per_entry * ppt, 4);
+    const bool paced = tiles * ppt > 8 * 4096;
     for (int64_t first = 0; first < num_entries; first += step) {
       const int64_t n = std::min<int64_t>(step, num_entries - first) * per_entry;
       const dim3 copy_grid{unsigned((n * ppt + 3) / 4)};
-      if (g.kv_dtype == PS_F32)
-        hipLaunchKernelGGL((ingest_copy_kernel<float>), copy_grid, block, 0, st, p, static_cast<const float*>(src_k),
-                           static_cast<const float*>(src_v), src_s_tok, src_s_head, entry0 + int(first), uint32_t(n), uint32_t(ppt));
-      else
-        hipLaunchKernelGGL((ingest_copy_kernel<uint16_t>), copy_grid, block, 0, st, p, static_cast<const uint16_t*>(src_k),
-                           static_cast<const uint16_t*>(src_v), src_s_tok, src_s_head, entry0 + int(first), uint32_t(n), uint32_t(ppt));
+#define PS_COPY(T, PACED)                                                                                              \
+  hipLaunchKernelGGL((ingest_copy_kernel<T, PACED>), copy_grid, block, 0, st, p, static_cast<const T*>(src_k),         \
+                     static_cast<const T*>(src_v), src_s_tok, src_s_head, entry0 + int(first), uint32_t(n), uint32_t(ppt))
+      if (g.kv_dtype == PS_F32) {
+        if (paced) PS_COPY(float, true); else PS_COPY(float, false);
+      } else {
+        if (paced) PS_COPY(uint16_t, true); else PS_COPY(uint16_t, false);
+      }
+#undef PS_COPY
     }
   } else {
     if (g.head_dim % 8) return PS_ERR_UNSUPPORTED;
@@ -509,15 +520,15 @@ int32_t launch_kv_stage(const ps_layout* lay, const void* dev_tables, bool to_im
   if (ppt > INT32_MAX / 256) return PS_ERR_INVALID_ARG;
   const int per_wave = esz >= 2 && tiles * ppt > 4 * 4096 ? 4 : 1;
   const int64_t per_entry = int64_t(g.num_kv_heads) * 2, step = entries_per_launch(entries, per_entry * ppt, 4 * per_wave);
-#define PS_STAGE(TO, N)                                                                                               \
-  hipLaunchKernelGGL((stage_copy_kernel<TO, N>), dim3{unsigned((n * ppt + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
+#define PS_STAGE(TO, N, LOADS)                                                                                               \
+  hipLaunchKernelGGL((stage_copy_kernel<TO, N, LOADS>), dim3{unsigned((n * ppt + 4 * N - 1) / (4 * N))}, dim3{256}, 0, st, p, img, \
                      img_scales, int(first), uint32_t(n), uint32_t(ppt), esz)
   for (int64_t first = 0; first < entries; first += step) {
     const int64_t n = std::min<int64_t>(step, entries - first) * per_entry;
     if (to_image) {
-      if (per_wave == 4) PS_STAGE(true, 4); else PS_STAGE(true, 1);
+      if (per_wave == 4) PS_STAGE(true, 4, 4); else if (tile_chunks > 128) PS_STAGE(true, 1, 4); else PS_STAGE(true, 1, 2);
     } else {
-      if (per_wave == 4) PS_STAGE(false, 4); else PS_STAGE(false, 1);
+      if (per_wave == 4) PS_STAGE(false, 4, 4); else if (tile_chunks > 128) PS_STAGE(false, 1, 4); else PS_STAGE(false, 1, 2);
     }
   }
 #undef PS_STAGE
