@@ -537,6 +537,9 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // us, with e4m3 43.3 / 39.1, 52.7 / 46.5, 89.7 / 88.3; 256-wide heads 168 / 158, 201 / 193, 296 / 311), since they end a shorter
   // launch (64-wide heads, 24 contexts of 1024 to 6144 tokens under four models 42.8 / 48.0, 48.7 / 55.0, 62.8 / 77.6, 90 of 300 to
   // 1500 with sixteen rows 37.4 / 40.5, 40.4 / 44.6, 55.8 / 56.2; though 12 of 500 to 3000 under eight 30.4 / 25.4, 36.5 / 29.0).
+  // Half as long where the private items are not many more than the resident workgroups, which would have one each and be done
+  // sooner (256-wide heads, without / 64 / 128 / 256: float32, 72 requests with up to 145 on 24 contexts of 533 to 2132 tokens 70.2 /
+  // 68.2 / 81.2, bf16, 71 with up to 188 on 18 46.1 / 45.6 / 44.8 / 48.3).
   lay->solo_limit = 0;
   {
     const int rows = std::max(group, lay->max_rows_prefix);
@@ -545,6 +548,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
         int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident) {
       const bool many = g.q_dtype == PS_BF16 && int64_t(suffix_items.size()) >= 4 * int64_t(num_cus) * resident;
       lay->solo_limit = g.kv_dtype == PS_F32 ? kPsSoloTokensTile / 2 : !many ? kPsSoloTokensTile : g.head_dim == 64 ? 1024 : 512;
+      if (3 * int64_t(suffix_items.size()) < 4 * int64_t(num_cus) * resident) lay->solo_limit /= 2;
     }
   }
   lay->num_prefix_items = int32_t(prefix_items.size());

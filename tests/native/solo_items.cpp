@@ -54,9 +54,9 @@ static int run(int32_t q_heads, int32_t kv_heads, int32_t head_dim, int32_t dtyp
         if (!(it.kind & kPsItemSuffix) || it.tok_end - it.tok_begin > limit || it.n_req * group > 16) return fail("item", step);
       }
       // (and all that are within it, whatever order the appends have left)
-      for (size_t i = size_t(lay->num_prefix_items); want_solo && i < lay->items.size() - size_t(lay->num_solo_items); ++i) {
+      for (size_t i = size_t(lay->num_prefix_items); i < lay->items.size() - size_t(lay->num_solo_items); ++i) {
         const ps_item& it = lay->items[i];
-        if (it.tok_end - it.tok_begin <= limit) return fail("missed", step);
+        if (it.tok_end - it.tok_begin <= lay->solo_limit) return fail("missed", step);
       }
     }
     // (every seventh request never grows)
@@ -83,6 +83,9 @@ int main() {
   if (int rc = run(32, 8, 64, PS_BF16, {6000, 600, 40}, 4, lens, 16, true, 256)) return rc;
   if (int rc = run(16, 4, 256, PS_BF16, {2000, 600, 40}, 4, lens, 8, true, 512)) return rc;
   if (int rc = run(16, 4, 256, PS_F32, {2000, 600, 40}, 4, lens, 4, true, 128)) return rc;
+  std::vector<int32_t> many_contexts;
+  for (int32_t i = 0; i < 24; ++i) many_contexts.push_back(533 + 467 * i % 1600);
+  if (int rc = run(8, 4, 256, PS_F32, many_contexts, 3, {40, 1, 64, 65, 128}, 256, true, 64)) return rc;   // 288 private items
   if (int rc = run(32, 1, 64, PS_F32, {2000, 600, 40}, 4, lens, 1, false)) return rc;     // thirty-two rows
   std::puts("ok");
   return 0;
