@@ -169,20 +169,26 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // all row tiles a wave: bf16, d = 128, 80 MB -11 to -8 and -14 to -11 %, 110 MB -4 to -2 and -9 to -3, 140 MB +1 to +3 and -2 to +6,
   // 170 MB +2 to +6 and -2 to +12, 280 MB +10 to +15 and +11 to +24; d = 64, 40 MB -13 to -11 and -5, 55 MB -5 to -3 and +3 to +4, 70 MB
   // +1 to +4 and +9 to +16, 140 MB +13 to +19 and +29 to +46; float32, d = 64, 300 MB -12 to -10 and -17 to -13, 400 MB -3 to +2 and
-  // -15 to -13, 650 MB +1 to +6 and -16 to -13 (two passes in the form with all row tiles).  Private segments beside them count: half
-  // of a bf16 batch of 220 MB, d = 128, -16 to +34, of one of 170, d = 64, -10 to +44.
-  // Where such groups hold under a quarter of the tokens (a short root), the rest decides: 16-row items, two workgroups a
-  // compute unit (14 contexts of 2999 to 11998 tokens with 64-wide heads under a root of 32: 44.0 -> 40.2 us).
+  // -15 to -13, 650 MB +1 to +6 and -16 to -13 (two passes in the form with all row tiles).
+  // Where such groups hold under a quarter of the tokens (a short root, or private segments beside them), under a third in bf16,
+  // the rest decides: 16-row items, two workgroups a compute unit and chunks for them (14 contexts of 2999 to 11998 tokens with
+  // 64-wide heads under a root of 32: 44.0 -> 40.2 us).  Bf16 batches of 70 to 600 MB with private segments of 30 to 2000 tokens, d =
+  // 64 and 128, against all row tiles a wave: 24 % of the tokens in such groups -38 to +5 %, 30 % -38 to +17, 39 % -35 to +21, 53 % -33 to
+  // +32.  Float32 with 64-wide heads of more than 400 MB, 24 % -10 to +14 %, 30 % -12 to +21, 39 % -12 to +12; 53 % and more than 32 rows -11 to -1.
   int64_t wide_group_tokens = 0;
   for (size_t p = 0; p + 1 < lay->group_indptr.size(); ++p)
     if (int64_t(lay->group_indptr[p + 1] - lay->group_indptr[p]) * group > 16) wide_group_tokens += lay->prefix_len[p];
   for (size_t t = 0; t + 1 < lay->root_group_indptr.size(); ++t)
     if (int64_t(lay->root_group_indptr[t + 1] - lay->root_group_indptr[t]) * group > 16) wide_group_tokens += lay->root_len[t];
-  const bool tile_narrow = group <= 16 && 4 * wide_group_tokens * g.num_kv_heads < total;
+  const bool tile_bf16 = g.kv_dtype == PS_BF16 && g.q_dtype == PS_BF16;
+  const bool tile_narrow = group <= 16 && (tile_bf16 ? 3 : 4) * wide_group_tokens * g.num_kv_heads < total;
   const int64_t kv_mb = total * 2 * g.head_dim * (g.kv_dtype == PS_F32 ? 4 : g.kv_dtype == PS_BF16 ? 2 : 1) / 1000000;
-  lay->tile_spread = tile_narrow || g.head_dim == 256 || g.kv_dtype == PS_FP8_E4M3 || g.kv_dtype != g.q_dtype ||
-                     (g.kv_dtype == PS_BF16 ? kv_mb <= (g.head_dim != 64 ? 140 : widest <= 32 ? 65 : 45)
-                                            : g.head_dim != 64 || widest > 32 || kv_mb <= 400);
+  if (tile_bf16 && g.head_dim != 256)
+    lay->tile_spread = tile_narrow || kv_mb <= (g.head_dim != 64 ? 140 : widest <= 32 ? 65 : 45);
+  else if (g.kv_dtype == PS_F32 && g.q_dtype == PS_F32 && g.head_dim == 64)
+    lay->tile_spread = kv_mb <= 400 || (widest > 32 && 2 * wide_group_tokens * g.num_kv_heads >= total);
+  else
+    lay->tile_spread = true;   // (there is no other form)
   // The tile kernel (PS_VARIANT_WAVE, blocks of 16 k tokens) has a workgroup per item.  Heads of up to 128 with up to 16 rows
   // a wave leave room for two and more of them per compute unit: half a compute unit's share (measured, chunks of 1 / 0.5 / 0.25
   // of it: 36 float32 requests on 12 contexts of 512 to 4096 tokens 47.9 / 44.7 / 48.7 us, 72 bf16 requests with 64-wide
@@ -537,9 +543,9 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // us, with e4m3 43.3 / 39.1, 52.7 / 46.5, 89.7 / 88.3; 256-wide heads 168 / 158, 201 / 193, 296 / 311), since they end a shorter
   // launch (64-wide heads, 24 contexts of 1024 to 6144 tokens under four models 42.8 / 48.0, 48.7 / 55.0, 62.8 / 77.6, 90 of 300 to
   // 1500 with sixteen rows 37.4 / 40.5, 40.4 / 44.6, 55.8 / 56.2; though 12 of 500 to 3000 under eight 30.4 / 25.4, 36.5 / 29.0).
-  // Half as long where the private items are not many more than the resident workgroups, which would have one each and be done
-  // sooner (256-wide heads, without / 64 / 128 / 256: float32, 72 requests with up to 145 on 24 contexts of 533 to 2132 tokens 70.2 /
-  // 68.2 / 81.2, bf16, 71 with up to 188 on 18 46.1 / 45.6 / 44.8 / 48.3).
+  // Half as long with 256-wide heads where the private items are not many more than the resident workgroups, which would have one
+  // each and be done sooner (without / 64 / 128 / 256: float32, 72 requests with up to 145 on 24 contexts of 533 to 2132 tokens 70.2 /
+  // 68.2 / 81.2, bf16, 71 with up to 188 on 18 46.1 / 45.6 / 44.8 / 48.3; but 64-wide heads, the 72 with up to 256 40.0 / 38.8).
   lay->solo_limit = 0;
   {
     const int rows = std::max(group, lay->max_rows_prefix);
@@ -548,7 +554,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
         int64_t(prefix_items.size() + suffix_items.size()) > 2 * int64_t(num_cus) * resident) {
       const bool many = g.q_dtype == PS_BF16 && int64_t(suffix_items.size()) >= 4 * int64_t(num_cus) * resident;
       lay->solo_limit = g.kv_dtype == PS_F32 ? kPsSoloTokensTile / 2 : !many ? kPsSoloTokensTile : g.head_dim == 64 ? 1024 : 512;
-      if (3 * int64_t(suffix_items.size()) < 4 * int64_t(num_cus) * resident) lay->solo_limit /= 2;
+      if (g.head_dim == 256 && 3 * int64_t(suffix_items.size()) < 4 * int64_t(num_cus) * resident) lay->solo_limit /= 2;
     }
   }
   lay->num_prefix_items = int32_t(prefix_items.size());

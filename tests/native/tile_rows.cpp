@@ -6,17 +6,18 @@
 
 #include "ps_internal.h"
 
-static int check(int32_t head_dim, int32_t q, int32_t kv, int32_t requests, int64_t megabytes, bool want_spread) {
+static int check(int32_t head_dim, int32_t q, int32_t kv, int32_t requests, int64_t megabytes, bool want_spread, double share = 1) {
   const int64_t tile = int64_t(16) * head_dim, bytes = kv == PS_F32 ? 4 : kv == PS_BF16 ? 2 : 1;
   ps_geometry g{32, 8, head_dim, 16, q, kv, 16 * tile, 2 * tile, tile, head_dim};
-  const int32_t tokens = int32_t(megabytes * 1000000 / (2 * 8 * head_dim * bytes));
-  std::vector<int32_t> prompt(size_t(requests), 0), model, suffix(size_t(requests), 0);
+  const double all = double(megabytes) * 1e6 / double(2 * 8 * head_dim * bytes);   // tokens, `share` of them in the context
+  const int32_t tokens = int32_t(all * share);
+  std::vector<int32_t> prompt(size_t(requests), 0), model, suffix(size_t(requests), int32_t(all * (1 - share) / requests));
   for (int32_t r = 0; r < requests; ++r) model.push_back(r);
   ps_pool* pool = nullptr;
   ps_layout* lay = nullptr;
   ps_plan_options opt{};
   opt.prefix_variant = opt.suffix_variant = PS_VARIANT_WAVE;
-  bool ok = ps_pool_create(tokens / 16 + 1, nullptr, &pool) == PS_OK &&
+  bool ok = ps_pool_create(int32_t(all / 16) + requests + 2, nullptr, &pool) == PS_OK &&
             ps_kv_layout(pool, &g, 1, &tokens, requests, prompt.data(), model.data(), suffix.data(), &lay) == PS_OK &&
             ps_layout_replan(lay, &opt) == PS_OK;
   ok = ok && lay->tile_spread == want_spread;
@@ -41,6 +42,11 @@ int main() {
           }
     }
   for (int32_t d : {64, 128}) bad += check(d, PS_BF16, PS_BF16, 4, 1500, true);   // 16 rows
+  // private segments beside the group
+  bad += check(64, PS_BF16, PS_BF16, 8, 300, true, 0.3) + check(64, PS_BF16, PS_BF16, 8, 300, false, 0.36);
+  bad += check(128, PS_BF16, PS_BF16, 16, 600, true, 0.3) + check(128, PS_BF16, PS_BF16, 16, 600, false, 0.36);
+  bad += check(64, PS_F32, PS_F32, 8, 600, false, 0.2) + check(64, PS_F32, PS_F32, 16, 600, false, 0.4) + check(64, PS_F32, PS_F32, 16, 600, true, 0.6);
+  bad += check(64, PS_F32, PS_F32, 8, 300, true, 0.2) + check(64, PS_BF16, PS_F32, 8, 300, true, 0.4);
   if (bad) return 1;
   std::puts("ok");
   return 0;
