@@ -65,8 +65,8 @@ struct KvWriteParams {
 // store; `ppt` pieces a tile.  HBM-bound; with a wave per tile a batch of a few hundred larger blocks left most of the chip
 // idle (25 contexts of 3130 tokens in blocks of 32, two launches: 36.3 -> 34.1 us).  The four loads of a small launch stand without
 // branches: a chunk past the tile's end reads the last one again, which costs less than the wait that a branch leaves behind each
-// (one context of 10366 tokens in blocks of 16: 15.0 -> 12.9 us).  PACED: a large one keeps them, HBM
-// bounds it anyway and takes shorter bursts better (a GB in blocks of 64: 90.7 us, without 91.5; in blocks of 16 209.7 / 210.3).
+// (one context of 10366 tokens in blocks of 16: 15.0 -> 13.2 us).  PACED: a large one keeps them, HBM bounds it anyway and takes
+// shorter bursts better (43 contexts in blocks of 64 90.7 us, without 91.5; 134 thousand pieces 209.7 / 210.3).
 template <typename T, bool PACED>
 __global__ __launch_bounds__(256) void ingest_copy_kernel(KvWriteParams p, const T* __restrict__ src_k,
                                                           const T* __restrict__ src_v, int64_t src_s_tok,
@@ -81,21 +81,35 @@ __global__ __launch_bounds__(256) void ingest_copy_kernel(KvWriteParams p, const
   const int h = int((tile >> 1) % uint32_t(p.num_kv_heads));
   const int e = p.ent_order[entry0 + int((tile >> 1) / uint32_t(p.num_kv_heads))];
   // a block adopted from another layout has no valid tokens here: its contents are already there
-  const int chunks = max(0, p.ent_valid[e]) * cpt;
+  const int valid = max(0, p.ent_valid[e]), chunks = valid * cpt;
   const int c0 = int(piece - uint64_t(tile) * ppt) * 256 + lane;
   const T* src = (which ? src_v : src_k) + int64_t(p.ent_tok0[e]) * src_s_tok + int64_t(h) * src_s_head;
   T* dst = static_cast<T*>(p.kv) + int64_t(p.blk[e]) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
   if (c0 - lane >= chunks) return;
+  // (rows of a power of two of chunks: the lane keeps its column from chunk to chunk, which saves the divisions in front of the loads;
+  // the context above 13.3 -> 12.9 us, 100 thousand pieces of float32 136.0 -> 134.5)
+  const int tok0 = c0 / cpt, col0 = c0 - tok0 * cpt, tok_step = 64 / cpt;
+  const bool same_column = 64 % cpt == 0;
   u32x4 v[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = PACED ? c0 + 64 * u : min(c0 + 64 * u, chunks - 1);
-    if (!PACED || c < chunks) v[u] = stream_load(reinterpret_cast<const u32x4*>(src + int64_t(c / cpt) * src_s_tok + (c % cpt) * kVec));
+    int tok = PACED ? tok0 + u * tok_step : min(tok0 + u * tok_step, valid - 1), col = col0;
+    if (!same_column) {
+      tok = c / cpt;
+      col = c % cpt;
+    }
+    if (!PACED || c < chunks) v[u] = stream_load(reinterpret_cast<const u32x4*>(src + int64_t(tok) * src_s_tok + col * kVec));
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = c0 + 64 * u;
-    if (c < chunks) stream_store(reinterpret_cast<u32x4*>(dst + int64_t(c / cpt) * p.s_tok + (c % cpt) * kVec), v[u]);
+    int tok = tok0 + u * tok_step, col = col0;
+    if (!same_column) {
+      tok = c / cpt;
+      col = c % cpt;
+    }
+    if (c < chunks) stream_store(reinterpret_cast<u32x4*>(dst + int64_t(tok) * p.s_tok + col * kVec), v[u]);
   }
 }
 

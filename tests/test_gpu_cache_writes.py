@@ -47,12 +47,13 @@ def test_append_e4m3(d, block, heads, aligned):
 
 
 # blocks of several pieces, of a piece and a bit, of less than one; enough pieces for four a wave, and a count that four do
-# not divide; launches past the size from which an ingest keeps its loads apart; tiles of 2 KiB and less
+# not divide; launches past the size from which an ingest keeps its loads apart; tiles of 2 KiB and less; rows of 9 and 5 chunks
 @pytest.mark.parametrize("geo,tokens", [((16, 2, 128, 64, "bf16", "bf16"), [700, 65]), ((8, 4, 256, 16, "f32", "f32"), [33, 100]),
                                         ((4, 2, 64, 48, "f32", "f32"), [100, 47]), ((4, 2, 64, 16, "bf16", "bf16"), [40, 3]),
                                         ((4, 1, 128, 16, "bf16", "bf16"), [16 * 8193 + 5]), ((8, 4, 128, 64, "bf16", "fp8_e4m3"), [500, 3]),
                                         ((4, 1, 128, 16, "bf16", "bf16"), [16 * 16384 + 5, 33]), ((4, 1, 128, 32, "f32", "f32"), [32 * 4100 + 9]),
-                                        ((8, 4, 128, 16, "bf16", "fp8_e4m3"), [500, 3]), ((8, 4, 64, 16, "bf16", "fp8_e4m3"), [90, 16])])
+                                        ((8, 4, 128, 16, "bf16", "fp8_e4m3"), [500, 3]), ((8, 4, 64, 16, "bf16", "fp8_e4m3"), [90, 16]),
+                                        ((4, 2, 72, 48, "bf16", "bf16"), [100, 3]), ((4, 2, 20, 16, "f32", "f32"), [40, 16])])
 def test_copies_in_pieces(geo, tokens):
     """Ingest, staging out and in: the image holds every block of the tables in order, and comes back into other blocks."""
     from paper_2602_12029_amd import binding as B
