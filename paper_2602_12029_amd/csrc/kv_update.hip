@@ -8,7 +8,7 @@
 // append whose token raises the tile's scale re-encodes the tokens already stored from their stored values:
 // y = (decode(code) * scale_old) / scale_new.
 //
-// Both kernels are plain streaming code: one wavefront per (block, kv head, K|V) tile (ingest) or per
+// Both kernels are plain streaming code: one wavefront per (block, kv head, K|V) tile or 4 KiB of one (ingest) or per
 // (request, kv head, K|V) row (append); HBM-bound, no matrix work.
 #include <algorithm>
 
