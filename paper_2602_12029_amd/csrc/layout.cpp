@@ -64,6 +64,34 @@ bool ps_mfma_supported(const ps_geometry& g) {
 static int64_t shared_cost(bool fours, int64_t tokens) { return fours ? 64 * (round_up(tokens, 32) + 256) + tokens : 64 * (tokens + 64); }
 static int64_t four_cost(int64_t longest, int64_t before) { return 64 * (4 * round_up(longest, 16) + (before ? 256 : 128)) + 4 * longest; }
 
+// What a schedule comes to with its items as long as they are now: its heaviest workgroup, all together, the longest item that a
+// wave takes alone, and what no schedule of these items avoids in some workgroup.
+struct schedule_work { int64_t most = 0, all = 0, longest_solo = 0, unavoidable = 0; };
+static schedule_work work_of(const ps_layout::packed_set& pk, int64_t num_cus) {
+  schedule_work out;
+  auto tokens = [&](int32_t i) { return int64_t(pk.items[size_t(i)].tok_end - pk.items[size_t(i)].tok_begin); };
+  const bool fours = !pk.solo.empty();
+  for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
+    const int32_t last = pk.indptr[w + 1], first_solo = fours ? pk.solo[w] : last;
+    int64_t load = 0;
+    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) {
+      load += shared_cost(fours, tokens(i));
+      out.unavoidable = std::max(out.unavoidable, shared_cost(fours, tokens(i)));
+    }
+    for (int32_t i = first_solo; i < last; i += 4) {
+      int64_t longest = 0;
+      for (int32_t k = i; k < std::min(i + 4, last); ++k) longest = std::max(longest, tokens(k));
+      load += four_cost(longest, load);
+      out.longest_solo = std::max(out.longest_solo, longest);
+      out.unavoidable = std::max(out.unavoidable, shared_cost(fours, longest));
+    }
+    out.most = std::max(out.most, load);
+    out.all += load;
+  }
+  out.unavoidable = std::max(out.unavoidable, ceil_div(out.all, num_cus * pk.occ));
+  return out;
+}
+
 // Whether the private segments have grown so far since the whole step's schedule was packed that it is worth planning anew: its
 // heaviest workgroup has a quarter more to do than any schedule of these items makes unavoidable, and it has got a sixteenth more, or
 // all together a hundredth, since (so that a batch that cannot be had more even is not planned at every step).  16 contexts
@@ -71,28 +99,9 @@ static int64_t four_cost(int64_t longest, int64_t before) { return 64 * (4 * rou
 // 202 / 58 and 281 / 72 us a launch (72, 121 and 159 with four waves on every item); a plan takes some 0.2 ms on the host.
 static bool outgrown(const ps_layout* lay) {
   const ps_layout::packed_set& pk = lay->pk_all;
-  auto tokens = [&](int32_t i) { return int64_t(pk.items[size_t(i)].tok_end - pk.items[size_t(i)].tok_begin); };
-  const bool fours = !pk.solo.empty();
-  int64_t most = 0, sum = 0, unavoidable = 0;
-  for (size_t w = 0; w + 1 < pk.indptr.size(); ++w) {
-    const int32_t last = pk.indptr[w + 1], first_solo = pk.solo.empty() ? last : pk.solo[w];
-    int64_t load = 0;
-    for (int32_t i = pk.indptr[w]; i < first_solo; ++i) {
-      load += shared_cost(fours, tokens(i));
-      unavoidable = std::max(unavoidable, shared_cost(fours, tokens(i)));
-    }
-    for (int32_t i = first_solo; i < last; i += 4) {
-      int64_t longest = 0;
-      for (int32_t k = i; k < std::min(i + 4, last); ++k) longest = std::max(longest, tokens(k));
-      if (longest > kPsSoloTokens * 3 / 2) return true;
-      load += four_cost(longest, load);
-      unavoidable = std::max(unavoidable, shared_cost(fours, longest));
-    }
-    most = std::max(most, load);
-    sum += load;
-  }
-  unavoidable = std::max(unavoidable, ceil_div(sum, int64_t(lay->num_cus) * pk.occ));
-  return 4 * most > 5 * unavoidable && (16 * most >= 17 * pk.heaviest || 100 * sum >= 101 * pk.all);
+  const schedule_work now = work_of(pk, lay->num_cus);
+  if (now.longest_solo > kPsSoloTokens * 3 / 2) return true;
+  return 4 * now.most > 5 * now.unavoidable && (16 * now.most >= 17 * pk.heaviest || 100 * now.all >= 101 * pk.all);
 }
 
 // The tile kernel's short private items, which a wave takes alone, are the last of all; those that have grown past their limit go
@@ -707,8 +716,6 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       if (units[n].first < n_full) ++full[size_t(least.second)];
       const int64_t spent = units[n].first < n_full ? units[n].cost : four_cost(cost(order[size_t(units[n].first)]) - 64, least.first);
       load.push({least.first + spent, least.second});
-      out.heaviest = std::max(out.heaviest, least.first + spent);
-      out.all += spent;
     }
     for (int w = 0; w < num_wg; ++w) fill[size_t(w) + 1] += fill[size_t(w)];
     out.indptr.assign(fill.begin(), fill.end());
@@ -723,6 +730,9 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       for (int i = 0; i < u.count; ++i) out.items[size_t(at++)] = lay->items[size_t(order[size_t(u.first + i)])];
     }
     if (count == 0) out.indptr.assign(1, 0);
+    const schedule_work packed_work = work_of(out, num_cus);
+    out.heaviest = packed_work.most;
+    out.all = packed_work.all;
     return out;
   };
   const int n_items = int(lay->items.size());

@@ -130,6 +130,24 @@ static int run(const Turn& t, int every) {
   return 0;
 }
 
+// Lengths that hardly change: one request appends at a step.  No plan is due, also where the schedule could be more even.
+static int stands_still(const Turn& t, int32_t shortest, int32_t longest) {
+  const int32_t n = t.contexts * t.models;
+  std::vector<int32_t> len, active(size_t(n), 0);
+  for (int32_t r = 0; r < n; ++r) len.push_back(shortest + 37 * r % (longest - shortest + 1));
+  Batch batch;
+  if (!batch.make(t, len, 16)) return fail(t, -1, 0, 0);
+  plans = 0;
+  for (int step = 0; step < 40; ++step) {
+    active[size_t(step % n)] = 1;
+    if (ps_layout_append(batch.pool, batch.lay, active.data(), nullptr) != PS_OK) return fail(t, step, 0, 0);
+    active[size_t(step % n)] = 0;
+  }
+  if (plans <= 4) return 0;
+  std::printf("FAILED: %s: planned %d times in 40 steps of one request each\n", t.what, plans);
+  return 1;
+}
+
 int main() {
   ps_device_num_cus_hook = count_plans;
   const Turn turns[] = {
@@ -143,6 +161,10 @@ int main() {
   };
   int bad = 0;
   for (const Turn& t : turns) bad += run(t, 1) + run(t, 3);
+  bad += stands_still({"69 contexts, three models", 16, 4, PS_BF16, 69, 370, 542, 3}, 114, 280);
+  bad += stands_still({"70 contexts, two models", 16, 4, PS_BF16, 70, 190, 1535, 2}, 180, 425);
+  bad += stands_still({"37 contexts, three models, e4m3", 32, 4, PS_FP8_E4M3, 37, 360, 1885, 3}, 106, 422);
+  bad += stands_still({"30 contexts, two models", 64, 8, PS_BF16, 30, 91, 1026, 2}, 102, 453);
   if (bad) return 1;
   std::puts("ok");
   return 0;
