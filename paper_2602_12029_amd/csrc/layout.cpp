@@ -730,9 +730,11 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       for (int i = 0; i < u.count; ++i) out.items[size_t(at++)] = lay->items[size_t(order[size_t(u.first + i)])];
     }
     if (count == 0) out.indptr.assign(1, 0);
-    const schedule_work packed_work = work_of(out, num_cus);
-    out.heaviest = packed_work.most;
-    out.all = packed_work.all;
+    if (solo_allowed) {   // the whole step's
+      const schedule_work packed_work = work_of(out, num_cus);
+      out.heaviest = packed_work.most;
+      out.all = packed_work.all;
+    }
     return out;
   };
   const int n_items = int(lay->items.size());

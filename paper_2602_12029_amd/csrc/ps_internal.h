@@ -90,7 +90,7 @@ struct ps_layout {
     std::vector<ps_item> items;
     std::vector<int32_t> indptr;
     std::vector<int32_t> solo;       // empty, or per workgroup where its solo items begin (see kPsSoloTokens)
-    int64_t heaviest = 0, all = 0;   // cost of the heaviest workgroup, and of all, when it was packed
+    int64_t heaviest = 0, all = 0;   // cost of the heaviest workgroup, and of all, when it was packed (whole step's only)
     int32_t max_rows = 0, occ = 1;   // occ: workgroups per compute unit (ps_mfma_occupancy)
     bool stream = true;
   };
