@@ -7,22 +7,31 @@
 //
 // One workgroup of eight waves takes one work item: a token range of one context and KV head, and up to 256 query
 // rows that see into it (four waves and 128 rows where the planner finds that enough, each then fetching two eighths of
-// a tile).  The rows are split over the waves, 32 each (the query rows resident in registers as MFMA
+// a tile, in a loop of its own: a wave alone on its SIMD has nobody to take turns with, and there the eight-wave loop is 6 to 13 %
+// slower).  The rows are split over the waves, 32 each (the query rows resident in registers as MFMA
 // B operands), and every wave walks the token range.  Two waves share a SIMD, so that the vector work of one
 // (exponentials, conversions) runs under the matrix instructions of the other.
 //
 // The products are v_mfma_f32_32x32x16_bf16: 32 tokens x 32 rows per instruction.  On this chip it keeps the matrix
 // core busy for 32 cycles and the SIMD's vector port for 8 of them, so six plain vector instructions fit into its
 // shadow, where the 16x16x32 form (16 cycles, 8 of them on the port) leaves room for two: the same flops take half
-// the issue slots, and issue slots are what this kernel runs out of.
+// the issue slots.
 //
 // K and V reach the waves through LDS, as ready-made A operands: per 32-token tile the eight waves fetch one eighth
 // of it each (K straight in operand layout; V as pairs of token rows, transposed inside the lane with one byte
-// permute per operand register; e4m3 codes converted to bf16 once), write it to a ring of three stages of one or two
-// tiles, and after the barrier that ends a stage every wave reads the 8 K and 8 V operands of the tile back, 16 bytes per lane and operand, each
-// lane exactly the slot of its own lane index (no bank conflicts).  A tile is thus fetched, transposed and
-// converted once per 256 rows.  Global loads run four (six) tiles ahead of the products (two tiles in registers, the
-// others in LDS), and a tile's K operands are requested from the ring while the tile before it is multiplied.
+// permute per operand register; e4m3 codes converted to bf16 once), write it to a ring of four tiles, and every wave reads the
+// 8 K and 8 V operands of a tile back, 16 bytes per lane and operand, each lane exactly the slot of its own lane index (no bank
+// conflicts).  A tile is thus fetched, transposed and converted once per 256 rows.  Global loads run five tiles ahead of the
+// products (two tiles in registers, the others in LDS).
+//
+// Bound: power.  The chip holds 1.6 to 1.9 GHz here (2.4 without matrix work), and what takes cycles out of a tile gives some of
+// them back in clock.  What the loop is built for is thus fewer cycles and fewer instructions a tile, in this order:
+// the two waves of a SIMD take turns at the matrix core (see the loop), nothing but the softmax stands between their turns, and
+// addresses are a scalar base and a 32-bit lane offset.  Per tile and pair of waves, before / now: 1726 / 1450 cycles, and 138 /
+// 127 instructions a wave (bf16), 155 / 150 (e4m3).  32 contexts of 4096 tokens with 64 to 256 new ones, 32 heads, bf16: 449 -> 417 us;
+// 64 of 8192, 64 heads, e4m3: 3031 -> 2800; 17 of 5626 to 11253, 32 heads, e4m3: 230 -> 197; short contexts, whose items are
+// mostly their start and their states, alike (22 of 65 to 130, 62 to 251 new ones: 107 / 108).  With half the operand reads left out
+// (a timing build) it would be another 3 %, which is what two row tiles a wave could gain.
 //
 // Per wave and tile: S^T = K Q^T (A = K: lane (m, g) holds elements 16 st + 8 g .. + 7 of token m for k-step st; B =
 // Q^T likewise for query row n), whose result leaves lane (n, g) with the scores of row n against tokens
@@ -48,6 +57,8 @@ constexpr int kTile = kTileTokens;
 constexpr float kLazy = kLazyRescale;
 constexpr float kLazyTop = 256.f;   // 2^kLazy
 static_assert(kLazyRescale == 8.f, "kLazyTop is 2^kLazyRescale");
+constexpr int kLdsDone = 0xc07f;     // s_waitcnt: LDS and scalar loads to zero (or to n: | n << 8), the other counters as they are
+constexpr int kScalarMayPass = 4;    // sched_barrier: only scalar instructions
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
@@ -67,14 +78,15 @@ __device__ __forceinline__ int wave_max(int x) {
 
 }  // namespace
 
-// TPB: tiles per ring stage, and per barrier.  W: waves, eight or four.
-template <int KVT, int TPB, int W>
+// W: waves, eight or four.
+template <int KVT, int W>
 __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams p, const ps_item* __restrict__ items) {
-  constexpr int kStages = 3 * TPB;
+  constexpr int kStages = W == 8 ? 4 : 3;   // tiles of the ring
   __shared__ u32x4 sm_k[kStages][8][64];   // [stage][k-step][lane]: K as that lane's A operand
   __shared__ u32x4 sm_v[kStages][8][64];   // [stage][2 * column class + 16-token step][lane]: V^T as that lane's A operand
   __shared__ f32x4 sm_sc[kStages][2];      // e4m3: [stage][block] = (score scale in log2 units, log2 of the V scale, 1 / V scale, -)
   __shared__ int sm_see[W];
+  __shared__ int sm_slot[W][kRowsPerWave];   // where the rows' states go, read ahead: first slot of the request, ~ of it where that is the only one
   constexpr int kShares = 8 / W;   // eighths of a tile a wave fetches: one, or the same place of both 16-token blocks
   const ps_item* it = items + blockIdx.x;
   const int blk_off = __builtin_amdgcn_readfirstlane(it->blk_off);
@@ -98,7 +110,7 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
   const bool has_rows = rows > row_base;   // a wave without rows only fetches
   const float neg_inf = -__builtin_inff();
 
-  // ---- addressing: block base in SGPRs (a buffer descriptor per 16-token block), loop-invariant lane offsets
+  // ---- addressing: block base in SGPRs, loop-invariant lane offsets
   const int sub_shift = __builtin_ctz(unsigned(p.block_size >> 4));
   const int sub_mask = (p.block_size >> 4) - 1;
   constexpr int kEsz = KVT == PS_BF16 ? 2 : 1;
@@ -108,9 +120,8 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
   const uint32_t blk_bytes = uint32_t(p.s_block * kEsz);
   const int sub_bytes = 16 * tok_bytes;
   const int sub0 = tok_begin >> 4;
-  int sub_end = (tok_end + 15) >> 4;   // (narrowed below to what some row of the workgroup sees)
   // What this wave fetches of every tile, all of it from one 16-token block (fblk) so that one block id and one
-  // buffer descriptor per tile do.  K: token n of the block, elements 32 kst + 8 kg .. + 7 -- that is lane
+  // address per tile do.  K: token n of the block, elements 32 kst + 8 kg .. + 7 -- that is lane
   // (16 fblk + n, kg % 2) of the operand of k-step 2 kst + kg / 2.  V: the pair of token rows (vrow, vrow + 1), columns
   // 8 n + 4 (kg % 2) + x, x = 0 .. 3 -- the pair is register wave % 4 of lane (n + 16 (kg % 2), kg / 2) = this very
   // lane in the operand of column class x and step fblk; the operand's row lane % 32 is thus column
@@ -127,15 +138,18 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const const_i32_ptr blk_seg = (const_i32_ptr)(p.blk + blk_off);
 
-  struct TileIds { int id[kShares]; };   // of this wave's block(s) of the tile
-  auto fetch_ids = [&](int k) __attribute__((always_inline)) {   // wave-uniform
-    // no branch around this load (the index is clamped into the range instead), so that the counting of
-    // outstanding loads in the streaming loop stays exact; a block past the range is never fetched from
-    TileIds r;
+  // Where this wave's block(s) of a tile lie: the physical block, and the byte offset of the 16 tokens in it.  The index is
+  // clamped into the range (last_sub), so that nothing here branches around a load: a tile past the range repeats its last block,
+  // which is never multiplied or masked out.
+  struct Place { int id[kShares], off[kShares]; };
+  int last_sub = max(sub0, ((tok_end + 15) >> 4) - 1);   // (narrowed below to what some row of the workgroup sees)
+  auto locate = [&](int k) __attribute__((always_inline)) {   // wave-uniform
+    Place r;
 #pragma unroll
     for (int s = 0; s < kShares; ++s) {
-      const int sub = max(sub0, min(sub0 + 2 * k + fblk(s), sub_end - 1));
-      r.id[s] = blk_seg[sub >> sub_shift];
+      const int sub = min(sub0 + 2 * k + fblk(s), last_sub);
+      r.id[s] = *(const_i32_ptr)((const __attribute__((address_space(4))) char*)blk_seg + (uint32_t(sub >> sub_shift) << 2));
+      r.off[s] = (sub & sub_mask) * sub_bytes;
     }
     return r;
   };
@@ -145,38 +159,28 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
     std::conditional_t<KVT == PS_BF16, u32x2, uint32_t> v[kShares][2];   // 4 columns of two token rows
     f32x2 sc[kShares];                                                   // e4m3: K and V scale of the block
   };
-  auto fetch = [&](Fetched& f, const TileIds& ids, int k) __attribute__((always_inline)) {
+  auto fetch = [&](Fetched& f, const Place& pl) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < kShares; ++s) {
-      const int sub = sub0 + 2 * k + fblk(s);
-      const bool valid = sub < sub_end;   // a block past the range gets a zero-sized descriptor: zeros, no traffic
-      const uint64_t addr = uint64_t(head_base) + uint64_t(uint32_t(ids.id[s])) * blk_bytes + uint32_t((sub & sub_mask) * sub_bytes);
-      const __amdgpu_buffer_rsrc_t rs =
-          __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(addr), 0, valid ? 0x7fffffff : 0, 0x00020000);
-      if constexpr (KVT == PS_BF16) {
-        f.k[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_lane_off, 0, 0);
-        f.v[s][0] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, 0, 0);
-        f.v[s][1] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_lane_off, tok_bytes, 0);
-      } else {
-        f.k[s] = __builtin_amdgcn_raw_buffer_load_b64(rs, k_lane_off, 0, 0);
-        f.v[s][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, 0, 0);
-        f.v[s][1] = __builtin_amdgcn_raw_buffer_load_b32(rs, v_lane_off, tok_bytes, 0);
-        // (the block id is clamped into the range, so the scales of a tile past it are some block's: never used)
-        f.sc[s] = *reinterpret_cast<const f32x2*>(p.scales + (int64_t(ids.id[s]) * p.num_kv_heads + kv_head) * 2);
-      }
+      typedef const __attribute__((address_space(1))) char* global_ptr;
+      const global_ptr at = (global_ptr)(uint64_t(head_base) + uint64_t(uint32_t(pl.id[s])) * blk_bytes + uint32_t(pl.off[s]));
+      typedef std::remove_reference_t<decltype(f.k[s])> k_word;
+      typedef std::remove_reference_t<decltype(f.v[s][0])> v_word;
+      f.k[s] = *(const __attribute__((address_space(1))) k_word*)(at + uint32_t(k_lane_off));
+      f.v[s][0] = *(const __attribute__((address_space(1))) v_word*)(at + uint32_t(v_lane_off));
+      f.v[s][1] = *(const __attribute__((address_space(1))) v_word*)(at + uint32_t(v_lane_off + tok_bytes));
+      if constexpr (KVT == PS_FP8_E4M3)
+        f.sc[s] = *(const __attribute__((address_space(1))) f32x2*)((global_ptr)p.scales + (int64_t(pl.id[s]) * p.num_kv_heads + kv_head) * 8);
     }
   };
   // The first two tiles and the block ids of the next two are requested at once, from the item's header alone: what
   // the rows see (request list -> visible lengths) is another two round trips to memory, which these need not wait for.
-  Fetched fa, fb;
-  fetch(fa, fetch_ids(0), 0);
-  fetch(fb, fetch_ids(1), 1);
-  const TileIds ids2 = fetch_ids(2), ids3 = fetch_ids(3);
-  Fetched fc, fd;
-  if constexpr (TPB == 2) {
-    fetch(fc, ids2, 2);
-    fetch(fd, ids3, 3);
-  }
+  Fetched fa, fb, fc;
+  fetch(fa, locate(0));
+  fetch(fb, locate(1));
+  if constexpr (W == 8) fetch(fc, locate(2));
+  constexpr int kAhead = W == 8 ? 3 : 2;   // tiles in the ring or about to be, ahead of the one multiplied
+  const Place at0 = locate(kAhead), at1 = locate(kAhead + 1);
 
   // ---- this lane's query row (row lane % 32 of the wave): request, visible length, and the row itself as the
   // eight B operands of S^T = K Q^T (k-step st, lane group g: elements 16 st + 8 g .. + 7)
@@ -190,12 +194,14 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
     if (row < rows) {
       const int req = p.req_list[req_off + row / G];
       req_of = req;
+      const int first_slot = p.slot_base[req], slots_end = p.slot_base[req + 1];
       lim = limited ? min(tok_end, p.visible[req]) : tok_end;
       const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + (int64_t(req) * p.num_q_heads + kv_head * G + row % G) * kD;
 #pragma unroll
       for (int st = 0; st < 8; ++st) qb[st] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 16 * st + 8 * g));
       lim_hi = lim;
       lim_lo = lim;
+      sm_slot[wave][lane & 31] = slots_end - first_slot == 1 ? ~first_slot : first_slot;
     }
   }
   const int see_end = max(tok_begin, wave_max(lim_hi));   // no row of this wave sees a token at or past this one
@@ -210,12 +216,11 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
   const int n_tiles = has_rows ? (see_end - tok_begin + kTile - 1) / kTile : 0;   // tiles this wave multiplies
   const int n_whole = min(n_tiles, max(0, (see_all - tok_begin) / kTile));   // ... of which these need no per-row limit
 
-  sub_end = (see_end_wg + 15) >> 4;   // blocks past it are not fetched: nobody sees them
+  last_sub = max(sub0, ((see_end_wg + 15) >> 4) - 1);   // blocks past it are not fetched: nobody sees them
 
   // ... and its way into the ring: K as it is (e4m3: converted), V transposed -- register vreg of this lane's slot
   // in the operand of column class x holds column 8 n + 4 (kg % 2) + x of the token rows (vrow, vrow + 1)
-  // ragged_tag: std::true_type = the tile may be the item's last, which can reach past its range
-  auto publish = [&](const Fetched& f, int stage, int k, auto ragged_tag) __attribute__((always_inline)) {
+  auto publish_k = [&](const Fetched& f, int stage) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < kShares; ++s) {
       const int b = fblk(s);
@@ -230,6 +235,13 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
           sm_sc[stage][b] = f32x4{p.scale_log2 * f.sc[s].x, lv, fast_exp2(-lv), 0.f};
         }
       }
+    }
+  };
+  // ragged_tag: std::true_type = the tile may be the item's last, which can reach past its range
+  auto publish_v = [&](const Fetched& f, int stage, int k, auto ragged_tag) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < kShares; ++s) {
+      const int b = fblk(s);
       // slots of tokens past the item's range may hold anything: zero them (their probabilities are zero)
       auto v0 = f.v[s][0], v1 = f.v[s][1];
       if (decltype(ragged_tag)::value && tok_begin + kTile * (k + 1) > tok_end) {   // (only the item's last tile can)
@@ -271,21 +283,13 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
     __builtin_amdgcn_sched_barrier(0);
     return ka;
   };
+  struct Probabilities { bf16x8 b[2]; };
   struct VOperands { u32x4 a[8]; };
-  auto read_v = [&](int stage) __attribute__((always_inline)) {   // the 8 V operands of a stage, requested in one go
+  auto read_v = [&](int stage) __attribute__((always_inline)) {   // the 8 V operands of a stage
     VOperands vt;
 #pragma unroll
     for (int op = 0; op < 8; ++op) vt.a[op] = sm_v[stage][op][lane];
-    __builtin_amdgcn_sched_barrier(0);
     return vt;
-  };
-  // O^T += V^T P^T: the two 16-token steps of the tile, one column class at a time
-  auto pv = [&](const VOperands& vt, const bf16x8 (&pb)[2]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-        acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vt.a[2 * x + ks]), pb[ks], acc[x], 0, 0, 0);
   };
   // raw scores S^T = K Q^T: register r of this lane = its row against token 8 (r / 4) + 4 g + r % 4 of the tile
   // (registers 0 .. 7 the first 16-token block, 8 .. 15 the second)
@@ -297,15 +301,24 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
     for (int st = 0; st < 8; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka.a[st]), qb[st], s, 0, 0, 0);
     return s;
   };
-  // softmax of a tile's scores and its P V products
-  auto finish = [&](f32x16 s, const VOperands& vt, int stage, int k, auto limited_tag) __attribute__((always_inline)) {
+  // softmax of a tile's scores: the probabilities as the operand of P V
+  struct TileScales { f32x4 b[2]; };
+  auto read_sc = [&](int stage) __attribute__((always_inline)) {
+    TileScales r{};
+    if constexpr (KVT == PS_FP8_E4M3) {
+      r.b[0] = sm_sc[stage][0];
+      r.b[1] = sm_sc[stage][1];
+    }
+    return r;
+  };
+  auto softmax = [&](f32x16 s, const TileScales& sc, int k, auto limited_tag) __attribute__((always_inline)) {
     constexpr bool kLimited = decltype(limited_tag)::value;
     const int tok0 = tok_begin + kTile * k;
     float sc_k[2], lvs[2], inv_v[2];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if constexpr (KVT == PS_FP8_E4M3) {
-        const f32x4 q4 = sm_sc[stage][b];
+        const f32x4 q4 = sc.b[b];
         sc_k[b] = q4.x;
         lvs[b] = q4.y;
         inv_v[b] = q4.z;
@@ -378,97 +391,169 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
       }
     }
     l_run += total;
-    bf16x8 pb[2];
+    Probabilities pb;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pb[b][j] = (__bf16)pw[8 * b + j];
-    pv(vt, pb);
+      for (int j = 0; j < 8; ++j) pb.b[b][j] = (__bf16)pw[8 * b + j];
+    return pb;
   };
 
-  // ---- stream the token range.  The ring holds three stages of TPB tiles: in iteration k the wave multiplies tile k (its
-  // K operands already in registers, requested during iteration k - 1), requests the K operands of tile k + 1 (complete
-  // in the ring since the last barrier), publishes its share of tile k + 2 TPB (fetched two iterations earlier) into the
-  // stage the tiles before k's left, requests tile k + 2 TPB + 2 from memory, and, at the end of a stage, meets the others
-  // at the barrier.  The products of a
-  // tile thus start right behind the barrier instead of waiting for operands that all eight waves ask for at once.
-  // No branch surrounds a load, so the counting of outstanding loads stays exact; every wave runs every iteration
-  // (and every barrier), whether it has rows or not.
-  TileIds ids_nxt;   // the block id of the tile fetched next, asked for one iteration ahead
-  if constexpr (TPB == 2) {
-    publish(fa, 0, 0, std::true_type{});
-    fetch(fa, fetch_ids(4), 4);
-    publish(fb, 1, 1, std::true_type{});
-    fetch(fb, fetch_ids(5), 5);
-    publish(fc, 2, 2, std::true_type{});
-    publish(fd, 3, 3, std::true_type{});
-    ids_nxt = fetch_ids(6);
-  } else {
-    publish(fa, 0, 0, std::true_type{});
-    fetch(fa, ids2, 2);
-    publish(fb, 1, 1, std::true_type{});
-    fetch(fb, ids3, 3);
-    ids_nxt = fetch_ids(4);
-  }
+  // ---- stream the token range.  No branch surrounds a load, so that the counting of outstanding loads stays exact; every wave runs
+  // every iteration (and every barrier), whether it has rows or not.  Two tiles per round at least, so that the fetch registers keep
+  // their roles.  Three loops rather than tests inside one (a branch around the products would have the accumulators copied
+  // where its sides meet): the tiles every row of the wave sees whole, then the rest of what the wave sees with the per-row limits
+  // (a tile past it is masked out entirely), then the tiles only other waves need.  Every wave passes the same number of barriers.
+  publish_k(fa, 0);
+  publish_v(fa, 0, 0, std::true_type{});
+  fetch(fa, at0);
+  publish_k(fb, 1);
+  publish_v(fb, 1, 1, std::true_type{});
+  fetch(fb, at1);
+  Place at_nxt = locate(kAhead + 2);   // of the tile fetched next, asked for one iteration ahead
   __syncthreads();
-  int st_cur = 0, st_nxt = 1, st_wr = 2;   // thirds of the ring: the tiles multiplied, the next ones, those written
-  KOperands ka_even, ka_odd;               // K operands of the even / odd tile in flight
-  if (n_tiles > 0) ka_even = read_k(0);
-  // what_tag: std::false_type / std::true_type = multiply without / with the per-row limits; void* = only fetch
-  auto one_tile = [&](int k, auto second_tag, Fetched& f_pub, const KOperands& ka, KOperands& ka_next, auto what_tag,
-                      auto ragged_tag) __attribute__((always_inline)) {
-    constexpr bool kMultiply = !std::is_pointer<decltype(what_tag)>::value;
-    // (the fetching stands in front of the score products in program order and the compiler weaves it into them:
-    // a wave issues in order, so vector work finds room under matrix instructions only between them -- with the
-    // products first and everything else behind a scheduling barrier the kernel is 3-13 % slower)
-    constexpr int kSecond = TPB == 2 ? decltype(second_tag)::value : 0;
-    // (the K operands of the tile after this one, on their way while this one is multiplied)
-    if constexpr (kMultiply) ka_next = read_k(TPB == 2 && !kSecond ? 2 * st_cur + 1 : TPB * st_nxt);
-    publish(f_pub, TPB * st_wr + kSecond, k + 2 * TPB, ragged_tag);
-    fetch(f_pub, ids_nxt, k + 2 * TPB + 2);
-    ids_nxt = fetch_ids(k + 2 * TPB + 3);
-    if constexpr (kMultiply) {
-      const f32x16 s = scores(ka);
-      // the V operands are requested now, all eight, so that they arrive under the softmax (left to itself the
-      // compiler requests each one right before its products, and the wave sits out the LDS latency eight times)
-      const VOperands vt = read_v(TPB * st_cur + kSecond);
-      finish(s, vt, TPB * st_cur + kSecond, k, what_tag);
+  const int n_complete = (tok_end - tok_begin) / kTile;
+  int k = 0;
+  if constexpr (W == 8) {
+    // Eight waves: a wave's work on a tile is two phases of about the same length, and the two waves of a SIMD take turns
+    // in them: while one multiplies, the other has its softmax, and a barrier ends each phase.
+    //   softmax phase k: the probabilities of tile k from its scores, nothing else
+    //   product phase k: P V of tile k and the scores of tile k + 1, sixteen matrix instructions, and in their shadows
+    //     everything else: each operand register is refilled from the ring right behind its product (V of tile k + 1, K of
+    //     tile k + 2), tile k + 3 goes into the ring and tile k + 5 is requested from memory
+    // Waves 4 .. 7 run one phase behind waves 0 .. 3.  A tile written in product phase k - 3 is complete when the later waves end
+    // that phase, one before the earlier ones read its K in product phase k - 2; its place is taken by tile k + 4 in product phase
+    // k + 1 of the earlier ones, after the later ones had its V in registers for product phase k: a ring of four tiles.
+    // (With everything but the products in the softmax phase that phase is twice as long as the other: 3970 us against 3006 on the
+    // 64 contexts above.  The product phase without its priority: 437 / 460 and 2942 / 3530.)
+    KOperands ka = read_k(0);
+    f32x16 s_cur = scores(ka);
+    ka = read_k(1);
+    VOperands vt = read_v(0);
+    TileScales sc = read_sc(0);
+    publish_k(fc, 2);
+    publish_v(fc, 2, 2, std::true_type{});
+    const bool second = wave >= 4;
+    __builtin_amdgcn_s_waitcnt(kLdsDone);   // (the first barrier of the loop does not wait for the writes)
+    if (second) __syncthreads();
+    auto one_tile = [&](int k, auto stage, Fetched& f_pub, auto what_tag, auto ragged_tag) __attribute__((always_inline)) {
+      constexpr bool kMultiply = !std::is_pointer<decltype(what_tag)>::value;
+      Probabilities pb;
+      if constexpr (kMultiply) pb = softmax(s_cur, sc, k, what_tag);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();   // (nothing to wait for: the wave has written nothing since the last one)
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (kMultiply) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int x = i & 3, ks = i >> 2;
+          acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vt.a[2 * x + ks]), pb.b[ks], acc[x], 0, 0, 0);
+          vt.a[2 * x + ks] = sm_v[(stage + 1) & 3][2 * x + ks][lane];
+          if (i == 1) publish_k(f_pub, (stage + 3) & 3);
+          if (i == 2) publish_v(f_pub, (stage + 3) & 3, k + 3, ragged_tag);
+          if (i == 3) {
+            asm volatile("" ::: "memory");   // the writes stand in front of the reads below, at least eight
+            fetch(f_pub, at_nxt);
+          }
+          if (i == 5) at_nxt = locate(k + 6);
+          __builtin_amdgcn_sched_barrier(kScalarMayPass);
+        }
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int st = 0; st < 8; ++st) {
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka.a[st]), qb[st], s, 0, 0, 0);
+          ka.a[st] = sm_k[(stage + 2) & 3][st][lane];
+          if (st == 1) sc = read_sc((stage + 1) & 3);
+          __builtin_amdgcn_sched_barrier(kScalarMayPass);
+        }
+        s_cur = s;
+        __builtin_amdgcn_s_setprio(0);
+        // The wave's writes to the ring are done, the eight reads of K behind them need not be.
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(kLdsDone | 8 << 8);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        publish_k(f_pub, (stage + 3) & 3);
+        publish_v(f_pub, (stage + 3) & 3, k + 3, ragged_tag);
+        fetch(f_pub, at_nxt);
+        at_nxt = locate(k + 6);
+        __syncthreads();
+      }
+    };
+    // (the first loops also stop short of the item's last complete tiles, so that the tiles they write, three ahead, are complete
+    // ones and need no zeroing of rows past the range)
+    const int n_fast = min(n_whole, n_complete - 3);
+    for (; k + 4 <= n_fast; k += 4) {
+      one_tile(k, std::integral_constant<int, 0>{}, fa, std::false_type{}, std::false_type{});
+      one_tile(k + 1, std::integral_constant<int, 1>{}, fb, std::false_type{}, std::false_type{});
+      one_tile(k + 2, std::integral_constant<int, 2>{}, fa, std::false_type{}, std::false_type{});
+      one_tile(k + 3, std::integral_constant<int, 3>{}, fb, std::false_type{}, std::false_type{});
     }
-    if constexpr (TPB == 1 || kSecond) {
+    if (k + 2 <= n_fast) {
+      one_tile(k, std::integral_constant<int, 0>{}, fa, std::false_type{}, std::false_type{});
+      one_tile(k + 1, std::integral_constant<int, 1>{}, fb, std::false_type{}, std::false_type{});
+      k += 2;
+    }
+    for (; k < n_tiles; k += 2) {
+      one_tile(k, k, fa, std::true_type{}, std::true_type{});
+      one_tile(k + 1, k + 1, fb, std::true_type{}, std::true_type{});
+    }
+    for (; k < n_tiles_wg; k += 2) {
+      one_tile(k, k, fa, static_cast<void*>(nullptr), std::true_type{});
+      one_tile(k + 1, k + 1, fb, static_cast<void*>(nullptr), std::true_type{});
+    }
+    if (!second) __syncthreads();
+  } else {
+    // Four waves: in iteration k the wave multiplies tile k (its K operands already in registers, requested during iteration
+    // k - 1), requests the K operands of tile k + 1, writes its shares of tile k + 2 into the ring of three tiles, requests tile
+    // k + 4 from memory, and meets the others at the barrier.
+    int st_cur = 0, st_nxt = 1, st_wr = 2;   // tiles of the ring: the one multiplied, the next one, the one written
+    KOperands ka_even, ka_odd;               // K operands of the even / odd tile in flight
+    if (n_tiles > 0) ka_even = read_k(0);
+    auto one_tile = [&](int k, Fetched& f_pub, const KOperands& ka, KOperands& ka_next, auto what_tag,
+                        auto ragged_tag) __attribute__((always_inline)) {
+      constexpr bool kMultiply = !std::is_pointer<decltype(what_tag)>::value;
+      // (the fetching stands in front of the score products in program order and the compiler weaves it into them)
+      if constexpr (kMultiply) ka_next = read_k(st_nxt);
+      publish_k(f_pub, st_wr);
+      publish_v(f_pub, st_wr, k + 2, ragged_tag);
+      fetch(f_pub, at_nxt);
+      at_nxt = locate(k + 5);
+      if constexpr (kMultiply) {
+        const f32x16 s = scores(ka);
+        // the V operands are requested now, all eight, so that they arrive under the softmax (left to itself the
+        // compiler requests each one right before its products, and the wave sits out the LDS latency eight times)
+        const VOperands vt = read_v(st_cur);
+        __builtin_amdgcn_sched_barrier(0);
+        const Probabilities pb = softmax(s, read_sc(st_cur), k, what_tag);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vt.a[2 * (i & 3) + (i >> 2)]), pb.b[i >> 2], acc[i & 3], 0, 0, 0);
+      }
       const int st_free = st_cur;
       st_cur = st_nxt;
       st_nxt = st_wr;
       st_wr = st_free;
       __syncthreads();
+    };
+    const int n_fast = min(n_whole, n_complete - 2);
+    for (; k + 2 <= n_fast; k += 2) {
+      one_tile(k, fa, ka_even, ka_odd, std::false_type{}, std::false_type{});
+      one_tile(k + 1, fb, ka_odd, ka_even, std::false_type{}, std::false_type{});
     }
-  };
-  // Two tiles per round, so that the fetch and operand registers keep their roles.  Three loops rather than tests
-  // inside one (a branch around the products would have the accumulators copied where its sides meet): the tiles
-  // every row of the wave sees whole, then the rest of what the wave sees with the per-row limits (a tile past it
-  // is masked out entirely), then the tiles only other waves need.  Every wave passes the same number of barriers.
-  // (Measured and dropped, all with parity green: giving the two waves of a SIMD different orders of the steps of a
-  // tile, or different priorities -- whichever phase or wave is favoured, 15-30 % slower than equal priorities;
-  // four-wave workgroups, two per item and per CU, which do not wait for each other but fetch every tile twice: 4 %
-  // slower; the scores of tile k + 1 issued one matrix instruction at a time between the exponentials of tile k: 9 %
-  // slower with the 16x16x32 products, and with the 32x32x16 ones, where the compiler weaves the two by itself, 2 %
-  // faster with bf16 KV and 4 % slower with e4m3 than requesting the K operands a tile ahead, which the registers
-  // do not allow next to it; four waves of 64 rows, one per SIMD, every operand read feeding two matrix instructions:
-  // 18-29 % slower, a wave alone on its SIMD has nobody to cover its waits.)
-  // (the first loop also stops short of the item's last complete tiles, so that the tiles it publishes, up to
-  // 2 TPB + 1 ahead, are complete ones and need no zeroing of rows past the range)
-  const int n_fast = min(n_whole, (tok_end - tok_begin) / kTile - 2 * TPB);
-  int k = 0;
-  for (; k + 2 <= n_fast; k += 2) {
-    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, std::false_type{}, std::false_type{});
-    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, std::false_type{}, std::false_type{});
-  }
-  for (; k < n_tiles; k += 2) {
-    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, std::true_type{}, std::true_type{});
-    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, std::true_type{}, std::true_type{});
-  }
-  for (; k < n_tiles_wg; k += 2) {
-    one_tile(k, std::integral_constant<int, 0>{}, fa, ka_even, ka_odd, static_cast<void*>(nullptr), std::true_type{});
-    one_tile(k + 1, std::integral_constant<int, 1>{}, fb, ka_odd, ka_even, static_cast<void*>(nullptr), std::true_type{});
+    for (; k < n_tiles; k += 2) {
+      one_tile(k, fa, ka_even, ka_odd, std::true_type{}, std::true_type{});
+      one_tile(k + 1, fb, ka_odd, ka_even, std::true_type{}, std::true_type{});
+    }
+    for (; k < n_tiles_wg; k += 2) {
+      one_tile(k, fa, ka_even, ka_odd, static_cast<void*>(nullptr), std::true_type{});
+      one_tile(k + 1, fb, ka_odd, ka_even, static_cast<void*>(nullptr), std::true_type{});
+    }
   }
 
   // ---- one partial state per row, straight from the accumulators: register r of column class x is column
@@ -480,9 +565,9 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
       const float inv = l > 0.f ? 1.f / l : 0.f;
       const int row = row_base + (lane & 31);
       const int h = kv_head * G + row % G;
-      const int first_slot = p.slot_base[req_of];
+      const int slot_entry = sm_slot[wave][lane & 31], first_slot = slot_entry < 0 ? ~slot_entry : slot_entry;
       const float lse = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
-      const bool direct = p.out && p.slot_base[req_of + 1] - first_slot == 1;
+      const bool direct = p.out && slot_entry < 0;
       if (!direct || p.keep_states) {
         const int64_t slot = int64_t(first_slot) + split_local;
         float* state = p.ws_o + (slot * p.num_q_heads + h) * kD + 32 * g;
@@ -524,11 +609,11 @@ int32_t launch_prefill_attention(const AttnParams& p, const ps_geometry& g, cons
     return PS_ERR_UNSUPPORTED;
   const dim3 grid(num_items);
   if (g.kv_dtype == PS_BF16) {
-    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 1, 4>), grid, dim3(256), 0, st, p, items);
-    else hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 2, 8>), grid, dim3(512), 0, st, p, items);
+    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 4>), grid, dim3(256), 0, st, p, items);
+    else hipLaunchKernelGGL((prefill_attention_kernel<PS_BF16, 8>), grid, dim3(512), 0, st, p, items);
   } else if (g.kv_dtype == PS_FP8_E4M3) {
-    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1, 4>), grid, dim3(256), 0, st, p, items);
-    else hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 1, 8>), grid, dim3(512), 0, st, p, items);
+    if (rows <= 128) hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 4>), grid, dim3(256), 0, st, p, items);
+    else hipLaunchKernelGGL((prefill_attention_kernel<PS_FP8_E4M3, 8>), grid, dim3(512), 0, st, p, items);
   }
   else
     return PS_ERR_UNSUPPORTED;

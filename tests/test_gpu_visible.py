@@ -229,3 +229,22 @@ def test_prefill_ring_edges(gpu, kv_dtype, heads, rows):
     assert (most <= 128) if rows == 128 else (128 < most <= 256)
     _run(case, visible, w.name)
     case.close()
+
+
+@pytest.mark.parametrize("heads,rows", [((32, 8), 128), ((64, 8), 256)])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+def test_prefill_tiles_past_the_range_in_large_blocks(gpu, kv_dtype, heads, rows):
+    """A tile past an item's tokens repeats the range's last 16-token block: ranges that end in each quarter of a block of 64,
+    whose slots behind them are poisoned, at every remainder of the four tiles the eight-wave loop takes at a time."""
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(heads[0], heads[1], 128, 64, "bf16", kv_dtype)
+    cached = [16 * k + 1 for k in range(4, 22)]
+    chunk = [24 + (i % 3) * 7 for i in range(len(cached))]
+    w, visible = wl.chunk_prefill_workload("past_" + kv_dtype, geo, cached, chunk, pool_factor=1.2, seed=33)
+    case = gpu(w)
+    case.set_visible(visible)
+    items = B.ps_layout_plan(case.layout, w.num_requests)["items"]
+    most = int(items[(items[:, 7] & 4) != 0][:, 4].max()) * geo.group
+    assert (most <= 128) if rows == 128 else (128 < most <= 256)
+    _run(case, visible, w.name)
+    case.close()
