@@ -503,8 +503,8 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     if (ra) return int64_t(a.tok_end - a.tok_begin) * a.n_req > int64_t(b.tok_end - b.tok_begin) * b.n_req;
     return by_cost(a, b);
   };
-  std::stable_sort(prefix_items.begin(), prefix_items.end(), rs_first);
-  std::stable_sort(suffix_items.begin(), suffix_items.end(), by_cost);
+  if (!std::is_sorted(prefix_items.begin(), prefix_items.end(), rs_first)) std::stable_sort(prefix_items.begin(), prefix_items.end(), rs_first);
+  if (!std::is_sorted(suffix_items.begin(), suffix_items.end(), by_cost)) std::stable_sort(suffix_items.begin(), suffix_items.end(), by_cost);
   lay->num_rowsplit_items = 0;
   for (const ps_item& it : prefix_items) lay->num_rowsplit_items += (it.kind & kPsItemRowSplit) ? 1 : 0;
   if (lay->num_rowsplit_items > 8) {
@@ -667,7 +667,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     const int split = std::min(std::max(lay->num_prefix_items, begin), end) - begin;
     if (!std::is_sorted(order.begin(), order.begin() + split, heavier)) std::stable_sort(order.begin(), order.begin() + split, heavier);
     if (!std::is_sorted(order.begin() + split, order.end(), heavier)) std::stable_sort(order.begin() + split, order.end(), heavier);
-    std::inplace_merge(order.begin(), order.begin() + split, order.end(), heavier);
+    if (split > 0 && split < count) std::inplace_merge(order.begin(), order.begin() + split, order.end(), heavier);
     // Short items go four to a workgroup, one per wave (which fetches up to ps_solo_rows of query rows): the waves then neither
     // share out a few tiles each nor meet to merge them, and a workgroup passes a quarter of the item boundaries.  Only where
     // the items outnumber the workgroups: where each has one, a wave alone takes longer (four models on one context of 2741
@@ -694,28 +694,43 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       return it.tok_end - it.tok_begin <= solo_tokens && it.n_req * group <= ps_solo_rows(out.max_rows);
     };
     if (out.max_rows > 32 && work < int64_t(kPsMfmaMaxChunk) * num_cus * out.occ && 4 * 256 * std::count_if(order.begin(), order.end(), solo) < work) solo_tokens = 0;
-    const int n_full = int(std::stable_partition(order.begin(), order.end(), [&](int i) { return !solo(i); }) - order.begin());
+    const int n_full = solo_tokens == 0 ? count : int(std::stable_partition(order.begin(), order.end(), [&](int i) { return !solo(i); }) - order.begin());
     struct unit { int64_t cost; int first, count; };   // of `order`
     std::vector<unit> units;
     units.reserve(size_t(count));
     for (int n = 0; n < n_full; ++n) units.push_back({shared_cost(n_full < count, cost(order[size_t(n)]) - 64), n, 1});
     for (int n = n_full; n < count; n += 4) units.push_back({four_cost(cost(order[size_t(n)]) - 64, 0), n, std::min(4, count - n)});
     auto heavier_unit = [](const unit& a, const unit& b) { return a.cost > b.cost; };
-    std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
+    if (n_full > 0 && n_full < count) std::inplace_merge(units.begin(), units.begin() + n_full, units.end(), heavier_unit);
     const int num_wg = std::max(1, std::min(int(units.size()), num_cus * out.occ));
-    // least-loaded workgroup first, lowest index on ties: a min-heap of (assigned cost, workgroup)
-    typedef std::pair<int64_t, int> slot;
-    std::priority_queue<slot, std::vector<slot>, std::greater<slot>> load;
-    for (int w = 0; w < num_wg; ++w) load.push({0, w});
+    // Least-loaded workgroup first, lowest index on ties.  As long as there are workgroups without a unit that is the next of them;
+    // from then on the root of a min-heap of (assigned cost, workgroup), whose new load sinks to its place (640 items a step on 512
+    // workgroups: with every unit through a queue the three schedules took 60 % of the plan).
+    typedef unsigned __int128 slot;   // cost above, workgroup below: one comparison, and no branch, for both
+    auto slot_of = [](int64_t assigned, int wg) { return slot(uint64_t(assigned)) << 32 | uint32_t(wg); };
     std::vector<int> wg_of(units.size(), 0), fill(size_t(num_wg) + 1, 0), full(size_t(num_wg), 0);
-    for (size_t n = 0; n < units.size(); ++n) {
-      const slot least = load.top();
-      load.pop();
-      wg_of[n] = least.second;
-      fill[size_t(least.second) + 1] += units[n].count;
-      if (units[n].first < n_full) ++full[size_t(least.second)];
-      const int64_t spent = units[n].first < n_full ? units[n].cost : four_cost(cost(order[size_t(units[n].first)]) - 64, least.first);
-      load.push({least.first + spent, least.second});
+    std::vector<slot> load;
+    load.reserve(size_t(num_wg));
+    auto take = [&](size_t n, int64_t assigned, int wg) {
+      const unit& u = units[n];
+      wg_of[n] = wg;
+      fill[size_t(wg) + 1] += u.count;
+      if (u.first < n_full) ++full[size_t(wg)];
+      return slot_of(assigned + (u.first < n_full ? u.cost : four_cost(cost(order[size_t(u.first)]) - 64, assigned)), wg);
+    };
+    const size_t direct = std::min(units.size(), size_t(num_wg));
+    for (size_t n = 0; n < direct; ++n) load.push_back(take(n, 0, int(n)));
+    if (units.size() > direct) std::make_heap(load.begin(), load.end(), std::greater<slot>());
+    for (size_t n = direct; n < units.size(); ++n) {
+      const slot sinking = take(n, int64_t(uint64_t(load[0] >> 32)), int(uint32_t(load[0])));
+      size_t at = 0;
+      for (size_t child = 1; child < load.size(); child = 2 * at + 1) {
+        child += child + 1 < load.size() && load[child + 1] < load[child];
+        if (load[child] > sinking) break;
+        load[at] = load[child];
+        at = child;
+      }
+      load[at] = sinking;
     }
     for (int w = 0; w < num_wg; ++w) fill[size_t(w) + 1] += fill[size_t(w)];
     out.indptr.assign(fill.begin(), fill.end());
@@ -814,7 +829,7 @@ int32_t ps_blob_build(ps_layout* lay) {
   // place instead of taking a fresh allocation every step)
   const size_t blob_words = size_t(std::max<int64_t>(words, 4));
   if (lay->blob.capacity() < blob_words) lay->blob.reserve(blob_words + blob_words / 4 + 1024);
-  lay->blob.assign(blob_words, 0);
+  lay->blob.resize(blob_words);   // (every word that a kernel reads is written below)
   int32_t* b = lay->blob.data();
   {
     const int32_t B = g.block_size;
