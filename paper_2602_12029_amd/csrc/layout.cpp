@@ -317,15 +317,58 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // Rows an item carries per KV head: up to 64 (four row tiles).  With e4m3 KV a sharing group is cut at 32 rows where
   // the matrix-core kernel runs: the two-tile kernel keeps two workgroups per compute unit and measured 19 % faster
   // on 64-row groups than the four-tile one (bf16 KV the other way round: the four-tile kernel is 9-12 % faster).
-  const bool narrow_items = g.kv_dtype == PS_FP8_E4M3 && resolve(opt.prefix_variant) == PS_VARIANT_MFMA;
-  const int32_t max_req = std::max(1, (narrow_items ? 32 : 64) / group);
+  const bool prefix_mfma = resolve(opt.prefix_variant) == PS_VARIANT_MFMA;
+  const bool narrow_items = g.kv_dtype == PS_FP8_E4M3 && prefix_mfma;
+  int32_t most_rows = narrow_items ? 32 : 64;
+  // Where a batch leaves the chip idle its row groups go out in narrower items: an item is one workgroup, and what bounds a small
+  // launch is that workgroup's time, which the rows make longer -- in the tile kernel a row tile to a wave, so that each wave walks
+  // all of the tokens (four of them share the tokens of a 16-row item), in the persistent kernel all row tiles in every wave, and
+  // above 16 (e4m3: 32) rows only one workgroup on a compute unit.  The K/V is then read once per 16 rows, out of the caches.  64 (e4m3
+  // on the persistent kernel: 32) / 16 rows, us a step: float32, 256-wide heads, 3 contexts of 85 to 171 tokens, 6 to 26 new ones
+  // 42.5 / 18.5; float32, 1 of 262 to 525, 76 rows 25.0 / 12.3; 256-wide, 2 of 264 to 528, 60 rows 21.6 / 12.4; 64-wide, 3 of 94 to
+  // 188, 160 rows 12.0 / 8.8; persistent kernel, 28 query on 4 KV heads, 56 and 30 rows on small contexts 17.0 / 9.9, 17.1 / 10.2, 64 on 8,
+  // 64 rows on 4 15.4 / 9.9, e4m3, 24 rows 13.0 / 11.0.
+  // The line lies where the items of 16 rows, private ones too, still have a compute unit each: 256-wide heads, 256 items 23.5 /
+  // 14.1, 244 16.4 / 13.5, 360 19.6 / 20.6, 364 24.6 / 22.1 (32 rows: 18.5), 432 27.7 / 36.0; 64-wide, 228 12.3 / 9.2, 492 20.2 / 22.1, 526
+  // 19.2 / 21.3; two of them with float32 products of up to 128, which are bound by the matrix cores (272 items 24.0 / 14.1, 352 24.8 /
+  // 16.5, 560 25.3 / 20.4, 608 26.6 / 22.7); in the persistent kernel, where short private ones go four to a workgroup, five to four
+  // (280 items 13.0 / 11.0, 312 13.4 / 11.8, 328 17.1 / 18.6, 424 20.1 / 20.7, 888 18.1 / 20.1).  32 rows by the same line, in the persistent
+  // kernel up to two a compute unit (352 items 20.3 / 16.1, 464 66.2 / 62.4, 552 62.3 / 63.6).
+  // And where the wide groups are few of the tokens (a short root), whatever the size: a launch without them runs the 16-row form
+  // everywhere (19 contexts of 1733 tokens under a root of 1030, 256-wide heads 59.9 / 40.4; 5 of 17613, 64-wide 25.7 / 20.9; e4m3, 13.9 /
+  // 11.8; not float32 of up to 128: 92.4 / 93.5).  Groups of 2 to 8 query heads were measured; a request of 16 rows fills a tile alone.
+  if (opt.prefix_chunk_tokens == 0 && group <= 8 && (prefix_mfma || g.block_size % 16 == 0)) {
+    struct shared_work { int64_t items = 0, tokens = 0; };   // of the shared segments, with items of at most that many rows
+    auto shared_at = [&](int32_t rows) {
+      shared_work w;
+      auto add = [&](int64_t len, int64_t reqs) {
+        if (limited && prefix_mfma && reqs * group > 64) return;   // (the prefill kernel's)
+        int32_t n = 0;
+        chunking(len, prefix_chunk, &n);
+        const int64_t walks = ceil_div(reqs, std::max(1, rows / group)) * g.num_kv_heads;
+        w.items += n * walks;
+        w.tokens += len * walks;
+      };
+      for (int32_t t = 0; t < lay->num_roots; ++t) add(lay->root_len[size_t(t)], lay->root_group_indptr[size_t(t) + 1] - lay->root_group_indptr[size_t(t)]);
+      for (int32_t p = 0; p < P; ++p) add(lay->prefix_len[size_t(p)], lay->group_indptr[size_t(p) + 1] - lay->group_indptr[size_t(p)]);
+      return w;
+    };
+    int64_t own = 0;
+    for (int32_t r = 0; r < R; ++r) own += ceil_div(lay->suffix_len[size_t(r)], suffix_chunk) * g.num_kv_heads;
+    const bool float_products = !prefix_mfma && g.head_dim < 256 && (g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
+    const int64_t room16 = prefix_mfma ? int64_t(num_cus) * 5 / 4 : int64_t(num_cus) * (float_products ? 2 : 1);
+    const int64_t room32 = prefix_mfma ? int64_t(num_cus) * 2 : room16;
+    const shared_work as_is = shared_at(most_rows), at16 = shared_at(16);
+    if (at16.items + own <= room16 || (!float_products && 8 * at16.tokens <= 9 * as_is.tokens)) most_rows = 16;
+    else if (most_rows > 32 && shared_at(32).items + own <= room32) most_rows = 32;
+  }
+  const int32_t max_req = std::max(1, most_rows / group);
   const int32_t total_prefix_blocks = int32_t(lay->prefix_blk.size());
   lay->max_rows_prefix = 0;
   lay->any_masked = false;
   lay->req_list.assign(lay->group_req.begin(), lay->group_req.end());
   for (int32_t r = 0; r < R; ++r) lay->req_list.push_back(r);
   lay->req_list.insert(lay->req_list.end(), lay->root_group_req.begin(), lay->root_group_req.end());
-  const bool prefix_mfma = resolve(opt.prefix_variant) == PS_VARIANT_MFMA;
   // Root segments: read whole by every request below the root (all models of all its prompts), so the sharing group
   // is large.  In a decode batch it goes out in ordinary items of at most 64 rows, packed into the one persistent
   // launch with everything else (the root's K/V is then fetched once per 64 rows, mostly from the last-level cache;

@@ -75,3 +75,24 @@ def test_row_tiles_in_every_wave_of_a_large_batch(dtype, d, heads, group, models
         assert (batch.lse[:, h * group:(h + 1) * group].reshape(-1) - lse).abs().max() <= 2e-5
     B.ps_layout_release(pool, lay)
     B.ps_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("kv,q,d,heads", [("f32", "f32", 64, (4, 2)), ("f32", "f32", 256, (8, 4)), ("bf16", "bf16", 64, (16, 2)),
+                                          ("bf16", "bf16", 256, (16, 4)), ("fp8_e4m3", "bf16", 64, (7, 1)), ("bf16", "f32", 128, (6, 2))])
+def test_small_batches_in_items_of_16_rows(kv, q, d, heads):
+    """Groups of up to 68 rows that a small batch sends out 16 rows at a time: a partly filled last item, and causal chunks whose rows
+    see different lengths."""
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(heads[0], heads[1], d, 16, q, kv)
+    group = heads[0] // heads[1]
+    new = 68 // group
+    lens = [250 + new, 31 + new]
+    w = wl.make_workload("narrow", geo, new, lens, [list(range(new))] * 2, [5, 33] + [0] * (2 * new - 2), pool_factor=1.3, seed=d)
+    case = _case(w)
+    for visible in (None, np.concatenate([np.arange(n - new, n) + 1 for n in lens]).astype(np.int32)):
+        if visible is not None:
+            case.set_visible(visible)
+        items = B.ps_layout_plan(case.layout, w.num_requests)["items"]
+        assert int(items[items[:, 7] & 1 == 0][:, 4].max()) * group <= 16
+        _step(case, visible)
+    case.close()

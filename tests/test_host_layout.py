@@ -845,3 +845,33 @@ def test_default_plans_stay_inside_the_static_workspace_where_coarser_chunks_do(
         _check_plan(w, lay, plan)
         B.ps_layout_release(pool, lay)
         B.ps_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("heads,d,dtype", [((4, 2), 64, "f32"), ((8, 4), 256, "f32"), ((16, 2), 64, "bf16"), ((16, 4), 256, "bf16"),
+                                           ((28, 4), 128, "bf16"), ((32, 8), 128, "bf16"), ((64, 8), 128, "fp8_e4m3")])
+def test_row_groups_of_small_batches_go_out_narrower(heads, d, dtype):
+    """Batches that leave the chip idle: items of at most 16 rows, the same partial states as with wider ones, every range tiled
+    once per row group; batches that fill it, and a chunk size asked for, keep the wide items."""
+    geo = wl.Geometry(heads[0], heads[1], d, 16, "f32" if dtype == "f32" else "bf16", dtype)
+    group, models = heads[0] // heads[1], 11
+    for prefix, narrow in (([40, 200, 333], True), ([3000] * 60, False)):
+        w = wl.make_workload("narrow", geo, models, prefix, [list(range(models))] * len(prefix), [7 * i if i < 6 else 0 for i in range(models * len(prefix))], seed=5)
+        pool, lay, _, _ = _both(w)
+        plans = []
+        for visible in (None, np.maximum(1, w.prefix_len[w.req_prompt] - np.arange(w.num_requests) % 29)):
+            B.ps_layout_set_visible(lay, w.num_requests, visible)
+            plan = B.ps_layout_plan(lay, w.num_requests)
+            _check_plan(w, lay, plan, visible)
+            shared = plan["items"][(plan["items"][:, 7] & 5) == 0]       # (row-split ones are the prefill kernel's)
+            if len(shared):
+                rows = int(shared[:, 4].max()) * group
+                assert rows <= 16 if narrow else rows > 16
+            plans.append(plan)
+        chunk = int(plans[0]["items"][:, 2].max())                       # (whole segments: what the plan chose is at least that)
+        B.ps_layout_set_visible(lay, w.num_requests, None)
+        B.ps_layout_replan(lay, B.plan_options(-(-chunk // 32) * 32, 0))
+        wide = B.ps_layout_plan(lay, w.num_requests)
+        _check_plan(w, lay, wide, None)
+        assert int(wide["items"][wide["items"][:, 7] & 1 == 0][:, 4].max()) * group > 16
+        B.ps_layout_release(pool, lay)
+        B.ps_pool_destroy(pool)
