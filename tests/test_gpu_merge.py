@@ -47,3 +47,42 @@ def test_rounds_of_the_merge(states, q_dtype):
         some = np.isfinite(rl)
         assert np.abs(got_lse[r][some] - rl[some]).max(initial=0.0) <= 1e-5
     case.close()
+
+
+@pytest.mark.parametrize("q_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,heads,states", [
+    (64, 4, [5, 17, 64, 65, 0]), (128, 4, [8, 9, 31, 33, 100]), (256, 4, [4, 5, 16, 17, 40]),   # a workgroup per row, around its rounds
+    (128, 64, [5, 16, 7, 1, 12]), (64, 256, [17, 33, 2, 16, 5])])                                # more rows: a thread per four columns
+def test_rows_of_many_states(d, heads, states, q_dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from gpu_helpers import GpuCase
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(heads, 2, d, 16, q_dtype, q_dtype)
+    w = wl.make_workload("many", geo, 2, [32 * n for n in states], [[0, 1]] * len(states), [0] * (2 * len(states)), seed=6)
+    case = GpuCase(w)
+    case.replan(32, 32, "wave", "wave")
+    o_ws, lse_ws = case.batch.workspace_views()
+    gen = torch.Generator().manual_seed(d + heads)
+    o = torch.randn(o_ws.shape, generator=gen)
+    lse = torch.randn(lse_ws.shape, generator=gen) * 3
+    lse[::5] = float("-inf")          # empty partial states
+    o[::5] = float("nan")             # ... whose values count for nothing
+    o_ws.copy_(o)
+    lse_ws.copy_(lse)
+    case.batch.merge_states()
+    torch.cuda.synchronize()
+    base = B.ps_layout_plan(case.layout, w.num_requests)["slot_base"]
+    assert [int(base[2 * p + 1] - base[2 * p]) for p in range(len(states))] == states
+    got, got_lse = case.batch.out.float().cpu().double().numpy(), case.batch.lse.cpu().double().numpy()
+    for r in range(w.num_requests):
+        s = slice(base[r], base[r + 1])
+        ro, rl = oa.merge_states(torch.nan_to_num(o[s]).double().numpy(), lse[s].double().numpy())
+        if states[r // 2] == 0:
+            ro, rl = np.zeros((heads, d)), np.full(heads, -np.inf)
+        bar = 1e-5 if q_dtype == "f32" else max(1e-5, np.abs(ro).max() * 2.0 ** -8)
+        assert np.abs(got[r] - ro).max() <= bar
+        assert np.array_equal(np.isneginf(got_lse[r]), np.isneginf(rl))
+        some = np.isfinite(rl)
+        assert np.abs(got_lse[r][some] - rl[some]).max(initial=0.0) <= 1e-5
+    case.close()
