@@ -86,7 +86,8 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
   __shared__ u32x4 sm_v[kStages][8][64];   // [stage][2 * column class + 16-token step][lane]: V^T as that lane's A operand
   __shared__ f32x4 sm_sc[kStages][2];      // e4m3: [stage][block] = (score scale in log2 units, log2 of the V scale, 1 / V scale, -)
   __shared__ int sm_see[W];
-  __shared__ int sm_slot[W][kRowsPerWave];   // where the rows' states go, read ahead: first slot of the request, ~ of it where that is the only one
+  struct RowPlace { int64_t state, out; };   // row of the workspace and, for a request's only state, of the output (else -1); -1: no row
+  __shared__ RowPlace sm_place[W][kRowsPerWave];   // looked up ahead
   constexpr int kShares = 8 / W;   // eighths of a tile a wave fetches: one, or the same place of both 16-token blocks
   const ps_item* it = items + blockIdx.x;
   const int blk_off = __builtin_amdgcn_readfirstlane(it->blk_off);
@@ -184,16 +185,16 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
 
   // ---- this lane's query row (row lane % 32 of the wave): request, visible length, and the row itself as the
   // eight B operands of S^T = K Q^T (k-step st, lane group g: elements 16 st + 8 g .. + 7)
-  int req_of = -1, lim = 0;   // a padding row sees nothing
+  int lim = 0;   // a padding row sees nothing
   bf16x8 qb[8];
 #pragma unroll
   for (int st = 0; st < 8; ++st) qb[st] = as_bf16x8(u32x4{0, 0, 0, 0});
   int lim_hi = 0, lim_lo = 0x7fffffff;
   {
     const int row = row_base + (lane & 31);
+    RowPlace place = {-1, -1};
     if (row < rows) {
       const int req = p.req_list[req_off + row / G];
-      req_of = req;
       const int first_slot = p.slot_base[req], slots_end = p.slot_base[req + 1];
       lim = limited ? min(tok_end, p.visible[req]) : tok_end;
       const uint16_t* qrow = static_cast<const uint16_t*>(p.q) + (int64_t(req) * p.num_q_heads + kv_head * G + row % G) * kD;
@@ -201,8 +202,11 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
       for (int st = 0; st < 8; ++st) qb[st] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 16 * st + 8 * g));
       lim_hi = lim;
       lim_lo = lim;
-      sm_slot[wave][lane & 31] = slots_end - first_slot == 1 ? ~first_slot : first_slot;
+      const int h = kv_head * G + row % G;
+      place.state = (int64_t(first_slot) + split_local) * p.num_q_heads + h;
+      if (slots_end - first_slot == 1) place.out = int64_t(req) * p.num_q_heads + h;
     }
+    if (lane < kRowsPerWave) sm_place[wave][lane] = place;
   }
   const int see_end = max(tok_begin, wave_max(lim_hi));   // no row of this wave sees a token at or past this one
   const int see_all = -wave_max(-lim_lo);                 // every row of this wave sees every token before this one
@@ -556,46 +560,69 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
     }
   }
 
-  // ---- one partial state per row, straight from the accumulators: register r of column class x is column
-  // 64 (r / 4 % 2) + 32 g + 8 (r % 4) + 4 (r / 8) + x of this lane's row
+  // ---- one partial state per row: register r of column class x is column
+  // 64 (r / 4 % 2) + 32 g + 8 (r % 4) + 4 (r / 8) + x of this lane's row.  The rows go through the ring, which is free now (8 KiB a
+  // wave, 16-byte pieces at their index xor the row's against bank conflicts), so that a store covers 256 bytes of four rows
+  // instead of 16 bytes of 64 places: 32 contexts of 4096 tokens 426 -> 408 us; where items are a few tiles and mostly their start and
+  // their stores, 22 contexts of 65 to 130 with 62 to 251 new tokens, 64 heads, e4m3 106 -> 84, 11 of 165 to 331 33 -> 26.
   if (has_rows) {
     float l = l_run;
     l += lane_xor(l, 32);
-    if (req_of >= 0) {
-      const float inv = l > 0.f ? 1.f / l : 0.f;
-      const int row = row_base + (lane & 31);
-      const int h = kv_head * G + row % G;
-      const int slot_entry = sm_slot[wave][lane & 31], first_slot = slot_entry < 0 ? ~slot_entry : slot_entry;
-      const float lse = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
-      const bool direct = p.out && slot_entry < 0;
-      if (!direct || p.keep_states) {
-        const int64_t slot = int64_t(first_slot) + split_local;
-        float* state = p.ws_o + (slot * p.num_q_heads + h) * kD + 32 * g;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const float lse = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf;
+    u32x4* const turn = wave < kStages ? &sm_k[wave][0][0] : &sm_v[wave - kStages][0][0];
+    const int my_row = lane & 31;
+    // piece c (of 16) of row r; and what a lane reads back: row 4 i + lane / 16, piece lane % 16
+    auto piece = [&](int r, int c) __attribute__((always_inline)) { return turn + 16 * r + (c ^ (r & 15)); };
+    auto row_at = [&](int i) __attribute__((always_inline)) { return 4 * i + (lane >> 4); };
+    const RowPlace mine = sm_place[wave][my_row];
+    const bool final_row = p.out && mine.out >= 0;
+    if (mine.state >= 0 && g == 0) {
+      if (!final_row || p.keep_states) p.ws_lse[mine.state] = lse;
+      if (final_row && p.out_lse) p.out_lse[mine.out] = lse;
+    }
+    if (__builtin_amdgcn_ballot_w64(mine.state >= 0 && (!final_row || p.keep_states)) != 0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = 8 * (i & 1) + (i >> 1);   // (in the order of the columns)
-          *reinterpret_cast<f32x4*>(state + 64 * ((r >> 2) & 1) + 8 * (r & 3) + 4 * (r >> 3)) =
-              f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]} * inv;
+      for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {   // columns 64 half ..: registers r with r / 4 % 2 == half
+          const int r = 4 * half + 8 * (i >> 2) + (i & 3);
+          *reinterpret_cast<f32x4*>(piece(my_row, 8 * g + 2 * (r & 3) + (r >> 3))) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]} * inv;
         }
-        if (g == 0) p.ws_lse[slot * p.num_q_heads + h] = lse;
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int r = row_at(i);
+          const f32x4 v = *reinterpret_cast<const f32x4*>(piece(r, lane & 15));
+          const RowPlace at = sm_place[wave][r];
+          if (at.state >= 0 && (at.out < 0 || !p.out || p.keep_states))
+            *reinterpret_cast<f32x4*>(p.ws_o + at.state * kD + 64 * half + 4 * (lane & 15)) = v;
+        }
+        wave_lds_order();
       }
-      if (direct) {
-        // The request's only partial state is the result: rounded and stored here as well, 16 bytes per lane and store, so
-        // that no merge has to read it back (32 contexts of 4096 + 64..256 tokens, a step with state and merge / state and
-        // row / row alone 415 / 403 / 383 us; 64 contexts of 8192 tokens, 64 query heads, e4m3 KV 2763 / 2704 / 2641 us).
-        uint16_t* o = static_cast<uint16_t*>(p.out) + (int64_t(req_of) * p.num_q_heads + h) * kD + 32 * g;
-        const bool some = l > 0.f;   // a row that saw nothing is zero
+    }
+    if (__builtin_amdgcn_ballot_w64(final_row) != 0) {
+      // The request's only partial state is the result: rounded and stored here as well, so
+      // that no merge has to read it back (32 contexts of 4096 + 64..256 tokens, a step with state and merge / state and
+      // row / row alone 415 / 403 / 383 us; 64 contexts of 8192 tokens, 64 query heads, e4m3 KV 2763 / 2704 / 2641 us).
+      const bool some = l > 0.f;   // a row that saw nothing is zero
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          bf16x8 w;
+      for (int r = 0; r < 8; ++r) {
+        bf16x8 w;
 #pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            w[x] = (__bf16)(some ? acc[x][r] * inv : 0.f);
-            w[4 + x] = (__bf16)(some ? acc[x][r + 8] * inv : 0.f);
-          }
-          *reinterpret_cast<bf16x8*>(o + 64 * (r >> 2) + 8 * (r & 3)) = w;
+        for (int x = 0; x < 4; ++x) {
+          w[x] = (__bf16)(some ? acc[x][r] * inv : 0.f);
+          w[4 + x] = (__bf16)(some ? acc[x][r + 8] * inv : 0.f);
         }
-        if (p.out_lse && g == 0) p.out_lse[int64_t(req_of) * p.num_q_heads + h] = lse;
+        *reinterpret_cast<bf16x8*>(piece(my_row, 8 * (r >> 2) + 4 * g + (r & 3))) = w;
+      }
+      wave_lds_order();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = row_at(i);
+        const u32x4 v = *piece(r, lane & 15);
+        const RowPlace at = sm_place[wave][r];
+        if (at.out >= 0) *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.out) + at.out * kD + 8 * (lane & 15)) = v;
       }
     }
   }
