@@ -296,6 +296,10 @@ int32_t ps_layout_append(ps_pool* pool, ps_layout* layout, const int32_t* active
  * x / scale.  kv_scales is read and written. */
 int32_t ps_kv_append(const ps_layout* layout, const void* dev_tables, const void* new_k, const void* new_v,
                      void* kv_pool, float* kv_scales, void* stream);
+/* ps_layout_upload_append: ps_layout_upload, then ps_kv_append, on one stream (in one launch where the tables are of a size
+ * that a kernel moves). */
+int32_t ps_layout_upload_append(const ps_layout* layout, void* dev_tables, const void* new_k, const void* new_v,
+                     void* kv_pool, float* kv_scales, void* stream);
 
 /* ps_kv_ingest (device, asynchronous): stores whole segments handed over as contiguous tensors.  which: 0 =
  * every prompt's shared prefix, 1 = every request's private suffix, 2 = every root.  src_k, src_v: device, token-major

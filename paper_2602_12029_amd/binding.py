@@ -27,7 +27,7 @@ EXPORTS = [
     "ps_layout_schedule", "ps_layout_device_bytes", "ps_layout_upload", "ps_layout_upload_wait", "ps_workspace_bytes",
     "ps_workspace_layout",
     "ps_prefix_attention", "ps_suffix_attention", "ps_prefix_suffix_attention", "ps_merge_states", "ps_decode_attention",
-    "ps_layout_lengths", "ps_layout_append", "ps_kv_append", "ps_kv_ingest",
+    "ps_layout_lengths", "ps_layout_append", "ps_kv_append", "ps_layout_upload_append", "ps_kv_ingest",
     "ps_layout_set_visible", "ps_layout_request_list", "ps_kv_layout_tree", "ps_layout_root_tables",
     "ps_kv_layout_adopt", "ps_blocks_needed", "ps_layout_state", "ps_stage_layout", "ps_kv_stage_out", "ps_kv_stage_in", "ps_layout_park",
     "ps_layout_resume", "ps_probe_read", "ps_decode_attention_static",
@@ -38,7 +38,7 @@ EXPORTS = [
 # entry points that enqueue device work or query the HIP runtime (csrc/abi.hip); the rest is host-only (csrc/layout.cpp)
 DEVICE_EXPORTS = {
     "ps_layout_upload", "ps_layout_upload_wait", "ps_prefix_attention", "ps_suffix_attention", "ps_prefix_suffix_attention", "ps_merge_states",
-    "ps_decode_attention", "ps_decode_attention_static", "ps_kv_append", "ps_kv_ingest", "ps_kv_stage_out", "ps_kv_stage_in",
+    "ps_decode_attention", "ps_decode_attention_static", "ps_kv_append", "ps_layout_upload_append", "ps_kv_ingest", "ps_kv_stage_out", "ps_kv_stage_in",
     "ps_probe_read",
     "ps_last_hip_error",
 }
@@ -96,7 +96,7 @@ def _lib():
         if not host_only:
             for name, count in {"ps_layout_upload": 3, "ps_prefix_attention": 7, "ps_suffix_attention": 7,
                                 "ps_prefix_suffix_attention": 7, "ps_merge_states": 6, "ps_decode_attention": 9,
-                                "ps_decode_attention_static": 8, "ps_kv_append": 7}.items():
+                                "ps_decode_attention_static": 8, "ps_kv_append": 7, "ps_layout_upload_append": 7}.items():
                 getattr(lib, name).argtypes = [C.c_void_p] + [C.c_size_t] * (count - 1)
         for name in EXPORTS:
             if not (host_only and name in DEVICE_EXPORTS):
@@ -381,6 +381,10 @@ def ps_decode_attention_static(layout, dev_tables, q, kv_pool, kv_scales, out, o
 
 def ps_kv_append(layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream=0):
     _launch(_lib().ps_kv_append, "ps_kv_append", layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream)
+
+
+def ps_layout_upload_append(layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream=0):
+    _launch(_lib().ps_layout_upload_append, "ps_layout_upload_append", layout, dev_tables, new_k, new_v, kv_pool, kv_scales, stream)
 
 
 def ps_kv_ingest(layout, dev_tables, which: int, src_k, src_v, src_stride_tok: int, src_stride_head: int, kv_pool,

@@ -179,11 +179,17 @@ int32_t check_pass_args(const ps_layout* lay, const void* dev_tables, const void
 
 }  // namespace
 
-extern "C" {
+namespace {
 
-int32_t ps_last_hip_error(void) { return g_last_hip_error; }
+// The tokens of the decode step that the tables are uploaded for; `stored`: they went out with the tables.
+struct StepTokens {
+  const void *k, *v;
+  void* kv;
+  float* scales;
+  bool stored;
+};
 
-int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
+int32_t upload_tables(const ps_layout* lay, void* dev_tables, void* stream, StepTokens* tokens) {
   if (!lay || !dev_tables) return PS_ERR_INVALID_ARG;
   // The tables go through one of the layout's two pinned host buffers, so the copy is truly asynchronous: the
   // call returns once it is enqueued, and the next ps_layout_append may rebuild the tables while it is in flight.
@@ -231,8 +237,10 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
     void* src = nullptr;
     if (int32_t rc = check_hip(hipHostGetDevicePointer(&src, s->buffer[i], 0))) return rc;
     const uint32_t pieces = uint32_t(bytes / 16);
-    hipLaunchKernelGGL(upload_tables_kernel, dim3((pieces + 255) / 256), dim3(256), 0, st, static_cast<const table_words*>(src),
-                       static_cast<table_words*>(dev_tables), pieces);
+    if (tokens) tokens->stored = psdev::launch_upload_append(lay, src, dev_tables, bytes, tokens->k, tokens->v, tokens->kv, tokens->scales, st);
+    if (!tokens || !tokens->stored)
+      hipLaunchKernelGGL(upload_tables_kernel, dim3((pieces + 255) / 256), dim3(256), 0, st, static_cast<const table_words*>(src),
+                         static_cast<table_words*>(dev_tables), pieces);
     if (int32_t rc = check_hip(hipGetLastError())) return rc;
   } else if (int32_t rc = check_hip(hipMemcpyAsync(dev_tables, s->buffer[i], bytes, hipMemcpyHostToDevice, st))) {
     return rc;
@@ -241,6 +249,23 @@ int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) {
   s->in_use[i] = true;
   s->unrecorded = unrecorded;
   return PS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int32_t ps_last_hip_error(void) { return g_last_hip_error; }
+
+int32_t ps_layout_upload(const ps_layout* lay, void* dev_tables, void* stream) { return upload_tables(lay, dev_tables, stream, nullptr); }
+
+int32_t ps_layout_upload_append(const ps_layout* lay, void* dev_tables, const void* new_k, const void* new_v, void* kv_pool,
+                                float* kv_scales, void* stream) {
+  StepTokens tokens{new_k, new_v, kv_pool, kv_scales, false};
+  const bool can_store = lay && !lay->parked && lay->num_requests > 0 && new_k && new_v && kv_pool &&
+                         (lay->geo.kv_dtype != PS_FP8_E4M3 || kv_scales);
+  if (int32_t rc = upload_tables(lay, dev_tables, stream, can_store ? &tokens : nullptr)) return rc;
+  return tokens.stored ? int32_t(PS_OK) : ps_kv_append(lay, dev_tables, new_k, new_v, kv_pool, kv_scales, stream);
 }
 
 int32_t ps_layout_upload_wait(const ps_layout* lay, void* stream) {

@@ -11,6 +11,7 @@
 // Both kernels are plain streaming code: one wavefront per (block, kv head, K|V) tile or 4 KiB of one (ingest) or per
 // (request, kv head, K|V) row (append); HBM-bound, no matrix work.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "launch.h"
@@ -208,16 +209,9 @@ __global__ __launch_bounds__(256) void ingest_e4m3_kernel(KvWriteParams p, const
 
 // ---- append: one wavefront per (request, kv head, K|V) ----------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void append_copy_kernel(KvWriteParams p, const T* __restrict__ new_k,
-                                                          const T* __restrict__ new_v, int num_requests) {
+__device__ __forceinline__ void append_copy_row(const KvWriteParams& p, const T* __restrict__ new_k, const T* __restrict__ new_v, int dest,
+                                                int r, int h, int which) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (row >= int64_t(num_requests) * p.num_kv_heads * 2) return;
-  const int which = int(row & 1);
-  const int h = int((row >> 1) % p.num_kv_heads);
-  const int r = int((row >> 1) / p.num_kv_heads);
-  const int dest = p.dest[r];
-  if (dest < 0) return;
   const int id = dest / p.block_size, slot = dest % p.block_size;
   const T* src = (which ? new_v : new_k) + (int64_t(r) * p.num_kv_heads + h) * p.head_dim;
   T* dst = static_cast<T*>(p.kv) + int64_t(id) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv +
@@ -225,19 +219,23 @@ __global__ __launch_bounds__(256) void append_copy_kernel(KvWriteParams p, const
   for (int c = lane; c < p.head_dim; c += 64) dst[c] = src[c];
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void append_copy_kernel(KvWriteParams p, const T* __restrict__ new_k,
+                                                          const T* __restrict__ new_v, int num_requests) {
+  const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (row >= int64_t(num_requests) * p.num_kv_heads * 2) return;
+  const int r = int((row >> 1) / p.num_kv_heads);
+  const int dest = p.dest[r];
+  if (dest >= 0) append_copy_row(p, new_k, new_v, dest, r, int((row >> 1) % p.num_kv_heads), int(row & 1));
+}
+
 // e4m3 with rows of 2^row_shift eight-element pieces: one wavefront per (request, kv head, K|V), eight elements a lane.  The
 // stored tokens of a tile whose scale has grown are rewritten 64 >> row_shift at a time, and four of those rounds are fetched
 // together: a block of sixteen 128-wide tokens in one round trip (a byte at a time the launch was bound by the chain of those
 // rewrites: 64 requests, eight heads, tokens of changing magnitude 8.5 -> 5.2 us).
-__global__ __launch_bounds__(256) void append_e4m3x8_kernel(KvWriteParams p, const u32x4* __restrict__ new_k,
-                                                            const u32x4* __restrict__ new_v, int row_shift) {
+__device__ __forceinline__ void append_e4m3x8_row(const KvWriteParams& p, const u32x4* __restrict__ new_k, const u32x4* __restrict__ new_v,
+                                                  int row_shift, int dest, int r, int h, int which) {
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x;
-  const int row = int(blockIdx.y) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);   // of the token: (head, K|V)
-  if (row >= 2 * p.num_kv_heads) return;
-  const int dest = p.dest[r];
-  if (dest < 0) return;
-  const int h = row >> 1, which = row & 1;
   const int id = dest / p.block_size, slot = dest % p.block_size;
   uint8_t* tile = static_cast<uint8_t*>(p.kv) + int64_t(id) * p.s_block + int64_t(h) * p.s_head + int64_t(which) * p.s_kv;
   float* scale_ptr = p.scales + (int64_t(id) * p.num_kv_heads + h) * 2 + which;
@@ -287,6 +285,41 @@ __global__ __launch_bounds__(256) void append_e4m3x8_kernel(KvWriteParams p, con
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = x[j] / scale;
     *reinterpret_cast<u32x2*>(tile + int64_t(slot) * p.s_tok + 8 * c) = encode(x);
+  }
+}
+
+__global__ __launch_bounds__(256) void append_e4m3x8_kernel(KvWriteParams p, const u32x4* __restrict__ new_k,
+                                                            const u32x4* __restrict__ new_v, int row_shift) {
+  const int r = blockIdx.x;
+  const int row = int(blockIdx.y) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);   // of the token: (head, K|V)
+  if (row >= 2 * p.num_kv_heads) return;
+  const int dest = p.dest[r];
+  if (dest >= 0) append_e4m3x8_row(p, new_k, new_v, row_shift, dest, r, row >> 1, row & 1);
+}
+
+// The tables on their way to the device and the tokens of the same decode step, which do not wait for them: a workgroup per request
+// reads where its token goes from the pinned buffer, across PCIe like the tables themselves (once a wave: a read is a transaction).
+// Bound: that link and its latency; two launches in a row cost a turn's step a launch on the host and the gap between them (16
+// contexts under four models, a turn of eight steps 520 -> 504 us; 25 of one, five steps 324 -> 294).
+template <int KVT>
+__global__ __launch_bounds__(256) void upload_append_kernel(const u32x4* __restrict__ tables, u32x4* __restrict__ dev_tables, uint32_t pieces,
+                                                            uint32_t upload_wgs, KvWriteParams p, const void* __restrict__ new_k,
+                                                            const void* __restrict__ new_v, int row_shift) {
+  if (blockIdx.x < upload_wgs) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < pieces) dev_tables[i] = tables[i];
+    return;
+  }
+  // (e4m3: a workgroup per four of a token's rows, each a chain of its own where the tile's scale grows; with all rows of a token
+  // in one a turn of twelve steps took 5 % longer than with two launches a step)
+  const int wgs = KVT == PS_FP8_E4M3 ? (2 * p.num_kv_heads + 3) / 4 : 1;
+  const int wg = int(blockIdx.x - upload_wgs), r = wg / wgs, dest = p.dest[r];
+  if (dest < 0) return;
+  for (int row = (wg - r * wgs) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); row < 2 * p.num_kv_heads; row += 4 * wgs) {
+    typedef std::conditional_t<KVT == PS_F32, float, std::conditional_t<KVT == PS_BF16, uint16_t, u32x4>> word;
+    const word *k = static_cast<const word*>(new_k), *v = static_cast<const word*>(new_v);
+    if constexpr (KVT == PS_FP8_E4M3) append_e4m3x8_row(p, k, v, row_shift, dest, r, row >> 1, row & 1);
+    else append_copy_row(p, k, v, dest, r, row >> 1, row & 1);
   }
 }
 
@@ -487,6 +520,41 @@ int32_t launch_kv_ingest(const ps_layout* lay, const void* dev_tables, int which
   return PS_OK;
 }
 
+namespace {
+
+// e4m3: eight elements a lane where a row is a power of two of such pieces and every address a multiple of one (pool
+// strides are multiples of 16 bytes).  The copying formats gain nothing from wider stores: their launch is its dependent reads.
+bool whole_pieces(const ps_layout* lay, const void* new_k, const void* new_v, const void* kv) {
+  const ps_geometry& g = lay->geo;
+  const int pieces = g.head_dim / 8;
+  return g.kv_dtype == PS_FP8_E4M3 && g.head_dim % 8 == 0 && pieces <= 64 && (pieces & (pieces - 1)) == 0 &&
+         (2 * g.num_kv_heads + 3) / 4 <= 65535 && lay->num_requests <= kMaxWorkgroups &&
+         (reinterpret_cast<uintptr_t>(new_k) | reinterpret_cast<uintptr_t>(new_v) | reinterpret_cast<uintptr_t>(kv)) % 16 == 0;
+}
+
+}  // namespace
+
+bool launch_upload_append(const ps_layout* lay, const void* host_tables, void* dev_tables, size_t bytes, const void* new_k,
+                          const void* new_v, void* kv, float* scales, hipStream_t st) {
+  const ps_geometry& g = lay->geo;
+  const uint32_t pieces = uint32_t(bytes / 16), upload_wgs = (pieces + 255) / 256;
+  const int64_t append_wgs = int64_t(lay->num_requests) * (g.kv_dtype == PS_FP8_E4M3 ? (2 * g.num_kv_heads + 3) / 4 : 1);
+  if (append_wgs == 0 || upload_wgs + append_wgs > kMaxWorkgroups) return false;
+  if (g.kv_dtype == PS_FP8_E4M3 && !whole_pieces(lay, new_k, new_v, kv)) return false;
+  KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);
+  p.dest = static_cast<const int32_t*>(host_tables) + lay->off_dest;
+  const dim3 grid{upload_wgs + uint32_t(append_wgs)}, block{256};
+  const auto *from = static_cast<const u32x4*>(host_tables);
+  auto* to = static_cast<u32x4*>(dev_tables);
+  const int row_shift = g.kv_dtype == PS_FP8_E4M3 ? __builtin_ctz(unsigned(g.head_dim / 8)) : 0;
+#define PS_LAUNCH(KVT) hipLaunchKernelGGL((upload_append_kernel<KVT>), grid, block, 0, st, from, to, pieces, upload_wgs, p, new_k, new_v, row_shift)
+  if (g.kv_dtype == PS_F32) PS_LAUNCH(PS_F32);
+  else if (g.kv_dtype == PS_BF16) PS_LAUNCH(PS_BF16);
+  else PS_LAUNCH(PS_FP8_E4M3);
+#undef PS_LAUNCH
+  return true;
+}
+
 int32_t launch_kv_append(const ps_layout* lay, const void* dev_tables, const void* new_k, const void* new_v, void* kv,
                          float* scales, hipStream_t st) {
   const ps_geometry& g = lay->geo;
@@ -494,14 +562,9 @@ int32_t launch_kv_append(const ps_layout* lay, const void* dev_tables, const voi
   const int64_t rows = int64_t(lay->num_requests) * g.num_kv_heads * 2;
   const dim3 grid{unsigned((rows + 3) / 4)}, block{256};
   const KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);
-  // e4m3: eight elements a lane where a row is a power of two of such pieces and every address a multiple of one (pool
-  // strides are multiples of 16 bytes).  The copying formats gain nothing from wider stores: their launch is its dependent reads.
-  const int pieces = g.head_dim / 8, wgs_y = (2 * g.num_kv_heads + 3) / 4;
-  const bool whole = g.kv_dtype == PS_FP8_E4M3 && g.head_dim % 8 == 0 && pieces <= 64 && (pieces & (pieces - 1)) == 0 && wgs_y <= 65535 && lay->num_requests <= kMaxWorkgroups &&
-                     (reinterpret_cast<uintptr_t>(new_k) | reinterpret_cast<uintptr_t>(new_v) | reinterpret_cast<uintptr_t>(kv)) % 16 == 0;
-  if (whole)
-    hipLaunchKernelGGL(append_e4m3x8_kernel, dim3(unsigned(lay->num_requests), unsigned(wgs_y)), block, 0, st, p,
-                       static_cast<const u32x4*>(new_k), static_cast<const u32x4*>(new_v), __builtin_ctz(unsigned(pieces)));
+  if (whole_pieces(lay, new_k, new_v, kv))
+    hipLaunchKernelGGL(append_e4m3x8_kernel, dim3(unsigned(lay->num_requests), unsigned((2 * g.num_kv_heads + 3) / 4)), block, 0, st, p,
+                       static_cast<const u32x4*>(new_k), static_cast<const u32x4*>(new_v), __builtin_ctz(unsigned(g.head_dim / 8)));
   else if (g.kv_dtype == PS_F32)
     hipLaunchKernelGGL(append_copy_kernel<float>, grid, block, 0, st, p, static_cast<const float*>(new_k),
                        static_cast<const float*>(new_v), lay->num_requests);

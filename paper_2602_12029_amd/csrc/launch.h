@@ -29,6 +29,10 @@ int32_t launch_kv_ingest(const ps_layout* lay, const void* dev_tables, int which
                          int64_t src_s_tok, int64_t src_s_head, void* kv, float* scales, hipStream_t st);
 int32_t launch_kv_append(const ps_layout* lay, const void* dev_tables, const void* new_k, const void* new_v, void* kv,
                          float* scales, hipStream_t st);
+// The tables (a multiple of 16 bytes, in pinned memory the device can address; both addresses on a 16-byte boundary) to the device and
+// the append in one launch; false: not this layout or these addresses, nothing is launched.
+bool launch_upload_append(const ps_layout* lay, const void* host_tables, void* dev_tables, size_t bytes, const void* new_k,
+                          const void* new_v, void* kv, float* scales, hipStream_t st);
 // Whole blocks of a layout, in table order, to (to_image) or from a dense staging image; e4m3 scales follow the
 // blocks at scales_offset_bytes.
 int32_t launch_kv_stage(const ps_layout* lay, const void* dev_tables, bool to_image, void* kv, float* scales,

@@ -53,15 +53,19 @@ class DecodeBatch:
         self.workspace = None
         self._sync_plan()
 
-    def _sync_plan(self, wait=True):
+    def _sync_plan(self, wait=True, tokens=None):
         self._home = _stream()               # tables and workspace belong to this stream
         nbytes = B.ps_layout_device_bytes(self.layout)
         self.tables = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        B.ps_layout_upload(self.layout, self.tables.data_ptr(), _stream())
+        self.workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
         self._pending = not wait             # other streams have to wait for the upload on the GPU
+        if tokens is None:
+            B.ps_layout_upload(self.layout, self.tables.data_ptr(), _stream())
+        else:
+            B.ps_layout_upload_append(self.layout, self.tables.data_ptr(), tokens[0].data_ptr(), tokens[1].data_ptr(),
+                                      self.kv.data_ptr(), self._sc(), _stream())
         if wait:
             torch.cuda.current_stream().synchronize()
-        self.workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
 
     def replan(self, options: B.ps_plan_options | None):
         B.ps_layout_replan(self.layout, options)
@@ -117,12 +121,11 @@ class DecodeBatch:
         if torch.cuda.is_current_stream_capturing():
             raise RuntimeError("append_step changes the tables on the host: it cannot be recorded into a graph")
         dest = B.ps_layout_append(pool, self.layout, self.num_requests, active)
-        # No wait on the host for the upload: it is ordered in front of the store below on this stream, and launches of this
+        # No wait on the host for the upload: it is ordered in front of what follows on this stream, and launches of this
         # batch on other streams wait for it there.
-        self._sync_plan(wait=False)
-        assert new_k.is_contiguous() and new_v.is_contiguous()
-        B.ps_kv_append(self.layout, self.tables.data_ptr(), new_k.data_ptr(), new_v.data_ptr(), self.kv.data_ptr(),
-                       self._sc(), self._stream())
+        storable = new_k.is_contiguous() and new_v.is_contiguous()
+        self._sync_plan(wait=False, tokens=(new_k, new_v) if storable else None)
+        assert storable
         return dest
 
     def stage_out(self, image: torch.Tensor):
