@@ -86,3 +86,41 @@ def test_rows_of_many_states(d, heads, states, q_dtype):
         some = np.isfinite(rl)
         assert np.abs(got_lse[r][some] - rl[some]).max(initial=0.0) <= 1e-5
     case.close()
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("heads,states", [(4, [8, 5, 33, 1, 3]), (128, [8, 5, 16, 1, 3]), (256, [17, 33, 2, 16, 4])])   # a workgroup per row; a thread per four columns
+def test_a_state_that_is_not_a_number(d, heads, states):
+    """A log-sum-exp that is not a number makes its row not a number, whichever states stand beside it: finite ones, empty ones, none;
+    the other heads of the request keep their values."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from gpu_helpers import GpuCase
+    from paper_2602_12029_amd import binding as B
+    geo = wl.Geometry(heads, 2, d, 16, "f32", "f32")
+    w = wl.make_workload("nan", geo, 2, [32 * n for n in states], [[0, 1]] * len(states), [0] * (2 * len(states)), seed=8)
+    case = GpuCase(w)
+    case.replan(32, 32, "wave", "wave")
+    o_ws, lse_ws = case.batch.workspace_views()
+    gen = torch.Generator().manual_seed(d + heads)
+    o = torch.randn(o_ws.shape, generator=gen)
+    lse = torch.randn(lse_ws.shape, generator=gen) * 3
+    base = B.ps_layout_plan(case.layout, w.num_requests)["slot_base"]
+    for r in range(w.num_requests):
+        n = int(base[r + 1] - base[r])
+        lse[int(base[r]) + n // 2, 0] = float("nan")       # one of several
+        lse[int(base[r]):int(base[r + 1]), 1] = float("nan")   # all
+        lse[int(base[r]):int(base[r + 1]), 2] = float("-inf")  # the only one that is not empty
+        lse[int(base[r]) + n - 1, 2] = float("nan")
+    o_ws.copy_(o)
+    lse_ws.copy_(lse)
+    case.batch.merge_states()
+    torch.cuda.synchronize()
+    got, got_lse = case.batch.out.cpu(), case.batch.lse.cpu()
+    assert torch.isnan(got[:, :3]).all() and torch.isnan(got_lse[:, :3]).all()
+    for r in range(w.num_requests):
+        s = slice(base[r], base[r + 1])
+        ro, rl = oa.merge_states(o[s, 3:].double().numpy(), lse[s, 3:].double().numpy())
+        assert np.abs(got[r, 3:].double().numpy() - ro).max() <= 1e-5
+        assert np.abs(got_lse[r, 3:].double().numpy() - rl).max() <= 1e-5
+    case.close()
