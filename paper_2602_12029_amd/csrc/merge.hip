@@ -64,13 +64,18 @@ __global__ __launch_bounds__(256) void merge_states_kernel(const int32_t* __rest
       }
     }
     float bm = mx;
-    bool some = false;                     // (fmaxf passes a log-sum-exp that is not a number by; it is no empty state)
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      bm = fmaxf(bm, lse[i]);
-      some |= lse[i] != neg_inf;
+    for (int i = 0; i < BATCH; ++i) bm = fmaxf(bm, lse[i]);
+    if (bm == neg_inf) {                   // nothing but empty states so far, or not a number, which fmaxf passes by
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i)
+        if (lse[i] != lse[i]) mx = lse[i];
+      if (mx != mx) {
+        total = mx;
+        acc = f32x4{mx, mx, mx, mx};
+      }
+      continue;
     }
-    if (!some) continue;                   // nothing but empty states
     const float keep = (mx == neg_inf) ? 0.f : fast_exp2((mx - bm) * kLog2e);
     total *= keep;
     acc *= keep;
@@ -84,10 +89,9 @@ __global__ __launch_bounds__(256) void merge_states_kernel(const int32_t* __rest
     }
     mx = bm;
   }
-  // (the largest state's weight is one: a sum of zero says that there is none)
-  if (total != 0.f) acc *= 1.f / total;
+  if (mx != neg_inf) acc *= 1.f / total;
   store_row<QT>(out, row, head_dim, c4, acc);
-  if (out_lse && c4 == 0) out_lse[row] = (total != 0.f) ? mx + __builtin_amdgcn_logf(total) * kLn2 : neg_inf;
+  if (out_lse && c4 == 0) out_lse[row] = (mx != neg_inf) ? mx + __builtin_amdgcn_logf(total) * kLn2 : neg_inf;
 }
 
 // Rows of many partial states: a workgroup per row, HD / 4 threads to a state and 1024 / HD states at a time; the groups of threads
@@ -120,13 +124,18 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const int32_t* __restri
       }
     }
     float bm = mx;
-    bool some = false;                     // (fmaxf passes a log-sum-exp that is not a number by; it is no empty state)
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      bm = fmaxf(bm, lse[i]);
-      some |= lse[i] != neg_inf;
+    for (int i = 0; i < kBatch; ++i) bm = fmaxf(bm, lse[i]);
+    if (bm == neg_inf) {                   // nothing but empty states so far, or not a number, which fmaxf passes by
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)
+        if (lse[i] != lse[i]) mx = lse[i];
+      if (mx != mx) {
+        total = mx;
+        acc = f32x4{mx, mx, mx, mx};
+      }
+      continue;
     }
-    if (!some) continue;                   // nothing but empty states
     const float keep = (mx == neg_inf) ? 0.f : fast_exp2((mx - bm) * kLog2e);
     total *= keep;
     acc *= keep;
@@ -150,19 +159,26 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const int32_t* __restri
   float top = neg_inf;
 #pragma unroll
   for (int g = 0; g < kGroups; ++g) top = fmaxf(top, sm_mx[g]);
+  if (top == neg_inf) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g)
+      if (sm_mx[g] != neg_inf) top = sm_mx[g];   // not a number
+  }
   float sum = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  if (top != neg_inf) {
 #pragma unroll
-  for (int g = 0; g < kGroups; ++g) {
-    if (sm_total[g] != 0.f) {              // (a group of empty states alone has a sum of zero)
-      const float w = fast_exp2((sm_mx[g] - top) * kLog2e);
-      sum += w * sm_total[g];
-      o += w * sm_acc[g][c4];
+    for (int g = 0; g < kGroups; ++g) {
+      if (sm_mx[g] != neg_inf) {
+        const float w = fast_exp2((sm_mx[g] - top) * kLog2e);
+        sum += w * sm_total[g];
+        o += w * sm_acc[g][c4];
+      }
     }
+    o *= 1.f / sum;
   }
-  if (sum != 0.f) o *= 1.f / sum;
   store_row<QT>(out, int64_t(r) * num_q_heads + h, HD, c4, o);
-  if (out_lse && c4 == 0) out_lse[int64_t(r) * num_q_heads + h] = (sum != 0.f) ? top + __builtin_amdgcn_logf(sum) * kLn2 : neg_inf;
+  if (out_lse && c4 == 0) out_lse[int64_t(r) * num_q_heads + h] = (top != neg_inf) ? top + __builtin_amdgcn_logf(sum) * kLn2 : neg_inf;
 }
 
 int32_t launch_merge(const int32_t* slot_base, const int32_t* requests, const float* ws_o, const float* ws_lse, void* out,
