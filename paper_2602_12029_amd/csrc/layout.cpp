@@ -314,96 +314,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   lay->suffix_chunk_size.assign(size_t(R), 0);
   lay->suffix_chunks.assign(size_t(R), 0);
   std::vector<ps_item> prefix_items, suffix_items;
-  // Rows an item carries per KV head: up to 64 (four row tiles).  With e4m3 KV a sharing group is cut at 32 rows where
-  // the matrix-core kernel runs: the two-tile kernel keeps two workgroups per compute unit and measured 19 % faster
-  // on 64-row groups than the four-tile one (bf16 KV the other way round: the four-tile kernel is 9-12 % faster).
   const bool prefix_mfma = resolve(opt.prefix_variant) == PS_VARIANT_MFMA;
-  const bool narrow_items = g.kv_dtype == PS_FP8_E4M3 && prefix_mfma;
-  int32_t most_rows = narrow_items ? 32 : 64;
-  // Where a batch leaves the chip idle its row groups go out in narrower items: an item is one workgroup, and what bounds a small
-  // launch is that workgroup's time, which the rows make longer -- in the tile kernel a row tile to a wave, so that each wave walks
-  // all of the tokens (four of them share the tokens of a 16-row item), in the persistent kernel all row tiles in every wave, and
-  // above 16 (e4m3: 32) rows only one workgroup on a compute unit.  The K/V is then read once per 16 rows, out of the caches.  64 (e4m3
-  // on the persistent kernel: 32) / 16 rows, us a step: float32, 256-wide heads, 3 contexts of 85 to 171 tokens, 6 to 26 new ones
-  // 42.5 / 18.5; float32, 1 of 262 to 525, 76 rows 25.0 / 12.3; 256-wide, 2 of 264 to 528, 60 rows 21.6 / 12.4; 64-wide, 3 of 94 to
-  // 188, 160 rows 12.0 / 8.8; persistent kernel, 28 query on 4 KV heads, 56 and 30 rows on small contexts 17.0 / 9.9, 17.1 / 10.2, 64 on 8,
-  // 64 rows on 4 15.4 / 9.9, e4m3, 24 rows 13.0 / 11.0.
-  // The line lies where the items of 16 rows, private ones too, still have a compute unit each: 256-wide heads, 256 items 23.5 /
-  // 14.1, 244 16.4 / 13.5, 360 19.6 / 20.6, 364 24.6 / 22.1 (32 rows: 18.5), 432 27.7 / 36.0; 64-wide, 228 12.3 / 9.2, 492 20.2 / 22.1, 526
-  // 19.2 / 21.3; two of them with float32 products of up to 128, which are bound by the matrix cores (272 items 24.0 / 14.1, 352 24.8 /
-  // 16.5, 560 25.3 / 20.4, 608 26.6 / 22.7); in the persistent kernel, where short private ones go four to a workgroup, five to four
-  // (280 items 13.0 / 11.0, 312 13.4 / 11.8, 328 17.1 / 18.6, 424 20.1 / 20.7, 888 18.1 / 20.1).  32 rows by the same line, in the persistent
-  // kernel up to two a compute unit (352 items 20.3 / 16.1, 464 66.2 / 62.4, 552 62.3 / 63.6).
-  // And where the wide groups are few of the tokens (a short root), whatever the size: a launch without them runs the 16-row form
-  // everywhere (19 contexts of 1733 tokens under a root of 1030, 256-wide heads 59.9 / 40.4; 5 of 17613, 64-wide 25.7 / 20.9; e4m3, 13.9 /
-  // 11.8; not float32 of up to 128: 92.4 / 93.5).  Groups of 2 to 8 query heads were measured; a request of 16 rows fills a tile alone.
-  if (opt.prefix_chunk_tokens == 0 && group <= 8 && (prefix_mfma || g.block_size % 16 == 0)) {
-    struct shared_work { int64_t items = 0, tokens = 0; };   // of the shared segments, with items of at most that many rows
-    auto shared_at = [&](int32_t rows) {
-      shared_work w;
-      auto add = [&](int64_t len, int64_t reqs) {
-        if (limited && prefix_mfma && reqs * group > 64) return;   // (the prefill kernel's)
-        int32_t n = 0;
-        chunking(len, prefix_chunk, &n);
-        const int64_t walks = ceil_div(reqs, std::max(1, rows / group)) * g.num_kv_heads;
-        w.items += n * walks;
-        w.tokens += len * walks;
-      };
-      for (int32_t t = 0; t < lay->num_roots; ++t) add(lay->root_len[size_t(t)], lay->root_group_indptr[size_t(t) + 1] - lay->root_group_indptr[size_t(t)]);
-      for (int32_t p = 0; p < P; ++p) add(lay->prefix_len[size_t(p)], lay->group_indptr[size_t(p) + 1] - lay->group_indptr[size_t(p)]);
-      return w;
-    };
-    int64_t own = 0;
-    for (int32_t r = 0; r < R; ++r) own += ceil_div(lay->suffix_len[size_t(r)], suffix_chunk) * g.num_kv_heads;
-    const bool float_products = !prefix_mfma && g.head_dim < 256 && (g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
-    const int64_t room16 = prefix_mfma ? int64_t(num_cus) * 5 / 4 : int64_t(num_cus) * (float_products ? 2 : 1);
-    const int64_t room32 = prefix_mfma ? int64_t(num_cus) * 2 : room16;
-    const shared_work as_is = shared_at(most_rows), at16 = shared_at(16);
-    if (at16.items + own <= room16 || (!float_products && 8 * at16.tokens <= 9 * as_is.tokens)) most_rows = 16;
-    else if (most_rows > 32 && shared_at(32).items + own <= room32) most_rows = 32;
-  }
-  const int32_t max_req = std::max(1, most_rows / group);
-  const int32_t total_prefix_blocks = int32_t(lay->prefix_blk.size());
-  lay->max_rows_prefix = 0;
-  lay->any_masked = false;
-  lay->req_list.assign(lay->group_req.begin(), lay->group_req.end());
-  for (int32_t r = 0; r < R; ++r) lay->req_list.push_back(r);
-  lay->req_list.insert(lay->req_list.end(), lay->root_group_req.begin(), lay->root_group_req.end());
-  // Root segments: read whole by every request below the root (all models of all its prompts), so the sharing group
-  // is large.  In a decode batch it goes out in ordinary items of at most 64 rows, packed into the one persistent
-  // launch with everything else (the root's K/V is then fetched once per 64 rows, mostly from the last-level cache;
-  // a separate launch for a handful of root items would leave most of the chip idle while it runs).  In a
-  // partial-prefill batch (visible lengths set) large groups go to the prefill kernel, roots included.
-  const int32_t root_blk0 = int32_t(lay->prefix_blk.size() + lay->suffix_blk.size());   // roots close the block array
-  lay->planned_root_blk0 = root_blk0;
-  for (int32_t t = 0; t < lay->num_roots; ++t) {
-    int32_t n = 0;
-    const int32_t g0 = lay->root_group_indptr[size_t(t)], count = lay->root_group_indptr[size_t(t) + 1] - g0;
-    const bool wide = limited && prefix_mfma && int64_t(count) * group > 64;
-    // (a root is seen whole by every request below it, so all its chunks go the same way)
-    const int64_t size = wide ? chunking_shared(lay->root_len[size_t(t)], wide_chunk, &n) : chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
-    for (int32_t i = 0; i < count; ++i) nsplit_root[size_t(lay->root_group_req[size_t(g0 + i)])] = n;
-    const bool row_split = limited && prefix_mfma && int64_t(count) * group > 64;
-    const int32_t per_item = row_split ? std::max(1, lay->rowsplit_rows / group) : max_req;
-    // Row groups outside, KV heads inside: items of equal cost reach the workgroups in this order (LPT, lowest
-    // index on ties) and workgroup i runs on XCD i mod 8, so with a multiple of eight KV heads the row groups that
-    // read one (range, head) start together on one XCD and share its L2.
-    for (int32_t c = 0; c < n; ++c)
-      for (int32_t m0 = 0; m0 < count; m0 += per_item)
-        for (int32_t h = 0; h < g.num_kv_heads; ++h) {
-          ps_item it{};
-          it.blk_off = root_blk0 + lay->root_blk_indptr[size_t(t)];
-          it.tok_begin = int32_t(c * size);
-          it.tok_end = int32_t(std::min<int64_t>(lay->root_len[size_t(t)], (c + 1) * size));
-          it.req_off = 2 * R + g0 + m0;
-          it.n_req = std::min(per_item, count - m0);
-          it.kv_head = h;
-          it.split_local = c;
-          it.kind = kPsItemRoot | (row_split ? kPsItemRowSplit : 0) | (count > per_item ? kPsItemReread : 0);
-          if (!row_split) lay->max_rows_prefix = std::max(lay->max_rows_prefix, it.n_req * group);
-          prefix_items.push_back(it);
-        }
-  }
   // The prefill kernel runs one workgroup per item, one item per compute unit at a time, and its items are long: with
   // a few items per compute unit the last round of the launch is badly filled (704 items of 132 tiles on 256 compute
   // units: three rounds for the work of 2.75).  The contexts whose items come last -- the shortest, the launch goes
@@ -450,25 +361,143 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       }
     }
   }
-  std::vector<int32_t> members;
-  for (int32_t p = 0; p < P; ++p) {
-    int32_t n = 0;
+  auto seen_by = [&](int32_t p, int64_t token) {   // requests that see past a token of their prompt's prefix
+    int64_t count = 0;
+    for (int32_t i = lay->group_indptr[p]; i < lay->group_indptr[p + 1]; ++i) count += visible_of(lay->group_req[size_t(i)]) > token;
+    return count;
+  };
+  // how a prompt's prefix is cut: the tokens of a chunk, and how many there are
+  auto cut_prefix = [&](int32_t p, int32_t* n) -> int64_t {
     const int32_t g0 = lay->group_indptr[p], g1 = lay->group_indptr[p + 1];
     const bool wide = limited && prefix_mfma && int64_t(g1 - g0) * group > 64;   // goes to the prefill kernel
-    int64_t size = wide ? chunking_shared(lay->prefix_len[p], wide_chunk, &n) : chunking(lay->prefix_len[p], prefix_chunk, &n);
-    if (wide && tail_cut[size_t(p)] > 1 && n > 0) {
-      size = round_up(ceil_div(int64_t(lay->prefix_len[p]), int64_t(n) * tail_cut[size_t(p)]), granule);
-      n = int32_t(ceil_div(int64_t(lay->prefix_len[p]), size));
+    int64_t size = wide ? chunking_shared(lay->prefix_len[p], wide_chunk, n) : chunking(lay->prefix_len[p], prefix_chunk, n);
+    if (wide && tail_cut[size_t(p)] > 1 && *n > 0) {
+      size = round_up(ceil_div(int64_t(lay->prefix_len[p]), int64_t(*n) * tail_cut[size_t(p)]), granule);
+      *n = int32_t(ceil_div(int64_t(lay->prefix_len[p]), size));
     }
     if (size > mfma_cap && prefix_mfma) {
       // chunks longer than the persistent kernel's items hold are fine only while every one of them goes to the
       // prefill kernel: a chunk that too few requests see into (64 rows or fewer) would be an ordinary item
-      for (int32_t c = 0; c < n && size > mfma_cap; ++c) {
-        int64_t seen_by = 0;
-        for (int32_t i = g0; i < g1; ++i) seen_by += visible_of(lay->group_req[size_t(i)]) > c * size;
-        if (seen_by * group <= 64) size = chunking(lay->prefix_len[p], prefix_chunk, &n);
+      for (int32_t c = 0; c < *n && size > mfma_cap; ++c)
+        if (seen_by(p, c * size) * group <= 64) size = chunking(lay->prefix_len[p], prefix_chunk, n);
+    }
+    return size;
+  };
+  // Rows an item carries per KV head: up to 64 (four row tiles).  With e4m3 KV a sharing group is cut at 32 rows where
+  // the matrix-core kernel runs: the two-tile kernel keeps two workgroups per compute unit and measured 19 % faster
+  // on 64-row groups than the four-tile one (bf16 KV the other way round: the four-tile kernel is 9-12 % faster).
+  const bool narrow_items = g.kv_dtype == PS_FP8_E4M3 && prefix_mfma;
+  int32_t most_rows = narrow_items ? 32 : 64;
+  // Where a batch leaves the chip idle its row groups go out in narrower items: an item is one workgroup, and what bounds a small
+  // launch is that workgroup's time, which the rows make longer -- in the tile kernel a row tile to a wave, so that each wave walks
+  // all of the tokens (four of them share the tokens of a 16-row item), in the persistent kernel all row tiles in every wave, and
+  // above 16 (e4m3: 32) rows only one workgroup on a compute unit.  The K/V is then read once per 16 rows, out of the caches.  64 (e4m3
+  // on the persistent kernel: 32) / 16 rows, us a step: float32, 256-wide heads, 3 contexts of 85 to 171 tokens, 6 to 26 new ones
+  // 42.5 / 18.5; float32, 1 of 262 to 525, 76 rows 25.0 / 12.3; 256-wide, 2 of 264 to 528, 60 rows 21.6 / 12.4; 64-wide, 3 of 94 to
+  // 188, 160 rows 12.0 / 8.8; persistent kernel, 28 query on 4 KV heads, 56 and 30 rows on small contexts 17.0 / 9.9, 17.1 / 10.2, 64 on 8,
+  // 64 rows on 4 15.4 / 9.9, e4m3, 24 rows 13.0 / 11.0.
+  // The line lies where the items of 16 rows, private ones too, still have a compute unit each: 256-wide heads, 256 items 23.5 /
+  // 14.1, 244 16.4 / 13.5, 360 19.6 / 20.6, 364 24.6 / 22.1 (32 rows: 18.5), 432 27.7 / 36.0; 64-wide, 228 12.3 / 9.2, 492 20.2 / 22.1, 526
+  // 19.2 / 21.3; two of them with float32 products of up to 128, which are bound by the matrix cores (272 items 24.0 / 14.1, 352 24.8 /
+  // 16.5, 560 25.3 / 20.4, 608 26.6 / 22.7); in the persistent kernel, where short private ones go four to a workgroup, five to four
+  // (280 items 13.0 / 11.0, 312 13.4 / 11.8, 328 17.1 / 18.6, 424 20.1 / 20.7, 888 18.1 / 20.1).  32 rows by the same line, in the persistent
+  // kernel up to two a compute unit (352 items 20.3 / 16.1, 464 66.2 / 62.4, 552 62.3 / 63.6).
+  // And where the wide groups are few of the tokens (a short root), whatever the size: a launch without them runs the 16-row form
+  // everywhere (19 contexts of 1733 tokens under a root of 1030, 256-wide heads 59.9 / 40.4; 5 of 17613, 64-wide 25.7 / 20.9; e4m3, 13.9 /
+  // 11.8; not float32 of up to 128: 92.4 / 93.5).
+  // Groups of 2 to 8 query heads were measured; a request of 16 rows fills a tile alone.
+  if (opt.prefix_chunk_tokens == 0 && group <= 8 && (prefix_mfma || g.block_size % 16 == 0)) {
+    // What goes out in ordinary items: in a batch with visible lengths the prefill kernel takes the groups of more than 64 rows,
+    // but not their chunks that few requests see into.
+    struct shared_range { int64_t tokens, chunks, reqs; };
+    std::vector<shared_range> ranges;
+    ranges.reserve(size_t(lay->num_roots) + size_t(P));
+    for (int32_t t = 0; t < lay->num_roots; ++t) {
+      const int64_t reqs = lay->root_group_indptr[size_t(t) + 1] - lay->root_group_indptr[size_t(t)];
+      int32_t n = 0;
+      chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
+      if (!(limited && prefix_mfma && reqs * group > 64)) ranges.push_back({lay->root_len[size_t(t)], n, reqs});
+    }
+    for (int32_t p = 0; p < P; ++p) {
+      const int64_t reqs = lay->group_indptr[size_t(p) + 1] - lay->group_indptr[size_t(p)], len = lay->prefix_len[size_t(p)];
+      int32_t n = 0;
+      const int64_t size = cut_prefix(p, &n);
+      if (!(limited && prefix_mfma && reqs * group > 64)) {
+        ranges.push_back({len, n, reqs});
+        continue;
+      }
+      for (int32_t c = 0; c < n; ++c) {
+        const int64_t count = seen_by(p, c * size);
+        if (count > 0 && count * group <= 64) ranges.push_back({std::min(size, len - c * size), 1, count});
       }
     }
+    struct shared_work { int64_t items = 0, tokens = 0; };   // with items of at most that many rows
+    auto shared_at = [&](int32_t rows) {
+      shared_work w;
+      for (const shared_range& s : ranges) {
+        const int64_t walks = ceil_div(s.reqs, std::max(1, rows / group)) * g.num_kv_heads;
+        w.items += s.chunks * walks;
+        w.tokens += s.tokens * walks;
+      }
+      return w;
+    };
+    int64_t own = 0;
+    for (int32_t r = 0; r < R; ++r) own += ceil_div(lay->suffix_len[size_t(r)], suffix_chunk) * g.num_kv_heads;
+    const bool float_products = !prefix_mfma && g.head_dim < 256 && (g.q_dtype == PS_F32 || g.kv_dtype == PS_F32);
+    const int64_t room16 = prefix_mfma ? int64_t(num_cus) * 5 / 4 : int64_t(num_cus) * (float_products ? 2 : 1);
+    const int64_t room32 = prefix_mfma ? int64_t(num_cus) * 2 : room16;
+    const shared_work as_is = shared_at(most_rows), at16 = shared_at(16);
+    const bool few_tokens = !float_products && as_is.tokens > 0 && 8 * at16.tokens <= 9 * as_is.tokens;
+    if (at16.items + own <= room16 || few_tokens) most_rows = 16;
+    else if (most_rows > 32 && shared_at(32).items + own <= room32) most_rows = 32;
+  }
+  const int32_t max_req = std::max(1, most_rows / group);
+  const int32_t total_prefix_blocks = int32_t(lay->prefix_blk.size());
+  lay->max_rows_prefix = 0;
+  lay->any_masked = false;
+  lay->req_list.assign(lay->group_req.begin(), lay->group_req.end());
+  for (int32_t r = 0; r < R; ++r) lay->req_list.push_back(r);
+  lay->req_list.insert(lay->req_list.end(), lay->root_group_req.begin(), lay->root_group_req.end());
+  // Root segments: read whole by every request below the root (all models of all its prompts), so the sharing group
+  // is large.  In a decode batch it goes out in ordinary items of at most 64 rows, packed into the one persistent
+  // launch with everything else (the root's K/V is then fetched once per 64 rows, mostly from the last-level cache;
+  // a separate launch for a handful of root items would leave most of the chip idle while it runs).  In a
+  // partial-prefill batch (visible lengths set) large groups go to the prefill kernel, roots included.
+  const int32_t root_blk0 = int32_t(lay->prefix_blk.size() + lay->suffix_blk.size());   // roots close the block array
+  lay->planned_root_blk0 = root_blk0;
+  for (int32_t t = 0; t < lay->num_roots; ++t) {
+    int32_t n = 0;
+    const int32_t g0 = lay->root_group_indptr[size_t(t)], count = lay->root_group_indptr[size_t(t) + 1] - g0;
+    const bool wide = limited && prefix_mfma && int64_t(count) * group > 64;
+    // (a root is seen whole by every request below it, so all its chunks go the same way)
+    const int64_t size = wide ? chunking_shared(lay->root_len[size_t(t)], wide_chunk, &n) : chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
+    for (int32_t i = 0; i < count; ++i) nsplit_root[size_t(lay->root_group_req[size_t(g0 + i)])] = n;
+    const bool row_split = limited && prefix_mfma && int64_t(count) * group > 64;
+    const int32_t per_item = row_split ? std::max(1, lay->rowsplit_rows / group) : max_req;
+    // Row groups outside, KV heads inside: items of equal cost reach the workgroups in this order (LPT, lowest
+    // index on ties) and workgroup i runs on XCD i mod 8, so with a multiple of eight KV heads the row groups that
+    // read one (range, head) start together on one XCD and share its L2.
+    for (int32_t c = 0; c < n; ++c)
+      for (int32_t m0 = 0; m0 < count; m0 += per_item)
+        for (int32_t h = 0; h < g.num_kv_heads; ++h) {
+          ps_item it{};
+          it.blk_off = root_blk0 + lay->root_blk_indptr[size_t(t)];
+          it.tok_begin = int32_t(c * size);
+          it.tok_end = int32_t(std::min<int64_t>(lay->root_len[size_t(t)], (c + 1) * size));
+          it.req_off = 2 * R + g0 + m0;
+          it.n_req = std::min(per_item, count - m0);
+          it.kv_head = h;
+          it.split_local = c;
+          it.kind = kPsItemRoot | (row_split ? kPsItemRowSplit : 0) | (count > per_item ? kPsItemReread : 0);
+          if (!row_split) lay->max_rows_prefix = std::max(lay->max_rows_prefix, it.n_req * group);
+          prefix_items.push_back(it);
+        }
+  }
+  std::vector<int32_t> members;
+  for (int32_t p = 0; p < P; ++p) {
+    int32_t n = 0;
+    const int32_t g0 = lay->group_indptr[p], g1 = lay->group_indptr[p + 1];
+    const int64_t size = cut_prefix(p, &n);
     for (int32_t i = g0; i < g1; ++i) {
       const int32_t r = lay->group_req[size_t(i)];
       nsplit_prefix[size_t(r)] = int32_t(ceil_div(visible_of(r), size));

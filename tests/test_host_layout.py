@@ -869,9 +869,34 @@ def test_row_groups_of_small_batches_go_out_narrower(heads, d, dtype):
             plans.append(plan)
         chunk = int(plans[0]["items"][:, 2].max())                       # (whole segments: what the plan chose is at least that)
         B.ps_layout_set_visible(lay, w.num_requests, None)
+        if narrow:                                                       # the same chunks, asked for: the same partial states
+            longest = int((plans[0]["items"][:, 2] - plans[0]["items"][:, 1]).max())
+            slots = plans[0]["slot_base"].copy()
+            B.ps_layout_replan(lay, B.plan_options(-(-longest // 32) * 32, 0))
+            assert np.array_equal(B.ps_layout_plan(lay, w.num_requests)["slot_base"], slots)
         B.ps_layout_replan(lay, B.plan_options(-(-chunk // 32) * 32, 0))
         wide = B.ps_layout_plan(lay, w.num_requests)
         _check_plan(w, lay, wide, None)
         assert int(wide["items"][wide["items"][:, 7] & 1 == 0][:, 4].max()) * group > 16
         B.ps_layout_release(pool, lay)
         B.ps_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("heads,dtype,prompts,prefix,new", [((32, 8), "bf16", 24, 5500, 33), ((28, 4), "bf16", 40, 16000, 12), ((64, 8), "fp8_e4m3", 12, 18000, 16)])
+def test_chunks_that_few_requests_see_count_as_shared_work(heads, dtype, prompts, prefix, new):
+    """Contexts whose requests all go to the prefill kernel, with visible lengths spread over them: the chunks that at most 64 rows see
+    into are ordinary items, more of them than the chip takes at once, and keep the wide form."""
+    geo = wl.Geometry(heads[0], heads[1], 128, 16, "bf16", dtype)
+    group = heads[0] // heads[1]
+    assert new * group > 64
+    w = wl.make_workload("spread", geo, new, [prefix] * prompts, [list(range(new))] * prompts, [0] * (prompts * new), seed=9)
+    pool, lay, _, _ = _both(w)
+    visible = (w.prefix_len[w.req_prompt] * (w.req_model.astype(np.int64) + 1) // new).astype(np.int32)
+    B.ps_layout_set_visible(lay, w.num_requests, visible)
+    plan = B.ps_layout_plan(lay, w.num_requests)
+    _check_plan(w, lay, plan, visible)
+    left = plan["items"][(plan["items"][:, 7] & 5) == 0]
+    assert (plan["items"][:, 7] & 4).any() and len(left) > 256
+    assert int(left[:, 4].max()) * group > 16
+    B.ps_layout_release(pool, lay)
+    B.ps_pool_destroy(pool)
