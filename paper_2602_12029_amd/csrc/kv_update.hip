@@ -297,10 +297,14 @@ __global__ __launch_bounds__(256) void append_e4m3x8_kernel(KvWriteParams p, con
   if (dest >= 0) append_e4m3x8_row(p, new_k, new_v, row_shift, dest, r, row >> 1, row & 1);
 }
 
-// The tables on their way to the device and the tokens of the same decode step, which do not wait for them: a workgroup per request
-// reads where its token goes from the pinned buffer, across PCIe like the tables themselves (once a wave: a read is a transaction).
+// The tables on their way to the device and the tokens of the same decode step, which do not wait for them: a wave per row of a token
+// reads where it goes from the pinned buffer, across PCIe like the tables themselves.
 // Bound: that link and its latency; two launches in a row cost a turn's step a launch on the host and the gap between them (16
-// contexts under four models, a turn of eight steps 520 -> 504 us; 25 of one, five steps 324 -> 294).
+// contexts under four models, a turn of eight steps 520 -> 504 us; 25 of one, five steps 324 -> 294).  A row is a chain of dependent
+// reads: with all rows of a request in one workgroup its waves walk them one after the other (bf16, 64 requests, a call with two
+// launches / so / with a wave per row: 8 KV heads 11.5 / 9.3 / 9.1 us, 32 heads 16.5 / 17.9 / 14.6; 32 requests, 64 heads 16.0 / 21.9 /
+// 14.3; float32, 64 requests, 64 heads 14.2 / 19.7 / 12.3; e4m3, where a row's tile may be rewritten, a turn of twelve steps 5 % longer so
+// than with two launches).
 template <int KVT>
 __global__ __launch_bounds__(256) void upload_append_kernel(const u32x4* __restrict__ tables, u32x4* __restrict__ dev_tables, uint32_t pieces,
                                                             uint32_t upload_wgs, KvWriteParams p, const void* __restrict__ new_k,
@@ -310,17 +314,14 @@ __global__ __launch_bounds__(256) void upload_append_kernel(const u32x4* __restr
     if (i < pieces) dev_tables[i] = tables[i];
     return;
   }
-  // (e4m3: a workgroup per four of a token's rows, each a chain of its own where the tile's scale grows; with all rows of a token
-  // in one a turn of twelve steps took 5 % longer than with two launches a step)
-  const int wgs = KVT == PS_FP8_E4M3 ? (2 * p.num_kv_heads + 3) / 4 : 1;
+  const int wgs = (2 * p.num_kv_heads + 3) / 4;   // of a token
   const int wg = int(blockIdx.x - upload_wgs), r = wg / wgs, dest = p.dest[r];
-  if (dest < 0) return;
-  for (int row = (wg - r * wgs) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); row < 2 * p.num_kv_heads; row += 4 * wgs) {
-    typedef std::conditional_t<KVT == PS_F32, float, std::conditional_t<KVT == PS_BF16, uint16_t, u32x4>> word;
-    const word *k = static_cast<const word*>(new_k), *v = static_cast<const word*>(new_v);
-    if constexpr (KVT == PS_FP8_E4M3) append_e4m3x8_row(p, k, v, row_shift, dest, r, row >> 1, row & 1);
-    else append_copy_row(p, k, v, dest, r, row >> 1, row & 1);
-  }
+  const int row = (wg - r * wgs) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);   // of the token: (head, K|V)
+  if (dest < 0 || row >= 2 * p.num_kv_heads) return;
+  typedef std::conditional_t<KVT == PS_F32, float, std::conditional_t<KVT == PS_BF16, uint16_t, u32x4>> word;
+  const word *k = static_cast<const word*>(new_k), *v = static_cast<const word*>(new_v);
+  if constexpr (KVT == PS_FP8_E4M3) append_e4m3x8_row(p, k, v, row_shift, dest, r, row >> 1, row & 1);
+  else append_copy_row(p, k, v, dest, r, row >> 1, row & 1);
 }
 
 // Any head size and alignment.
@@ -538,7 +539,7 @@ bool launch_upload_append(const ps_layout* lay, const void* host_tables, void* d
                           const void* new_v, void* kv, float* scales, hipStream_t st) {
   const ps_geometry& g = lay->geo;
   const uint32_t pieces = uint32_t(bytes / 16), upload_wgs = (pieces + 255) / 256;
-  const int64_t append_wgs = int64_t(lay->num_requests) * (g.kv_dtype == PS_FP8_E4M3 ? (2 * g.num_kv_heads + 3) / 4 : 1);
+  const int64_t append_wgs = int64_t(lay->num_requests) * ((2 * g.num_kv_heads + 3) / 4);
   if (append_wgs == 0 || upload_wgs + append_wgs > kMaxWorkgroups) return false;
   if (g.kv_dtype == PS_FP8_E4M3 && !whole_pieces(lay, new_k, new_v, kv)) return false;
   KvWriteParams p = make_write_params(lay, dev_tables, kv, scales);

@@ -59,3 +59,9 @@ def test_one_launch_stores_what_two_do(kv, d, heads, prompts, tokens, kernel_siz
     for a, b in zip(*results):
         assert torch.equal(a, b)
     assert not torch.equal(results[0][1], pool_bits.view(torch.uint8))
+
+
+@pytest.mark.parametrize("kv,d,heads", [("bf16", 64, (32, 32)), ("f32", 64, (33, 33)), ("bf16", 128, (5, 5)), ("bf16", 64, (1, 1))])
+def test_a_wave_per_row_of_a_token(kv, d, heads):
+    """Tokens of 2 to 66 rows, four to a workgroup: a last one that is full, half full, and the only one."""
+    test_one_launch_stores_what_two_do(kv, d, heads, 20, 1000, True)
