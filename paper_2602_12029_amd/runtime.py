@@ -120,12 +120,12 @@ class DecodeBatch:
         tokens ([R, Hkv, d], contiguous) are stored.  Returns the destinations the host chose."""
         if torch.cuda.is_current_stream_capturing():
             raise RuntimeError("append_step changes the tables on the host: it cannot be recorded into a graph")
+        if not (new_k.is_contiguous() and new_v.is_contiguous()):
+            raise ValueError("append_step stores tokens from contiguous tensors")
         dest = B.ps_layout_append(pool, self.layout, self.num_requests, active)
         # No wait on the host for the upload: it is ordered in front of what follows on this stream, and launches of this
         # batch on other streams wait for it there.
-        storable = new_k.is_contiguous() and new_v.is_contiguous()
-        self._sync_plan(wait=False, tokens=(new_k, new_v) if storable else None)
-        assert storable
+        self._sync_plan(wait=False, tokens=(new_k, new_v))
         return dest
 
     def stage_out(self, image: torch.Tensor):

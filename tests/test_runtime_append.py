@@ -1,0 +1,32 @@
+"""DecodeBatch.append_step without a GPU: what it refuses before the layout grows."""
+import pytest
+import torch
+
+from paper_2602_12029_amd import binding as B
+from paper_2602_12029_amd import runtime
+
+
+@pytest.fixture
+def batch(monkeypatch):
+    """A batch whose library calls are only written down."""
+    b = runtime.DecodeBatch.__new__(runtime.DecodeBatch)
+    b.layout, b.num_requests, b.device, b.scales, b.kv = 1, 2, "cpu", None, torch.zeros(4)
+    b.tables, b.workspace, b._home, b._pending = torch.zeros(8, dtype=torch.uint8), torch.zeros(8, dtype=torch.uint8), 0, False
+    b.calls = []
+    for name, result in (("ps_layout_append", [0, 1]), ("ps_layout_upload", None), ("ps_layout_upload_append", None), ("ps_kv_append", None),
+                         ("ps_layout_device_bytes", 64), ("ps_workspace_bytes", 128)):
+        monkeypatch.setattr(B, name, lambda *a, _n=name, _r=result: (b.calls.append(_n), _r)[1])
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    monkeypatch.setattr(runtime, "_stream", lambda: 0)
+    return b
+
+
+def test_a_token_that_is_not_contiguous_is_refused_before_the_layout_grows(batch):
+    good, bad = torch.zeros(2, 1, 4), torch.zeros(4, 1, 2).permute(2, 1, 0)
+    assert good.shape == bad.shape and not bad.is_contiguous()
+    for new_k, new_v in ((bad, good), (good, bad)):
+        with pytest.raises(ValueError):
+            batch.append_step(0, new_k, new_v)
+    assert batch.calls == []
+    assert batch.append_step(0, good, good) == [0, 1]
+    assert batch.calls[0] == "ps_layout_append" and "ps_layout_upload_append" in batch.calls
