@@ -54,16 +54,19 @@ class DecodeBatch:
         self._sync_plan()
 
     def _sync_plan(self, wait=True, tokens=None):
+        # (the layout has changed: where the new tables cannot be had, the old ones must not be launched from)
+        old, self.tables, self.workspace = (self.tables, self.workspace), None, None
         self._home = _stream()               # tables and workspace belong to this stream
-        nbytes = B.ps_layout_device_bytes(self.layout)
-        self.tables = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        self.workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
+        tables = torch.empty(B.ps_layout_device_bytes(self.layout), dtype=torch.uint8, device=self.device)
+        workspace = torch.empty(B.ps_workspace_bytes(self.layout), dtype=torch.uint8, device=self.device)
+        del old
         self._pending = not wait             # other streams have to wait for the upload on the GPU
         if tokens is None:
-            B.ps_layout_upload(self.layout, self.tables.data_ptr(), _stream())
+            B.ps_layout_upload(self.layout, tables.data_ptr(), _stream())
         else:
-            B.ps_layout_upload_append(self.layout, self.tables.data_ptr(), tokens[0].data_ptr(), tokens[1].data_ptr(),
+            B.ps_layout_upload_append(self.layout, tables.data_ptr(), tokens[0].data_ptr(), tokens[1].data_ptr(),
                                       self.kv.data_ptr(), self._sc(), _stream())
+        self.tables, self.workspace = tables, workspace
         if wait:
             torch.cuda.current_stream().synchronize()
 

@@ -30,3 +30,29 @@ def test_a_token_that_is_not_contiguous_is_refused_before_the_layout_grows(batch
     assert batch.calls == []
     assert batch.append_step(0, good, good) == [0, 1]
     assert batch.calls[0] == "ps_layout_append" and "ps_layout_upload_append" in batch.calls
+
+
+def test_a_batch_whose_new_tables_cannot_be_had_keeps_none(batch, monkeypatch):
+    """The layout has grown by then: neither the tables of before nor new ones without contents may be launched from; the next
+    upload makes the batch whole again."""
+    token = torch.zeros(2, 1, 4)
+    real, made = torch.empty, []
+
+    def empty(*a, **kw):
+        if len(made) == 1:
+            raise torch.cuda.OutOfMemoryError("no room for the workspace")
+        made.append(1)
+        return real(*a, **kw)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        batch.append_step(0, token, token)
+    assert batch.tables is None and batch.workspace is None
+    assert batch.calls.count("ps_layout_append") == 1 and "ps_layout_upload_append" not in batch.calls
+    monkeypatch.setattr(torch, "empty", real)
+    monkeypatch.setattr(B, "ps_layout_upload_append", lambda *a: (_ for _ in ()).throw(RuntimeError("upload")))
+    with pytest.raises(RuntimeError):
+        batch.append_step(0, token, token)
+    assert batch.tables is None and batch.workspace is None
+    batch._sync_plan(wait=False)
+    assert batch.tables.numel() == 64 and batch.workspace.numel() == 128
