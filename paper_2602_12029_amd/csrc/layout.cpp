@@ -405,30 +405,37 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   // And where the wide groups are few of the tokens (a short root), whatever the size: a launch without them runs the 16-row form
   // everywhere (19 contexts of 1733 tokens under a root of 1030, 256-wide heads 59.9 / 40.4; 5 of 17613, 64-wide 25.7 / 20.9; e4m3, 13.9 /
   // 11.8; not float32 of up to 128: 92.4 / 93.5).
-  // Groups of 2 to 8 query heads were measured; a request of 16 rows fills a tile alone.
+  // Groups of 2 to 8 query heads were measured, and groups of one (20 to 64 requests a context, 40 batches of the three kinds 7 to 46 %
+  // faster: bf16, 8 heads, 48 on one of 340 16.0 / 12.3; float32, 48 on one of 660 23.9 / 13.0); a request of 16 rows fills a tile alone.
   if (opt.prefix_chunk_tokens == 0 && group <= 8 && (prefix_mfma || g.block_size % 16 == 0)) {
     // What goes out in ordinary items: in a batch with visible lengths the prefill kernel takes the groups of more than 64 rows,
     // but not their chunks that few requests see into.
     struct shared_range { int64_t tokens, chunks, reqs; };
     std::vector<shared_range> ranges;
     ranges.reserve(size_t(lay->num_roots) + size_t(P));
+    int64_t longest_item = 0;   // tokens
     for (int32_t t = 0; t < lay->num_roots; ++t) {
       const int64_t reqs = lay->root_group_indptr[size_t(t) + 1] - lay->root_group_indptr[size_t(t)];
       int32_t n = 0;
-      chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
-      if (!(limited && prefix_mfma && reqs * group > 64)) ranges.push_back({lay->root_len[size_t(t)], n, reqs});
+      const int64_t size = chunking(lay->root_len[size_t(t)], prefix_chunk, &n);
+      if (limited && prefix_mfma && reqs * group > 64) continue;
+      ranges.push_back({lay->root_len[size_t(t)], n, reqs});
+      longest_item = std::max(longest_item, std::min<int64_t>(size, lay->root_len[size_t(t)]));
     }
     for (int32_t p = 0; p < P; ++p) {
       const int64_t reqs = lay->group_indptr[size_t(p) + 1] - lay->group_indptr[size_t(p)], len = lay->prefix_len[size_t(p)];
       int32_t n = 0;
       const int64_t size = cut_prefix(p, &n);
-      if (!(limited && prefix_mfma && reqs * group > 64)) {
+      if (!limited) {
         ranges.push_back({len, n, reqs});
+        longest_item = std::max(longest_item, std::min(size, len));
         continue;
       }
       for (int32_t c = 0; c < n; ++c) {
         const int64_t count = seen_by(p, c * size);
-        if (count > 0 && count * group <= 64) ranges.push_back({std::min(size, len - c * size), 1, count});
+        if (count == 0 || (prefix_mfma && count * group > 64)) continue;
+        ranges.push_back({std::min(size, len - c * size), 1, count});
+        longest_item = std::max(longest_item, ranges.back().tokens);
       }
     }
     struct shared_work { int64_t items = 0, tokens = 0; };   // with items of at most that many rows
@@ -448,8 +455,29 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     const int64_t room32 = prefix_mfma ? int64_t(num_cus) * 2 : room16;
     const shared_work as_is = shared_at(most_rows), at16 = shared_at(16);
     const bool few_tokens = !float_products && as_is.tokens > 0 && 8 * at16.tokens <= 9 * as_is.tokens;
-    if (at16.items + own <= room16 || few_tokens) most_rows = 16;
-    else if (most_rows > 32 && shared_at(32).items + own <= room32) most_rows = 32;
+    // Not into a second round that the wide items do not need: where the persistent kernel's narrow ones outnumber the compute units
+    // and the wide ones do not, the launch lasts two items (or one that shares its compute unit) instead of one.  Shared items wide /
+    // narrow, us a step wide / narrow: 24 rows in 16, 256 / 288 of 2656 tokens 57.9 / 79.8, 252 / 294 of 832 23.8 / 29.9, 240 / 280 of 352
+    // 14.9 / 17.7, of 256 and less the other way round (92 / 276 18.1 / 14.0); 35 to 64 rows in 32, 204 / 408 of 256 18.7 / 21.9, 240 / 300 of
+    // 832 27.5 / 34.6, 256 / 320 of 3840 88.7 / 115.5; partial prefill, the prefill kernel's items counted in, 464 / 712 of 8100 252 / 418, 376
+    // / 544 of 6208 182 / 251.  For 32 rows the line lies where the wide items and the private ones are no more than 9/8 of the compute
+    // units (118 batches 15 % slower narrow, none faster), and a sixteenth of these is idle (256 and 32 private ones 30.7 / 17.8): beyond
+    // it the narrow form gains about as often as it loses, but with items of more than 2048 tokens, and so it does in a partial prefill.
+    // (What counts there is the rows that see into a chunk, not those of the whole group.)
+    auto second_round = [&](const shared_work& narrow, int32_t rows) {
+      if (!prefix_mfma || narrow_items || narrow.items <= num_cus || as_is.items > num_cus) return false;
+      if (rows == 16) return longest_item > round_up(256, granule);
+      return longest_item > 2048 || (!limited && 8 * (as_is.items + own) <= 9 * int64_t(num_cus) && 16 * as_is.items <= 15 * int64_t(num_cus));
+    };
+    // (few tokens of a batch with many private items beside them: the 16-row form everywhere gains more than the round costs; 256 /
+    // 264 shared items, 536 / 544 in all 34.8 / 27.8, 256 / 320, 656 / 720 32.6 / 25.6; 282 / 314 39.2 / 47.9, 304 / 336 57.9 / 79.8)
+    const bool again16 = second_round(at16, 16);
+    if ((few_tokens && !(again16 && !unequal && 4 * (as_is.items + own) <= 5 * int64_t(num_cus))) || (at16.items + own <= room16 && !again16)) {
+      most_rows = 16;
+    } else if (most_rows > 32) {
+      const shared_work at32 = shared_at(32);
+      if (at32.items + own <= room32 && !second_round(at32, 32)) most_rows = 32;
+    }
   }
   const int32_t max_req = std::max(1, most_rows / group);
   const int32_t total_prefix_blocks = int32_t(lay->prefix_blk.size());

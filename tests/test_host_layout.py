@@ -900,3 +900,27 @@ def test_chunks_that_few_requests_see_count_as_shared_work(heads, dtype, prompts
     assert int(left[:, 4].max()) * group > 16
     B.ps_layout_release(pool, lay)
     B.ps_pool_destroy(pool)
+
+
+
+
+@pytest.mark.parametrize("heads,prefix,models,private,new,rows", [
+    ((32, 4), [21000] * 8, [3, 1, 1, 1, 1, 1, 1, 1], 10, 0, 24),   # 16 rows: compute units with two long items, few of the tokens in wide groups
+    ((32, 4), [4219] * 3, [5] * 3, 60, 0, 40),                     # 32 rows: twice the items, private ones on idle compute units
+    ((28, 4), [3959] * 3, [5] * 3, 100, 0, 35),
+    ((64, 8), [30662] * 4, [5, 1, 1, 2], 100, 0, 40),              # long items
+    ((32, 8), [8084] * 40, [10 + i % 9 for i in range(40)], 0, 1, 64)])   # partial prefill: what the prefill kernel leaves
+def test_row_groups_are_not_narrowed_into_a_second_round(heads, prefix, models, private, new, rows):
+    """Batches whose wide items have a compute unit each, and whose narrower ones would not, keep the wide ones."""
+    geo = wl.Geometry(heads[0], heads[1], 128, 16, "bf16", "bf16")
+    w = wl.make_workload("round", geo, max(models), [n + (c if new else 0) for n, c in zip(prefix, models)], [list(range(c)) for c in models],
+                         [private] * sum(models), seed=12)
+    visible = np.concatenate([n + 1 + np.arange(c) for n, c in zip(prefix, models)]).astype(np.int32) if new else None
+    pool, lay, _, _ = _both(w)
+    B.ps_layout_set_visible(lay, w.num_requests, visible)
+    plan = B.ps_layout_plan(lay, w.num_requests)
+    _check_plan(w, lay, plan, visible)
+    shared = plan["items"][(plan["items"][:, 7] & 5) == 0]
+    assert int(shared[:, 4].max()) * heads[0] // heads[1] == rows and len(shared) <= 256
+    B.ps_layout_release(pool, lay)
+    B.ps_pool_destroy(pool)
