@@ -165,7 +165,9 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   int32_t shortest = INT32_MAX, longest = 0;   // of the shared segments
   for (int32_t l : lay->prefix_len) { shortest = std::min(shortest, l); longest = std::max(longest, l); }
   const bool unequal = longest > 0 && int64_t(longest) * 10 > int64_t(shortest) * 11;
-  const int64_t ideal = std::max<int64_t>(1, ceil_div(two_per_cu && unequal ? total * 3 / 5 : total, int64_t(num_cus)));
+  auto share_of = [&](bool two) { return std::max<int64_t>(1, ceil_div(two && unequal ? total * 3 / 5 : total, int64_t(num_cus))); };
+  const int64_t ideal = share_of(two_per_cu);
+  int64_t aim = ideal;   // of the persistent kernel's chunks: another where its items turn out narrower (see most_rows below)
   auto resolve = [&](int32_t v) { return v == PS_VARIANT_AUTO ? (mfma_ok ? PS_VARIANT_MFMA : PS_VARIANT_WAVE) : v; };
   // Row groups of more than 16 rows in the tile kernel: a wave per row tile (spread), where the waves of a tile's row groups
   // fetch it one after the other out of the caches, or all row tiles in every wave.  The first carries no more registers than
@@ -216,7 +218,7 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
   auto pick = [&](int32_t asked, int32_t variant, bool fewer) -> int64_t {
     if (asked > 0) return round_up(asked, granule);
     const bool tiles = variant == PS_VARIANT_WAVE && g.block_size % 16 == 0 && !fewer;
-    return std::min<int64_t>(std::max<int64_t>(round_up(tiles ? tile_ideal : ideal, granule), round_up(tiles ? 128 : 256, granule)),
+    return std::min<int64_t>(std::max<int64_t>(round_up(tiles ? tile_ideal : fewer ? ideal : aim, granule), round_up(tiles ? 128 : 256, granule)),
                              round_up(kPsMfmaMaxChunk, granule));
   };
   const int64_t mfma_cap = std::max<int64_t>(granule, kPsMfmaMaxChunk / granule * granule);
@@ -224,14 +226,12 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
     const int64_t chunk = pick(asked, variant, fewer);
     return variant == PS_VARIANT_MFMA ? std::min(chunk, mfma_cap) : chunk;
   };
-  const int64_t prefix_chunk = chunk_for(opt.prefix_chunk_tokens, resolve(opt.prefix_variant), fewer_states);
-  const int64_t suffix_chunk = chunk_for(opt.suffix_chunk_tokens, resolve(opt.suffix_variant), fewer_states);
+  int64_t prefix_chunk = chunk_for(opt.prefix_chunk_tokens, resolve(opt.prefix_variant), fewer_states);
+  int64_t suffix_chunk = chunk_for(opt.suffix_chunk_tokens, resolve(opt.suffix_variant), fewer_states);
 
   lay->opt = opt;
   lay->prefix_variant = resolve(opt.prefix_variant);
   lay->suffix_variant = resolve(opt.suffix_variant);
-  lay->prefix_chunk = int32_t(prefix_chunk);
-  lay->suffix_chunk = int32_t(suffix_chunk);
 
   // equal-sized chunks of a segment of `len` tokens: returns the chunk size used
   auto chunking = [&](int64_t len, int64_t chunk, int32_t* n) -> int64_t {
@@ -478,7 +478,22 @@ static int32_t build_plan(ps_layout* lay, const ps_plan_options* user, bool fewe
       const shared_work at32 = shared_at(32);
       if (at32.items + own <= room32 && !second_round(at32, 32)) most_rows = 32;
     }
+    // Two workgroups of the persistent kernel on a compute unit where the wide items had left room for one: chunks for two, as above.
+    // Cut for the wide items / for two, us a step: under a root, 10 contexts of 2857 to 11430 tokens and eight models 55.3 / 45.2, 44 of 752
+    // to 12047 153.7 / 141.3, 6 of 5357 to 21428 81.7 / 61.4; 405 batches with a share of 2048 tokens and more 11 % faster in the mean
+    // (7 of them 1 to 6 % slower).  With a smaller share only where the items are few, up to nine to four compute units (45 batches 0 to
+    // 25 % faster) or three to two: many small segments even out by themselves, and a finer cut adds states (43 of 160 to 2566 under a
+    // root of 49, 40.2 / 42.8; 132 of 23 to 378 21.7 / 24.3).
+    const int64_t share = ceil_div(total, int64_t(num_cus)), items16 = at16.items + own;
+    const bool coarse = share >= 2048 || (share >= 1200 && 4 * items16 <= 9 * int64_t(num_cus)) || (share >= 800 && 2 * items16 <= 3 * int64_t(num_cus));
+    if (most_rows == 16 && prefix_mfma && !limited && !fewer_states && !two_per_cu && ps_mfma_occupancy(most_rows, g.kv_dtype) == 2 && coarse) {
+      aim = share_of(true);
+      prefix_chunk = chunk_for(opt.prefix_chunk_tokens, resolve(opt.prefix_variant), false);
+      suffix_chunk = chunk_for(opt.suffix_chunk_tokens, resolve(opt.suffix_variant), false);
+    }
   }
+  lay->prefix_chunk = int32_t(prefix_chunk);
+  lay->suffix_chunk = int32_t(suffix_chunk);
   const int32_t max_req = std::max(1, most_rows / group);
   const int32_t total_prefix_blocks = int32_t(lay->prefix_blk.size());
   lay->max_rows_prefix = 0;

@@ -924,3 +924,34 @@ def test_row_groups_are_not_narrowed_into_a_second_round(heads, prefix, models, 
     assert int(shared[:, 4].max()) * heads[0] // heads[1] == rows and len(shared) <= 256
     B.ps_layout_release(pool, lay)
     B.ps_pool_destroy(pool)
+
+
+def test_chunks_of_row_groups_that_are_narrowed_are_cut_for_two_workgroups():
+    """Few of the tokens in wide groups (a short root): items of 16 rows, two workgroups on a compute unit, and chunks of 0.6 of a compute
+    unit's share as without the root; whole shares where the lengths are alike, where the segments are many and short, and where a
+    caller asks for a chunk size."""
+    geo = wl.Geometry(32, 8, 128, 16, "bf16", "bf16")
+    rng = np.random.default_rng(4)
+
+    def plan_of(prefix, models, root, options=None):
+        w = wl.make_tree_workload("aims", geo, models, [root], [0] * len(prefix), prefix, [list(range(models))] * len(prefix),
+                                  [20] * (models * len(prefix)), seed=3) if root else \
+            wl.make_workload("aims", geo, models, prefix, [list(range(models))] * len(prefix), [20] * (models * len(prefix)), seed=3)
+        pool, lay, _, _ = _both(w)
+        if options:
+            B.ps_layout_replan(lay, options)
+        plan = B.ps_layout_plan(lay, w.num_requests)
+        _check_plan(w, lay, plan)
+        share = int((w.prefix_len.sum() + w.suffix_len.sum() + (root or 0)) * 8 / 256)
+        items = plan["items"]
+        out = int(items[:, 4].max()) * 4, int((items[:, 2] - items[:, 1]).max()) / share
+        B.ps_layout_release(pool, lay)
+        B.ps_pool_destroy(pool)
+        return out
+
+    ragged = [int(n) for n in rng.integers(2500, 10001, 24)]
+    rows, cut = plan_of(ragged, 2, 100)
+    assert rows == 16 and cut <= 0.65 and abs(cut - plan_of(ragged, 2, None)[1]) < 0.05
+    assert plan_of([4000] * 36, 2, 100)[1] > 0.8
+    assert plan_of([int(n) for n in rng.integers(100, 1401, 60)], 2, 40)[1] > 0.8
+    assert plan_of(ragged, 2, 100, B.plan_options(8192, 0))[1] > 0.9
