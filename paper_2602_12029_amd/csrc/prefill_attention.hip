@@ -24,12 +24,14 @@
 // conflicts).  A tile is thus fetched, transposed and converted once per 256 rows.  Global loads run five tiles ahead of the
 // products (two tiles in registers, the others in LDS).
 //
-// Bound: power.  The chip holds 1.4 to 1.8 GHz here (2.4 without matrix work), and what takes cycles out of a tile gives most of
-// them back in clock.  What the loop is built for is thus fewer cycles and fewer instructions a tile, in this order:
+// Bound: power.  The chip holds 1.6 to 1.8 GHz here (2.4 without matrix work), and what takes cycles out of a tile gives about half
+// of them back in clock.  What the loop is built for is thus fewer cycles and fewer instructions a tile, in this order:
 // the two waves of a SIMD take turns at the matrix core (see the loop), nothing but the softmax stands between their turns, and
-// addresses are a scalar base and a 32-bit lane offset.  Per tile and pair of waves, before / now: 1726 / 1354 cycles (e4m3
-// 1853 / 1520; the clock 1.77 / 1.39 and 2.04 / 1.79 GHz in the same runs), and 138 / 127 instructions a wave (bf16), 155 / 150 (e4m3).  32 contexts of 4096 tokens with 64 to 256 new ones, 32 heads, bf16: 449 -> 417 us;
-// 64 of 8192, 64 heads, e4m3: 3031 -> 2800; 17 of 5626 to 11253, 32 heads, e4m3: 230 -> 197; short contexts, whose items are
+// addresses are a scalar base and a 32-bit lane offset.  Before / now, whole launches under the profiler, the stores below
+// included: 32 contexts of 4096 tokens with 64 to 256 new ones, 32 heads, bf16 842 / 652 thousand cycles at 1.86 / 1.64 GHz, 452 / 398 us,
+// matrix cores 38 / 49 % busy; 64 of 8192, 64 heads, e4m3 5.81 / 4.58 million at 2.11 / 1.82, 2753 / 2513, 44 / 56 %.  A tile is 138 / 127
+// instructions a wave (bf16), 155 / 150 (e4m3).  The loop alone, without the profiler: 449 -> 417 us and 3031 -> 2800;
+// 17 of 5626 to 11253, 32 heads, e4m3: 230 -> 197; short contexts, whose items are
 // mostly their start and their states, alike (22 of 65 to 130, 62 to 251 new ones: 107 / 108).  With half the operand reads left out
 // (a timing build) it would be another 3 %, which is what two row tiles a wave could gain.
 //
@@ -405,9 +407,10 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_attention_kernel(AttnParams
 
   // ---- stream the token range.  No branch surrounds a load, so that the counting of outstanding loads stays exact; every wave runs
   // every iteration (and every barrier), whether it has rows or not.  Two tiles per round at least, so that the fetch registers keep
-  // their roles.  Three loops rather than tests inside one (a branch around the products would have the accumulators copied
-  // where its sides meet): the tiles every row of the wave sees whole, then the rest of what the wave sees with the per-row limits
-  // (a tile past it is masked out entirely), then the tiles only other waves need.  Every wave passes the same number of barriers.
+  // their roles.  A loop each rather than tests inside one (a branch around the products would have the accumulators copied
+  // where its sides meet): the tiles every row of the wave sees whole (eight waves: by fours, then a pair), then the rest of what the
+  // wave sees with the per-row limits (a tile past it is masked out entirely), then the tiles only other waves need.  Every wave
+  // passes the same number of barriers.
   publish_k(fa, 0);
   publish_v(fa, 0, 0, std::true_type{});
   fetch(fa, at0);
